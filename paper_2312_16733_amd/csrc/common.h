@@ -11,7 +11,7 @@ typedef unsigned short bf16_t;   // raw bfloat16 bits
 
 enum KClass {
   KC_IGEMM = 0,      // sliced implicit-GEMM conv / linear on bf16 MFMA
-  KC_DIRECT = 1,     // direct conv (stems, fp32 tiny net)
+  KC_DIRECT = 1,     // fp32 family's convs and linears, bf16 heads of odd width
   KC_DEPTHWISE = 2,
   KC_POOL = 3,       // max pool, global average pool
   KC_SE = 4,         // squeeze-excite gate + channel scale
@@ -205,7 +205,8 @@ hipError_t launch_mbv3_head(const Mbv3HeadArgs& a, hipStream_t s);
 int mbv3_head_channels();                          // the width launch_mbv3_head is built for
 void igemm_tile_shape(int variant, int* bm, int* bn);
 int igemm_num_variants();
-hipError_t launch_direct_conv(const ConvGroupArgs& a, int dtype, hipStream_t s);
+hipError_t launch_direct_conv(const ConvGroupArgs& a, hipStream_t s);      // bf16
+hipError_t launch_conv_f32(const ConvGroupArgs& a, hipStream_t s);
 hipError_t launch_maxpool(const PoolGroupArgs& a, int dtype, hipStream_t s);
 hipError_t launch_gap(const PoolGroupArgs& a, int dtype, hipStream_t s);
 hipError_t launch_depthwise(const DwGroupArgs& a, hipStream_t s);

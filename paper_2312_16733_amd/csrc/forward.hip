@@ -1199,7 +1199,8 @@ static hipError_t run_op(const PlanOp& op, hipStream_t s) {
   switch (op.type) {
     case PlanOp::IGEMM: return launch_igemm(*(const ConvGroupArgs*)a, op.variant, op.flag != 0, s);
     case PlanOp::KREDUCE: return launch_splitk_reduce(*(const ConvGroupArgs*)a, s);
-    case PlanOp::DIRECT: return launch_direct_conv(*(const ConvGroupArgs*)a, op.flag, s);
+    case PlanOp::DIRECT:
+      return op.flag == SNA_DTYPE_FP32 ? launch_conv_f32(*(const ConvGroupArgs*)a, s) : launch_direct_conv(*(const ConvGroupArgs*)a, s);
     case PlanOp::MAXPOOL: return launch_maxpool(*(const PoolGroupArgs*)a, op.flag, s);
     case PlanOp::GAP: return launch_gap(*(const PoolGroupArgs*)a, op.flag, s);
     case PlanOp::DW: return launch_depthwise(*(const DwGroupArgs*)a, s);

@@ -1,4 +1,4 @@
-// Direct convolution (stems, fp32 tiny net), pooling, request gather / scatter and the
+// Direct convolution (bf16 heads of odd width), pooling, request gather / scatter and the
 // load-time folding of SubnetNorm statistics.  All forward kernels are grouped launches.
 #include "common.h"
 
@@ -8,8 +8,8 @@ namespace sna {
 // Direct WeightSlice convolution: one thread = one output pixel x KT consecutive output channels.
 // The block's KT-channel slab of the ACTIVE weight slice (leading C input channels, centre RxS
 // window) is staged once in LDS as fp32 [R*S*C][KT]; every lane then reads the same LDS address
-// (a broadcast) while walking its own input patch.  Used where the input has too few channels
-// for the MFMA path (3-channel stems) and for the fp32 family.
+// (a broadcast) while walking its own input patch.  Used for bf16 heads whose width is not a
+// multiple of 8, which the matrix kernel does not take.
 // ---------------------------------------------------------------------------------------------
 constexpr int DIRECT_KT = 16;
 constexpr int DIRECT_THREADS = 256;
@@ -21,8 +21,8 @@ template <typename T> __device__ __forceinline__ void st_f32(T* p, float v);
 template <> __device__ __forceinline__ void st_f32<float>(float* p, float v) { *p = v; }
 template <> __device__ __forceinline__ void st_f32<bf16_t>(bf16_t* p, float v) { *p = f32_to_bf16(v); }
 
-template <typename T>
 __global__ __launch_bounds__(DIRECT_THREADS) void direct_conv_kernel(const ConvGroupArgs args) {
+  typedef bf16_t T;
   extern __shared__ float wlds[];                       // [R*S*C][KT]
   const int g = find_problem(args, blockIdx.x);
   const ConvProblem& p = args.p[g];
@@ -95,30 +95,18 @@ size_t direct_lds_bytes(const ConvGroupArgs& a) {
   return mx;
 }
 
-hipError_t launch_direct_conv(const ConvGroupArgs& a, int dtype, hipStream_t s) {
+hipError_t launch_direct_conv(const ConvGroupArgs& a, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
   const int blocks = a.p[a.n - 1].tile_start + a.p[a.n - 1].tiles;
   const size_t lds = direct_lds_bytes(a);
   if (lds > 150 * 1024) return hipErrorInvalidValue;
-  if (dtype == SNA_DTYPE_FP32) {
-    static bool attr32 = false;
-    if (!attr32) {
-      hipError_t e = hipFuncSetAttribute((const void*)direct_conv_kernel<float>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
-      if (e != hipSuccess) return e;
-      attr32 = true;
-    }
-    hipLaunchKernelGGL(direct_conv_kernel<float>, dim3(blocks), dim3(DIRECT_THREADS), lds, s, a);
-  } else {
-    static bool attr16 = false;
-    if (!attr16) {
-      hipError_t e = hipFuncSetAttribute((const void*)direct_conv_kernel<bf16_t>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
-      if (e != hipSuccess) return e;
-      attr16 = true;
-    }
-    hipLaunchKernelGGL(direct_conv_kernel<bf16_t>, dim3(blocks), dim3(DIRECT_THREADS), lds, s, a);
+  static bool attr16 = false;
+  if (!attr16) {
+    hipError_t e = hipFuncSetAttribute((const void*)direct_conv_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
+    if (e != hipSuccess) return e;
+    attr16 = true;
   }
+  hipLaunchKernelGGL(direct_conv_kernel, dim3(blocks), dim3(DIRECT_THREADS), lds, s, a);
   return hipGetLastError();
 }
 

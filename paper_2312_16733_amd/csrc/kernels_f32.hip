@@ -1,0 +1,160 @@
+// WeightSlice convolution / linear of the fp32 family on the fp32 matrix instruction (gfx950).
+//
+//   Y[m, k] = sum_{r,s,c} X[n, p*st + r - pad, q*st + s - pad, c] * W[k, r, s, c]
+//
+// These layers are short (at 4 images of 32 x 32 the largest has 1024 output pixels) and what bounds them is the
+// serial chain of one output's reduction: with one thread per pixel and 16 channels a layer of 1152 terms took 150 us
+// on 8 CUs.  Here an output tile is 16 pixels x 16 channels of v_mfma_f32_16x16x4_f32 (fp32 products and sums), and a
+// long reduction is spread over the 8 waves of a block, which add their sums through LDS: the chain becomes 1/8 as long
+// and there are 32 .. 512 tiles where there were 4 .. 32.  Operands go from global memory (the whole net stays in L2)
+// straight to registers: a lane loads 4 consecutive reduction elements of its pixel and of its channel with one
+// 16-byte bounds-checked load each, which four MFMAs take element by element; the loads of four steps are in flight
+// ahead of the MFMAs that use them.
+//
+// Measured on the largest tiny subnet (thread per pixel -> here, event-bracketed): 4 images, 64 x 128 x 1152 (pixels x
+// channels x reduction) 153 -> 10.1 us, 256 x 64 x 576 96 -> 8.2, 1024 x 32 x 288 63 -> 8.1, the whole forward
+// 514 -> 51 us, where an empty launch takes 6; 64 images, 1024 x 128 x 1152 166 -> 14.5, 16384 x 32 x 288 62 -> 17.5.
+//
+// The reduction order depends on the layer's reduction length alone (wave w sums its run of steps in order, the waves'
+// sums are added in wave order), so a request's result does not depend on what it is batched with.
+#include "common.h"
+
+namespace sna {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
+
+constexpr int F32_WAVES = 8;          // waves per block
+constexpr int F32_TILE = 16;
+constexpr int F32_STEP = 16;          // reduction elements per step: 4 lanes groups x 4 elements
+constexpr int F32_AHEAD = 4;          // steps whose loads are in flight together
+
+// Waves that share one output tile: with fewer than 4 steps each, adding up through LDS costs more than it saves.
+__host__ __device__ __forceinline__ int f32_k_waves(int steps) {
+  return steps >= 32 ? 8 : (steps >= 16 ? 4 : (steps >= 8 ? 2 : 1));
+}
+
+// VEC: the input channels come in fours, so that a lane's 4 elements lie inside one tap
+template <bool VEC>
+__global__ __launch_bounds__(64 * F32_WAVES) void conv_f32_kernel(const ConvGroupArgs args) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __shared__ float red[F32_WAVES][F32_TILE * F32_TILE];
+  const int g = find_problem(args, blockIdx.x);
+  const ConvProblem& p = args.p[g];
+  const int local = blockIdx.x - p.tile_start;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int RSC = p.R * p.S * p.C;
+  const int steps = (RSC + F32_STEP - 1) / F32_STEP;
+  const int kw = f32_k_waves(steps);                       // waves per tile
+  const int tiles_b = F32_WAVES / kw;                      // pixel tiles per block
+  const int tn = local % p.tiles_n, tmb = local / p.tiles_n;
+  const int tile = tmb * tiles_b + wave / kw, part = wave % kw;
+  const int l16 = lane & 15, grp = lane >> 4;
+  const int m = tile * F32_TILE + l16, k = tn * F32_TILE + l16;
+
+  constexpr unsigned OOB = 0x80000000u;
+  const __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc((void*)p.x, 0, (int)p.x_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc((void*)p.w, 0, (int)p.w_bytes, 0x00020000);
+  const bool m_ok = m < p.M, k_ok = k < p.K;
+  const int t = p.Wo == 1 ? m : (int)__umulhi((unsigned)m, p.magic_wo);
+  const int q = m - t * p.Wo;
+  const int n = p.Ho == 1 ? t : (int)__umulhi((unsigned)t, p.magic_ho);
+  const int pp = t - n * p.Ho;
+  const int ih0 = pp * p.stride - p.pad, iw0 = q * p.stride - p.pad;
+  const int xbase = ((n * p.H + ih0) * p.W + iw0) * p.C, wbase = k * p.wk;
+  // x / C = mulhi(x, magic) for x < 2^32 / C; a reduction is far shorter
+  const unsigned magic_c = p.C > 1 ? 0xFFFFFFFFu / (unsigned)p.C + 1u : 0u;
+
+  // byte offsets of reduction element e (of its run of 4, if VEC) in this lane's pixel window and weight row
+  auto locate = [&](int e, int e_end, unsigned& ox, unsigned& ow) {
+    const int rs = p.C > 1 ? (int)__umulhi((unsigned)e, magic_c) : e;
+    const int c = e - rs * p.C;
+    const int r = (rs * p.inv_s) >> 16, s = rs - r * p.S;
+    const int ih = ih0 + r, iw = iw0 + s;
+    const bool in = e < e_end;
+    ox = in && m_ok && (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W
+             ? (unsigned)(xbase + (r * p.W + s) * p.C + c) * 4u : OOB;
+    ow = in && k_ok ? (unsigned)(wbase + r * p.wr + s * p.ws + c) * 4u : OOB;
+  };
+  struct Operands { f32x4 a, b; };
+  auto load = [&](int step, int e_end) {
+    Operands o;
+    if constexpr (VEC) {
+      unsigned ox, ow;
+      locate(step * F32_STEP + grp * 4, e_end, ox, ow);
+      o.a = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, ox, 0, 0));
+      o.b = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, ow, 0, 0));
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        unsigned ox, ow;
+        locate(step * F32_STEP + grp * 4 + j, e_end, ox, ow);
+        o.a[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc_x, ox, 0, 0));
+        o.b[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc_w, ow, 0, 0));
+      }
+    }
+    return o;
+  };
+
+  const int s0 = part * steps / kw, s1 = (part + 1) * steps / kw;
+  const int e_end = s1 * F32_STEP < RSC ? s1 * F32_STEP : RSC;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  Operands cur[F32_AHEAD];
+#pragma unroll
+  for (int i = 0; i < F32_AHEAD; ++i) cur[i] = load(s0 + i, e_end);
+  for (int s = s0; s < s1; s += F32_AHEAD) {
+    Operands nxt[F32_AHEAD];
+    if (s + F32_AHEAD < s1) {
+#pragma unroll
+      for (int i = 0; i < F32_AHEAD; ++i) nxt[i] = load(s + F32_AHEAD + i, e_end);
+    }
+#pragma unroll
+    for (int i = 0; i < F32_AHEAD; ++i)                    // a step past the end multiplies zeros
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(cur[i].a[j], cur[i].b[j], acc, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < F32_AHEAD; ++i) cur[i] = nxt[i];
+  }
+
+  // accumulator element v of lane l: pixel 4 (l / 16) + v, channel l % 16 of the tile
+#pragma unroll
+  for (int v = 0; v < 4; ++v) red[wave][(4 * grp + v) * F32_TILE + l16] = acc[v];
+  __syncthreads();
+  for (int i = threadIdx.x; i < tiles_b * F32_TILE * F32_TILE; i += 64 * F32_WAVES) {
+    const int tl = i >> 8, e = i & 255;
+    const int mo = (tmb * tiles_b + tl) * F32_TILE + (e >> 4), ko = tn * F32_TILE + (e & 15);
+    if (mo >= p.M || ko >= p.K) continue;
+    float v = red[tl * kw][e];
+    for (int w = 1; w < kw; ++w) v += red[tl * kw + w][e];
+    v = fmaf(v, p.scale ? p.scale[ko] : 1.f, p.shift ? p.shift[ko] : 0.f);
+    const float rv = p.res ? ((const float*)p.res)[(long)mo * p.res_stride + ko] : 0.f;
+    if (p.res && !p.res_after_act) v += rv;
+    v = apply_act(v, p.act);
+    if (p.res && p.res_after_act) v += rv;
+    ((float*)p.y)[(long)mo * p.y_stride + ko] = v;
+  }
+#endif
+}
+
+hipError_t launch_conv_f32(const ConvGroupArgs& a, hipStream_t s) {
+  if (a.n == 0) return hipSuccess;
+  ConvGroupArgs b = a;
+  int start = 0;
+  bool vec = true;
+  for (int i = 0; i < b.n; ++i) {
+    ConvProblem& p = b.p[i];
+    const int steps = (p.R * p.S * p.C + F32_STEP - 1) / F32_STEP;
+    const int rows_b = F32_TILE * F32_WAVES / f32_k_waves(steps);
+    vec = vec && p.C % 4 == 0;
+    p.tiles_n = (p.K + F32_TILE - 1) / F32_TILE;
+    p.tiles = (p.M + rows_b - 1) / rows_b * p.tiles_n;
+    p.tile_start = start;
+    start += p.tiles;
+  }
+  b.total_tiles = start;
+  if (vec) hipLaunchKernelGGL(conv_f32_kernel<true>, dim3(start), dim3(64 * F32_WAVES), 0, s, b);
+  else hipLaunchKernelGGL(conv_f32_kernel<false>, dim3(start), dim3(64 * F32_WAVES), 0, s, b);
+  return hipGetLastError();
+}
+
+}  // namespace sna

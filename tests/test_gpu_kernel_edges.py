@@ -1,0 +1,45 @@
+"""Kernels at the sizes where a tile, a remainder or a dispatch rule can go wrong, against the oracle (needs an MI355X)."""
+import numpy as np
+import pytest
+
+import synth
+from helpers import check_parity, setup
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_mod():
+    import torch
+    assert torch.cuda.is_available()
+    return torch
+
+
+def forward(torch, net, spec, cfgs, route, x, **kw):
+    t = torch.from_numpy(np.ascontiguousarray(x))
+    t = (t.to(torch.bfloat16) if spec.dtype == "bf16" else t).to("cuda:0")
+    out = net.forward(cfgs, np.asarray(route, np.int32), t, **kw)
+    torch.cuda.synchronize()
+    return out.cpu().numpy()
+
+
+# fp32 convolutions: reductions of 27 (scalar loads), 72 (one wave per tile), 8..31 and >= 32 steps of 16 (2, 4 and 8
+# waves per tile), channel counts around the 16-wide tile, pixel counts around the 16 x waves a block covers.
+# Tolerance: a sum of n fp32 terms in another order moves by about sqrt(n) 2^-24 of its size; n <= 1152 and 8 layers
+# in a row give 8 * 34 * 6e-8 = 1.6e-5.
+@pytest.mark.parametrize("stages,res,batch", [((8, 8, 16), 9, 1), ((16, 24, 40), 17, 3), ((32, 64, 128), 32, 5),
+                                              ((56, 72, 120), 11, 2), ((128, 8, 128), 8, 16)])
+def test_fp32_conv_tile_edges(torch_mod, stages, res, batch):
+    import oracle
+    import paper_2312_16733_amd as sna
+    spec = synth.TinySpec(stage_ch=stages, width_choices=(1.0,), res_choices=(res,))
+    W, S, C = setup(spec, 2)
+    net = sna.Supernet(spec, W, S, 2, 16)
+    try:
+        for c in (C[0], C[-1]):
+            x = synth.make_inputs(spec, batch, res, res, 11)
+            print("fp32 conv", stages, res, batch, c.depth, flush=True)
+            got = forward(torch_mod, net, spec, [c], np.zeros(batch), x)
+            check_parity(got, oracle.forward(spec, W, S, c, x), "fp32", f"{stages} {res} x{batch}", tol=1.6e-5)
+    finally:
+        net.close()
