@@ -99,6 +99,23 @@ struct DwProblem {
 };
 struct DwGroupArgs { int n; DwProblem p[SNA_MAX_GROUPS]; };
 
+// Pointwise expand and depthwise convolution of an inverted-residual block in one launch
+struct ExpDwProblem {
+  const void* x;        // [N][H][W][Cin] block input
+  const void* w_e; const float* sc_e; const float* sh_e;      // expand: leading [C][Cin] of the stored weights, SubnetNorm
+  const void* w_d; const float* sc_d; const float* sh_d;      // depthwise: centre window's first tap, SubnetNorm
+  void* y;              // [N][Ho][Wo][C]
+  float* pool_part;     // squeeze-excite pool: sums of the stored outputs, [N][tiles][C], or nullptr
+  int N, H, W, Cin, C, Ho, Wo, k, stride;
+  int we_k, wd_r, wd_s; // element strides of the stored weights: expand output channel, depthwise tap row / column
+  int act;              // of both layers
+  unsigned x_bytes, we_bytes;
+  // filled by the launcher: output rows, 16-wide row segments and requests per block; tiles, channel groups; LDS layout
+  int th, ntx, rq, tiles_x, tiles_y, chunks, CW, plane, req_plane, x_lds;
+  int tile_start, tiles;
+};
+struct ExpDwArgs { int n; int total_tiles; ExpDwProblem p[SNA_MAX_GROUPS]; };
+
 struct SeProblem {
   const void* x;        // [N][HW][C] depthwise output
   void* y;              // gated output (may alias x)
@@ -213,6 +230,10 @@ hipError_t launch_depthwise(const DwGroupArgs& a, hipStream_t s);
 hipError_t launch_norm_calibrate(const NormCalArgs& a, hipStream_t s);
 hipError_t launch_norm_apply(const NormApplyArgs& a, int dtype, hipStream_t s);
 int depthwise_pool_blocks(int Ho, int Wo, int C);   // blocks per request of a depthwise layer with the fused pool
+hipError_t launch_expand_dw(const ExpDwArgs& a, hipStream_t s);
+bool expand_dw_ok(const ExpDwProblem& p);                          // can the fused kernel run this block
+int expand_dw_pool_parts(int Ho, int Wo, int k, int stride);              // pool sums per request it leaves
+int expand_dw_pool_parts_max(int side);                            // ... at most, over outputs up to side x side
 hipError_t launch_se(const SeGroupArgs& a, hipStream_t s);
 hipError_t launch_layernorm(const LnGroupArgs& a, hipStream_t s);
 hipError_t launch_attention(const AttnGroupArgs& a, hipStream_t s);

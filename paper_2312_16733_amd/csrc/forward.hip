@@ -608,6 +608,48 @@ struct Fwd {
     p.k = k; p.stride = stride; p.pad = k / 2;
     p.Ho = out_size(p.H, k, stride); p.Wo = out_size(p.W, k, stride);
   }
+  // MBV3: expand and depthwise of block j of stage s as one launch, for the groups it can serve (g.fused_xd tells the
+  // slots that follow).  Left to the separate layers: calibration, which wants every layer's bare output, and shapes
+  // outside the fused kernel's range (a matter of the layer's shape alone, so a request always takes the same path).
+  void expand_dw_slot(const std::string& pre, int s, int j, int st) {
+    const sna_arch_desc& a = T().arch;
+    ExpDwArgs xa;
+    xa.n = 0;
+    double flops = 0, bytes = 0, mac_sum = 0;
+    for (Group& g : groups) {
+      g.fused_xd = false;
+      if (net->calibrating || j >= g.cfg->depth[s]) continue;                     // LayerSelect
+      ConvProblem e;
+      memset(&e, 0, sizeof(e));
+      e.N = g.n; e.H = g.H; e.W = g.W; e.C = g.C;
+      slice_conv(e, tensor(pre + "expand.w"), g.cfg->block_mid_ch[s][j], 1, 1);
+      DwProblem d;
+      memset(&d, 0, sizeof(d));
+      d.H = g.H; d.W = g.W;
+      slice_dw(d, tensor(pre + "dw.w"), g.cfg->block_kernel[s][j], st);
+      ExpDwProblem p;
+      memset(&p, 0, sizeof(p));
+      p.x = g.cur; p.x_bytes = e.x_bytes;
+      p.w_e = e.w; p.we_k = e.wk; p.we_bytes = e.w_bytes;
+      p.sc_e = scale_of(pre + "sn1", g.cfg->subnet_id); p.sh_e = shift_of(pre + "sn1", g.cfg->subnet_id);
+      p.w_d = d.w; p.wd_r = d.wr; p.wd_s = d.ws;
+      p.sc_d = scale_of(pre + "sn2", g.cfg->subnet_id); p.sh_d = shift_of(pre + "sn2", g.cfg->subnet_id);
+      p.y = g.buf[3];
+      p.pool_part = a.stage_se[s] ? g.small : nullptr;        // the gate's average pool rides on this launch
+      p.N = g.n; p.H = g.H; p.W = g.W; p.Cin = g.C; p.C = e.K; p.Ho = d.Ho; p.Wo = d.Wo; p.k = d.k; p.stride = st;
+      p.act = a.stage_act[s];
+      if (!expand_dw_ok(p)) continue;
+      g.fused_xd = true;
+      const double px_in = (double)p.N * p.H * p.W, px_out = (double)p.N * p.Ho * p.Wo;
+      const double mac = px_in * p.Cin * p.C + px_out * p.C * p.k * p.k;
+      mac_sum += mac;
+      flops += 2 * mac;
+      bytes += 2.0 * (px_in * p.Cin + px_out * p.C) + 2.0 * p.C * (p.Cin + p.k * p.k) + 16.0 * p.C;
+      xa.p[xa.n++] = p;
+    }
+    macs += (int64_t)mac_sum;
+    if (xa.n) emit(PlanOp::EXPDW, 0, 0, KC_DEPTHWISE, flops, bytes, xa);
+  }
   void se_slot(const std::function<bool(Group&, SeProblem&)>& fill) {
     SeGroupArgs a;
     a.n = 0;
@@ -973,8 +1015,9 @@ sna_status Fwd::run_mbv3(const void*, float* logits) {
       const int st = j == 0 ? a.stage_stride[s] : 1;
       const int act = a.stage_act[s];
       auto on = [&](const Group& g) { return j < g.cfg->depth[s]; };      // LayerSelect
+      expand_dw_slot(pre, s, j, st);
       conv_slot(false, [&](Group& g, ConvProblem& p) {
-        if (!on(g)) return false;
+        if (!on(g) || g.fused_xd) return false;
         p.x = g.cur; p.N = g.n; p.H = g.H; p.W = g.W; p.C = g.C;
         slice_conv(p, tensor(pre + "expand.w"), g.cfg->block_mid_ch[s][j], 1, 1);
         sn(p, pre + "sn1", g);
@@ -982,7 +1025,7 @@ sna_status Fwd::run_mbv3(const void*, float* logits) {
         return true;
       });
       dw_slot([&](Group& g, DwProblem& p) {
-        if (!on(g)) return false;
+        if (!on(g) || g.fused_xd) return false;
         p.x = g.buf[2]; p.N = g.n; p.H = g.H; p.W = g.W; p.C = g.cfg->block_mid_ch[s][j];
         slice_dw(p, tensor(pre + "dw.w"), g.cfg->block_kernel[s][j], st);
         p.scale = scale_of(pre + "sn2", g.cfg->subnet_id); p.shift = shift_of(pre + "sn2", g.cfg->subnet_id);
@@ -1011,7 +1054,7 @@ sna_status Fwd::run_mbv3(const void*, float* logits) {
           p.w2 = wptr(t2); p.b2 = (const float*)wptr(tensor(pre + "se.fc2.b")); p.w2_stride = t2.dims[1];
           const int ho = out_size(g.H, 3, st), wo = out_size(g.W, 3, st);
           p.N = g.n; p.HW = ho * wo; p.C = m; p.Q = g.cfg->block_aux_ch[s][j];
-          p.pool_segs = depthwise_pool_blocks(ho, wo, m); p.inv_hw = 1.f / (float)p.HW;
+          p.pool_segs = g.fused_xd ? expand_dw_pool_parts(ho, wo, g.cfg->block_kernel[s][j], st) : depthwise_pool_blocks(ho, wo, m); p.inv_hw = 1.f / (float)p.HW;
           if (net->calibrating) { p.pool_segs = 1; p.inv_hw = 1.f; }      // g.small holds the mean itself
           p.pooled = g.small;                                  // written by the depthwise launch above
           p.hidden = g.small + (size_t)p.pool_segs * g.n * m;
@@ -1211,6 +1254,7 @@ static hipError_t run_op(const PlanOp& op, hipStream_t s) {
     case PlanOp::PAD: return launch_pad_input(*(const PadArgs*)a, s);
     case PlanOp::STEMPOOL: return launch_stem_pool(*(const StemPoolArgs*)a, s);
     case PlanOp::MBV3HEAD: return launch_mbv3_head(*(const Mbv3HeadArgs*)a, s);
+    case PlanOp::EXPDW: return launch_expand_dw(*(const ExpDwArgs*)a, s);
     case PlanOp::NORMCAL: return launch_norm_calibrate(*(const NormCalArgs*)a, s);
     case PlanOp::NORMAPPLY: return launch_norm_apply(*(const NormApplyArgs*)a, op.flag, s);
   }
@@ -1266,6 +1310,11 @@ static void visit_io_pointers(const PlanOp& op, F&& f) {
       for (int i = 0; i < a->n; ++i) { at(&a->p[i].x); at(&a->p[i].y); }
       break;
     }
+    case PlanOp::EXPDW: {
+      const ExpDwArgs* a = (const ExpDwArgs*)base;
+      for (int i = 0; i < a->n; ++i) { at(&a->p[i].x); at(&a->p[i].y); }
+      break;
+    }
     case PlanOp::NORMCAL: break;          // reads the scratch region, writes the statistics table
     case PlanOp::NORMAPPLY: { const NormApplyArgs* a = (const NormApplyArgs*)base; at(&a->res); at(&a->y); break; }
   }
@@ -1309,6 +1358,13 @@ static std::string describe_op(const PlanOp& op) {
     for (int i = 0; i < a.n; ++i) {
       const DwProblem& q = a.p[i];
       snprintf(t, sizeof(t), " [N=%d H=%d C=%d %dx%d/%d]", q.N, q.H, q.C, q.k, q.k, q.stride);
+      out += t;
+    }
+  } else if (op.type == PlanOp::EXPDW) {
+    const ExpDwArgs& a = *(const ExpDwArgs*)op.args.data();
+    for (int i = 0; i < a.n; ++i) {
+      const ExpDwProblem& q = a.p[i];
+      snprintf(t, sizeof(t), " [N=%d H=%d W=%d Cin=%d C=%d %dx%d/%d]", q.N, q.H, q.W, q.Cin, q.C, q.k, q.k, q.stride);
       out += t;
     }
   } else if (op.type == PlanOp::SE) {

@@ -46,6 +46,7 @@ struct Group {
   std::vector<int> reqs;             // their positions in the call, ascending
   bool contiguous = true;
   bool raw_input = false;            // cur points at the caller's unpadded request images
+  bool fused_xd = false;             // the block being emitted runs its expand and depthwise layers as one launch
   char* buf[NBUF] = {nullptr};
   char* inbuf = nullptr;
   float* small = nullptr;
@@ -57,7 +58,7 @@ struct Group {
 
 // One recorded kernel launch of a forward call.
 struct PlanOp {
-  enum Type { IGEMM, KREDUCE, DIRECT, MAXPOOL, GAP, DW, SE, LN, ATTN, COPY, PAD, STEMPOOL, MBV3HEAD, NORMCAL, NORMAPPLY } type;
+  enum Type { IGEMM, KREDUCE, DIRECT, MAXPOOL, GAP, DW, SE, LN, ATTN, COPY, PAD, STEMPOOL, MBV3HEAD, EXPDW, NORMCAL, NORMAPPLY } type;
   int variant = 0, flag = 0;         // igemm: tile variant, chunked kernel; direct / pool: dtype
   int kc = 0;                        // kernel class for the per-launch timing
   double flops = 0, bytes = 0;

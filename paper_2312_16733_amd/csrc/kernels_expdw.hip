@@ -1,0 +1,418 @@
+// First half of an inverted-residual block in one launch: pointwise expand + SubnetNorm + activation, and the depthwise
+// k x k convolution on its output + SubnetNorm + activation, with the squeeze-excite pool's partial sums; both
+// convolutions on bf16 MFMA.
+//
+// The expanded tensor is the widest of the network (3 to 6 times the block's input); as two launches it was written to
+// memory and fetched back (3 + k) / 4 * k times per element by a depthwise kernel bound by the texture path and by
+// instruction issue (95 VALU instructions per output at k = 7).  Here a block owns a spatial tile (of one request, or of
+// the same small image in several) and 16 expanded channels:
+//   A  the in-image input pixels the tile needs, halo included, go through v_mfma_f32_16x16x32_bf16 16 pixels at a time
+//      (pixels as rows, channels as columns: a lane ends up with 4 pixels of one channel), are normalised, activated and
+//      rounded to bf16 as a stored activation would be, and go to LDS channel by channel, [channel][row][column], with
+//      zeros outside the image;
+//   B  the depthwise convolution is a contraction per channel and kernel row r: 16 output columns q of a row are
+//      Y[q] += sum_j X[j] T_r[j][q] with the band matrix T_r[j][q] = w[r][j - q], so that one MFMA takes 16 row segments
+//      of 16 outputs (its rows: any 16 segments of the tile, each reading 32 consecutive columns of its row at one
+//      16-byte LDS read per lane), 7 MFMAs a 7 x 7 kernel.  A lane's part of T_r is a window of the kernel row shifted
+//      by the lane's place in the band: the rows lie in LDS between zeros, once at even and once at odd alignment, so
+//      that it is four aligned words.  The zeros of the band are 78 % of the products at k = 7, and it is still 5 times
+//      the rate of the dot-product instructions; what bounds B is its LDS reads (1 KB per MFMA).
+// The results wait in registers until the block is done with the planes, are turned channel-fastest through LDS and
+// stored, 32 bytes per pixel.
+//
+// Measured, batch 64, expand + depthwise as two launches -> here (event-bracketed): 56^2, 24 -> 144, 7 x 7: 23.7 + 91.5 ->
+// 55.6 us; 28^2, 40 -> 240: 12.6 + 47.9 -> 30.3; 14^2, 112 -> 672: 12.3 + 42.7 -> 35.2; 7^2, 160 -> 960: 8.5 + 21.1 -> 28.1;
+// 112^2, stride 2, 16 -> 96: 44.8 + 90.4 -> 105.9; one request, 12^2, 112 -> 336: 7.1 + 17.9 -> 9.3.  With 4 waves per block
+// instead of 8 the first took 71.6 us (waves wait for each other's phases), with half the LDS per block, 3 blocks per CU
+// and more halo, 82; the same design with v_dot2_f32_bf16 in B (56 VGPRs of weight pairs) 87.8 us and 15.7 us for a lone
+// 6^2 x 960 layer against 8.7.
+//
+// The tile depends on the layer's shape alone, and every sum is taken in a fixed order, so a request's result does not
+// depend on what it is batched with.
+#include "igemm_common.h"
+
+namespace sna {
+
+constexpr int XD_CH = 16;           // expanded channels per block
+constexpr int XD_NT = 512;          // threads: with the LDS two blocks fit on a CU, 4 waves per SIMD
+constexpr int XD_SEG = 16;          // outputs per row segment
+constexpr int XD_GROUPS = 4;        // MFMA groups of 16 segments per block, at most
+constexpr int XD_OUT_PX = XD_CH / 2 + 1;                 // staged output: words per pixel, padded against bank conflicts
+constexpr int XD_OUT_SEG = XD_SEG * XD_OUT_PX + 4;       // words per segment: 4 segments on lie 16 banks away
+constexpr int XD_TROW = 16;         // words per kernel row of the band table: 4 even-aligned, 4 zeros, 4 odd-aligned, 4 zeros
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef unsigned u32x4w __attribute__((ext_vector_type(4), aligned(4)));
+
+// LDS layout and tile of one problem, the same on host and device
+struct XdGeom {
+  int th, ntx, rq;                  // output rows, 16-wide segments per row, requests per block
+  int tiles_y, tiles_x;
+  int IH, CW;                       // rows and columns (elements) of a channel plane; column 0 is input column x0 * stride - 4
+  int plane, req_plane;             // bytes per channel plane (an odd number of 16-byte units) and per request
+};
+
+template <int K, int STRIDE>
+__global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs args) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  // consecutive items (the channel groups of a tile, which read the same input) on one XCD
+  const int per_xcd = gridDim.x >> 3;
+  const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (item >= args.total_tiles) return;
+  ExpDwProblem p = args.p[0];
+  if (args.n > 1) {
+    const int g = find_problem(args, item);
+    if (g > 0) p = args.p[g];
+  }
+  int local = item - p.tile_start;
+  const int chunk = local % p.chunks; local /= p.chunks;
+  const int tx = local % p.tiles_x; local /= p.tiles_x;
+  const int ty = local % p.tiles_y;
+  const int n0 = local / p.tiles_y * p.rq;                      // first request of the block
+  const int rq = p.N - n0 < p.rq ? p.N - n0 : p.rq;
+  constexpr int PAD = K / 2, OFF = 4 - PAD;                     // output column q reads plane columns q * STRIDE + OFF + s
+  constexpr int KB = ((XD_SEG - 1) * STRIDE + OFF + K + 31) / 32;     // MFMAs per kernel row
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, grp = lane >> 4;
+  const int Cin = p.Cin, C = p.C, KS = (Cin + 31) >> 5, c0 = chunk * XD_CH;
+  const int py0 = ty * p.th, qx0 = tx * p.ntx * XD_SEG;         // first output of the tile
+  const int iy0 = py0 * STRIDE - PAD, ix0 = qx0 * STRIDE - 4;   // input pixel behind plane cell (0, 0)
+  const int th_v = p.Ho - py0 < p.th ? p.Ho - py0 : p.th;
+  const int tw_v = p.Wo - qx0 < p.ntx * XD_SEG ? p.Wo - qx0 : p.ntx * XD_SEG;
+
+  char* const planes = smem;
+  unsigned* const ttab = (unsigned*)(smem + p.x_lds);           // [4 zeros][XD_CH][K][XD_TROW]
+  char* const wfrag = (char*)(ttab + 4 + XD_CH * K * XD_TROW);  // [KS][64 lanes][16 bytes]: expand weights as MFMA columns
+  uint4* const qtab = (uint4*)(wfrag + KS * 1024);              // per quad of pixels: plane offset, masks, input offset
+
+  // in-image rectangle of input pixels that valid outputs of this tile read, in quads of 4 columns
+  const int y0 = iy0 < 0 ? 0 : iy0, y_need = iy0 + (th_v - 1) * STRIDE + K, y1 = y_need < p.H ? y_need : p.H;
+  const int xa = ix0 < 0 ? 0 : ix0, x_need = ix0 + OFF + (tw_v - 1) * STRIDE + K, x1 = x_need < p.W ? x_need : p.W;
+  const int rh = y1 - y0, nq = (x1 - xa + 3) >> 2, quads = rq * rh * nq, ngroups = (quads + 3) >> 2;
+
+  constexpr unsigned OOB = 0x80000000u;
+  const __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc((void*)p.x, 0, (int)p.x_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrc_we = __builtin_amdgcn_make_buffer_rsrc((void*)p.w_e, 0, (int)p.we_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrc_y = __builtin_amdgcn_make_buffer_rsrc(p.y, 0, p.N * p.Ho * p.Wo * C * 2, 0x00020000);
+
+  // ---- set-up: every load goes out before its first use ----------------------------------------
+  constexpr int WF_U = 1;                                       // 64 KS fragments: up to 256 input channels without a loop
+  auto we_off = [&](int i) {                                    // fragment i: channel i % 16, elements 8 (i / 16) ..
+    const int c = c0 + (i & 15), k = (i >> 4) * 8;
+    return c < C && k < Cin ? (unsigned)((c * p.we_k + k) * 2) : OOB;
+  };
+  u32x4 wf[WF_U];
+#pragma unroll
+  for (int u = 0; u < WF_U; ++u) wf[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc_we, we_off(tid + u * XD_NT), 0, 0));
+  // thread (r, c) fetches kernel row r of channel c
+  static_assert(K * XD_CH <= XD_NT, "one thread per kernel row");
+  unsigned wrow[8];
+  {
+    const int c = c0 + (tid & 15), r = tid >> 4;
+    const bf16_t* w = (const bf16_t*)p.w_d + (long)r * p.wd_r + c;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) wrow[s] = s < K && r < K && c < C ? (unsigned)w[s * p.wd_s] : 0u;
+  }
+  const int ce = c0 + l16;                                      // this lane's expanded channel
+  const float se = ce < C ? p.sc_e[ce] : 0.f, he = ce < C ? p.sh_e[ce] : 0.f;
+
+  const unsigned magic_nq = nq > 1 ? 0xFFFFFFFFu / (unsigned)nq + 1u : 0u, magic_rh = rh > 1 ? 0xFFFFFFFFu / (unsigned)rh + 1u : 0u;
+  for (int i = tid; i < ngroups * 4; i += XD_NT) {
+    const int t = nq > 1 ? (int)__umulhi((unsigned)i, magic_nq) : i, cq = i - t * nq;
+    const int rr = rh > 1 ? (int)__umulhi((unsigned)t, magic_rh) : t, ry = t - rr * rh;
+    const int x = xa + 4 * cq, left = x1 - x;
+    uint4 e;
+    e.x = (unsigned)(rr * p.req_plane + ((y0 - iy0 + ry) * p.CW + x - ix0) * 2);
+    e.y = left >= 2 ? 0xffffffffu : 0xffffu;
+    e.z = left >= 4 ? 0xffffffffu : (left == 3 ? 0xffffu : 0u);
+    e.w = (unsigned)((((n0 + rr) * p.H + y0 + ry) * p.W + x) * Cin * 2);
+    if (i >= quads) { e.x = 0xffffffffu; e.w = OOB; }
+    qtab[i] = e;
+  }
+  for (int i = tid; i < rq * p.req_plane / 16; i += XD_NT) *(uint4*)(planes + i * 16) = make_uint4(0, 0, 0, 0);
+  __syncthreads();
+
+#pragma unroll
+  for (int u = 0; u < WF_U; ++u)
+    if (tid + u * XD_NT < KS * 64) *(u32x4*)(wfrag + (tid + u * XD_NT) * 16) = wf[u];
+  for (int i = tid + WF_U * XD_NT; i < KS * 64; i += XD_NT)
+    *(u32x4*)(wfrag + i * 16) = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc_we, we_off(i), 0, 0));
+  if (tid < K * XD_CH) {
+    unsigned* const row = ttab + 4 + ((tid & 15) * K + (tid >> 4)) * XD_TROW;
+    *(uint4*)row = make_uint4(wrow[0] | (wrow[1] << 16), wrow[2] | (wrow[3] << 16), wrow[4] | (wrow[5] << 16), wrow[6]);
+    *(uint4*)(row + 4) = make_uint4(0, 0, 0, 0);
+    *(uint4*)(row + 8) = make_uint4(wrow[0] << 16, wrow[1] | (wrow[2] << 16), wrow[3] | (wrow[4] << 16), wrow[5] | (wrow[6] << 16));
+    *(uint4*)(row + 12) = make_uint4(0, 0, 0, 0);
+  }
+  if (tid == 0) *(uint4*)ttab = make_uint4(0, 0, 0, 0);
+  __syncthreads();
+
+  // ---- A: expand ------------------------------------------------------------------------------
+  // A wave takes G groups of 16 pixels at a time, with the loads of the next G in flight: 4 where one step of 32 input
+  // channels is the whole reduction, 2 for two steps, else one group, 5 steps at a time.
+  auto expand = [&](auto act_c, auto g_c) {
+    constexpr int ACT = decltype(act_c)::value, G = decltype(g_c)::value, KU = G == 4 ? 1 : (G == 2 ? 2 : 5);
+    auto load_px = [&](int pg, int ks0, u32x4 (&v)[G][KU]) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const unsigned off = pg + g < ngroups ? qtab[(pg + g) * 4 + (l16 >> 2)].w : OOB;
+        const unsigned base = off + (unsigned)((l16 & 3) * Cin * 2 + grp * 16);
+#pragma unroll
+        for (int j = 0; j < KU; ++j)
+          if (KU == 1 || ks0 + j < KS)
+            v[g][j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                rsrc_x, (ks0 + j) * 32 + grp * 8 < Cin && off != OOB ? base + (ks0 + j) * 64 : OOB, 0, 0));
+      }
+    };
+    u32x4 cur[G][KU], nxt[G][KU];
+    constexpr int STEP = G * (XD_NT / 64);
+    load_px(wave * G, 0, cur);
+    for (int pg = wave * G; pg < ngroups; pg += STEP) {
+      f32x4 acc[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int ks0 = 0; ks0 < KS; ks0 += KU) {
+        if (G == 1 && ks0 + KU < KS) load_px(pg, ks0 + KU, nxt);
+        else if (pg + STEP < ngroups) load_px(pg + STEP, 0, nxt);
+#pragma unroll
+        for (int j = 0; j < KU; ++j)
+          if (KU == 1 || ks0 + j < KS) {
+            const uint4 w = *(const uint4*)(wfrag + ((ks0 + j) * 64 + lane) * 16);
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+              acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, cur[g][j]), __builtin_bit_cast(bf16x8, w), acc[g], 0, 0, 0);
+          }
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+          for (int j = 0; j < KU; ++j) cur[g][j] = nxt[g][j];
+      }
+#pragma unroll
+      for (int g = 0; g < G; ++g) {                             // rows 4 grp .. 4 grp + 3 of the 16 pixels: one quad
+        if (pg + g >= ngroups) break;
+        const uint4 e = qtab[(pg + g) * 4 + grp];
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = apply_act(fmaf(acc[g][i], se, he), ACT);
+        if (e.x != 0xffffffffu)
+          *(uint2*)(planes + l16 * p.plane + e.x) = make_uint2(pack_bf16x2(v[0], v[1]) & e.y, pack_bf16x2(v[2], v[3]) & e.z);
+      }
+    }
+  };
+  auto expand_k = [&](auto act_c) {
+    if (KS == 1) expand(act_c, std::integral_constant<int, 4>{});
+    else if (KS == 2) expand(act_c, std::integral_constant<int, 2>{});
+    else expand(act_c, std::integral_constant<int, 1>{});
+  };
+  if (p.act == SNA_ACT_RELU) expand_k(std::integral_constant<int, SNA_ACT_RELU>{});
+  else expand_k(std::integral_constant<int, SNA_ACT_HSWISH>{});
+  __syncthreads();
+
+  // ---- B: depthwise ---------------------------------------------------------------------------
+  const int seg_req = p.th * p.ntx, nseg = rq * seg_req, ng = (nseg + 15) >> 4;
+  const unsigned magic_ntx = p.ntx > 1 ? 0xFFFFFFFFu / (unsigned)p.ntx + 1u : 0u;
+  const unsigned magic_sr = seg_req > 1 ? 0xFFFFFFFFu / (unsigned)seg_req + 1u : 0u;
+  int seg_off[XD_GROUPS];                                       // plane offset of this lane's segment, MFMA row l16
+#pragma unroll
+  for (int g = 0; g < XD_GROUPS; ++g) {
+    int i = g * 16 + l16;
+    i = i < nseg ? i : nseg - 1;
+    const int rr = seg_req > 1 ? (int)__umulhi((unsigned)i, magic_sr) : i, ii = i - rr * seg_req;
+    const int pr = p.ntx > 1 ? (int)__umulhi((unsigned)ii, magic_ntx) : ii, t = ii - pr * p.ntx;
+    seg_off[g] = rr * p.req_plane + (pr * STRIDE * p.CW + t * XD_SEG * STRIDE) * 2;
+  }
+  // this lane's 8 elements of the band: columns 32 kb + 8 grp .. + 7 against output l16
+  int col_off[KB], t_off[KB];
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb) {
+    const int j0 = 32 * kb + 8 * grp, sh = l16 * STRIDE + OFF - j0;
+    col_off[kb] = j0 < (XD_SEG - 1) * STRIDE + OFF + K ? j0 * 2 : 0;      // past the band every weight is 0: read any column
+    int b = -(sh >> 1);                                         // floor
+    b = b < -4 ? -4 : (b > 4 ? 4 : b);
+    t_off[kb] = ((sh & 1) ? 8 : 0) + b;
+  }
+  constexpr int PAIRS = XD_CH / 2 / (XD_NT / 64);               // channel pairs per wave
+  unsigned packed[PAIRS][XD_GROUPS][4];
+  auto depthwise = [&](auto act_c) {
+    constexpr int ACT = decltype(act_c)::value;
+#pragma unroll
+    for (int pi = 0; pi < PAIRS; ++pi) {
+      float first[XD_GROUPS][4];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int cl = (wave * PAIRS + pi) * 2 + h, c = c0 + cl;
+        const float sc = c < C ? p.sc_d[c] : 0.f, sh = c < C ? p.sh_d[c] : 0.f;
+        u32x4 band[K][KB];
+#pragma unroll
+        for (int r = 0; r < K; ++r)
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb) band[r][kb] = *(const u32x4w*)(ttab + 4 + (cl * K + r) * XD_TROW + t_off[kb]);
+#pragma unroll
+        for (int g = 0; g < XD_GROUPS; ++g) {
+          if (g >= ng) continue;
+          const char* src = planes + cl * p.plane + seg_off[g];
+          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int r = 0; r < K; ++r) {
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) {
+              const uint4 a = *(const uint4*)(src + col_off[kb]);
+              acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, band[r][kb]), acc, 0, 0, 0);
+            }
+            src += p.CW * 2;
+          }
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const float y = apply_act(fmaf(acc[v], sc, sh), ACT);
+            if (h == 0) first[g][v] = y;
+            else packed[pi][g][v] = pack_bf16x2(first[g][v], y);
+          }
+        }
+      }
+    }
+  };
+  if (p.act == SNA_ACT_RELU) depthwise(std::integral_constant<int, SNA_ACT_RELU>{});
+  else depthwise(std::integral_constant<int, SNA_ACT_HSWISH>{});
+  __syncthreads();                                              // every wave is done with the planes
+
+  // ---- output: [segment][16 columns][channel pairs] through LDS --------------------------------
+  unsigned* const outs = (unsigned*)smem;
+#pragma unroll
+  for (int g = 0; g < XD_GROUPS; ++g) {
+    if (g >= ng) continue;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int pi = 0; pi < PAIRS; ++pi)
+        outs[(g * 16 + 4 * grp + v) * XD_OUT_SEG + l16 * XD_OUT_PX + wave * PAIRS + pi] = packed[pi][g][v];
+  }
+  __syncthreads();
+  const int cp = tid & 7, slot = tid >> 3, q = slot & 15, c = c0 + 2 * cp;
+  for (int rr = 0; rr < rq; ++rr) {
+    float s0 = 0.f, s1 = 0.f;
+    for (int i = slot >> 4; i < seg_req; i += XD_NT / 128) {
+      const int pr = p.ntx > 1 ? (int)__umulhi((unsigned)i, magic_ntx) : i, qq = (i - pr * p.ntx) * XD_SEG + q;
+      const unsigned v = outs[(rr * seg_req + i) * XD_OUT_SEG + q * XD_OUT_PX + cp];
+      if (pr < th_v && qq < tw_v && c < C) {
+        __builtin_amdgcn_raw_buffer_store_b32(v, rsrc_y, (unsigned)(((((n0 + rr) * p.Ho + py0 + pr) * p.Wo + qx0 + qq) * C + c) * 2), 0, 0);
+        s0 += __uint_as_float(v << 16);
+        s1 += __uint_as_float(v & 0xffff0000u);
+      }
+    }
+    if (!p.pool_part) continue;
+    // pool: each thread over its segments in order, the 8 columns of a wave by a fixed tree, the waves in order
+#pragma unroll
+    for (int d = 8; d <= 32; d <<= 1) { s0 += __shfl_xor(s0, d, 64); s1 += __shfl_xor(s1, d, 64); }
+    float2* const red = (float2*)ttab;
+    __syncthreads();
+    if (lane < 8) red[wave * 8 + lane] = make_float2(s0, s1);
+    __syncthreads();
+    if (tid < 8 && c < C) {
+      float2 a = red[tid];
+#pragma unroll
+      for (int w = 1; w < XD_NT / 64; ++w) { const float2 b = red[w * 8 + tid]; a.x += b.x; a.y += b.y; }
+      float* out = p.pool_part + ((long)((n0 + rr) * p.tiles_y + ty) * p.tiles_x + tx) * C + c;
+      out[0] = a.x; out[1] = a.y;
+    }
+  }
+#endif
+}
+
+// Tile of a layer, from its shape alone.  Stride 1: whole rows up to 64 columns and as many rows as leave two blocks per
+// CU their LDS (halo rows are computed twice, so tall tiles), small images several requests to a block, which share the
+// band fragments.  Stride 2: 16 columns (twice the input columns, two MFMAs a kernel row) and 16 rows.
+constexpr size_t XD_PLANES_MAX = 52 * 1024;
+static XdGeom xd_geometry(int Ho, int Wo, int k, int stride) {
+  XdGeom g;
+  const int segs = (Wo + XD_SEG - 1) / XD_SEG, off = 4 - k / 2;
+  const int max_x = stride == 1 ? 4 : 1;
+  g.tiles_x = (segs + max_x - 1) / max_x;
+  g.ntx = (segs + g.tiles_x - 1) / g.tiles_x;
+  g.tiles_x = (segs + g.ntx - 1) / g.ntx;
+  int units = ((g.ntx - 1) * XD_SEG * stride + (XD_SEG - 1) * stride + off + k + 7) / 8;
+  units |= 1;                                                   // odd: 16 rows then start on 16 different bank groups
+  g.CW = units * 8;
+  auto plane = [&](int th) { return ((((th - 1) * stride + k) * units) | 1) * 16; };
+  int th = XD_GROUPS * 16 / g.ntx;
+  if (stride == 2 && th > 16) th = 16;
+  if (th > Ho) th = Ho;
+  while (th > 1 && (size_t)plane(th) * XD_CH > XD_PLANES_MAX) --th;
+  g.tiles_y = (Ho + th - 1) / th;
+  g.th = (Ho + g.tiles_y - 1) / g.tiles_y;
+  g.tiles_y = (Ho + g.th - 1) / g.th;
+  g.IH = (g.th - 1) * stride + k;
+  g.plane = plane(g.th);
+  g.req_plane = g.plane * XD_CH;
+  g.rq = 1;
+  if (g.tiles_x == 1 && g.tiles_y == 1)
+    while (g.rq < 4 && (g.rq + 1) * g.th * g.ntx <= 32 && (size_t)(g.rq + 1) * g.req_plane <= XD_PLANES_MAX) ++g.rq;
+  return g;
+}
+static size_t xd_planes(const XdGeom& g) {                      // also holds the staged output
+  const size_t x = (size_t)g.rq * g.req_plane, o = (size_t)((g.rq * g.th * g.ntx + 15) / 16 * 16) * XD_OUT_SEG * 4;
+  return (x > o ? x : o);
+}
+static size_t xd_lds(const XdGeom& g, int k, int Cin) {
+  return xd_planes(g) + (size_t)(4 + XD_CH * k * XD_TROW) * 4 + (size_t)((Cin + 31) / 32) * 1024 +
+         (size_t)(g.rq * g.IH * (g.CW / 4) + 3) / 4 * 4 * 16;
+}
+constexpr size_t XD_LDS_MAX = 160 * 1024;
+
+int expand_dw_pool_parts(int Ho, int Wo, int k, int stride) {
+  const XdGeom g = xd_geometry(Ho, Wo, k, stride);
+  return g.tiles_x * g.tiles_y;
+}
+// Tiles are at least 16 x 16 or the whole image (see xd_geometry: the planes of 16 rows fit for every k and stride).
+int expand_dw_pool_parts_max(int side) { return ((side + 15) / 16) * ((side + 15) / 16); }
+
+bool expand_dw_ok(const ExpDwProblem& p) {
+  if ((p.k != 3 && p.k != 5 && p.k != 7) || (p.stride != 1 && p.stride != 2) || p.Cin % 8 || p.C % 8) return false;
+  if (p.act != SNA_ACT_RELU && p.act != SNA_ACT_HSWISH) return false;
+  if ((double)p.N * p.H * p.W * p.Cin * 2 >= 2147483648.0 || (double)p.N * p.Ho * p.Wo * p.C * 2 >= 2147483648.0) return false;  // 32-bit buffer offsets
+  const XdGeom g = xd_geometry(p.Ho, p.Wo, p.k, p.stride);
+  return xd_lds(g, p.k, p.Cin) <= XD_LDS_MAX && g.tiles_x * g.tiles_y <= expand_dw_pool_parts_max(p.Ho > p.Wo ? p.Ho : p.Wo);
+}
+
+hipError_t launch_expand_dw(const ExpDwArgs& a, hipStream_t s) {
+  // one launch per (kernel size, stride) present among the problems
+  for (int k = 3; k <= 7; k += 2)
+    for (int st = 1; st <= 2; ++st) {
+      ExpDwArgs b;
+      b.n = 0;
+      int start = 0;
+      size_t lds = 0;
+      for (int i = 0; i < a.n; ++i) {
+        if (a.p[i].k != k || a.p[i].stride != st) continue;
+        if (!expand_dw_ok(a.p[i])) return hipErrorInvalidValue;
+        ExpDwProblem& p = b.p[b.n++];
+        p = a.p[i];
+        const XdGeom g = xd_geometry(p.Ho, p.Wo, k, st);
+        p.th = g.th; p.ntx = g.ntx; p.rq = g.rq; p.tiles_x = g.tiles_x; p.tiles_y = g.tiles_y;
+        p.CW = g.CW; p.plane = g.plane; p.req_plane = g.req_plane; p.x_lds = (int)xd_planes(g);
+        p.chunks = (p.C + XD_CH - 1) / XD_CH;
+        p.tile_start = start;
+        p.tiles = (p.N + g.rq - 1) / g.rq * g.tiles_x * g.tiles_y * p.chunks;
+        start += p.tiles;
+        const size_t l = xd_lds(g, k, p.Cin);
+        if (l > lds) lds = l;
+      }
+      if (!b.n) continue;
+      b.total_tiles = start;
+      const int blocks = (start + 7) / 8 * 8;
+      hipError_t e = hipSuccess;
+#define SNA_XD(KK, SS)                                                                                                \
+  if (k == KK && st == SS) {                                                                                          \
+    e = hipFuncSetAttribute((const void*)expand_dw_kernel<KK, SS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)XD_LDS_MAX); \
+    if (e != hipSuccess) return e;                                                                                    \
+    hipLaunchKernelGGL((expand_dw_kernel<KK, SS>), dim3(blocks), dim3(XD_NT), lds, s, b);                             \
+  }
+      SNA_XD(3, 1); SNA_XD(5, 1); SNA_XD(7, 1); SNA_XD(3, 2); SNA_XD(5, 2); SNA_XD(7, 2);
+#undef SNA_XD
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+  return hipSuccess;
+}
+
+}  // namespace sna

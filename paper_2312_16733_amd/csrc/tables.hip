@@ -5,6 +5,8 @@
 
 #include "host.h"
 
+#include <algorithm>
+
 namespace sna {
 
 static thread_local char g_err[512] = "";
@@ -164,7 +166,7 @@ sna_status build_tables(const sna_arch_desc* a, ArchTables* t) {
         upd((int64_t)ho * ho * (m > c ? m : c));
         if (a->stage_se[s]) {                        // pool partial sums of the depthwise blocks, then the gate's hidden layer
           if (m / 8 > 256) return fail(SNA_E_ARCH, "block_max_mid[%d][%d]=%d: squeeze-excite layers take at most 2048 channels", s, j, m);
-          const int64_t need = (int64_t)depthwise_pool_blocks(ho, ho, m) * m + q;
+          const int64_t need = (int64_t)std::max(depthwise_pool_blocks(ho, ho, m), expand_dw_pool_parts_max(ho)) * m + q;
           if (need > small) small = need;
         }
       }

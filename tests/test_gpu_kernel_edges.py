@@ -43,3 +43,27 @@ def test_fp32_conv_tile_edges(torch_mod, stages, res, batch):
             check_parity(got, oracle.forward(spec, W, S, c, x), "fp32", f"{stages} {res} x{batch}", tol=1.6e-5)
     finally:
         net.close()
+
+
+# Fused expand + depthwise: images whose stage outputs are 65 x 33, 33 x 17, 17 x 9 .. and 1 x 1 (segments of 16 outputs
+# with remainders 1 and 15, several column tiles, several requests per block with a partial last block), every kernel
+# size.  Tolerance: the family's 2e-2 (each stored tensor is rounded to bf16 once); requests are bitwise independent of
+# the batch they come in.
+@pytest.mark.parametrize("h,w,batch", [(130, 66, 2), (36, 140, 3), (260, 30, 1), (8, 9, 17), (57, 57, 5)])
+def test_expand_depthwise_tile_edges(torch_mod, h, w, batch):
+    import oracle
+    import paper_2312_16733_amd as sna
+    spec = synth.MBV3Spec(n_classes=40, res_choices=(260,))
+    W, S, C = setup(spec, 4)
+    net = sna.Supernet(spec, W, S, 4, 20)
+    try:
+        for c in C:
+            c.in_h, c.in_w = h, w
+            x = synth.make_inputs(spec, batch, h, w, 12)
+            print("expand + depthwise", h, w, batch, c.block_kernel, flush=True)
+            got = forward(torch_mod, net, spec, [c], np.zeros(batch), x)
+            check_parity(got[:2], oracle.forward(spec, W, S, c, x[:2]), "bf16", f"{h} x {w}")
+            last = forward(torch_mod, net, spec, [c], np.zeros(1), x[-1:])
+            np.testing.assert_array_equal(got[-1:], last)
+    finally:
+        net.close()
