@@ -17,7 +17,7 @@ constexpr int AT_LD = AT_S + 8;    // LDS row stride (bf16) for V^T and P
 // The scores are computed transposed (K as the row operand, Q as the column operand), so that a lane
 // of the accumulator holds one query (column lane % 32) and 16 of the 32 keys of each key block:
 // the softmax reduction over keys runs inside a lane plus one exchange with lane ^ 32, and the
-// probabilities are already laid out as the row operand of the second product (row = query, 8
+// probabilities are already laid out as the column operand of the second product (column = query, 8
 // values per K slice) without a trip through LDS.  The slice's 8 values are keys
 // {base + 4 hi + 0..3, base + 8 + 4 hi + 0..3} (hi = lane / 32) instead of 8 consecutive keys; a
 // sum over keys may take them in any order as long as the V operand uses the same one, and V^T in
@@ -36,40 +36,55 @@ __global__ __launch_bounds__(256) void attention_kernel(const AttnGroupArgs args
   const bf16_t* Kp = (const bf16_t*)p.k + (long)b * S * ld + h * AT_D;
   const bf16_t* V = (const bf16_t*)p.v + (long)b * S * ld + h * AT_D;
 
-  // V^T into LDS: Vt[d][key], zero for keys >= S
-  for (int idx = tid; idx < AT_S * (AT_D / 8); idx += 256) {
-    const int key = idx >> 3, d8 = idx & 7;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (key < S) v = *(const uint4*)(V + (long)key * ld + d8 * 8);
-    const unsigned u[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      Vt[(d8 * 8 + 2 * e) * AT_LD + key] = (bf16_t)(u[e] & 0xffffu);
-      Vt[(d8 * 8 + 2 * e + 1) * AT_LD + key] = (bf16_t)(u[e] >> 16);
-    }
-  }
-
+  // Bound by latency: a load round trip, two short chains of MFMAs and the softmax between them (36 to 384 blocks), so
+  // all of a thread's loads go out together, from rows clamped to the last one: a guarded load would be waited for
+  // before the next guard.  128 tokens x 3 requests x 12 heads: 9.7 -> 7.1 us a launch, 32 requests 13.5 -> 12.3, with
+  // the dword V^T writes and 8-byte output stores below.  Scores of keys >= S are masked below and query rows >= S are not stored, so only V needs zeros.
   const int r32 = lane & 31, hi = lane >> 5;
   const int qrow = wave * 32 + r32;
-  bf16x8 qf[4];
+  const int qld = qrow < S ? qrow : S - 1;
+  uint4 qv[4], kv[4][4], vv[2][2];
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (qrow < S) v = *(const uint4*)(Q + (long)qrow * ld + ks * 16 + hi * 8);
-    qf[ks] = __builtin_bit_cast(bf16x8, v);
+  for (int ks = 0; ks < 4; ++ks) qv[ks] = *(const uint4*)(Q + (long)qld * ld + ks * 16 + hi * 8);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int key = j * 32 + r32 < S ? j * 32 + r32 : S - 1;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) kv[j][ks] = *(const uint4*)(Kp + (long)key * ld + ks * 16 + hi * 8);
   }
+  // V: a lane takes two neighbouring keys of a head-dim octet, so that it writes V^T as whole dwords and a wave's 64
+  // lanes write 64 consecutive ones
+#pragma unroll
+  for (int it = 0; it < 2; ++it)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int key = 2 * lane + e < S ? 2 * lane + e : S - 1;
+      vv[it][e] = *(const uint4*)(V + (long)key * ld + (wave + 4 * it) * 8);
+    }
+  __builtin_amdgcn_sched_barrier(0);     // keep the loads ahead of everything that waits for one of them
+
   // sc[j][v]: query qrow, key 32 j + 8 (v / 4) + 4 hi + v % 4
   f32x16 sc[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) sc[j][v] = 0.f;
-    const int key = j * 32 + r32;
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (key < S) v = *(const uint4*)(Kp + (long)key * ld + ks * 16 + hi * 8);
-      sc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), qf[ks], sc[j], 0, 0, 0);
+    for (int ks = 0; ks < 4; ++ks)
+      sc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kv[j][ks]),
+                                                      __builtin_bit_cast(bf16x8, qv[ks]), sc[j], 0, 0, 0);
+  }
+  // V^T into LDS: Vt[d][key], zero for keys >= S
+#pragma unroll
+  for (int it = 0; it < 2; ++it) {
+    const unsigned lo_ok = 2 * lane < S ? 0xffffffffu : 0u, hi_ok = 2 * lane + 1 < S ? 0xffffffffu : 0u;
+    const unsigned a[4] = {vv[it][0].x & lo_ok, vv[it][0].y & lo_ok, vv[it][0].z & lo_ok, vv[it][0].w & lo_ok};
+    const unsigned c[4] = {vv[it][1].x & hi_ok, vv[it][1].y & hi_ok, vv[it][1].z & hi_ok, vv[it][1].w & hi_ok};
+    bf16_t* col = Vt + (wave + 4 * it) * 8 * AT_LD + 2 * lane;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      *(unsigned*)(col + (2 * e) * AT_LD) = (a[e] & 0xffffu) | (c[e] << 16);
+      *(unsigned*)(col + (2 * e + 1) * AT_LD) = (a[e] >> 16) | (c[e] & 0xffff0000u);
     }
   }
   // softmax over the keys of this lane's query, in base 2: exp(x / 8 - max) = exp2((x - max') * log2(e) / 8)
@@ -117,17 +132,20 @@ __global__ __launch_bounds__(256) void attention_kernel(const AttnGroupArgs args
         const bf16_t* vrow = Vt + (jd * 32 + r32) * AT_LD + key0;
         const uint2 v0 = *(const uint2*)vrow, v1 = *(const uint2*)(vrow + 8);
         const u32x4 vw = {v0.x, v0.y, v1.x, v1.y};
-        oc[jd] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, pw), __builtin_bit_cast(bf16x8, vw), oc[jd], 0, 0, 0);
+        oc[jd] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vw), __builtin_bit_cast(bf16x8, pw), oc[jd], 0, 0, 0);
       }
     }
-  bf16_t* O = (bf16_t*)p.o + (long)b * S * ld + h * AT_D;
+  // the second product is transposed as well: oc[jd][v] is query qrow, head dim 32 jd + 8 (v / 4) + 4 hi + v % 4, so a
+  // lane stores four neighbouring values at a time
+  if (qrow < S) {
+    bf16_t* O = (bf16_t*)p.o + (long)b * S * ld + h * AT_D + (long)qrow * ld + 4 * hi;
 #pragma unroll
-  for (int jd = 0; jd < 2; ++jd)
+    for (int jd = 0; jd < 2; ++jd)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int row = wave * 32 + 8 * (v >> 2) + 4 * hi + (v & 3);
-      if (row < S) O[(long)row * ld + jd * 32 + r32] = f32_to_bf16(oc[jd][v]);
-    }
+      for (int v4 = 0; v4 < 4; ++v4)
+        *(uint2*)(O + jd * 32 + 8 * v4) = make_uint2(pack_bf16x2(oc[jd][4 * v4], oc[jd][4 * v4 + 1]),
+                                                     pack_bf16x2(oc[jd][4 * v4 + 2], oc[jd][4 * v4 + 3]));
+  }
 }
 
 hipError_t launch_attention(const AttnGroupArgs& a, hipStream_t s) {

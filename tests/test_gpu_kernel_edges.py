@@ -67,3 +67,25 @@ def test_expand_depthwise_tile_edges(torch_mod, h, w, batch):
             np.testing.assert_array_equal(got[-1:], last)
     finally:
         net.close()
+
+
+# Attention and LayerNorm: token counts around the 32-query waves and the key pairs a lane transposes (odd counts, one
+# token, a full block), hidden sizes whose last 64-lane group of octets is partial (9, 65 octets) or full (256).
+# Tolerance: the family's.
+@pytest.mark.parametrize("tokens,hidden,heads", [(1, 72, 1), (2, 520, 3), (31, 72, 2), (65, 520, 1), (127, 136, 2),
+                                                 (128, 2048, 1)])
+def test_attention_layernorm_edges(torch_mod, tokens, hidden, heads):
+    import oracle
+    import paper_2312_16733_amd as sna
+    spec = synth.TransformerSpec(n_classes=40, hidden=hidden, n_heads=heads, ffn=96, max_layers=2, seq_len=tokens,
+                                 depth_choices=(1, 2))
+    W, S, C = setup(spec, 2)
+    net = sna.Supernet(spec, W, S, 2, 5)
+    try:
+        c = C[-1]
+        x = synth.make_inputs(spec, 5, c.in_h, c.in_w, 13)
+        print("attention", tokens, hidden, heads, flush=True)
+        got = forward(torch_mod, net, spec, [c], np.zeros(5), x)
+        check_parity(got, oracle.forward(spec, W, S, c, x), "bf16", f"{tokens} x {hidden}")
+    finally:
+        net.close()
