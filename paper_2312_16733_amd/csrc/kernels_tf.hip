@@ -176,14 +176,28 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const LnGroupArgs args) 
   if (row >= p.rows) return;
   const int octs = p.cols >> 3;
   const bf16_t* x = (const bf16_t*)p.x + row * p.cols;
-  float v[LN_MAX_OCT][8];
+  // The row, gamma and beta are requested together: the per-column vectors then arrive under the two reductions instead of
+  // a round trip after them (384 rows of 768, 24 launches a forward: 715 -> 703 us for the forward; 4096 rows: unchanged).  An octet past the row reads the last one and is left out of the sums and the store.
+  uint4 u[LN_MAX_OCT];
+  float v[LN_MAX_OCT][8], ga[LN_MAX_OCT][8], be[LN_MAX_OCT][8];
+#pragma unroll
+  for (int i = 0; i < LN_MAX_OCT; ++i)
+    if (64 * i < octs) {                                   // uniform
+      const int o = lane + 64 * i < octs ? lane + 64 * i : octs - 1;
+      u[i] = *(const uint4*)(x + o * 8);
+    }
+#pragma unroll
+  for (int i = 0; i < LN_MAX_OCT; ++i)
+    if (64 * i < octs) {
+      const int o = lane + 64 * i < octs ? lane + 64 * i : octs - 1;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { ga[i][e] = p.gamma[o * 8 + e]; be[i][e] = p.beta[o * 8 + e]; }
+    }
   float sum = 0.f;
 #pragma unroll
   for (int i = 0; i < LN_MAX_OCT; ++i) {
-    const int o = lane + 64 * i;
-    if (o < octs) {
-      const uint4 u = *(const uint4*)(x + o * 8);
-      const unsigned w[4] = {u.x, u.y, u.z, u.w};
+    if (lane + 64 * i < octs) {
+      const unsigned w[4] = {u[i].x, u[i].y, u[i].z, u[i].w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         v[i][2 * e] = __uint_as_float(w[e] << 16);
@@ -213,7 +227,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const LnGroupArgs args) 
     if (o < octs) {
       float r[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) r[e] = fmaf((v[i][e] - mean) * rstd, p.gamma[o * 8 + e], p.beta[o * 8 + e]);
+      for (int e = 0; e < 8; ++e) r[e] = fmaf((v[i][e] - mean) * rstd, ga[i][e], be[i][e]);
       uint4 out;
       out.x = pack_bf16x2(r[0], r[1]);
       out.y = pack_bf16x2(r[2], r[3]);
