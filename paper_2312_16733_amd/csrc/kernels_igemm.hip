@@ -30,8 +30,8 @@ namespace sna {
 
 // Waves per SIMD the register allocation must leave room for: tiles with short reductions are
 // launched with a small LDS request and then run that many blocks per CU.
-constexpr int igemm_min_waves(int bm, int bn) {
-  return bm * bn > 128 * 128 ? 2 : (bm * bn >= 128 * 128 ? 3 : (bm * bn >= 128 * 96 ? 4 : 5));
+constexpr int igemm_min_waves(int bm, int bn, int ns) {
+  return bm * bn > 128 * 128 ? 2 : (bm * bn >= 128 * 128 ? 3 : (bm * bn >= 128 * 96 || (bm * bn == 128 * 64 && ns == 2) ? 4 : 5));
 }
 
 // Accesses that are coherent across the chip without cache-wide flushes: relaxed atomics at agent
@@ -150,7 +150,7 @@ __device__ __forceinline__ void reduce_octet(const ConvProblem& p, const float* 
 template <int BM, int BN, int WARPS_M, int WARPS_N, int NS, bool CHUNKED, bool WS>
 __global__ __launch_bounds__(64 * WARPS_M * WARPS_N * (WS ? 2 : 1),
                              WS ? (BM * BN >= 128 * 128 ? 2 : 4)
-                                : (CHUNKED ? (BM * BN == 128 * 64 ? 3 : (BM * BN > 128 * 128 ? 1 : 2)) : igemm_min_waves(BM, BN)))
+                                : (CHUNKED ? (BM * BN == 128 * 64 ? 3 : (BM * BN > 128 * 128 ? 1 : 2)) : igemm_min_waves(BM, BN, NS)))
 void igemm_kernel(const ConvGroupArgs args) {
 #if defined(__HIP_DEVICE_COMPILE__)        // the host pass needs the symbol only, not the body
   using Cfg = IgemmCfg<BM, BN, WARPS_M, WARPS_N, NS>;
@@ -309,28 +309,46 @@ void igemm_kernel(const ConvGroupArgs args) {
   // `fresh`: the accumulators start a new sum at this step (first MFMA of each takes C = 0)
   auto compute = [&](int stage, const bool fresh) {
     const unsigned ab = a_lane + stage * Cfg::STAGE_B, bb = b_lane + stage * Cfg::STAGE_B;
-    if constexpr (TM * TN == 1) {
+    if constexpr (TM * TN == 1 || (TM * TN == 2 && NS == 2)) {
       if (fresh) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[0][0][v] = 0.f;
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
       }
-      // one 32x32 tile per wave: a slice is one MFMA, too short to hide an LDS read, so the reads of the whole step go
-      // out together and each MFMA waits only for its own pair (64x64 tiles, a lone request: 100 x 136 outputs of a 3x3
-      // over 136 channels 13.6 -> 12.6 us, 32x128 tiles 13.8 -> 12.9; the smallest ResNet-shaped subnet 419 -> 412)
-      constexpr int NSL = BK / 16;
-      u32x4 a1[NSL], b1[NSL];
+      // one or two 32x32 tiles per wave: a slice's MFMAs are too short to hide an LDS read, so the reads of the whole step
+      // go out together and each slice waits only for its own (64x64 tiles, a lone request: 100 x 136 outputs of a 3x3
+      // over 136 channels 13.6 -> 12.6 us, 32x128 tiles 13.8 -> 12.9; the smallest ResNet-shaped subnet 419 -> 412).
+      // Two tiles per wave: only with the two-stage ring, which full batches use (three blocks share a CU; 64 requests of
+      // the largest ResNet-shaped subnet 3083 -> 2969 us, four waves per SIMD so that nothing spills).  The deeper
+      // rings serve calls of few tiles, one block per CU, and lose by it: 64x128 tiles, one request of the largest
+      // ResNet-shaped subnet 989 -> 1013 us.
+      constexpr int NSL = BK / 16, RD = TM + TN;      // slices per step, reads per slice
+      static_assert(RD * NSL <= 15, "lgkmcnt range");
+      u32x4 a1[NSL][TM], b1[NSL][TN];
 #pragma unroll
       for (int ks = 0; ks < NSL; ++ks) {
-        a1[ks] = lds_read_b128(ab + frag_off[ks], 0);
-        b1[ks] = lds_read_b128(bb + frag_off[ks], 0);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) a1[ks][i] = lds_read_b128(ab + frag_off[ks], i * 32 * ROW_B);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) b1[ks][j] = lds_read_b128(bb + frag_off[ks], j * 32 * ROW_B);
       }
       auto slice = [&](auto ks_c) {
         constexpr int ks = decltype(ks_c)::value;
-        __builtin_amdgcn_s_waitcnt(0xc07f | ((2 * (NSL - 1 - ks)) << 8));       // lgkmcnt: the later slices' reads
-        asm volatile("" : "+v"(a1[ks]), "+v"(b1[ks]));
+        __builtin_amdgcn_s_waitcnt(0xc07f | ((RD * (NSL - 1 - ks)) << 8));      // lgkmcnt: the later slices' reads
+#pragma unroll
+        for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(a1[ks][i]));
+#pragma unroll
+        for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(b1[ks][j]));
         __builtin_amdgcn_sched_barrier(0);
-        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a1[ks]), __builtin_bit_cast(bf16x8, b1[ks]),
-                                                            acc[0][0], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a1[ks][i]),
+                                                                __builtin_bit_cast(bf16x8, b1[ks][j]), acc[i][j], 0, 0, 0);
       };
       static_assert(NSL == 4, "four slices per step");
       slice(std::integral_constant<int, 0>{});
