@@ -89,3 +89,39 @@ def test_attention_layernorm_edges(torch_mod, tokens, hidden, heads):
         check_parity(got, oracle.forward(spec, W, S, c, x), "bf16", f"{tokens} x {hidden}")
     finally:
         net.close()
+
+
+# Non-finite activations of the fused expand + depthwise layer: one pixel of request 0 is so large that the expanded tensor
+# overflows to Inf around it.  The depthwise weights are negative, so that every output whose own taps see it is ReLU(-Inf)
+# = 0 and the logits stay finite; an output that does not see it keeps its value.  (Inf times the zeros of the band matrix
+# would make NaN, and ReLU 0, of all 16 outputs of the row segment.)  The oracle refuses to overflow; a pixel of 2^40 in
+# the place of 2^100 drives the same outputs below zero without.  Tolerance: the family's.
+@pytest.mark.parametrize("stride,h,w", [(1, 24, 20), (2, 24, 20), (1, 14, 76), (2, 22, 76)])
+@pytest.mark.parametrize("k", [3, 5, 7])
+def test_overflow_stays_in_its_window(torch_mod, k, stride, h, w):
+    import oracle
+    import paper_2312_16733_amd as sna
+    spec = synth.MBV3Spec(n_classes=40, stage_ch=(24,), stage_stride=(stride,), stage_se=(False,), stage_act=("relu",),
+                          max_depth=(1,), depth_choices=(1,), kernel_choices=(k,), res_choices=(80,), tail_ch=64, fc_ch=64)
+    W, S, C = setup(spec, 2)
+    W["s0.b0.dw.w"] = -np.abs(W["s0.b0.dw.w"])
+    S["s0.b0.sn1"][:, 2] *= 1e10
+    S["s0.b0.sn2"][:, 2] *= 1e-10
+    S["s0.b0.sn2"][:, 3] += 3.0
+    c, batch = C[-1], 3
+    c.in_h, c.in_w = h, w
+    x = synth.make_inputs(spec, batch, h, w, 14)
+    ref_plain = oracle.forward(spec, W, S, c, x)
+    x[0, h // 2, w // 2] = 2.0 ** 40
+    ref = oracle.forward(spec, W, S, c, x)
+    x[0, h // 2, w // 2] = 2.0 ** 100
+    assert np.abs(ref[0] - ref_plain[0]).max() > 0.04 * np.abs(ref[0]).max()
+    net = sna.Supernet(spec, W, S, 2, batch)
+    try:
+        print("overflow", k, stride, h, w, flush=True)
+        got = forward(torch_mod, net, spec, [c], np.zeros(batch), x)
+        check_parity(got, ref, "bf16", f"{k} x {k} / {stride}, {h} x {w}")
+        for i in range(1, batch):
+            np.testing.assert_array_equal(got[i:i + 1], forward(torch_mod, net, spec, [c], np.zeros(1), x[i:i + 1]))
+    finally:
+        net.close()
