@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 import synth
-from helpers import check_parity, setup
+from helpers import check_parity, rel_err, setup
 
 pytestmark = pytest.mark.gpu
 
@@ -123,5 +123,33 @@ def test_overflow_stays_in_its_window(torch_mod, k, stride, h, w):
         check_parity(got, ref, "bf16", f"{k} x {k} / {stride}, {h} x {w}")
         for i in range(1, batch):
             np.testing.assert_array_equal(got[i:i + 1], forward(torch_mod, net, spec, [c], np.zeros(1), x[i:i + 1]))
+    finally:
+        net.close()
+
+
+# A weight of -Inf at the first tap of one fp32 stem channel, over positive pixels: every output whose window holds that tap
+# inside the image is ReLU(-Inf) = 0, and the outputs of the first row and column, whose tap lies in the padding, keep their
+# value (padding zeros times the weight would make NaN of them, and ReLU 0).  A weight of -2^60 does the same with finite
+# numbers.  in_ch 3 takes the scalar loads, 4 the vector ones.  Tolerance: as for the fp32 convolutions above.
+@pytest.mark.parametrize("in_ch", [3, 4])
+def test_infinite_weight_stays_in_its_tap(torch_mod, in_ch):
+    import oracle
+    import paper_2312_16733_amd as sna
+    spec = synth.TinySpec(in_ch=in_ch, res_choices=(9,))
+    W, S, C = setup(spec, 2)
+    c, batch = C[-1], 3
+    x = np.abs(synth.make_inputs(spec, batch, 9, 9, 15)) + np.float32(0.1)
+    W["stem.w"][1, 0, 0, :] = -2.0 ** 60
+    ref = oracle.forward(spec, W, S, c, x)
+    all_zero = dict(W)
+    all_zero["stem.w"] = W["stem.w"].copy()
+    all_zero["stem.w"][1] = -2.0 ** 60
+    assert rel_err(oracle.forward(spec, all_zero, S, c, x), ref).min() > 5e-4
+    W["stem.w"][1, 0, 0, :] = -np.inf
+    net = sna.Supernet(spec, W, S, 2, batch)
+    try:
+        print("infinite weight", in_ch, flush=True)
+        got = forward(torch_mod, net, spec, [c], np.zeros(batch), x)
+        check_parity(got, ref, "fp32", f"in_ch {in_ch}", tol=1.6e-5)
     finally:
         net.close()
