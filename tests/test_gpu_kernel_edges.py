@@ -45,10 +45,23 @@ def test_fp32_conv_tile_edges(torch_mod, stages, res, batch):
         net.close()
 
 
+def depthwise_launches(torch, net, spec, cfgs, route, x):
+    """-> (problems that ran expand and depthwise as one launch, problems of separate depthwise launches) of a forward."""
+    net.profile_enable(True)
+    try:
+        forward(torch, net, spec, cfgs, route, x)
+        lines = [l for l in net.profile_read_launches().split("\n") if " depthwise " in l]
+        net.profile_read()                                      # forgets the launches read
+    finally:
+        net.profile_enable(False)
+    fused = sum(l.count("Cin=") for l in lines)
+    return fused, sum(l.count("[N=") for l in lines) - fused
+
+
 # Fused expand + depthwise: images whose stage outputs are 65 x 33, 33 x 17, 17 x 9 .. and 1 x 1 (segments of 16 outputs
 # with remainders 1 and 15, several column tiles, several requests per block with a partial last block), every kernel
-# size.  Tolerance: the family's 2e-2 (each stored tensor is rounded to bf16 once); requests are bitwise independent of
-# the batch they come in.
+# size, all of a forward's blocks in one launch each.  Tolerance: the family's 2e-2 (each stored tensor is rounded to bf16
+# once); requests are bitwise independent of the batch and of the other subnets of the call they come in.
 @pytest.mark.parametrize("h,w,batch", [(130, 66, 2), (36, 140, 3), (260, 30, 1), (8, 9, 17), (57, 57, 5)])
 def test_expand_depthwise_tile_edges(torch_mod, h, w, batch):
     import oracle
@@ -57,14 +70,48 @@ def test_expand_depthwise_tile_edges(torch_mod, h, w, batch):
     W, S, C = setup(spec, 4)
     net = sna.Supernet(spec, W, S, 4, 20)
     try:
+        x = synth.make_inputs(spec, batch, h, w, 12)
+        alone = []
         for c in C:
             c.in_h, c.in_w = h, w
-            x = synth.make_inputs(spec, batch, h, w, 12)
             print("expand + depthwise", h, w, batch, c.block_kernel, flush=True)
             got = forward(torch_mod, net, spec, [c], np.zeros(batch), x)
-            check_parity(got[:2], oracle.forward(spec, W, S, c, x[:2]), "bf16", f"{h} x {w}")
+            check_parity(got, oracle.forward(spec, W, S, c, x), "bf16", f"{h} x {w}")
             last = forward(torch_mod, net, spec, [c], np.zeros(1), x[-1:])
             np.testing.assert_array_equal(got[-1:], last)
+            assert depthwise_launches(torch_mod, net, spec, [c], np.zeros(batch), x) == (sum(c.depth), 0)
+            alone.append(got)
+        route = np.arange(batch) * 3 % len(C)
+        mixed = forward(torch_mod, net, spec, C, route, x)
+        np.testing.assert_array_equal(mixed, np.stack([alone[r][i] for i, r in enumerate(route)]))
+    finally:
+        net.close()
+
+
+# Wide block inputs.  168 and 264 channels: a reduction of more than one pass of five steps, and more weight fragments than
+# one per thread.  4800 channels: the expand weights no longer fit in LDS beside the tile, and the block runs as separate
+# expand and depthwise launches, with the gate's pool in the depthwise one.  Tolerance: the family's.
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("k", [3, 5, 7])
+def test_expand_depthwise_wide_inputs(torch_mod, k, stride):
+    import oracle
+    import paper_2312_16733_amd as sna
+    spec = synth.MBV3Spec(n_classes=40, stage_ch=(168, 264, 4800, 24), stage_stride=(1, 2, 1, stride),
+                          stage_se=(False, True, False, True), stage_act=("relu", "hswish", "relu", "hswish"),
+                          max_depth=(1, 1, 1, 1), depth_choices=(1,), expand_choices=(0.1,), kernel_choices=(k,),
+                          res_choices=(80,), tail_ch=64, fc_ch=64)
+    W, S, C = setup(spec, 2)
+    c, batch, h, w = C[-1], 3, 70, 62
+    c.in_h, c.in_w = h, w
+    x = synth.make_inputs(spec, batch, h, w, 16)
+    ref = oracle.forward(spec, W, S, c, x)
+    net = sna.Supernet(spec, W, S, 2, batch)
+    try:
+        print("wide inputs", k, stride, c.block_mid_ch, flush=True)
+        got = forward(torch_mod, net, spec, [c], np.zeros(batch), x)
+        check_parity(got, ref, "bf16", f"{k} x {k} / {stride}")
+        np.testing.assert_array_equal(got[-1:], forward(torch_mod, net, spec, [c], np.zeros(1), x[-1:]))
+        assert depthwise_launches(torch_mod, net, spec, [c], np.zeros(batch), x) == (3, 1)
     finally:
         net.close()
 
