@@ -224,6 +224,7 @@ void igemm_tile_shape(int variant, int* bm, int* bn);
 int igemm_num_variants();
 hipError_t launch_direct_conv(const ConvGroupArgs& a, hipStream_t s);      // bf16
 hipError_t launch_conv_f32(const ConvGroupArgs& a, hipStream_t s);
+void conv_f32_tiles(ConvProblem& p);               // fills the tile counts launch_conv_f32 expects
 hipError_t launch_maxpool(const PoolGroupArgs& a, int dtype, hipStream_t s);
 hipError_t launch_gap(const PoolGroupArgs& a, int dtype, hipStream_t s);
 hipError_t launch_depthwise(const DwGroupArgs& a, hipStream_t s);
@@ -231,7 +232,7 @@ hipError_t launch_norm_calibrate(const NormCalArgs& a, hipStream_t s);
 hipError_t launch_norm_apply(const NormApplyArgs& a, int dtype, hipStream_t s);
 int depthwise_pool_blocks(int Ho, int Wo, int C);   // blocks per request of a depthwise layer with the fused pool
 hipError_t launch_expand_dw(const ExpDwArgs& a, hipStream_t s);
-bool expand_dw_ok(const ExpDwProblem& p);                          // can the fused kernel run this block
+bool expand_dw_ok(const ExpDwProblem& p);                          // can the fused kernel run this block (its shape, any batch)
 int expand_dw_pool_parts(int Ho, int Wo, int k, int stride);              // pool sums per request it leaves
 int expand_dw_pool_parts_max(int side);                            // ... at most, over outputs up to side x side
 hipError_t launch_se(const SeGroupArgs& a, hipStream_t s);

@@ -432,8 +432,12 @@ struct Fwd {
     int start = 0;
     double flops = 0, bytes = 0;
     for (ConvProblem& p : ps) {
-      p.tiles_n = (p.K + 15) / 16;
-      p.tiles = ((p.M + 255) / 256) * p.tiles_n;
+      if (T().arch.dtype == SNA_DTYPE_FP32) {
+        conv_f32_tiles(p);
+      } else {
+        p.tiles_n = (p.K + 15) / 16;
+        p.tiles = ((p.M + 255) / 256) * p.tiles_n;
+      }
       p.tile_start = start;
       start += p.tiles;
       a.p[a.n++] = p;
@@ -610,7 +614,9 @@ struct Fwd {
   }
   // MBV3: expand and depthwise of block j of stage s as one launch, for the groups it can serve (g.fused_xd tells the
   // slots that follow).  Left to the separate layers: calibration, which wants every layer's bare output, and shapes
-  // outside the fused kernel's range (a matter of the layer's shape alone, so a request always takes the same path).
+  // outside the fused kernel's range, block inputs of some 3000 channels and more (a matter of the layer's shape alone,
+  // so a request takes the same path in any batch).  The fused launch leaves the same bits as the separate ones but for
+  // the pool's sums, which it adds tile by tile: where fp32 does not hold such a sum exactly, a gate's last bit can differ.
   void expand_dw_slot(const std::string& pre, int s, int j, int st) {
     const sna_arch_desc& a = T().arch;
     ExpDwArgs xa;

@@ -391,13 +391,14 @@ int expand_dw_pool_parts(int Ho, int Wo, int k, int stride) {
   const XdGeom g = xd_geometry(Ho, Wo, k, stride);
   return g.tiles_x * g.tiles_y;
 }
-// Tiles are at least 16 x 16 or the whole image (see xd_geometry: the planes of 16 rows fit for every k and stride).
+// Each tile column has at least one 16-wide segment, and there are at most ceil(Ho / 16) tile rows: before the rows are
+// spread evenly a tile has min(16, Ho) at least (64 segments over at most 4 a row, and the planes of 17 rows fit for
+// every k and stride), and spreading them adds no tile.
 int expand_dw_pool_parts_max(int side) { return ((side + 15) / 16) * ((side + 15) / 16); }
 
 bool expand_dw_ok(const ExpDwProblem& p) {
   if ((p.k != 3 && p.k != 5 && p.k != 7) || (p.stride != 1 && p.stride != 2) || p.Cin % 8 || p.C % 8) return false;
   if (p.act != SNA_ACT_RELU && p.act != SNA_ACT_HSWISH) return false;
-  if ((double)p.N * p.H * p.W * p.Cin * 2 >= 2147483648.0 || (double)p.N * p.Ho * p.Wo * p.C * 2 >= 2147483648.0) return false;  // 32-bit buffer offsets
   const XdGeom g = xd_geometry(p.Ho, p.Wo, p.k, p.stride);
   return xd_lds(g, p.k, p.Cin) <= XD_LDS_MAX && g.tiles_x * g.tiles_y <= expand_dw_pool_parts_max(p.Ho > p.Wo ? p.Ho : p.Wo);
 }
@@ -415,6 +416,8 @@ hipError_t launch_expand_dw(const ExpDwArgs& a, hipStream_t s) {
         if (!expand_dw_ok(a.p[i])) return hipErrorInvalidValue;
         ExpDwProblem& p = b.p[b.n++];
         p = a.p[i];
+        if ((double)p.N * p.H * p.W * p.Cin * 2 >= 2147483648.0 || (double)p.N * p.Ho * p.Wo * p.C * 2 >= 2147483648.0)
+          return hipErrorInvalidValue;                          // 32-bit buffer offsets; slice_conv has refused such a call
         const XdGeom g = xd_geometry(p.Ho, p.Wo, k, st);
         p.th = g.th; p.ntx = g.ntx; p.rq = g.rq; p.tiles_x = g.tiles_x; p.tiles_y = g.tiles_y;
         p.CW = g.CW; p.plane = g.plane; p.req_plane = g.req_plane; p.x_lds = (int)xd_planes(g);

@@ -2,11 +2,11 @@
 //
 //   Y[m, k] = sum_{r,s,c} X[n, p*st + r - pad, q*st + s - pad, c] * W[k, r, s, c]
 //
-// These layers are short (at 4 images of 32 x 32 the largest has 1024 output pixels) and what bounds them is the
+// These layers are short (at 4 images of 32 x 32: 4096 output pixels of 16 channels down to 64 of 128) and what bounds them is the
 // serial chain of one output's reduction: with one thread per pixel and 16 channels a layer of 1152 terms took 150 us
 // on 8 CUs.  Here an output tile is 16 pixels x 16 channels of v_mfma_f32_16x16x4_f32 (fp32 products and sums), and a
 // long reduction is spread over the 8 waves of a block, which add their sums through LDS: the chain becomes 1/8 as long
-// and there are 32 .. 512 tiles where there were 4 .. 32.  Operands go from global memory (the whole net stays in L2)
+// and there are 32 .. 256 tiles where there were 4 .. 16 blocks.  Operands go from global memory (the whole net stays in L2)
 // straight to registers: a lane loads 4 consecutive reduction elements of its pixel and of its channel with one
 // 16-byte bounds-checked load each, which four MFMAs take element by element; the loads of four steps are in flight
 // ahead of the MFMAs that use them.
@@ -160,24 +160,19 @@ __global__ __launch_bounds__(64 * F32_WAVES) void conv_f32_kernel(const ConvGrou
 #endif
 }
 
+void conv_f32_tiles(ConvProblem& p) {
+  const int steps = (p.R * p.S * p.C + F32_STEP - 1) / F32_STEP;
+  const int rows_b = F32_TILE * F32_WAVES / f32_k_waves(steps);
+  p.tiles_n = (p.K + F32_TILE - 1) / F32_TILE;
+  p.tiles = (p.M + rows_b - 1) / rows_b * p.tiles_n;
+}
+
 hipError_t launch_conv_f32(const ConvGroupArgs& a, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
-  ConvGroupArgs b = a;
-  int start = 0;
   bool vec = true;
-  for (int i = 0; i < b.n; ++i) {
-    ConvProblem& p = b.p[i];
-    const int steps = (p.R * p.S * p.C + F32_STEP - 1) / F32_STEP;
-    const int rows_b = F32_TILE * F32_WAVES / f32_k_waves(steps);
-    vec = vec && p.C % 4 == 0;
-    p.tiles_n = (p.K + F32_TILE - 1) / F32_TILE;
-    p.tiles = (p.M + rows_b - 1) / rows_b * p.tiles_n;
-    p.tile_start = start;
-    start += p.tiles;
-  }
-  b.total_tiles = start;
-  if (vec) hipLaunchKernelGGL(conv_f32_kernel<true>, dim3(start), dim3(64 * F32_WAVES), 0, s, b);
-  else hipLaunchKernelGGL(conv_f32_kernel<false>, dim3(start), dim3(64 * F32_WAVES), 0, s, b);
+  for (int i = 0; i < a.n; ++i) vec = vec && a.p[i].C % 4 == 0;
+  if (vec) hipLaunchKernelGGL(conv_f32_kernel<true>, dim3(a.total_tiles), dim3(64 * F32_WAVES), 0, s, a);
+  else hipLaunchKernelGGL(conv_f32_kernel<false>, dim3(a.total_tiles), dim3(64 * F32_WAVES), 0, s, a);
   return hipGetLastError();
 }
 

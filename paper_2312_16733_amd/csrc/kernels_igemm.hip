@@ -297,7 +297,7 @@ void igemm_kernel(const ConvGroupArgs args) {
     }
   };
 
-  f32x16 acc[TM][TN];                      // written by the first MFMA of the first step
+  f32x16 acc[TM][TN];                      // written at the first step of a sum
 
   const int frag_row = lane & 31, frag_hi = lane >> 5, frag_sw = (frag_row >> 1) & 7;
   unsigned frag_off[BK / 16];              // swizzled byte offset of this lane's chunk in each 16-wide slice
@@ -306,7 +306,8 @@ void igemm_kernel(const ConvGroupArgs args) {
   const unsigned a_lane = lds0 + (wm * WTM + frag_row) * ROW_B;
   const unsigned b_lane = lds0 + (BM + wn * WTN + frag_row) * ROW_B;
 
-  // `fresh`: the accumulators start a new sum at this step (first MFMA of each takes C = 0)
+  // `fresh`: the accumulators start a new sum at this step (wave tiles of one or two 32x32 tiles clear them, the larger
+  // ones have the first MFMA of each take C = 0)
   auto compute = [&](int stage, const bool fresh) {
     const unsigned ab = a_lane + stage * Cfg::STAGE_B, bb = b_lane + stage * Cfg::STAGE_B;
     if constexpr (TM * TN == 1 || (TM * TN == 2 && NS == 2)) {
