@@ -38,7 +38,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const AttnGroupArgs args
 
   // Bound by latency: a load round trip, two short chains of MFMAs and the softmax between them (36 to 384 blocks), so
   // all of a thread's loads go out together, from rows clamped to the last one: a guarded load would be waited for
-  // before the next guard.  128 tokens x 3 requests x 12 heads: 9.7 -> 7.1 us a launch, 32 requests 13.5 -> 12.3, with
+  // before the next guard.  128 tokens x 3 requests x 12 heads: 9.6 -> 7.1 us a launch, 32 requests 13.4 -> 11.9, with
   // the dword V^T writes and 8-byte output stores below.  Scores of keys >= S are masked below and query rows >= S are not stored, so only V needs zeros.
   const int r32 = lane & 31, hi = lane >> 5;
   const int qrow = wave * 32 + r32;
