@@ -2,6 +2,7 @@
 // the SuperNet in layer order and issues one grouped launch per layer slot.  LayerSelect is
 // decided here: a block beyond a cfg's depth produces no problem, hence no launch and no copy.
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <functional>
@@ -140,23 +141,74 @@ struct Fwd {
     p.w_bytes = (unsigned)(wb - ((size_t)r0 * p.wr + (size_t)s0 * p.ws) * esize);
   }
 
-  // Tile choice (measured on MI355X): 128-row tiles with two blocks per CU; the column tile that
-  // pads the active out-channels least, wider for deep reductions; 64-row tiles when a layer has
-  // too few 128-row tiles to fill 256 CUs; 32 rows for head-sized M.
-  static int pick_variant(int M, int K, int depth) {
-    // variants: 0 128x128, 1 128x64, 2 128x96, 3 128x32, 4 64x64, 5 64x128, 6 32x128
-    if (M <= 32) return 6;
-    if (K <= 32) return 3;
-    int bn = 128, best = 1 << 30;
-    const int cand[3] = {128, 96, 64};
-    for (int c : cand) {
-      const int padded = (K + c - 1) / c * c;
-      const bool better = padded < best || (padded == best && depth < 1024);   // ties: narrower for shallow K
-      if (better) { best = padded; bn = c; }
-    }
-    const long tiles128 = (long)((M + 127) / 128) * ((K + bn - 1) / bn);
-    if (tiles128 < 256) return K <= 64 ? 4 : 5;
-    return bn == 128 ? 0 : (bn == 64 ? 1 : 2);
+  // Tile choice.  The expected time of a launch with a tile variant, in microseconds on MI355X, is
+  //   launch + per_cu * (block + steps * (step or step_taps [+ walk]))
+  // and, when reductions are spread over blocks, 1.9 us + 1.6 us per MB of partial sums.  per_cu is the launch's blocks per
+  // CU (whole below four: a second block on some CUs lasts as long as on all), `steps` the K steps one block walks, averaged
+  // over the blocks; step_taps is the step of a convolution with more than one tap, `walk` what folding chunk sums in
+  // registers adds to it where it costs occupancy.  The constants were fitted to 612 launch shapes of the three bf16
+  // families (batches 1 to 64, every variant with and without split reductions, in place inside a forward); the variant
+  // the formula picks is on average 3 % slower than the fastest of all variants (the best of some 70 timings each), where
+  // the rule it replaces, 128-row tiles and 64-row ones for launches below 256 tiles, was 35 % slower.
+  struct TileCost { int variant; float launch, block, step, step_taps, walk; };
+  static const TileCost* tile_costs(int* n) {
+    static const TileCost costs[] = {
+        {28, 3.69f, 0.25f, 0.088f, 0.117f, 0.f},         // 32x32, deep ring
+        {29, 3.01f, 0.91f, 0.212f, 0.259f, 0.f},         // 64x64, deep ring
+        {4, 3.20f, 0.46f, 0.247f, 0.312f, 0.f},          // 64x64
+        {27, 4.45f, 0.35f, 0.225f, 0.262f, 0.f},         // 64x64, one stage
+        {25, 4.08f, 0.50f, 0.345f, 0.421f, 0.054f},      // 64x128, one stage
+        {1, 3.88f, 0.79f, 0.357f, 0.363f, 0.f},          // 128x64
+        {2, 4.34f, 1.18f, 0.495f, 0.495f, 0.f},          // 128x96
+        {8, 3.46f, 1.28f, 0.305f, 0.349f, 0.f},          // 64x128, fetching waves
+        {9, 3.38f, 1.41f, 0.311f, 0.345f, 0.f},          // 128x64, fetching waves
+        {11, 2.55f, 3.03f, 0.484f, 0.481f, 0.f},         // 128x128, fetching waves
+        {22, 4.57f, 1.42f, 0.526f, 0.545f, 0.077f},      // 128x128, one stage
+        {12, 3.46f, 0.41f, 0.283f, 0.272f, 0.f},         // 128x32, two stages
+        {24, 5.17f, 1.11f, 0.457f, 0.451f, 0.091f},      // 128x96, one stage
+    };
+    *n = sizeof(costs) / sizeof(costs[0]);
+    return costs;
+  }
+  struct TileChoice { int variant; bool split; };
+  // For the problems ps[0 .. n), launched together: the variant, and whether chunked reductions are spread over blocks
+  // (split_mode 1: never, 2 and 3: always).
+  static TileChoice pick_tile(const ConvProblem* ps, size_t n, int split_mode) {
+    int n_costs = 0;
+    const TileCost* costs = tile_costs(&n_costs);
+    TileChoice best{1, split_mode >= 2};
+    double best_us = 0;
+    bool any = false;
+    for (int c = 0; c < n_costs; ++c)
+      for (int split = split_mode >= 2; split <= (split_mode == 1 ? 0 : 1); ++split) {
+        int bm, bn;
+        igemm_tile_shape(costs[c].variant, &bm, &bn);
+        double blocks = 0, work = 0, sums_mb = 0;
+        bool ok = true;
+        for (size_t i = 0; i < n; ++i) {
+          ConvProblem q = ps[i];
+          const int kt_all = (q.K8 + 7) / 8, per = chunk_steps(kt_all), parts = split ? (kt_all + per - 1) / per : 1;
+          q.parts = parts;
+          q.kt_part = parts > 1 ? per : 1 << 30;
+          ok = ok && igemm_variant_ok(costs[c].variant, q);
+          if (parts > 1) sums_mb += 4e-6 * parts * q.M * q.K;
+          const double b = (double)((q.M + bm - 1) / bm) * ((q.K + bn - 1) / bn) * parts;
+          blocks += b;
+          work += b * (parts > 1 ? per : kt_all) *
+                  ((q.R * q.S > 1 ? costs[c].step_taps : costs[c].step) + (parts == 1 && per < kt_all ? costs[c].walk : 0.f));
+        }
+        if (!ok) continue;
+        double per_cu = blocks / 256;
+        if (per_cu < 4) per_cu = std::ceil(per_cu);
+        double us = costs[c].launch + per_cu * (costs[c].block + work / blocks);
+        if (sums_mb > 0) us += 1.9 + 1.6 * sums_mb;
+        if (!any || us < best_us) {
+          any = true;
+          best_us = us;
+          best = {costs[c].variant, split != 0};
+        }
+      }
+    return best;
   }
 
   // Fill the launch-side fields of a problem for tile variant v (parts already decided).
@@ -255,7 +307,7 @@ struct Fwd {
       }
       return net->tuned.end();
     };
-    long tiles_all = 0;
+    const TileChoice choice = pick_tile(ps.data(), n, net->split_mode);
     for (size_t i = 0; i < n; ++i) {
       ConvProblem& q = ps[i];
       if (q.C % 8 || q.K % 8 || q.y_stride % 8 || q.res_stride % 8 || q.R * q.S > 64 ||
@@ -266,16 +318,15 @@ struct Fwd {
       q.parts = 1;
       q.kt_part = 1 << 30;
       auto it = find_tuned(q, 1, twins[i]);
-      var[i] = it != net->tuned.end() ? it->second : pick_variant(q.M, q.K, q.C * q.R * q.S);
+      var[i] = it != net->tuned.end() ? it->second : choice.variant;
       place(q, var[i]);
-      tiles_all += q.tiles_base;
       const int kt_all = (q.K8 + 7) / 8;
       q.kt_chunk = chunk_steps(kt_all);
       chunks[i] = (kt_all + q.kt_chunk - 1) / q.kt_chunk;
     }
-    // Too few tiles for the chip: give every chunk its own blocks and sum them in a second launch
-    // (a measured per-shape decision, where there is one, takes precedence).
-    const bool split_rule = net->split_mode >= 2 || (net->split_mode == 0 && tiles_all < 256);
+    // Too few tiles for the chip: every chunk gets its own blocks (a measured per-shape decision, where there is one,
+    // takes precedence).
+    const bool split_rule = choice.split;
     std::vector<ConvProblem> reduce;
     char* part_cur = net->partials;
     size_t counters_used = 0;
@@ -341,7 +392,7 @@ struct Fwd {
       auto it = find_tuned(q, q.parts, twins[i]);
       if (it != net->tuned.end()) var[i] = it->second;
       if (net->forced_variant >= 0 && igemm_variant_ok(net->forced_variant, q)) var[i] = net->forced_variant;
-      if (!igemm_variant_ok(var[i], q)) var[i] = pick_variant(q.M, q.K, q.C * q.R * q.S);
+      if (!igemm_variant_ok(var[i], q)) var[i] = pick_tile(&q, 1, q.parts > 1 ? 2 : 1).variant;
       place(q, var[i]);
     }
     if ((unify || n > 1) && !net->tuning) {

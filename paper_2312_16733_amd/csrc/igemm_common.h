@@ -18,9 +18,10 @@ constexpr int ROW_B = 128;         // bytes per LDS row (one K step of one tile 
 // (vmcnt is split over bits [3:0] and [15:14]; expcnt and lgkmcnt fields left at "no wait").
 constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 
-template <int BM, int BN, int WARPS_M, int WARPS_N, int NS>
+// FW: waves that only fetch, beside the computing ones (0: every wave does both)
+template <int BM, int BN, int WARPS_M, int WARPS_N, int NS, int FW = 0>
 struct IgemmCfg {
-  static constexpr int NWAVES = WARPS_M * WARPS_N, NTHREADS = 64 * NWAVES;
+  static constexpr int NWAVES = WARPS_M * WARPS_N, NTHREADS = 64 * (FW ? FW : NWAVES);   // computing waves, fetching threads
   static constexpr int WTM = BM / WARPS_M, WTN = BN / WARPS_N;
   static constexpr int TM = WTM / 32, TN = WTN / 32;
   static constexpr int PASS_ROWS = NTHREADS / 8;                 // tile rows fetched per pass of the block

@@ -1,0 +1,13 @@
+// Tile variants of the implicit-GEMM kernel with deep rings, for launches of few tiles.
+#include "igemm_kernel.h"
+
+namespace sna {
+
+#define SNA_DEEP_VARIANT(BM, BN, WM, WN, NS, FW) \
+  { BM, BN, 64 * (WM * WN + FW), IgemmCfg<BM, BN, WM, WN, NS, FW>::SMEM, NS, IgemmCfg<BM, BN, WM, WN, NS, FW>::STAGE_B, \
+    IgemmCfg<BM, BN, WM, WN, NS, FW>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, FW>, igemm_kernel<BM, BN, WM, WN, NS, true, FW>, false, true }
+const Variant kDeepVariants[kDeepVariantCount] = {
+    SNA_DEEP_VARIANT(32, 32, 1, 1, 8, 4), SNA_DEEP_VARIANT(64, 64, 2, 2, 8, 4),
+};
+
+}  // namespace sna

@@ -200,3 +200,33 @@ def test_infinite_weight_stays_in_its_tap(torch_mod, in_ch):
         check_parity(got, ref, "fp32", f"in_ch {in_ch}", tol=1.6e-5)
     finally:
         net.close()
+
+
+# Deep-ring tiles of the matrix kernel (the last variants): reductions of 1, 2 and 7..9 steps around the 8 stages of the
+# ring, whole and half groups of steps, 25 and 65 steps (two and four chunks, folded or spread over blocks) and 129 steps,
+# more than the tap table holds unless they are spread.  Same bits as the 128x64 tile, which walks the same order; the
+# oracle's tolerance is the family's.
+@pytest.mark.parametrize("hidden,ffn", [(64, 64), (72, 440), (128, 512), (136, 520), (192, 640), (72, 1544), (64, 4160),
+                                        (64, 8256)])
+def test_deep_ring_step_counts(torch_mod, hidden, ffn):
+    import oracle
+    import paper_2312_16733_amd as sna
+    spec = synth.TransformerSpec(n_classes=40, hidden=hidden, n_heads=1, ffn=ffn, max_layers=1, seq_len=11,
+                                 depth_choices=(1,))
+    W, S, C = setup(spec, 2)
+    net = sna.Supernet(spec, W, S, 2, 7)
+    try:
+        c = C[-1]
+        x = synth.make_inputs(spec, 7, c.in_h, c.in_w, 17)
+        net.set_tile_variant(1)
+        ref = forward(torch_mod, net, spec, [c], np.zeros(7), x)
+        check_parity(ref, oracle.forward(spec, W, S, c, x), "bf16", f"{hidden} x {ffn}")
+        nv = sna.lib().sna_tile_variant_count()
+        for v in (nv - 2, nv - 1):
+            for split in (1, 2):
+                net.set_tile_variant(v)
+                net.set_k_split(split)
+                print("deep ring", hidden, ffn, "variant", v, "split", split, flush=True)
+                np.testing.assert_array_equal(forward(torch_mod, net, spec, [c], np.zeros(7), x), ref)
+    finally:
+        net.close()
