@@ -151,7 +151,7 @@ __device__ __forceinline__ void reduce_octet(const ConvProblem& p, const float* 
 // which matters when a CU has a single block to overlap with itself.
 template <int BM, int BN, int WARPS_M, int WARPS_N, int NS, bool CHUNKED, int FW>
 __global__ __launch_bounds__(64 * (WARPS_M * WARPS_N + FW),
-                             FW ? (BM * BN >= 128 * 128 ? 2 : 4)
+                             FW ? (BM * BN >= 128 * 128 ? 2 : (CHUNKED && deep_ring(BM, BN, WARPS_M * WARPS_N, NS, FW) ? 3 : 4))
                                 : (CHUNKED ? (BM * BN == 128 * 64 ? 3 : (BM * BN > 128 * 128 ? 1 : 2)) : igemm_min_waves(BM, BN, NS)))
 void igemm_kernel(const ConvGroupArgs args) {
 #if defined(__HIP_DEVICE_COMPILE__)        // the host pass needs the symbol only, not the body
@@ -533,12 +533,20 @@ void igemm_kernel(const ConvGroupArgs args) {
       for (int v = 0; v < 16; ++v) acc[0][0][v] = 0.f;
       // The next step's fragments are requested ahead of this step's MFMAs and arrive under them (reads between the MFMAs
       // measured 0.14 us a step: the last ones are then waited for; a branch in a step costs as much as an MFMA's issue)
+      // (Plain loads, whose waits the compiler places: the fragments cross the loop's back edge in flight, where it may
+      // copy registers.  These waves fetch nothing, so that no wait for a fetch comes with them.)
+      typedef __attribute__((address_space(3))) const u32x4 lds_frag;
       auto read_step = [&](int st, int b) {
 #pragma unroll
         for (int ks = 0; ks < BK / 16; ++ks) {
-          fa[b][ks] = lds_read_b128(a_lane + st * Cfg::STAGE_B + frag_off[ks], 0);
-          fb[b][ks] = lds_read_b128(b_lane + st * Cfg::STAGE_B + frag_off[ks], 0);
+          fa[b][ks] = *(lds_frag*)(a_lane + st * Cfg::STAGE_B + frag_off[ks]);
+          fb[b][ks] = *(lds_frag*)(b_lane + st * Cfg::STAGE_B + frag_off[ks]);
         }
+      };
+      auto meet = [&] {                          // barrier; no LDS read moves across it
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
       };
       auto mfma = [&](int b, int ks) {
         acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[b][ks]),
@@ -547,10 +555,6 @@ void igemm_kernel(const ConvGroupArgs args) {
       auto step = [&](auto i_c, auto more_c) {   // step i of a group; more: another one follows
         constexpr int b = decltype(i_c)::value & 1;
         constexpr bool more = decltype(more_c)::value;
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) asm volatile("" : "+v"(fa[b][ks]), "+v"(fb[b][ks]));
-        __builtin_amdgcn_sched_barrier(0);
         stage = stage + 1 == NS ? 0 : stage + 1;
         if (more) read_step(stage, b ^ 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -570,13 +574,13 @@ void igemm_kernel(const ConvGroupArgs args) {
       typedef std::integral_constant<bool, false> last_t;
       typedef std::integral_constant<int, 0> s0_t;
       typedef std::integral_constant<int, 1> s1_t;
-      __builtin_amdgcn_s_barrier();
+      meet();
       read_step(0, 0);
       int kt = 0;
 #pragma unroll 1
       for (; kt + G < KT; kt += G) {
         step(s0_t{}, more_t{});
-        __builtin_amdgcn_s_barrier();            // the group before this one is in registers
+        meet();                                  // the group before this one is in registers
         step(s1_t{}, more_t{});
       }
       if (KT - kt == 1) {                        // the last group: one or two steps
