@@ -454,7 +454,8 @@ hipError_t launch_igemm(const ConvGroupArgs& a, int variant, bool chunked, hipSt
   int kt_max = 1;
   for (int i = 0; i < a.n; ++i) kt_max = steps_of(a.p[i]) > kt_max ? steps_of(a.p[i]) : kt_max;
   const int stages = kt_max < v.ns ? kt_max : v.ns;
-  int smem = stages * v.stage_bytes + (v.deep ? (kt_max + 3) / 4 * 4 * ROW_B : 0);
+  int smem = stages * v.stage_bytes;
+  if (v.deep) smem += (kt_max + 1) / 2 * 2 * ROW_B + (chunked ? v.bm * v.bn * 4 : 0);      // tap table, running totals
   if (smem < v.epi_bytes) smem = v.epi_bytes;
   if (v.deep && kt_max > kDeepMaxSteps) return hipErrorInvalidValue;
   if (v.slab) {
