@@ -429,6 +429,11 @@ struct Fwd {
         }
       if (slot > kTileCounters) { err = hipErrorInvalidValue; return; }
     }
+    // One block walking several chunks folds them in registers, in its own kernel instantiation, which runs short reductions
+    // as well (same bits: a sum is its first chunk plus zero).  So the problems of a tile variant share a launch.
+    std::vector<char> walks(igemm_num_variants(), 0);
+    for (size_t i = 0; i < n; ++i)
+      if (ps[i].parts == 1 && chunks[i] > 1) walks[var[i]] = 1;
     for (int chunked = 0; chunked < 2; ++chunked)
       for (int v = 0; v < igemm_num_variants(); ++v) {
         ConvGroupArgs a;
@@ -437,9 +442,7 @@ struct Fwd {
         double flops = 0, bytes = 0;
         for (size_t i = 0; i < n; ++i) {
           ConvProblem& p = ps[i];
-          // one block walking several chunks folds them in registers: its own kernel instantiation
-          const bool in_block_chunks = p.parts == 1 && chunks[i] > 1;
-          if (var[i] != v || in_block_chunks != (chunked == 1)) continue;
+          if (var[i] != v || walks[v] != chunked) continue;
           if (a.n == SNA_MAX_GROUPS) {       // more problems than one launch carries: flush
             a.total_tiles = start;
             emit(PlanOp::IGEMM, v, chunked, KC_IGEMM, flops, bytes, a);
@@ -812,13 +815,13 @@ struct Fwd {
   }
   void scatter_logits(float* logits) {
     const int nc = T().arch.n_classes;
+    std::vector<CopyItem> items;           // of all groups: their scratch lies in one arena, so that one launch moves them
     for (Group& g : groups) {
       if (g.contiguous) continue;
-      std::vector<CopyItem> items;
       for (int i = 0; i < g.n; ++i)
-        items.push_back({(size_t)i * nc * 4, (size_t)g.reqs[i] * nc * 4, (size_t)nc * 4});
-      copy_items(g.small, logits, items);
+        items.push_back({(size_t)((const char*)g.small - net->arena) + (size_t)i * nc * 4, (size_t)g.reqs[i] * nc * 4, (size_t)nc * 4});
     }
+    copy_items(net->arena, logits, items);
   }
 };
 
@@ -1267,11 +1270,11 @@ sna_status Fwd::run_transformer(const void*, float* logits, void* hidden) {
   scatter_logits(logits);
   if (hidden) {
     const size_t rb = (size_t)S * hd * T().esz;
-    for (Group& g : groups) {
-      std::vector<CopyItem> items;
-      for (int i = 0; i < g.n; ++i) items.push_back({(size_t)i * rb, (size_t)g.reqs[i] * rb, rb});
-      copy_items(g.cur, hidden, items);
-    }
+    std::vector<CopyItem> items;
+    for (Group& g : groups)
+      for (int i = 0; i < g.n; ++i)
+        items.push_back({(size_t)((const char*)g.cur - net->arena) + (size_t)i * rb, (size_t)g.reqs[i] * rb, rb});
+    copy_items(net->arena, hidden, items);
   }
   return SNA_OK;
 }
