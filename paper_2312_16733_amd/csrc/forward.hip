@@ -146,26 +146,28 @@ struct Fwd {
   // and, when reductions are spread over blocks, 1.9 us + 1.6 us per MB of partial sums.  per_cu is the launch's blocks per
   // CU (whole below four: a second block on some CUs lasts as long as on all), `steps` the K steps one block walks, averaged
   // over the blocks; step_taps is the step of a convolution with more than one tap, `walk` what folding chunk sums in
-  // registers adds to it where it costs occupancy.  The constants were fitted to 612 launch shapes of the three bf16
-  // families (batches 1 to 64, every variant with and without split reductions, in place inside a forward); the variant
-  // the formula picks is on average 3 % slower than the fastest of all variants (the best of some 70 timings each), where
-  // the rule it replaces, 128-row tiles and 64-row ones for launches below 256 tiles, was 35 % slower.
+  // registers adds to it where it costs occupancy.  The constants were fitted, for the order of the variants where they lie
+  // close, to 612 launch shapes of the three bf16 families (batches 1 to 64, every variant with and without split
+  // reductions, in place inside a forward); the variant the formula picks is on average 2 % slower than the fastest of all
+  // (the best of some 40 timings each), where the rule it replaces, 128-row tiles and 64-row ones for launches below 256
+  // tiles, was 35 % slower.
   struct TileCost { int variant; float launch, block, step, step_taps, walk; };
   static const TileCost* tile_costs(int* n) {
     static const TileCost costs[] = {
-        {28, 3.69f, 0.25f, 0.088f, 0.117f, 0.f},         // 32x32, deep ring
-        {29, 3.01f, 0.91f, 0.212f, 0.259f, 0.f},         // 64x64, deep ring
-        {4, 3.20f, 0.46f, 0.247f, 0.312f, 0.f},          // 64x64
-        {27, 4.45f, 0.35f, 0.225f, 0.262f, 0.f},         // 64x64, one stage
-        {25, 4.08f, 0.50f, 0.345f, 0.421f, 0.054f},      // 64x128, one stage
-        {1, 3.88f, 0.79f, 0.357f, 0.363f, 0.f},          // 128x64
-        {2, 4.34f, 1.18f, 0.495f, 0.495f, 0.f},          // 128x96
-        {8, 3.46f, 1.28f, 0.305f, 0.349f, 0.f},          // 64x128, fetching waves
-        {9, 3.38f, 1.41f, 0.311f, 0.345f, 0.f},          // 128x64, fetching waves
-        {11, 2.55f, 3.03f, 0.484f, 0.481f, 0.f},         // 128x128, fetching waves
-        {22, 4.57f, 1.42f, 0.526f, 0.545f, 0.077f},      // 128x128, one stage
-        {12, 3.46f, 0.41f, 0.283f, 0.272f, 0.f},         // 128x32, two stages
-        {24, 5.17f, 1.11f, 0.457f, 0.451f, 0.091f},      // 128x96, one stage
+        {28, 2.76f, 0.36f, 0.111f, 0.134f, 0.f},            // 32x32, deep ring
+        {29, 2.64f, 1.30f, 0.247f, 0.317f, 0.f},            // 64x64, deep ring
+        {30, 1.82f, 4.83f, 0.426f, 0.456f, 0.f},            // 128x96, deep ring
+        {4, 2.77f, 0.37f, 0.354f, 0.571f, 0.f},             // 64x64
+        {27, 5.80f, 0.31f, 0.368f, 0.323f, 0.055f},         // 64x64, one stage
+        {25, 4.31f, 0.25f, 0.364f, 0.536f, 0.061f},         // 64x128, one stage
+        {1, 5.06f, 0.34f, 0.414f, 0.410f, 0.f},             // 128x64
+        {2, 6.81f, 0.56f, 0.945f, 0.478f, 0.f},             // 128x96
+        {8, 2.26f, 1.62f, 0.340f, 0.412f, 0.f},             // 64x128, fetching waves
+        {9, 2.77f, 2.48f, 0.338f, 0.357f, 0.f},             // 128x64, fetching waves
+        {11, 1.73f, 4.21f, 0.488f, 0.702f, 0.f},            // 128x128, fetching waves
+        {22, 5.72f, 1.37f, 0.497f, 0.684f, 0.047f},         // 128x128, one stage
+        {12, 3.14f, 0.28f, 0.440f, 0.463f, 0.f},            // 128x32, two stages
+        {24, 7.46f, 0.54f, 0.442f, 0.442f, 0.132f},         // 128x96, one stage
     };
     *n = sizeof(costs) / sizeof(costs[0]);
     return costs;

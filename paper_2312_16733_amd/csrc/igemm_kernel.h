@@ -33,8 +33,10 @@ constexpr int igemm_min_waves(int bm, int bn, int ns) {
   return bm * bn > 128 * 128 ? 2 : (bm * bn >= 128 * 128 ? 3 : (bm * bn >= 128 * 96 || (bm * bn == 128 * 64 && ns == 2) ? 4 : 5));
 }
 
-// Rings deep enough to hold a long chain of K steps, with one 32x32 tile per computing wave and waves that only fetch
-constexpr bool deep_ring(int bm, int bn, int n_math, int ns, int fw) { return fw > 0 && ns >= 5 && bm * bn == n_math * 32 * 32; }
+// Deep rings: tap table, waves that only fetch, fragments read ahead across K steps.  `small`: one 32x32 tile per computing
+// wave and eight stages, for launches of few tiles; `large`: several tiles per wave and four stages, one block per CU.
+constexpr bool deep_small(int bm, int bn, int n_math, int ns, int fw) { return fw > 0 && ns >= 5 && bm * bn == n_math * 32 * 32; }
+constexpr bool deep_large(int bm, int bn, int n_math, int ns, int fw) { return fw > 0 && ns >= 4 && bm * bn > n_math * 32 * 32; }
 
 // Accesses that are coherent across the chip without cache-wide flushes: relaxed atomics at agent
 // scope.  Such a store is written through to memory and such a load is not served from the CU's own
@@ -151,15 +153,15 @@ __device__ __forceinline__ void reduce_octet(const ConvProblem& p, const float* 
 // which matters when a CU has a single block to overlap with itself.
 template <int BM, int BN, int WARPS_M, int WARPS_N, int NS, bool CHUNKED, int FW>
 __global__ __launch_bounds__(64 * (WARPS_M * WARPS_N + FW),
-                             FW ? (BM * BN >= 128 * 128 ? 2 : 4)
+                             FW ? (BM * BN >= 128 * 128 || deep_large(BM, BN, WARPS_M * WARPS_N, NS, FW) ? 2 : 4)
                                 : (CHUNKED ? (BM * BN == 128 * 64 ? 3 : (BM * BN > 128 * 128 ? 1 : 2)) : igemm_min_waves(BM, BN, NS)))
 void igemm_kernel(const ConvGroupArgs args) {
 #if defined(__HIP_DEVICE_COMPILE__)        // the host pass needs the symbol only, not the body
   using Cfg = IgemmCfg<BM, BN, WARPS_M, WARPS_N, NS, FW>;
   constexpr bool WS = FW > 0;
-  constexpr bool DEEP = deep_ring(BM, BN, WARPS_M * WARPS_N, NS, FW);
-  constexpr int G = 2;                     // deep rings: K steps between barriers
-  static_assert(!DEEP || (NS % G == 0 && NS >= 3 * G), "whole groups of stages");
+  constexpr bool LARGE = deep_large(BM, BN, WARPS_M * WARPS_N, NS, FW), DEEP = LARGE || deep_small(BM, BN, WARPS_M * WARPS_N, NS, FW);
+  constexpr int G = LARGE ? 1 : 2;         // deep rings: K steps between barriers
+  static_assert(!DEEP || (NS % G == 0 && NS >= 3 * G && NS / G <= 7), "whole groups of stages");
   constexpr int WTM = Cfg::WTM, WTN = Cfg::WTN, TM = Cfg::TM, TN = Cfg::TN;
   static_assert(TM >= 1 && TN >= 1 && WTM % 32 == 0 && WTN % 32 == 0, "wave tile");
   static_assert(BM % 8 == 0 && BN % 8 == 0 && Cfg::PASS_ROWS % 16 == 0, "a thread's rows in all passes share one swizzle, (row >> 1) & 7");
@@ -521,12 +523,82 @@ void igemm_kernel(const ConvGroupArgs args) {
 #pragma unroll 1
       for (int kt = 0; kt + G < KT; kt += G) {
         landed((requested - kt - 2 * G) / G);
-        __builtin_amdgcn_s_barrier();            // the group after step kt's is in LDS, the one before it is free
-        if (kt != 0 && requested < KT) {
+        __builtin_amdgcn_s_barrier();            // the group after step kt's is in LDS, the one before it is free (LARGE: step kt's too)
+        if ((LARGE || kt != 0) && requested < KT) {
           request_steps(requested, std::integral_constant<int, G>{});
           requested += G;
         }
       }
+    } else if constexpr (LARGE) {
+      // Several 32x32 tiles per wave, one block per CU.  Half a step's fragments (two 16-wide slices) are read under the
+      // MFMAs of the half before; the waves meet in a step's second half, when the step is in registers altogether and
+      // the next one has landed.  128x96 tiles, 4096 x 768 outputs over 3072 channels: 29.7 -> 27.0 us (the wave-specialised
+      // 128x128 tile before), 3136 x 720 of a 3x3 over 720 channels 68 -> 61.  Bound by the CU's fetch rate (28 KB a step at
+      // 97 B/ns where the rows are line-aligned, 57 where not) and its LDS reads (64 KB a step); a 128x128 tile of this kind
+      // takes as long per output as 128x96.
+      typedef __attribute__((address_space(3))) const u32x4 lds_frag;
+      u32x4 fa[2][2][TM], fb[2][2][TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+      auto read_half = [&](int st, auto h_c) {
+        constexpr int h = decltype(h_c)::value;
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+#pragma unroll
+          for (int i = 0; i < TM; ++i) fa[h][s2][i] = *(lds_frag*)(a_lane + st * Cfg::STAGE_B + frag_off[2 * h + s2] + i * 32 * ROW_B);
+#pragma unroll
+          for (int j = 0; j < TN; ++j) fb[h][s2][j] = *(lds_frag*)(b_lane + st * Cfg::STAGE_B + frag_off[2 * h + s2] + j * 32 * ROW_B);
+        }
+      };
+      auto mfma_half = [&](auto h_c) {
+        constexpr int h = decltype(h_c)::value;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[h][s2][i]),
+                                                                  __builtin_bit_cast(bf16x8, fb[h][s2][j]), acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      typedef std::integral_constant<int, 0> h0_t;
+      typedef std::integral_constant<int, 1> h1_t;
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      read_half(0, h0_t{});
+#pragma unroll 1
+      for (int kt = 0; kt + 1 < KT; ++kt) {
+        read_half(stage, h1_t{});
+        mfma_half(h0_t{});
+        stage = stage + 1 == NS ? 0 : stage + 1;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // step kt is in registers
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        read_half(stage, h0_t{});
+        mfma_half(h1_t{});
+        if (CHUNKED && --to_fold == 0) {                          // chunk boundary: bank the chunk's sum
+          to_fold = p.kt_chunk;
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+              for (int v = 0; v < 16; ++v) {
+                tot[i][j][v] = tot[i][j][v] + acc[i][j][v];
+                acc[i][j][v] = 0.f;
+              }
+        }
+      }
+      read_half(stage, h1_t{});
+      mfma_half(h0_t{});
+      mfma_half(h1_t{});
     } else {
       u32x4 fa[2][BK / 16], fb[2][BK / 16];
 #pragma unroll
@@ -788,9 +860,10 @@ struct Variant {
   void (*fn)(const ConvGroupArgs); void (*fn_chunked)(const ConvGroupArgs);
   bool slab;             // conv3_slab_kernel: 3x3 stride-1 layers only; stage_bytes is the weight ring's
   bool deep;             // tap table in front of the ring: at most kDeepMaxSteps K steps per block
+  bool totals_lds;       // its chunk-folding kernel keeps the running totals in LDS
 };
 constexpr int kDeepMaxSteps = 128;
-constexpr int kDeepVariantCount = 2;
+constexpr int kDeepVariantCount = 3;
 extern const Variant kDeepVariants[kDeepVariantCount];
 
 }  // namespace sna

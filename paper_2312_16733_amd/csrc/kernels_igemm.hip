@@ -384,13 +384,13 @@ hipError_t launch_splitk_reduce(const ConvGroupArgs& a, hipStream_t s) {
 
 #define SNA_VARIANT(BM, BN, WM, WN, NS) \
   { BM, BN, 64 * WM * WN, IgemmCfg<BM, BN, WM, WN, NS>::SMEM, NS, IgemmCfg<BM, BN, WM, WN, NS>::STAGE_B, \
-    IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, 0>, igemm_kernel<BM, BN, WM, WN, NS, true, 0>, false, false }
+    IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, 0>, igemm_kernel<BM, BN, WM, WN, NS, true, 0>, false, false, false }
 #define SNA_WS_VARIANT(BM, BN, WM, WN, NS) \
   { BM, BN, 128 * WM * WN, IgemmCfg<BM, BN, WM, WN, NS>::SMEM, NS, IgemmCfg<BM, BN, WM, WN, NS>::STAGE_B, \
-    IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, WM * WN>, igemm_kernel<BM, BN, WM, WN, NS, true, WM * WN>, false, false }
+    IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, WM * WN>, igemm_kernel<BM, BN, WM, WN, NS, true, WM * WN>, false, false, false }
 #define SNA_SLAB_VARIANT(BM, BN, WM, WN, NS) \
   { BM, BN, 64 * WM * WN, 0, NS, BN * ROW_B, IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, \
-    conv3_slab_kernel<BM, BN, WM, WN, NS, false>, conv3_slab_kernel<BM, BN, WM, WN, NS, true>, true, false }
+    conv3_slab_kernel<BM, BN, WM, WN, NS, false>, conv3_slab_kernel<BM, BN, WM, WN, NS, true>, true, false, false }
 // 0..6 are the variants the shape heuristic chooses from; the rest are reached through tuning only.
 static const Variant kPlain[] = {
     SNA_VARIANT(128, 128, 2, 2, 2), SNA_VARIANT(128, 64, 2, 2, 2), SNA_VARIANT(128, 96, 4, 1, 2),
@@ -455,7 +455,7 @@ hipError_t launch_igemm(const ConvGroupArgs& a, int variant, bool chunked, hipSt
   for (int i = 0; i < a.n; ++i) kt_max = steps_of(a.p[i]) > kt_max ? steps_of(a.p[i]) : kt_max;
   const int stages = kt_max < v.ns ? kt_max : v.ns;
   int smem = stages * v.stage_bytes;
-  if (v.deep) smem += (kt_max + 1) / 2 * 2 * ROW_B + (chunked ? v.bm * v.bn * 4 : 0);      // tap table, running totals
+  if (v.deep) smem += (kt_max + 1) / 2 * 2 * ROW_B + (chunked && v.totals_lds ? v.bm * v.bn * 4 : 0);      // tap table, running totals
   if (smem < v.epi_bytes) smem = v.epi_bytes;
   if (v.deep && kt_max > kDeepMaxSteps) return hipErrorInvalidValue;
   if (v.slab) {
