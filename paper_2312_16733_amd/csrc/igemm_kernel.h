@@ -209,7 +209,7 @@ void igemm_kernel(const ConvGroupArgs args) {
   const int KT_all = (p.K8 + 7) >> 3;      // K steps of 64 elements in the whole reduction
   const int KT = KT_all - kt0 < p.kt_part ? KT_all - kt0 : p.kt_part;
   // bytes of the tap table in front of the ring (whole groups: the entries past the last step fetch zeros)
-  const int tab_steps = DEEP ? (KT + G - 1) / G * G : 0;
+  const int tab_steps = DEEP && RS > 1 ? (KT + G - 1) / G * G : 0;
   const unsigned tab_b = (unsigned)tab_steps * ROW_B;
   if constexpr (DEEP) {
     // Tap table: where the 8 units of every K step lie.  One 16-byte entry per unit: byte offset from a row's first tap
@@ -325,14 +325,22 @@ void igemm_kernel(const ConvGroupArgs args) {
   // ring fills (a launch of fewer steps than stages has no LDS for the others).
   auto request_steps = [&](int kt, auto n_c) {
     constexpr int n = decltype(n_c)::value;
-    u32x4 e[n];
+    if (RS == 1) {                               // a pointwise layer has nothing to look up
 #pragma unroll
-    for (int i = 0; i < n; ++i) e[i] = lds_read_b128(tab_lane + (n == NS && kt + i >= KT ? 0 : kt + i) * ROW_B, 0);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      for (int i = 0; i < n; ++i) {
+        const unsigned u = (unsigned)((kt0 + kt + i) * 8 + kc);
+        if (n < NS || kt + i < KT) issue_at(stage0 + i, u32x4{u * 16, u * 16, 0u, u < (unsigned)p.C8 ? 0u : 0x80000000u});
+      }
+    } else {
+      u32x4 e[n];
 #pragma unroll
-    for (int i = 0; i < n; ++i) {
-      asm volatile("" : "+v"(e[i]));
-      if (n < NS || kt + i < KT) issue_at(stage0 + i, e[i]);
+      for (int i = 0; i < n; ++i) e[i] = lds_read_b128(tab_lane + (n == NS && kt + i >= KT ? 0 : kt + i) * ROW_B, 0);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int i = 0; i < n; ++i) {
+        asm volatile("" : "+v"(e[i]));
+        if (n < NS || kt + i < KT) issue_at(stage0 + i, e[i]);
+      }
     }
     stage0 = stage0 + n == NS ? 0 : stage0 + n;
   };
@@ -459,7 +467,7 @@ void igemm_kernel(const ConvGroupArgs args) {
 
   // ---- main loop: ring of NS stages ----------------------------------------------------------
   if constexpr (DEEP) {
-    __syncthreads();                             // the tap table is written
+    if (RS > 1) __syncthreads();                 // the tap table is written
     if (do_load) request_steps(0, std::integral_constant<int, NS>{});
   } else if (do_load) {
 #pragma unroll
@@ -479,6 +487,18 @@ void igemm_kernel(const ConvGroupArgs args) {
     const int k = n0 + wn * WTN + j * 32 + col_l;
     sc[j] = (do_math && !in_kernel_reduce && p.scale && k < p.K) ? p.scale[k] : 1.f;
     sh[j] = (do_math && !in_kernel_reduce && p.shift && k < p.K) ? p.shift[k] : 0.f;
+  }
+
+  // The deep rings' tiles have the registers to request the residual rows here, too (one round trip less at the end)
+  constexpr bool RES_EARLY = DEEP && !LARGE;
+  uint4 res_early[RES_EARLY ? 32 * (WTN / 8) / 64 : 1];
+  if (RES_EARLY && do_math && p.res && !in_kernel_reduce) {
+#pragma unroll
+    for (int t = 0; t < 32 * (WTN / 8) / 64; ++t) {
+      const int id = t * 64 + lane, row = id / (WTN / 8), oct = id - row * (WTN / 8);
+      const int m = m0 + wm * WTM + row, k = n0 + wn * WTN + oct * 8;
+      res_early[t] = (m < p.M && k < p.K) ? *(const uint4*)((const bf16_t*)p.res + (long)m * p.res_stride + k) : make_uint4(0, 0, 0, 0);
+    }
   }
 
   // CHUNKED: the reduction is summed in chunks of p.kt_chunk steps, each accumulated from zero and
@@ -728,6 +748,11 @@ void igemm_kernel(const ConvGroupArgs args) {
     constexpr bool RES_UP_FRONT = TM > 1;
     uint4 r4[TM][PAIRS];
     auto load_res = [&](int i) {
+      if constexpr (RES_EARLY) {
+#pragma unroll
+        for (int t = 0; t < PAIRS; ++t) r4[i][t] = res_early[t];
+        return;
+      }
 #pragma unroll
       for (int t = 0; t < PAIRS; ++t) {
         const int id = t * 64 + lane;

@@ -296,27 +296,33 @@ __global__ __launch_bounds__(256) void channel_stats_partial_kernel(const NormCa
   float n = 0.f, mean = 0.f, m2 = 0.f;
   if (ch < a.K) {
     const float* src = a.raw + ch;
-    for (int r = r0 + rl; r < r1; r += 32) {      // 8 rows of this lane: r, r+4, ..., r+28
-      float v[8];
-      int cnt = 0;
+    // groups of 8 rows of this lane, r, r + 4, ..., r + 28; the loads of four groups go out together (a group at a time
+    // was a round trip each, eight in a row: 7.2 us whatever the layer)
+    for (int r = r0 + rl; r < r1; r += 128) {
+      float v[4][8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int rr = r + 4 * j;
-        const bool in = rr < r1;
-        v[j] = in ? src[(long)rr * a.K] : 0.f;
-        cnt += in;
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int rr = r + 32 * g + 4 * j;
+          v[g][j] = rr < r1 ? src[(long)rr * a.K] : 0.f;
+        }
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        if (r + 32 * g >= r1) break;
+        int cnt = 0;
+        float sum = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { sum += v[g][j]; cnt += r + 32 * g + 4 * j < r1; }
+        const float nb = (float)cnt, gm = sum / nb;
+        float g2 = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const float d = (r + 32 * g + 4 * j < r1) ? v[g][j] - gm : 0.f;
+          g2 = fmaf(d, d, g2);
+        }
+        chan_merge(n, mean, m2, nb, gm, g2);
       }
-      float sum = 0.f;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) sum += v[j];
-      const float nb = (float)cnt, gm = sum / nb;
-      float g2 = 0.f;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float d = (r + 4 * j < r1) ? v[j] - gm : 0.f;
-        g2 = fmaf(d, d, g2);
-      }
-      chan_merge(n, mean, m2, nb, gm, g2);
     }
   }
   red[0][rl][threadIdx.x & 63] = n; red[1][rl][threadIdx.x & 63] = mean; red[2][rl][threadIdx.x & 63] = m2;
@@ -344,14 +350,25 @@ __global__ __launch_bounds__(256) void channel_stats_final_kernel(const NormCalA
   const int ch = blockIdx.x * 16 + cl;
   double n = 0, mean = 0, m2 = 0;
   if (ch < a.K)
-    for (int b = lane; b < a.nrb; b += 16) {
-      const float* q = a.part + ((long)b * a.K + ch) * 3;
-      chan_merge_d(n, mean, m2, q[0], q[1], q[2]);
+    for (int b0 = lane; b0 < a.nrb; b0 += 64) {     // four row blocks' loads at a time
+      float q[4][3];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const bool in = b0 + 16 * u < a.nrb;
+        const float* src = a.part + ((long)(in ? b0 + 16 * u : b0) * a.K + ch) * 3;
+        q[u][0] = in ? src[0] : 0.f; q[u][1] = src[1]; q[u][2] = src[2];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) chan_merge_d(n, mean, m2, q[u][0], q[u][1], q[u][2]);      // count 0: nothing to merge
     }
-  red[0][lane][cl] = n; red[1][lane][cl] = mean; red[2][lane][cl] = m2;
-  __syncthreads();
+  // the 16 lanes of a channel by a fixed tree (two fp64 divisions a merge: 15 in a row took 2 us)
+#pragma unroll
+  for (int d = 8; d >= 1; d >>= 1) {
+    if (lane < 2 * d && lane >= d) { red[0][lane][cl] = n; red[1][lane][cl] = mean; red[2][lane][cl] = m2; }
+    __syncthreads();
+    if (lane < d) chan_merge_d(n, mean, m2, red[0][lane + d][cl], red[1][lane + d][cl], red[2][lane + d][cl]);
+  }
   if (lane != 0 || ch >= a.K) return;
-  for (int j = 1; j < 16; ++j) chan_merge_d(n, mean, m2, red[0][j][cl], red[1][j][cl], red[2][j][cl]);
   const float mean_f = (float)mean, var_f = (float)(m2 / n);
   a.mean[ch] = mean_f;
   a.var[ch] = var_f;

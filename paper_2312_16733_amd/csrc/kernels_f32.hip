@@ -27,7 +27,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
 constexpr int F32_WAVES = 8;          // waves per block
 constexpr int F32_TILE = 16;
 constexpr int F32_STEP = 16;          // reduction elements per step: 4 lanes groups x 4 elements
-constexpr int F32_AHEAD = 4;          // steps whose loads are in flight together
+constexpr int F32_AHEAD = 5;          // steps whose loads are requested together, twice that many in flight: a wave's share of 72
 
 // Waves that share one output tile: with fewer than 4 steps each, adding up through LDS costs more than it saves.
 __host__ __device__ __forceinline__ int f32_k_waves(int steps) {
@@ -102,6 +102,18 @@ __global__ __launch_bounds__(64 * F32_WAVES) void conv_f32_kernel(const ConvGrou
   Operands cur[F32_AHEAD];
 #pragma unroll
   for (int i = 0; i < F32_AHEAD; ++i) cur[i] = load(s0 + i, e_end);
+  // What the outputs of this thread need at the end, requested here so that no second round trip follows the sums
+  constexpr int EPI = F32_TILE * F32_TILE / 64;            // outputs per thread, at most: one tile per wave
+  float e_sc[EPI], e_sh[EPI], e_rv[EPI];
+#pragma unroll
+  for (int it = 0; it < EPI; ++it) {
+    const int i = threadIdx.x + it * 64 * F32_WAVES, e = i & 255;
+    const int mo = (tmb * tiles_b + (i >> 8)) * F32_TILE + (e >> 4), ko = tn * F32_TILE + (e & 15);
+    const bool ok = i < tiles_b * F32_TILE * F32_TILE && mo < p.M && ko < p.K;
+    e_sc[it] = ok && p.scale ? p.scale[ko] : 1.f;
+    e_sh[it] = ok && p.shift ? p.shift[ko] : 0.f;
+    e_rv[it] = ok && p.res ? ((const float*)p.res)[(long)mo * p.res_stride + ko] : 0.f;
+  }
   for (int s = s0; s < s1; s += F32_AHEAD) {
     Operands nxt[F32_AHEAD];
     if (s + F32_AHEAD < s1) {
@@ -143,18 +155,18 @@ __global__ __launch_bounds__(64 * F32_WAVES) void conv_f32_kernel(const ConvGrou
 #pragma unroll
   for (int v = 0; v < 4; ++v) red[wave][(4 * grp + v) * F32_TILE + l16] = acc[v];
   __syncthreads();
-  for (int i = threadIdx.x; i < tiles_b * F32_TILE * F32_TILE; i += 64 * F32_WAVES) {
-    const int tl = i >> 8, e = i & 255;
+#pragma unroll
+  for (int it = 0; it < EPI; ++it) {
+    const int i = threadIdx.x + it * 64 * F32_WAVES, tl = i >> 8, e = i & 255;
     const int mo = (tmb * tiles_b + tl) * F32_TILE + (e >> 4), ko = tn * F32_TILE + (e & 15);
-    if (mo >= p.M || ko >= p.K) continue;
+    if (i >= tiles_b * F32_TILE * F32_TILE || mo >= p.M || ko >= p.K) continue;
     float v = red[tl * kw][e];
     for (int w = 1; w < kw; ++w) v += red[tl * kw + w][e];
     if (__builtin_expect(!(fabsf(v) < __builtin_inff()), 0)) v = own_taps(mo, ko);
-    v = fmaf(v, p.scale ? p.scale[ko] : 1.f, p.shift ? p.shift[ko] : 0.f);
-    const float rv = p.res ? ((const float*)p.res)[(long)mo * p.res_stride + ko] : 0.f;
-    if (p.res && !p.res_after_act) v += rv;
+    v = fmaf(v, e_sc[it], e_sh[it]);
+    if (p.res && !p.res_after_act) v += e_rv[it];
     v = apply_act(v, p.act);
-    if (p.res && p.res_after_act) v += rv;
+    if (p.res && p.res_after_act) v += e_rv[it];
     ((float*)p.y)[(long)mo * p.y_stride + ko] = v;
   }
 #endif

@@ -451,11 +451,15 @@ hipError_t launch_igemm(const ConvGroupArgs& a, int variant, bool chunked, hipSt
   }
   // a launch whose problems all have fewer K steps than the ring has stages only touches the
   // leading stages: asking for less LDS lets more blocks share a CU
-  int kt_max = 1;
-  for (int i = 0; i < a.n; ++i) kt_max = steps_of(a.p[i]) > kt_max ? steps_of(a.p[i]) : kt_max;
+  int kt_max = 1, kt_taps = 0;         // of all problems; of those that look their taps up
+  for (int i = 0; i < a.n; ++i) {
+    const int kt = steps_of(a.p[i]);
+    if (kt > kt_max) kt_max = kt;
+    if (a.p[i].R * a.p[i].S > 1 && kt > kt_taps) kt_taps = kt;
+  }
   const int stages = kt_max < v.ns ? kt_max : v.ns;
   int smem = stages * v.stage_bytes;
-  if (v.deep) smem += (kt_max + 1) / 2 * 2 * ROW_B + (chunked && v.totals_lds ? v.bm * v.bn * 4 : 0);      // tap table, running totals
+  if (v.deep) smem += (kt_taps + 1) / 2 * 2 * ROW_B + (chunked && v.totals_lds ? v.bm * v.bn * 4 : 0);      // tap table, running totals
   if (smem < v.epi_bytes) smem = v.epi_bytes;
   if (v.deep && kt_max > kDeepMaxSteps) return hipErrorInvalidValue;
   if (v.slab) {
