@@ -373,7 +373,9 @@ struct Fwd {
           float t_one = 0.f, t_split = 0.f;
           net->tuned[tune_key(q, 1, twins[i])] = measure_variants(q, true, nullptr, &t_one);
           net->tuned[tune_key(q, chunks[i], twins[i])] = measure_variants(qs, false, fuse_reduce ? nullptr : &r, &t_split);
-          net->tuned_split[key] = t_split < t_one ? 1 : 0;
+          // whether to spread the chunks stays the formula's choice, which was fitted in place: timed alone, a split layer
+          // finds its partial sums in the caches (3136 x 720 over 6480: 55 us alone, 107 inside a forward)
+          net->tuned_split[key] = split_rule ? 1 : 0;
         }
         auto it = net->tuned_split.end();
         for (int tw = twins[i]; tw >= 1 && it == net->tuned_split.end(); --tw) it = net->tuned_split.find(tune_key(q, 0, tw));

@@ -391,7 +391,7 @@ hipError_t launch_splitk_reduce(const ConvGroupArgs& a, hipStream_t s) {
 #define SNA_SLAB_VARIANT(BM, BN, WM, WN, NS) \
   { BM, BN, 64 * WM * WN, 0, NS, BN * ROW_B, IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, \
     conv3_slab_kernel<BM, BN, WM, WN, NS, false>, conv3_slab_kernel<BM, BN, WM, WN, NS, true>, true, false, false }
-// 0..6 are the variants the shape heuristic chooses from; the rest are reached through tuning only.
+// The formula of pick_tile chooses from 14 variants; the others are reached through tuning.  Ids 28.. are the deep rings.
 static const Variant kPlain[] = {
     SNA_VARIANT(128, 128, 2, 2, 2), SNA_VARIANT(128, 64, 2, 2, 2), SNA_VARIANT(128, 96, 4, 1, 2),
     SNA_VARIANT(128, 32, 4, 1, 4),  SNA_VARIANT(64, 64, 2, 2, 4),  SNA_VARIANT(64, 128, 1, 4, 3),
