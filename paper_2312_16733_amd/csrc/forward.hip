@@ -1880,7 +1880,16 @@ sna_status sna_subnet_tune(sna_supernet* net, const sna_subnet_cfg* cfgs, int32_
       const double med = t[t.size() / 2];
       if (best < 0 || med < best_t) { best = v; best_t = med; }
     }
-    if (best >= 0) net->tuned[kv.first] = best;
+    if (best < 0) continue;
+    // The least of some thirty noisy medians is often a slower variant's: the formula's choice stays unless beaten by 4 %
+    const TuneKey& k = kv.first;
+    ConvProblem q;
+    memset(&q, 0, sizeof(q));
+    q.M = k[0]; q.K = k[1]; q.C = k[2]; q.R = k[3]; q.S = 1; q.C8 = q.C / 8; q.K8 = q.R * q.C8;
+    const int formula = Fwd::pick_tile(std::vector<ConvProblem>(k[6], q).data(), k[6], k[5] > 1 ? 2 : 1).variant;
+    const std::vector<double>& tf = kv.second[formula];
+    if (!tf.empty() && best_t > 0.96 * tf[tf.size() / 2]) best = formula;
+    net->tuned[k] = best;
   }
   if (hipStreamSynchronize((hipStream_t)hip_stream) != hipSuccess) return fail(SNA_E_HIP, "stream synchronize");
   // leave the caller's outputs as a plain forward would
