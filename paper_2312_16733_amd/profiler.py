@@ -22,16 +22,26 @@ import numpy as np
 POW2_BATCHES = (1, 2, 4, 8, 16, 32, 64)
 
 
+BLOCK = 4       # forwards between one pair of events
+
+
 def profile_latency(net, spec, cfgs, make_inputs, batches: Sequence[int] = POW2_BATCHES, reps: int = 7,
                     warmup: int = 2) -> np.ndarray:
-    """Median forward latency in milliseconds, shape [len(cfgs)][len(batches)].
+    """Median forward latency on the GPU in milliseconds, shape [len(cfgs)][len(batches)].
 
     make_inputs(cfg, batch) returns the device tensor of `batch` requests for cfg.  Every (cfg,
     batch) is passed through `net.tune` first, so the table describes the tuned kernels a server
     would run.
+
+    The figures must compare cell by cell, so none may hold what only its moment brought along.  A
+    small forward takes the GPU 0.26 ms, and the host 0.17 ms to submit, but 0.4 ms or more when its
+    thread has just been idle or busy elsewhere: one forward between two events is then a measure of
+    the host (the smallest cell came out slower than eight times its batch).  So each sample is BLOCK
+    forwards behind `warmup` untimed ones, without a wait in between, whose submission the GPU's work
+    covers, and the `reps` samples of a cell are taken in as many rounds over all cells.
     """
     torch = net.torch
-    table = np.zeros((len(cfgs), len(batches)), np.float64)
+    cells = []
     for i, c in enumerate(cfgs):
         cfgs_c = net.prepare_cfgs([c])
         for j, b in enumerate(batches):
@@ -39,18 +49,20 @@ def profile_latency(net, spec, cfgs, make_inputs, batches: Sequence[int] = POW2_
             route = np.zeros(b, np.int32)
             logits = torch.empty((b, spec.n_classes), dtype=torch.float32, device=x.device)
             net.tune(cfgs_c, route, x)
-            for _ in range(warmup):
+            cells.append((i, j, cfgs_c, route, x, logits))
+    samples = np.zeros((len(cfgs), len(batches), reps), np.float64)
+    for r in range(reps):
+        for i, j, cfgs_c, route, x, logits in cells:
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            for _ in range(max(warmup, 1)):
                 net.forward(cfgs_c, route, x, logits=logits)
-            times = []
-            for _ in range(reps):
-                e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-                e0.record()
+            e0.record()
+            for _ in range(BLOCK):
                 net.forward(cfgs_c, route, x, logits=logits)
-                e1.record()
-                e1.synchronize()
-                times.append(e0.elapsed_time(e1))
-            table[i, j] = float(np.median(times))
-    return table
+            e1.record()
+            e1.synchronize()
+            samples[i, j, r] = e0.elapsed_time(e1) / BLOCK
+    return np.median(samples, axis=2)
 
 
 def check_properties(table: np.ndarray, slack: float = 0.03) -> dict:
@@ -160,7 +172,7 @@ def main():
     front = pareto_subset(table)
     pprops = check_properties(table[front])
     bks = latency_buckets(table, batches, args.buckets)
-    lines = [f"latency profile l_phi(B) in ms, {args.family}-shaped synthetic SuperNet, one MI355X, median of 7 forwards",
+    lines = [f"latency profile l_phi(B) in ms, {args.family}-shaped synthetic SuperNet, one MI355X, median of 7 rounds of %d forwards" % BLOCK,
              "command: python -m paper_2312_16733_amd.profiler --family %s --buckets %d" % (args.family, args.buckets), "",
              format_table(table, batches, labels), "",
              "P1 (latency rises with batch): %d of %d adjacent pairs fall by more than 3 %%" % (props["p1_violations"], props["p1_pairs"]),

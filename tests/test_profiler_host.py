@@ -1,5 +1,7 @@
 """Host logic of the supernet profiler (no GPU): latency buckets and the slack rule against their
 definitions written out by brute force, and the property counters on hand-made tables."""
+import types
+
 import numpy as np
 
 from paper_2312_16733_amd import profiler
@@ -80,3 +82,57 @@ def test_pareto_subset_against_the_definition():
         assert all(t[a, -1] < t[b, -1] for a, b in zip(keep, keep[1:]))
     t = synthetic_table()
     assert profiler.pareto_subset(t) == list(range(6))
+
+
+class FakeGpu:
+    """A clock for host and stream: a forward takes `submit` ms of host time, `device` ms on the stream, and its last
+    launch cannot run before the host has submitted it.  The host is slow for the first calls and at each stall."""
+
+    def __init__(self, device_ms, slow_calls, stall_every):
+        self.device_ms, self.slow_calls, self.stall_every = device_ms, slow_calls, stall_every
+        self.host = self.stream = 0.0
+        self.calls = 0
+        gpu = self
+
+        class Event:
+            def __init__(self, enable_timing=False):
+                self.at = None
+
+            def record(self):
+                self.at = max(gpu.host, gpu.stream)
+
+            def synchronize(self):
+                gpu.host = max(gpu.host, self.at)
+
+            def elapsed_time(self, end):
+                return end.at - self.at
+
+        self.torch = types.SimpleNamespace(cuda=types.SimpleNamespace(Event=Event), float32=None,
+                                           empty=lambda shape, dtype=None, device=None: None)
+
+    def prepare_cfgs(self, cfgs):
+        return cfgs
+
+    def tune(self, cfgs_c, route, x):
+        self.host = max(self.host, self.stream) + 500.0
+
+    def forward(self, cfgs_c, route, x, logits=None):
+        self.calls += 1
+        slow = self.calls <= self.slow_calls or self.calls % self.stall_every == 0
+        begin = self.host
+        self.host += 0.42 if slow else 0.17
+        self.stream = max(max(self.stream, begin) + self.device_ms[cfgs_c[0]][len(route)], self.host)
+
+
+def test_latency_table_holds_the_gpu_time_and_not_the_hosts():
+    """Forwards shorter on the GPU than a slow host needs to submit them (the first calls of a process, a stall now and
+    then): the table's cells are the GPU's time whatever their place in the loop."""
+    batches = (1, 8, 32)
+    device = {0: {1: 0.26, 8: 0.30, 32: 0.40}, 1: {1: 0.38, 8: 0.48, 32: 0.69}, 2: {1: 0.49, 8: 0.85, 32: 1.71}}
+    want = np.array([[device[i][b] for b in batches] for i in range(3)])
+    for slow_calls, stall_every in ((0, 10 ** 9), (8, 10 ** 9), (0, 17), (8, 13)):
+        net = FakeGpu(device, slow_calls, stall_every)
+        spec = types.SimpleNamespace(n_classes=10)
+        got = profiler.profile_latency(net, spec, [0, 1, 2], lambda c, b: types.SimpleNamespace(device=None), batches, reps=5)
+        np.testing.assert_allclose(got, want, rtol=0.05)
+        assert profiler.check_properties(got, slack=0.10)["p1_violations"] == 0
