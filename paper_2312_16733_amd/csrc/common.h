@@ -221,6 +221,7 @@ hipError_t launch_stem_pool(const StemPoolArgs& a, hipStream_t s);
 hipError_t launch_mbv3_head(const Mbv3HeadArgs& a, hipStream_t s);
 int mbv3_head_channels();                          // the width launch_mbv3_head is built for
 void igemm_tile_shape(int variant, int* bm, int* bn);
+int igemm_max_steps(int variant);                             // the most K steps one block may walk
 int igemm_num_variants();
 hipError_t launch_direct_conv(const ConvGroupArgs& a, hipStream_t s);      // bf16
 hipError_t launch_conv_f32(const ConvGroupArgs& a, hipStream_t s);

@@ -2,7 +2,6 @@
 // the SuperNet in layer order and issues one grouped launch per layer slot.  LayerSelect is
 // decided here: a block beyond a cfg's depth produces no problem, hence no launch and no copy.
 #include <algorithm>
-#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <functional>
@@ -11,6 +10,7 @@
 #include <set>
 
 #include "host.h"
+#include "tile_choice.h"
 
 namespace sna {
 const char* last_error_text();
@@ -141,76 +141,19 @@ struct Fwd {
     p.w_bytes = (unsigned)(wb - ((size_t)r0 * p.wr + (size_t)s0 * p.ws) * esize);
   }
 
-  // Tile choice.  The expected time of a launch with a tile variant, in microseconds on MI355X, is
-  //   launch + per_cu * (block + steps * (step or step_taps [+ walk]))
-  // and, when reductions are spread over blocks, 1.9 us + 1.6 us per MB of partial sums.  per_cu is the launch's blocks per
-  // CU (whole below four: a second block on some CUs lasts as long as on all), `steps` the K steps one block walks, averaged
-  // over the blocks; step_taps is the step of a convolution with more than one tap, `walk` what folding chunk sums in
-  // registers adds to it where it costs occupancy.  The constants were fitted, for the order of the variants where they lie
-  // close, to 612 launch shapes of the three bf16 families (batches 1 to 64, every variant with and without split
-  // reductions, in place inside a forward); the variant the formula picks is on average 2 % slower than the fastest of all
-  // (the best of some 40 timings each), where the rule it replaces, 128-row tiles and 64-row ones for launches below 256
-  // tiles, was 35 % slower.
-  struct TileCost { int variant; float launch, block, step, step_taps, walk; };
-  static const TileCost* tile_costs(int* n) {
-    static const TileCost costs[] = {
-        {28, 2.76f, 0.36f, 0.111f, 0.134f, 0.f},            // 32x32, deep ring
-        {29, 2.64f, 1.30f, 0.247f, 0.317f, 0.f},            // 64x64, deep ring
-        {30, 1.82f, 4.83f, 0.426f, 0.456f, 0.f},            // 128x96, deep ring
-        {4, 2.77f, 0.37f, 0.354f, 0.571f, 0.f},             // 64x64
-        {27, 5.80f, 0.31f, 0.368f, 0.323f, 0.055f},         // 64x64, one stage
-        {25, 4.31f, 0.25f, 0.364f, 0.536f, 0.061f},         // 64x128, one stage
-        {1, 5.06f, 0.34f, 0.414f, 0.410f, 0.f},             // 128x64
-        {2, 6.81f, 0.56f, 0.945f, 0.478f, 0.f},             // 128x96
-        {8, 2.26f, 1.62f, 0.340f, 0.412f, 0.f},             // 64x128, fetching waves
-        {9, 2.77f, 2.48f, 0.338f, 0.357f, 0.f},             // 128x64, fetching waves
-        {11, 1.73f, 4.21f, 0.488f, 0.702f, 0.f},            // 128x128, fetching waves
-        {22, 5.72f, 1.37f, 0.497f, 0.684f, 0.047f},         // 128x128, one stage
-        {12, 3.14f, 0.28f, 0.440f, 0.463f, 0.f},            // 128x32, two stages
-        {24, 7.46f, 0.54f, 0.442f, 0.442f, 0.132f},         // 128x96, one stage
-    };
-    *n = sizeof(costs) / sizeof(costs[0]);
-    return costs;
-  }
-  struct TileChoice { int variant; bool split; };
-  // For the problems ps[0 .. n), launched together: the variant, and whether chunked reductions are spread over blocks
-  // (split_mode 1: never, 2 and 3: always).
-  static TileChoice pick_tile(const ConvProblem* ps, size_t n, int split_mode) {
-    int n_costs = 0;
-    const TileCost* costs = tile_costs(&n_costs);
-    TileChoice best{1, split_mode >= 2};
-    double best_us = 0;
-    bool any = false;
-    for (int c = 0; c < n_costs; ++c)
-      for (int split = split_mode >= 2; split <= (split_mode == 1 ? 0 : 1); ++split) {
-        int bm, bn;
-        igemm_tile_shape(costs[c].variant, &bm, &bn);
-        double blocks = 0, work = 0, sums_mb = 0;
-        bool ok = true;
-        for (size_t i = 0; i < n; ++i) {
-          ConvProblem q = ps[i];
-          const int kt_all = (q.K8 + 7) / 8, per = chunk_steps(kt_all), parts = split ? (kt_all + per - 1) / per : 1;
-          q.parts = parts;
-          q.kt_part = parts > 1 ? per : 1 << 30;
-          ok = ok && igemm_variant_ok(costs[c].variant, q);
-          if (parts > 1) sums_mb += 4e-6 * parts * q.M * q.K;
-          const double b = (double)((q.M + bm - 1) / bm) * ((q.K + bn - 1) / bn) * parts;
-          blocks += b;
-          work += b * (parts > 1 ? per : kt_all) *
-                  ((q.R * q.S > 1 ? costs[c].step_taps : costs[c].step) + (parts == 1 && per < kt_all ? costs[c].walk : 0.f));
-        }
-        if (!ok) continue;
-        double per_cu = blocks / 256;
-        if (per_cu < 4) per_cu = std::ceil(per_cu);
-        double us = costs[c].launch + per_cu * (costs[c].block + work / blocks);
-        if (sums_mb > 0) us += 1.9 + 1.6 * sums_mb;
-        if (!any || us < best_us) {
-          any = true;
-          best_us = us;
-          best = {costs[c].variant, split != 0};
-        }
+  // The tile choice (tile_choice.h) for the problems ps[0 .. n), launched together
+  static TileChoice choose_tile(const ConvProblem* ps, size_t n, int split_mode) {
+    static const std::vector<TileShape> shapes = [] {
+      std::vector<TileShape> t(igemm_num_variants());
+      for (int v = 0; v < igemm_num_variants(); ++v) {
+        igemm_tile_shape(v, &t[v].bm, &t[v].bn);
+        t[v].max_steps = igemm_max_steps(v);
       }
-    return best;
+      return t;
+    }();
+    std::vector<TileWork> ws(n);
+    for (size_t i = 0; i < n; ++i) ws[i] = {ps[i].M, ps[i].K, (ps[i].K8 + 7) / 8, ps[i].R * ps[i].S};
+    return pick_tile(ws.data(), n, split_mode, shapes.data());
   }
 
   // Fill the launch-side fields of a problem for tile variant v (parts already decided).
@@ -282,13 +225,6 @@ struct Fwd {
     return {q.M, q.K, q.C, q.R * q.S, q.stride, parts, twins};
   }
 
-  // K chunking, a function of the reduction length only: the same layer of the same subnet is
-  // summed in the same order whatever it is batched with and however its blocks are laid out.
-  static int chunk_steps(int kt_all) {
-    const int n = kt_all <= 24 ? 1 : (kt_all <= 64 ? 2 : 4);
-    return (kt_all + n - 1) / n;
-  }
-
   void run_igemm(std::vector<ConvProblem>& ps, bool unify = false) {
     if (ps.empty()) return;
     const size_t n = ps.size();
@@ -309,7 +245,12 @@ struct Fwd {
       }
       return net->tuned.end();
     };
-    const TileChoice choice = pick_tile(ps.data(), n, net->split_mode);
+    // asked for once, and only where no table entry decides (a mixed call's lists are built anew for every routing)
+    TileChoice made{-1, false};
+    auto choice = [&]() -> const TileChoice& {
+      if (made.variant < 0) made = choose_tile(ps.data(), n, net->split_mode);
+      return made;
+    };
     for (size_t i = 0; i < n; ++i) {
       ConvProblem& q = ps[i];
       if (q.C % 8 || q.K % 8 || q.y_stride % 8 || q.res_stride % 8 || q.R * q.S > 64 ||
@@ -320,15 +261,12 @@ struct Fwd {
       q.parts = 1;
       q.kt_part = 1 << 30;
       auto it = find_tuned(q, 1, twins[i]);
-      var[i] = it != net->tuned.end() ? it->second : choice.variant;
+      var[i] = it != net->tuned.end() ? it->second : choice().variant;
       place(q, var[i]);
       const int kt_all = (q.K8 + 7) / 8;
       q.kt_chunk = chunk_steps(kt_all);
       chunks[i] = (kt_all + q.kt_chunk - 1) / q.kt_chunk;
     }
-    // Too few tiles for the chip: every chunk gets its own blocks (a measured per-shape decision, where there is one,
-    // takes precedence).
-    const bool split_rule = choice.split;
     std::vector<ConvProblem> reduce;
     char* part_cur = net->partials;
     size_t counters_used = 0;
@@ -350,7 +288,7 @@ struct Fwd {
         qs.y = part_cur; qs.y_stride = q.K; qs.out_fp32 = 1;
         qs.scale = nullptr; qs.shift = nullptr; qs.res = nullptr; qs.act = SNA_ACT_NONE;
       }
-      bool split = can_split && split_rule;
+      bool split = can_split && net->split_mode >= 2;
       // the reduction can finish inside the matrix launch when the layer's tile counters fit the table
       // (mode 3 keeps the separate reduction kernel: a test knob for that path)
       // (room is reserved for the smallest tile any variant has, 32 x 32; the slots are handed out below,
@@ -375,11 +313,11 @@ struct Fwd {
           net->tuned[tune_key(q, chunks[i], twins[i])] = measure_variants(qs, false, fuse_reduce ? nullptr : &r, &t_split);
           // whether to spread the chunks stays the formula's choice, which was fitted in place: timed alone, a split layer
           // finds its partial sums in the caches (3136 x 720 over 6480: 55 us alone, 107 inside a forward)
-          net->tuned_split[key] = split_rule ? 1 : 0;
+          net->tuned_split[key] = choice().split ? 1 : 0;
         }
         auto it = net->tuned_split.end();
         for (int tw = twins[i]; tw >= 1 && it == net->tuned_split.end(); --tw) it = net->tuned_split.find(tune_key(q, 0, tw));
-        if (it != net->tuned_split.end()) split = it->second != 0;
+        split = it != net->tuned_split.end() ? it->second != 0 : choice().split;
       }
       if (split) {
         q = qs;
@@ -396,7 +334,7 @@ struct Fwd {
       auto it = find_tuned(q, q.parts, twins[i]);
       if (it != net->tuned.end()) var[i] = it->second;
       if (net->forced_variant >= 0 && igemm_variant_ok(net->forced_variant, q)) var[i] = net->forced_variant;
-      if (!igemm_variant_ok(var[i], q)) var[i] = pick_tile(&q, 1, q.parts > 1 ? 2 : 1).variant;
+      if (!igemm_variant_ok(var[i], q)) var[i] = choose_tile(&q, 1, q.parts > 1 ? 2 : 1).variant;
       place(q, var[i]);
     }
     if ((unify || n > 1) && !net->tuning) {
@@ -1886,7 +1824,7 @@ sna_status sna_subnet_tune(sna_supernet* net, const sna_subnet_cfg* cfgs, int32_
     ConvProblem q;
     memset(&q, 0, sizeof(q));
     q.M = k[0]; q.K = k[1]; q.C = k[2]; q.R = k[3]; q.S = 1; q.C8 = q.C / 8; q.K8 = q.R * q.C8;
-    const int formula = Fwd::pick_tile(std::vector<ConvProblem>(k[6], q).data(), k[6], k[5] > 1 ? 2 : 1).variant;
+    const int formula = Fwd::choose_tile(std::vector<ConvProblem>(k[6], q).data(), k[6], k[5] > 1 ? 2 : 1).variant;
     const std::vector<double>& tf = kv.second[formula];
     if (!tf.empty() && best_t > 0.96 * tf[tf.size() / 2]) best = formula;
     net->tuned[k] = best;

@@ -415,6 +415,7 @@ void igemm_tile_shape(int variant, int* bm, int* bn) {
   *bm = variant_of(variant).bm;
   *bn = variant_of(variant).bn;
 }
+int igemm_max_steps(int variant) { return variant_of(variant).deep ? kDeepMaxSteps : 1 << 30; }
 
 // LDS a slab variant needs for one problem (all ring stages)
 static int slab_smem(const Variant& v, const ConvProblem& p, int stages) {
@@ -431,7 +432,7 @@ static int steps_of(const ConvProblem& p) {
 bool igemm_variant_ok(int variant, const ConvProblem& p) {
   if (variant < 0 || variant >= kNumVariants) return false;
   const Variant& v = variant_of(variant);
-  if (v.deep) return steps_of(p) <= kDeepMaxSteps;
+  if (v.deep) return steps_of(p) <= igemm_max_steps(variant);
   if (!v.slab) return true;
   return p.R == 3 && p.S == 3 && p.stride == 1 && p.pad == 1 && p.parts == 1 && !p.out_fp32 && p.W >= 2 &&
          p.Ho == p.H && p.Wo == p.W && (long)(v.bm + 2 * p.W + 2) * (p.C8 | 1) < (1 << 20) &&
