@@ -163,7 +163,7 @@ def main():
         if args.save_tuning:
             os.makedirs(os.path.dirname(table), exist_ok=True)
             with open(table, "w") as fh:
-                fh.write("# tile variant / K-split choices measured on MI355X by: python bench.py --family %s --save-tuning\n"
+                fh.write("# tile variants measured on MI355X by: python bench.py --family %s --save-tuning\n"
                          % args.family)
                 fh.write(net.tuning_export())
     torch.cuda.synchronize()

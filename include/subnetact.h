@@ -233,10 +233,9 @@ int64_t sna_static_scratch_bytes(void);
 /* Same arguments and result as sna_subnet_forward, but every conv / linear layer
  * shape met for the first time on this handle gets a measured tile variant of the
  * matrix kernel, remembered for later sna_subnet_forward calls with that shape.
- * Two steps: each new shape alone, launched back to back with every variant (this
- * also decides whether a long reduction is split over blocks); then, if the call
- * met any new shape, the whole forward is run with every launch forced to one
- * variant, for each variant in turn, every launch timed between two events, and a
+ * Two steps: each new shape alone, launched back to back with every variant; then,
+ * if the call met any new shape, the whole forward is run with every launch forced
+ * to one variant, for each variant in turn, every launch timed between two events, and a
  * new shape keeps the variant with the least time inside the forward (operands
  * come from HBM there, not from caches warmed by the previous repeat).  Step 2 is
  * skipped while sna_profile_enable is on.  The paper's serving system profiles
@@ -276,7 +275,8 @@ sna_status sna_subnet_calibrate(sna_supernet* net, const sna_subnet_cfg* cfg,
 int32_t sna_tuned_count(const sna_supernet* net);
 
 /* The measured choices as text, one per line ("v M K C RS stride parts twins variant" for a tile
- * variant, "s M K C RS stride 0 twins flag" for the K-split decision; twins = problems of this
+ * variant, "s M K C RS stride 0 twins flag" for a K-split decision, which
+ * is taken from an imported table but which sna_subnet_tune leaves to the library; twins = problems of this
  * shape that share the launch, e.g. 3 for a layer's Q, K and V projections; a line without the
  * twins field is read as twins = 1), so that a deployment can ship them instead of measuring at
  * every start.  Export writes at most `cap` bytes (host memory,
@@ -292,7 +292,7 @@ void sna_supernet_free(sna_supernet* net);
 /* How long reductions are laid out over blocks.  A conv / linear whose reduction is
  * longer than 1536 elements is summed in 2 or 4 chunks (a function of the layer's
  * active shape only), chunk sums added in order in fp32.  mode 0 (default): when a
- * layer has too few output tiles to fill the GPU (or a measured table entry says
+ * layer has too few output tiles to fill the GPU (or an imported table entry says
  * so), each chunk gets its own blocks, which leave fp32 chunk sums in the
  * workspace; the block that arrives last at a tile adds them in chunk order and
  * finishes the layer inside the same launch.  Otherwise one block walks all

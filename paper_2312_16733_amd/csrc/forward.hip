@@ -168,10 +168,10 @@ struct Fwd {
   }
 
   // Time every tile variant on this one problem (followed by its reduction launch when the
-  // reduction is split over blocks) and return the fastest; *best_ms gets its time per run.
+  // reduction is split over blocks) and return the fastest.
   // Runs the problem for real (outputs are rewritten with the same values each time) and
   // synchronises on the stream.
-  int measure_variants(const ConvProblem& q, bool chunked, const ConvProblem* reduce, float* best_ms, int copies = 1) {
+  int measure_variants(const ConvProblem& q, bool chunked, const ConvProblem* reduce, int copies) {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) { err = hipErrorUnknown; return 0; }
     ConvGroupArgs ra;
@@ -183,7 +183,7 @@ struct Fwd {
       ra.total_tiles = ra.p[0].tiles;
     }
     int best = -1;
-    *best_ms = 0.f;
+    float best_ms = 0.f;
     for (int v = 0; v < igemm_num_variants() && err == hipSuccess; ++v) {
       if (!igemm_variant_ok(v, q)) continue;
       ConvGroupArgs a;
@@ -212,7 +212,7 @@ struct Fwd {
         ms /= reps;
         if (trial == 0 || ms < v_ms) v_ms = ms;
       }
-      if (err == hipSuccess && (best < 0 || v_ms < *best_ms)) { best = v; *best_ms = v_ms; }
+      if (err == hipSuccess && (best < 0 || v_ms < best_ms)) { best = v; best_ms = v_ms; }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
@@ -305,16 +305,9 @@ struct Fwd {
         qs.counters = net->counters + counters_used;
       }
       if (can_split && net->split_mode == 0) {
-        const auto key = tune_key(q, 0, twins[i]);
-        if (net->tuning && !net->tuned_split.count(key)) {
-          // (a split layer is timed alone: copies of it would share its tile counters)
-          float t_one = 0.f, t_split = 0.f;
-          net->tuned[tune_key(q, 1, twins[i])] = measure_variants(q, true, nullptr, &t_one);
-          net->tuned[tune_key(q, chunks[i], twins[i])] = measure_variants(qs, false, fuse_reduce ? nullptr : &r, &t_split);
-          // whether to spread the chunks stays the formula's choice, which was fitted in place: timed alone, a split layer
-          // finds its partial sums in the caches (3136 x 720 over 6480: 55 us alone, 107 inside a forward)
-          net->tuned_split[key] = choice().split ? 1 : 0;
-        }
+        // An imported table may say; else the formula does, from all problems of the launch.  The tuner records no such
+        // decision: a shape's entry would carry what its launch mates had decided into launches without them, and a split
+        // layer timed alone finds its partial sums in the caches (3136 x 720 over 6480: 55 us alone, 107 inside a forward).
         auto it = net->tuned_split.end();
         for (int tw = twins[i]; tw >= 1 && it == net->tuned_split.end(); --tw) it = net->tuned_split.find(tune_key(q, 0, tw));
         split = it != net->tuned_split.end() ? it->second != 0 : choice().split;
@@ -325,12 +318,11 @@ struct Fwd {
         else reduce.push_back(r);
         part_cur += part_bytes;
       }
-      if (net->tuning && !net->tuned.count(tune_key(q, q.parts, twins[i]))) {
-        float t = 0.f;
+      // (a split layer is timed alone: copies of it would share its tile counters)
+      if (net->tuning && !net->tuned.count(tune_key(q, q.parts, twins[i])))
         net->tuned[tune_key(q, q.parts, twins[i])] = measure_variants(q, q.parts == 1 && chunks[i] > 1,
-                                                                      (split && !fuse_reduce) ? &r : nullptr, &t,
+                                                                      (split && !fuse_reduce) ? &r : nullptr,
                                                                       q.parts == 1 ? twins[i] : 1);
-      }
       auto it = find_tuned(q, q.parts, twins[i]);
       if (it != net->tuned.end()) var[i] = it->second;
       if (net->forced_variant >= 0 && igemm_variant_ok(net->forced_variant, q)) var[i] = net->forced_variant;
@@ -1756,8 +1748,7 @@ sna_status sna_subnet_tune(sna_supernet* net, const sna_subnet_cfg* cfgs, int32_
   if (!net) return fail(SNA_E_NULL, "net is NULL");
   std::set<TuneKey> known;
   for (const auto& kv : net->tuned) known.insert(kv.first);
-  // Step 1: every new layer shape alone, launched back to back with each variant (also decides
-  // whether a chunked reduction is split over blocks).
+  // Step 1: every new layer shape alone, in the layout it runs in, launched back to back with each variant.
   net->tuning = true;
   net->plans.clear();                      // launch lists built before this call may use other tile variants
   sna_status st = sna_subnet_forward(net, cfgs, n_cfgs, req_cfg, n_requests, inputs_dev, logits_dev, hidden_dev, hip_stream);

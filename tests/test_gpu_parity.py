@@ -502,8 +502,8 @@ def test_k_split_modes_give_identical_bits(torch_mod, resnet_full, tf_full):
 
 
 def test_tuned_tile_variants_do_not_change_bits(torch_mod):
-    """sna_subnet_tune measures tile variants (and whether to spread K chunks over blocks) per layer
-    shape; the choice must not change the result, and the tuned forward still matches the oracle."""
+    """sna_subnet_tune measures tile variants per layer shape; the choice must not change the result,
+    and the tuned forward still matches the oracle."""
     import oracle
     import paper_2312_16733_amd as sna
     torch = torch_mod
@@ -524,6 +524,30 @@ def test_tuned_tile_variants_do_not_change_bits(torch_mod):
             np.testing.assert_array_equal(before, tuned_out.cpu().numpy())
             np.testing.assert_array_equal(before, after)
             check_parity(after[:1], oracle.forward(spec, W, S, c, x[:1]), "bf16", f"tuned cfg {ci}")
+    finally:
+        net.close()
+
+
+def test_tuner_leaves_the_split_to_the_launch(torch_mod):
+    """Whether a long reduction is spread over blocks depends on all problems of a launch: the tuner must not file it
+    under one problem's shape, and measures a shape in the layout that it runs in."""
+    import paper_2312_16733_amd as sna
+    torch = torch_mod
+    spec = synth.ResNetSpec()
+    W, S, C = setup(spec, 16)
+    net = sna.Supernet(spec, W, S, 16, 1)
+    try:
+        c = C[15]
+        x = synth.make_inputs(spec, 1, c.in_h, c.in_w, 16)
+        net.tune([c], np.zeros(1, np.int32), to_dev(torch, spec, x))
+        torch.cuda.synchronize()
+        lines = [ln.split() for ln in net.tuning_export().splitlines()]
+        assert lines and all(ln[0] == "v" for ln in lines)
+        layouts = {}
+        for ln in lines:                     # v M K C taps stride parts twins variant
+            layouts.setdefault((*ln[1:6], ln[7]), set()).add(int(ln[6]))
+        assert all(len(v) == 1 for v in layouts.values()), layouts
+        assert any(p > 1 for v in layouts.values() for p in v)       # a lone request spreads its long reductions
     finally:
         net.close()
 
