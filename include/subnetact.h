@@ -233,12 +233,15 @@ int64_t sna_static_scratch_bytes(void);
 /* Same arguments and result as sna_subnet_forward, but every conv / linear layer
  * shape met for the first time on this handle gets a measured tile variant of the
  * matrix kernel, remembered for later sna_subnet_forward calls with that shape.
- * Two steps: each new shape alone, launched back to back with every variant; then,
- * if the call met any new shape, the whole forward is run with every launch forced
- * to one variant, for each variant in turn, every launch timed between two events, and a
- * new shape keeps the variant with the least time inside the forward (operands
- * come from HBM there, not from caches warmed by the previous repeat).  Step 2 is
- * skipped while sna_profile_enable is on.  The paper's serving system profiles
+ * Three steps: each new shape alone, launched back to back with every variant;
+ * then, if the call met any new shape, the whole forward is run with every launch
+ * forced to one variant, for each variant in turn, every launch timed between two
+ * events, and a new shape is to have the variant with the least time inside the
+ * forward (operands come from HBM there, not from caches warmed by the previous
+ * repeat) where that is clearly below its time without an entry; last, the forward
+ * is timed whole with these picks and without, and if they do not make it
+ * shorter, the new shapes are remembered with the variants they had.  The last two
+ * steps are skipped while sna_profile_enable is on.  The paper's serving system profiles
  * each subnet offline before serving; this is the same step for the kernels.
  * Tile variants do not change a bit of the result.  Synchronises on the stream
  * many times; returns after it has drained.  Not for use under stream capture.

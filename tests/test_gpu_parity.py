@@ -552,6 +552,47 @@ def test_tuner_leaves_the_split_to_the_launch(torch_mod):
         net.close()
 
 
+@pytest.mark.parametrize("table", ["tuned here", "shipped"])
+def test_a_tuning_table_does_not_slow_a_call_down(torch_mod, table):
+    """A lone request and a small batch with measured choices and without, forwards timed whole and in turn: choices that
+    only measured well launch by launch must not stay.  3 % is six times what medians of such blocks differ by."""
+    import os
+    import paper_2312_16733_amd as sna
+    torch = torch_mod
+    spec = synth.ResNetSpec()
+    W, S, C = setup(spec, 16)
+    nets = [sna.Supernet(spec, W, S, 16, 16) for _ in range(2)]
+    try:
+        if table == "shipped":
+            path = os.path.join(os.path.dirname(sna.library_path()), "tuned", "gfx950_resnet.txt")
+            nets[1].tuning_import(open(path).read())
+        for ci, batch in ((0, 1), (8, 1), (15, 1), (15, 16)):
+            c = C[ci]
+            x = to_dev(torch, spec, synth.make_inputs(spec, batch, c.in_h, c.in_w, 16))
+            cfgs, route = nets[0].prepare_cfgs([c]), np.zeros(batch, np.int32)
+            logits = torch.empty((batch, spec.n_classes), dtype=torch.float32, device=x.device)
+            if table == "tuned here":
+                nets[1].tune(cfgs, route, x)
+            ms = [[], []]
+            for r in range(12):
+                for side in ((0, 1) if r % 2 else (1, 0)):
+                    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                    for i in range(7):
+                        if i == 2:
+                            e0.record()
+                        nets[side].forward(cfgs, route, x, logits=logits)
+                    e1.record()
+                    e1.synchronize()
+                    if r >= 2:
+                        ms[side].append(e0.elapsed_time(e1) / 5)
+            without, with_table = float(np.median(ms[0])), float(np.median(ms[1]))
+            say(f"cfg {ci} batch {batch}: {without * 1e3:.1f} us without, {with_table * 1e3:.1f} us {table}")
+            assert with_table < 1.03 * without, (ci, batch, without, with_table)
+    finally:
+        for net in nets:
+            net.close()
+
+
 def test_replayed_launch_list_follows_the_callers_buffers(torch_mod, resnet_full):
     """The second call with the same cfgs and routing replays a recorded launch list; inputs, logits
     (and a different routing) must still be honoured."""
