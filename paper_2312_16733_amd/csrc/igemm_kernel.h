@@ -333,14 +333,13 @@ void igemm_kernel(const ConvGroupArgs args) {
       }
     } else {
       u32x4 e[n];
+      unsigned at[n];
 #pragma unroll
-      for (int i = 0; i < n; ++i) e[i] = lds_read_b128(tab_lane + (n == NS && kt + i >= KT ? 0 : kt + i) * ROW_B, 0);
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      for (int i = 0; i < n; ++i) at[i] = tab_lane + (n == NS && kt + i >= KT ? 0 : kt + i) * ROW_B;
+      lds_read_b128_now(e, at);
 #pragma unroll
-      for (int i = 0; i < n; ++i) {
-        asm volatile("" : "+v"(e[i]));
+      for (int i = 0; i < n; ++i)
         if (n < NS || kt + i < KT) issue_at(stage0 + i, e[i]);
-      }
     }
     stage0 = stage0 + n == NS ? 0 : stage0 + n;
   };
