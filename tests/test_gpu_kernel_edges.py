@@ -204,7 +204,7 @@ def test_infinite_weight_stays_in_its_tap(torch_mod, in_ch):
 
 # Deep-ring tiles of the matrix kernel (the last variants): reductions of 1, 2 and 7..9 steps around the 8 stages of the
 # ring, whole and half groups of steps, 25 and 65 steps (two and four chunks, folded or spread over blocks) and 129 steps,
-# more than the tap table holds unless they are spread.  Same bits as the 128x64 tile, which walks the same order; the
+# more than a deep ring walks: unless they are spread, another tile runs them.  Same bits as the 128x64 tile, which walks the same order; the
 # oracle's tolerance is the family's.
 @pytest.mark.parametrize("hidden,ffn", [(64, 64), (72, 440), (128, 512), (136, 520), (192, 640), (72, 1544), (64, 4160),
                                         (64, 8256)])
@@ -228,5 +228,46 @@ def test_deep_ring_step_counts(torch_mod, hidden, ffn):
                 net.set_k_split(split)
                 print("deep ring", hidden, ffn, "variant", v, "split", split, flush=True)
                 np.testing.assert_array_equal(forward(torch_mod, net, spec, [c], np.zeros(7), x), ref)
+    finally:
+        net.close()
+
+
+# The same tiles with taps: 3x3 layers of 2, 7, 8, 9, 25 and 65 steps, 128 (the longest table, the folding 64x64 kernel's
+# whole LDS) and 129, which only fits when it is spread over blocks; odd images whose windows cross every border, two
+# requests in a tile.  The launch list says which tile ran.  Same bits as the 128x64 tile.
+@pytest.mark.parametrize("mid", [8, 48, 56, 64, 176, 456, 904, 912])
+def test_deep_ring_taps(torch_mod, mid):
+    import oracle
+    import paper_2312_16733_amd as sna
+    steps = -(-9 * mid // 64)
+    spec = synth.ResNetSpec(n_classes=24, stem_ch=16, stage_ch=(64, 64), stage_stride=(1, 2), max_depth=(2, 1), depth_minus=(0, 1),
+                            expand_choices=(mid / 64,), width_choices=(1.0,), res_choices=(40,))
+    W, S, C = setup(spec, 2)
+    net = sna.Supernet(spec, W, S, 2, 3)
+    try:
+        c = C[-1]
+        c.in_h, c.in_w = 37, 27
+        assert c.block_mid_ch[0][0] == mid
+        x = synth.make_inputs(spec, 3, c.in_h, c.in_w, 19)
+        net.set_tile_variant(1)
+        ref = forward(torch_mod, net, spec, [c], np.zeros(3), x)
+        check_parity(ref, oracle.forward(spec, W, S, c, x), "bf16", f"mid {mid}")
+        nv = sna.lib().sna_tile_variant_count()
+        for v in (nv - 3, nv - 2, nv - 1):
+            for split in (1, 2, 3):
+                net.set_tile_variant(v)
+                net.set_k_split(split)
+                print("deep ring taps", mid, "variant", v, "split", split, flush=True)
+                np.testing.assert_array_equal(forward(torch_mod, net, spec, [c], np.zeros(3), x), ref)
+                net.profile_enable(True)
+                try:
+                    forward(torch_mod, net, spec, [c], np.zeros(3), x)
+                    lines = [l for l in net.profile_read_launches().split("\n") if " igemm_conv_linear " in l and " 3x3/" in l]
+                    net.profile_read()
+                finally:
+                    net.profile_enable(False)
+                assert len(lines) == sum(c.depth)
+                ran = {int(l.split("tile=")[1].split(" ")[0]) for l in lines}
+                assert (ran == {v}) == (split > 1 or steps <= 128), (steps, split, lines)
     finally:
         net.close()
