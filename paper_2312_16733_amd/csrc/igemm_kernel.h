@@ -14,10 +14,13 @@
 // destination, 16 bytes per lane; an out-of-range offset writes zeros, which feeds padding taps,
 // ragged rows and the K tail).  LDS holds a ring of NS stages of one K step (64 elements) each;
 // rows are 128 bytes with the 16-byte chunks XOR-swizzled by (row >> 1) & 7 so that both the
-// linear DMA writes and the column-wise fragment reads are bank-conflict free.  Loads for step
-// kt + NS - 1 are issued before the MFMAs of step kt; waits are explicit (s_waitcnt vmcnt with
-// the number of newer loads still allowed in flight, then s_barrier).  Fragment reads are
-// software-pipelined one 16-wide slice ahead of the v_mfma_f32_32x32x16_bf16 that use them.
+// linear DMA writes and the column-wise fragment reads are bank-conflict free.  Plain rings: loads
+// for step kt + NS - 1 are issued before the MFMAs of step kt; waits are explicit (s_waitcnt vmcnt
+// with the number of newer loads still allowed in flight, then s_barrier); fragment reads are
+// software-pipelined one 16-wide slice ahead of the v_mfma_f32_32x32x16_bf16 that use them.  Deep
+// rings (launches of few tiles, long reductions): waves of their own fetch several steps ahead with
+// the taps looked up in an LDS table, the others read a step's fragments (half a step's, where a wave
+// has several tiles) under the MFMAs before it, and the two meet once in one or two steps.
 // The epilogue (fused SubnetNorm scale/shift, residual, activation) goes through a per-wave
 // fp32 LDS tile so that residual loads and output stores are 16 bytes per lane.  Blocks are
 // renumbered so that consecutive tiles (which share activation rows) run on the same XCD.
@@ -208,7 +211,7 @@ void igemm_kernel(const ConvGroupArgs args) {
   const int kt0 = part * p.kt_part;        // first K step of this block's range
   const int KT_all = (p.K8 + 7) >> 3;      // K steps of 64 elements in the whole reduction
   const int KT = KT_all - kt0 < p.kt_part ? KT_all - kt0 : p.kt_part;
-  // bytes of the tap table in front of the ring (whole groups: the entries past the last step fetch zeros)
+  // bytes of the tap table in front of the ring (whole groups: the step that fills up the last one is fetched and never read)
   const int tab_steps = DEEP && RS > 1 ? (KT + G - 1) / G * G : 0;
   const unsigned tab_b = (unsigned)tab_steps * ROW_B;
   if constexpr (DEEP) {
@@ -321,8 +324,9 @@ void igemm_kernel(const ConvGroupArgs args) {
   };
   const unsigned tab_lane = lds0 + kc * 16;      // this thread's unit in the tap table
   int stage0 = 0;                                // stage of the next step to request
-  // The n steps from kt on, into the stages from kt % NS on (n divides NS).  Past the last step: zeros, except while the
-  // ring fills (a launch of fewer steps than stages has no LDS for the others).
+  // The n steps from kt on, into the stages from kt % NS on (n divides NS).  A step past the block's
+  // last is fetched too, and never read (zeros, or what the next part of a split reduction begins with), except while the
+  // ring fills: a launch of fewer steps than stages has no LDS for the others.
   auto request_steps = [&](int kt, auto n_c) {
     constexpr int n = decltype(n_c)::value;
     if (RS == 1) {                               // a pointwise layer has nothing to look up
@@ -388,9 +392,9 @@ void igemm_kernel(const ConvGroupArgs args) {
       // go out together and each slice waits only for its own (64x64 tiles, a lone request: 100 x 136 outputs of a 3x3
       // over 136 channels 13.6 -> 12.6 us, 32x128 tiles 13.8 -> 12.9; the smallest ResNet-shaped subnet 419 -> 412).
       // Two tiles per wave: only with the two-stage ring, which full batches use (three blocks share a CU; 64 requests of
-      // the largest ResNet-shaped subnet 3083 -> 2969 us, four waves per SIMD so that nothing spills).  The deeper
-      // rings serve calls of few tiles, one block per CU, and lose by it: 64x128 tiles, one request of the largest
-      // ResNet-shaped subnet 989 -> 1013 us.
+      // the largest ResNet-shaped subnet 3083 -> 2969 us, four waves per SIMD so that nothing spills).  The plain
+      // rings of three and four stages lose by it where a CU has one block (64x128 tiles, one request of the largest
+      // ResNet-shaped subnet 989 -> 1013 us, before such launches went to the deep rings).
       constexpr int NSL = BK / 16, RD = TM + TN;      // slices per step, reads per slice
       static_assert(RD * NSL <= 15, "lgkmcnt range");
       u32x4 a1[NSL][TM], b1[NSL][TN];
@@ -522,8 +526,9 @@ void igemm_kernel(const ConvGroupArgs args) {
     // looked up, the loads run NS - 2 G steps ahead, a step's fragments are read under the MFMAs of the step before, and
     // the fetching and the computing waves meet once in G steps, in the second: then the next group has landed, and the
     // group before is in registers, its stages free.  0.10 us a step for a 32x32 tile on its own (49 x 720 outputs, 16 to
-    // 64 steps), of which 0.107 are its chain of four dependent MFMAs: the chain's order is the bits' order.  One request
-    // of the largest ResNet-shaped subnet 991 -> 495 us, of the smallest 412 -> 266, 3 sequences 703 -> 520.
+    // 64 steps); with nothing but its four dependent MFMAs left in a step it took 0.11, so that chain is all there is (its
+    // order is the bits' order).  One request of the largest ResNet-shaped subnet 991 -> 491 us, of the smallest 412 -> 263,
+    // 3 sequences 703 -> 502.
     if (do_load) {
       // wait until at most the n newest groups are in flight (n >= NG - 1 is the start of the ring)
       constexpr int NG = NS / G;
@@ -883,7 +888,8 @@ struct Variant {
   int bm, bn, threads, smem, ns, stage_bytes, epi_bytes;
   void (*fn)(const ConvGroupArgs); void (*fn_chunked)(const ConvGroupArgs);
   bool slab;             // conv3_slab_kernel: 3x3 stride-1 layers only; stage_bytes is the weight ring's
-  bool deep;             // tap table in front of the ring: at most kDeepMaxSteps K steps per block
+  bool deep;             // a deep ring: at most kDeepMaxSteps K steps per block, which is the LDS its tap table has (and a
+                         // bound for pointwise layers as well, which have no table but whose times were not measured beyond)
   bool totals_lds;       // its chunk-folding kernel keeps the running totals in LDS
 };
 constexpr int kDeepMaxSteps = 128;

@@ -278,7 +278,7 @@ hipError_t launch_pad_input(const PadArgs& a, hipStream_t s) {
 // pairwise with Chan's formula, always in the same order: a thread takes its rows in groups of 8
 // (group mean, then squared deviations from it, all 8 values in registers), merges group after
 // group, the 4 row lanes of a block merge in lane order, the row blocks in lane-strided order by 16
-// lanes that merge in lane order.  The variance stored is the population one (M2 / n).
+// lanes, which then merge by a tree: lane l with l + 8, then l + 4, l + 2 and l + 1.  The variance stored is the population one (M2 / n).
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ void chan_merge(float& n, float& mean, float& m2, float nb, float meanb, float m2b) {
   if (nb == 0.f) return;

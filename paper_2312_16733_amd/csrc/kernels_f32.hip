@@ -8,8 +8,8 @@
 // long reduction is spread over the 8 waves of a block, which add their sums through LDS: the chain becomes 1/8 as long
 // and there are 32 .. 256 tiles where there were 4 .. 16 blocks.  Operands go from global memory (the whole net stays in L2)
 // straight to registers: a lane loads 4 consecutive reduction elements of its pixel and of its channel with one
-// 16-byte bounds-checked load each, which four MFMAs take element by element; the loads of four steps are in flight
-// ahead of the MFMAs that use them.
+// 16-byte bounds-checked load each, which four MFMAs take element by element; the loads of five steps are requested
+// together, ahead of the MFMAs that use the five before.
 //
 // Measured on the largest tiny subnet (thread per pixel -> here, event-bracketed): 4 images, 64 x 128 x 1152 (pixels x
 // channels x reduction) 153 -> 10.1 us, 256 x 64 x 576 96 -> 8.2, 1024 x 32 x 288 63 -> 8.1, the whole forward
@@ -27,7 +27,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
 constexpr int F32_WAVES = 8;          // waves per block
 constexpr int F32_TILE = 16;
 constexpr int F32_STEP = 16;          // reduction elements per step: 4 lanes groups x 4 elements
-constexpr int F32_AHEAD = 5;          // steps whose loads are requested together, twice that many in flight: a wave's share of 72
+constexpr int F32_AHEAD = 5;          // steps whose loads are requested together, twice that many in flight (a wave's share of 18, 36 and 72 steps is 5, 5 and 9)
 
 // Waves that share one output tile: with fewer than 4 steps each, adding up through LDS costs more than it saves.
 __host__ __device__ __forceinline__ int f32_k_waves(int steps) {
