@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "../../include/subnetact.h"
+#include "tile_map.h"
 
 namespace sna {
 
@@ -28,7 +29,8 @@ enum KClass {
 // ---- one problem of a grouped launch -------------------------------------------------------
 // A grouped launch carries up to SNA_MAX_GROUPS problems by value in the kernel
 // arguments; block b belongs to the problem whose [tile_start, tile_start + tiles)
-// range holds b.  One problem = one layer of one subnet cfg over that cfg's requests.
+// range holds b (matrix and expand + depthwise kernels: tile_map.h).  One problem = one layer of one subnet cfg
+// over that cfg's requests.
 
 struct ConvProblem {
   const void* x;        // [N][H][W][C] activations (active channels, dense)
@@ -72,7 +74,7 @@ struct ConvProblem {
 
 struct ConvGroupArgs {
   int n;
-  int total_tiles;      // sum of tiles over the problems
+  int total_tiles;      // blocks of the launch (matrix kernel: 8 per row of blocks)
   ConvProblem p[SNA_MAX_GROUPS];
 };
 
@@ -284,6 +286,10 @@ __device__ __forceinline__ int find_problem(const Args& a, int b) {
   for (int i = 1; i < a.n; ++i)
     if (b >= a.p[i].tile_start) g = i;
   return g;
+}
+template <class Problem>
+__device__ __forceinline__ int tile_of_block(const Problem& p) {
+  return tile_of_block(p.tiles, p.tile_start, (int)(blockIdx.x));
 }
 #endif
 

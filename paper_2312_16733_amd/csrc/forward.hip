@@ -192,8 +192,8 @@ struct Fwd {
       for (int c = 0; c < a.n; ++c) {
         a.p[c] = q;
         place(a.p[c], v);
-        a.p[c].tile_start = a.total_tiles;
-        a.total_tiles += a.p[c].tiles;
+        a.p[c].tile_start = a.total_tiles / kXcds;
+        a.total_tiles += tile_rows(a.p[c].tiles) * kXcds;
       }
       auto once = [&] {
         err = launch_igemm(a, v, chunked, stream);
@@ -368,22 +368,27 @@ struct Fwd {
     std::vector<char> walks(igemm_num_variants(), 0);
     for (size_t i = 0; i < n; ++i)
       if (ps[i].parts == 1 && chunks[i] > 1) walks[var[i]] = 1;
+    // The problems whose tiles take longest go first: their last tiles are not what the launch ends on.
+    std::vector<size_t> order(n);
+    for (size_t i = 0; i < n; ++i) order[i] = i;
+    auto steps = [&](size_t i) { const int kt = (ps[i].K8 + 7) / 8; return kt < ps[i].kt_part ? kt : ps[i].kt_part; };
+    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return steps(a) > steps(b); });
     for (int chunked = 0; chunked < 2; ++chunked)
       for (int v = 0; v < igemm_num_variants(); ++v) {
         ConvGroupArgs a;
         a.n = 0;
         int start = 0;
         double flops = 0, bytes = 0;
-        for (size_t i = 0; i < n; ++i) {
+        for (size_t i : order) {
           ConvProblem& p = ps[i];
           if (var[i] != v || walks[v] != chunked) continue;
           if (a.n == SNA_MAX_GROUPS) {       // more problems than one launch carries: flush
-            a.total_tiles = start;
+            a.total_tiles = start * kXcds;
             emit(PlanOp::IGEMM, v, chunked, KC_IGEMM, flops, bytes, a);
             a.n = 0; start = 0; flops = 0; bytes = 0;
           }
           p.tile_start = start;
-          start += p.tiles;
+          start += tile_rows(p.tiles);
           a.p[a.n++] = p;
           const int cc = p.c_count ? p.c_count : p.C;     // channel padding is not algorithmic work
           const double mac = (double)p.M * p.K * cc * p.R * p.S;
@@ -394,7 +399,7 @@ struct Fwd {
                    ((p.out_fp32 && (p.parts == 1 || p.counters)) ? 4.0 : 2.0) * (double)p.M * p.K + 8.0 * p.K +
                    (p.res ? 2.0 * p.M * p.K : 0.0);
         }
-        a.total_tiles = start;
+        a.total_tiles = start * kXcds;
         if (a.n) emit(PlanOp::IGEMM, v, chunked, KC_IGEMM, flops, bytes, a);
       }
     for (size_t i = 0; i < reduce.size(); i += SNA_MAX_GROUPS) {

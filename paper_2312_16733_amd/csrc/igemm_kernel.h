@@ -176,19 +176,15 @@ void igemm_kernel(const ConvGroupArgs args) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const unsigned lds0 = (unsigned)(size_t)(lds_char*)smem;              // LDS byte address of the tiles
 
-  // XCD-aware renumbering: hardware block b runs on XCD b % 8; give each XCD a contiguous tile range
-  const int per_xcd = gridDim.x >> 3;
-  const int tile_id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (tile_id >= args.total_tiles) return;
-
   // by value: uniform fields live in SGPRs across the asm blocks.  The first problem's descriptor sits at
   // a fixed kernarg offset, so its load does not wait for the problem search (most launches carry one).
   ConvProblem p = args.p[0];
   if (args.n > 1) {
-    const int g = find_problem(args, tile_id);
+    const int g = find_problem(args, blockIdx.x >> 3);
     if (g > 0) p = args.p[g];
   }
-  int local = tile_id - p.tile_start;
+  int local = tile_of_block(p);
+  if (local < 0) return;
   int part = 0;                            // which K range of the problem this block reduces over
   if (p.parts > 1) {
     part = local / p.tiles_base;

@@ -59,16 +59,13 @@ template <int K, int STRIDE>
 __global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs args) {
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  // consecutive items (the channel groups of a tile, which read the same input) on one XCD
-  const int per_xcd = gridDim.x >> 3;
-  const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (item >= args.total_tiles) return;
   ExpDwProblem p = args.p[0];
   if (args.n > 1) {
-    const int g = find_problem(args, item);
+    const int g = find_problem(args, blockIdx.x >> 3);
     if (g > 0) p = args.p[g];
   }
-  int local = item - p.tile_start;
+  int local = tile_of_block(p);                     // the channel groups of a tile, which read the same input, on one XCD
+  if (local < 0) return;
   const int chunk = local % p.chunks; local /= p.chunks;
   const int tx = local % p.tiles_x; local /= p.tiles_x;
   const int ty = local % p.tiles_y;
@@ -426,13 +423,13 @@ hipError_t launch_expand_dw(const ExpDwArgs& a, hipStream_t s) {
         p.chunks = (p.C + XD_CH - 1) / XD_CH;
         p.tile_start = start;
         p.tiles = (p.N + g.rq - 1) / g.rq * g.tiles_x * g.tiles_y * p.chunks;
-        start += p.tiles;
+        start += tile_rows(p.tiles);
         const size_t l = xd_lds(g, k, p.Cin);
         if (l > lds) lds = l;
       }
       if (!b.n) continue;
-      b.total_tiles = start;
-      const int blocks = (start + 7) / 8 * 8;
+      b.total_tiles = start * kXcds;
+      const int blocks = b.total_tiles;
       hipError_t e = hipSuccess;
 #define SNA_XD(KK, SS)                                                                                                \
   if (k == KK && st == SS) {                                                                                          \

@@ -41,15 +41,13 @@ void conv3_slab_kernel(const ConvGroupArgs args) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const unsigned lds0 = (unsigned)(size_t)(lds_char*)smem;
 
-  const int per_xcd = gridDim.x >> 3;
-  const int tile_id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (tile_id >= args.total_tiles) return;
   ConvProblem p = args.p[0];
   if (args.n > 1) {
-    const int g = find_problem(args, tile_id);
+    const int g = find_problem(args, blockIdx.x >> 3);
     if (g > 0) p = args.p[g];
   }
-  const int local = tile_id - p.tile_start;
+  const int local = tile_of_block(p);
+  if (local < 0) return;
   const int tn = local % p.tiles_n, tm = local / p.tiles_n;
   const int m0 = tm * BM, n0 = tn * BN;
 
@@ -471,8 +469,7 @@ hipError_t launch_igemm(const ConvGroupArgs& a, int variant, bool chunked, hipSt
       if (need > smem) smem = need;
     }
   }
-  const int blocks = (a.total_tiles + 7) / 8 * 8;
-  hipLaunchKernelGGL(fn, dim3(blocks), dim3(v.threads), smem, s, a);
+  hipLaunchKernelGGL(fn, dim3(a.total_tiles), dim3(v.threads), smem, s, a);
   return hipGetLastError();
 }
 
