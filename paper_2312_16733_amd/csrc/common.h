@@ -113,7 +113,7 @@ struct ExpDwProblem {
   int act;              // of both layers
   unsigned x_bytes, we_bytes;
   // filled by the launcher: output rows, 16-wide row segments and requests per block; tiles, channel groups; LDS layout
-  int th, ntx, rq, tiles_x, tiles_y, chunks, CW, plane, req_plane, x_lds;
+  int th, ntx, rq, ng, na, tiles_x, tiles_y, chunks, CW, plane, req_plane, x_lds;
   int tile_start, tiles;
 };
 struct ExpDwArgs { int n; int total_tiles; ExpDwProblem p[SNA_MAX_GROUPS]; };

@@ -16,9 +16,11 @@
 //      16-byte LDS read per lane), 7 MFMAs a 7 x 7 kernel.  A lane's part of T_r is a window of the kernel row shifted
 //      by the lane's place in the band: the rows lie in LDS between zeros, once at even and once at odd alignment, so
 //      that it is four aligned words.  The zeros of the band are 78 % of the products at k = 7, and it is still 5 times
-//      the rate of the dot-product instructions; what bounds B is its LDS reads (1 KB per MFMA).
-// The results wait in registers until the block is done with the planes, are turned channel-fastest through LDS and
-// stored, 32 bytes per pixel.
+//      the rate of the dot-product instructions.  The tile's output rows are dealt out to the MFMA groups in turn (group g
+//      has rows g, g + ng, g + 2 ng ..), so that what group g reads for kernel row r is what group g + 1 reads for kernel
+//      row r - stride: a row fragment is read once for all groups, 10 reads for the 28 MFMAs of four groups at k = 7.
+// The pool's sums are taken from the registers (a wave holds all outputs of its channels).  The results wait there until
+// the block is done with the planes, are turned channel-fastest through LDS and stored, 16 bytes per lane.
 //
 // Measured, batch 64, expand + depthwise as two launches -> here (event-bracketed): 56^2, 24 -> 144, 7 x 7: 23.7 + 91.5 ->
 // 55.6 us; 28^2, 40 -> 240: 12.6 + 47.9 -> 30.3; 14^2, 112 -> 672: 12.3 + 42.7 -> 35.2; 7^2, 160 -> 960: 8.5 + 21.1 -> 28.1;
@@ -38,8 +40,8 @@ constexpr int XD_CH = 16;           // expanded channels per block
 constexpr int XD_NT = 512;          // threads: with the LDS two blocks fit on a CU, 4 waves per SIMD
 constexpr int XD_SEG = 16;          // outputs per row segment
 constexpr int XD_GROUPS = 4;        // MFMA groups of 16 segments per block, at most
-constexpr int XD_OUT_PX = XD_CH / 2 + 1;                 // staged output: words per pixel, padded against bank conflicts
-constexpr int XD_OUT_SEG = XD_SEG * XD_OUT_PX + 4;       // words per segment: 4 segments on lie 16 banks away
+constexpr int XD_OUT_PX = XD_CH / 2 + 2;                 // staged output: words per pixel, padded against bank conflicts
+constexpr int XD_OUT_SEG = XD_SEG * XD_OUT_PX + 2;       // words per segment
 constexpr int XD_TROW = 16;         // words per kernel row of the band table: 4 even-aligned, 4 zeros, 4 odd-aligned, 4 zeros
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -48,6 +50,7 @@ typedef unsigned u32x4w __attribute__((ext_vector_type(4), aligned(4)));
 // LDS layout and tile of one problem, the same on host and device
 struct XdGeom {
   int th, ntx, rq;                  // output rows, 16-wide segments per row, requests per block
+  int ng, na;                       // MFMA groups, rows of a request in one (group g has rows g, g + ng, ..): rq na ntx <= 16 segments
   int tiles_y, tiles_x;
   int IH, CW;                       // rows and columns (elements) of a channel plane; column 0 is input column x0 * stride - 4
   int plane, req_plane;             // bytes per channel plane (an odd number of 16-byte units) and per request
@@ -130,7 +133,8 @@ __global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs arg
     if (i >= quads) { e.x = 0xffffffffu; e.w = OOB; }
     qtab[i] = e;
   }
-  for (int i = tid; i < rq * p.req_plane / 16; i += XD_NT) *(uint4*)(planes + i * 16) = make_uint4(0, 0, 0, 0);
+  // (the planes, and behind them what the last segments of a tile whose rows ng does not divide read, and drop)
+  for (int i = tid; i < p.x_lds / 16; i += XD_NT) *(uint4*)(planes + i * 16) = make_uint4(0, 0, 0, 0);
   __syncthreads();
 
 #pragma unroll
@@ -210,17 +214,20 @@ __global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs arg
   __syncthreads();
 
   // ---- B: depthwise ---------------------------------------------------------------------------
-  const int seg_req = p.th * p.ntx, nseg = rq * seg_req, ng = (nseg + 15) >> 4;
+  // Row l of every MFMA group is a segment (request rr, rows ng aa + g, column segment tt)
+  const int ng = p.ng, seg_req = p.na * p.ntx;
   const unsigned magic_ntx = p.ntx > 1 ? 0xFFFFFFFFu / (unsigned)p.ntx + 1u : 0u;
   const unsigned magic_sr = seg_req > 1 ? 0xFFFFFFFFu / (unsigned)seg_req + 1u : 0u;
-  int seg_off[XD_GROUPS];                                       // plane offset of this lane's segment, MFMA row l16
-#pragma unroll
-  for (int g = 0; g < XD_GROUPS; ++g) {
-    int i = g * 16 + l16;
-    i = i < nseg ? i : nseg - 1;
-    const int rr = seg_req > 1 ? (int)__umulhi((unsigned)i, magic_sr) : i, ii = i - rr * seg_req;
-    const int pr = p.ntx > 1 ? (int)__umulhi((unsigned)ii, magic_ntx) : ii, t = ii - pr * p.ntx;
-    seg_off[g] = rr * p.req_plane + (pr * STRIDE * p.CW + t * XD_SEG * STRIDE) * 2;
+  struct Seg { int rr, row, tt; };                              // row: of group 0
+  auto segment = [&](int l) {
+    const int rr = seg_req > 1 ? (int)__umulhi((unsigned)l, magic_sr) : l, ii = l - rr * seg_req;
+    const int aa = p.ntx > 1 ? (int)__umulhi((unsigned)ii, magic_ntx) : ii;
+    return Seg{rr, aa * ng, ii - aa * p.ntx};
+  };
+  int seg_off;                                                  // plane offset of this lane's segment, MFMA row l16
+  {
+    const Seg s = segment(l16 < p.rq * seg_req ? l16 : 0);
+    seg_off = s.rr * p.req_plane + (s.row * STRIDE * p.CW + s.tt * XD_SEG * STRIDE) * 2;
   }
   // this lane's 8 elements of the band: columns 32 kb + 8 grp .. + 7 against output l16
   int col_off[KB], t_off[KB];
@@ -241,10 +248,9 @@ __global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs arg
     for (int v = 0; v < 4; ++v) {
       const float a = v == 0 ? acc[0] : (v == 1 ? acc[1] : (v == 2 ? acc[2] : acc[3]));
       if (xd_finite(a)) continue;
-      int i = g * 16 + 4 * grp + v;
-      i = i < nseg ? i : nseg - 1;
-      const int rr = seg_req > 1 ? (int)__umulhi((unsigned)i, magic_sr) : i, ii = i - rr * seg_req;
-      const int pr = p.ntx > 1 ? (int)__umulhi((unsigned)ii, magic_ntx) : ii, q = (ii - pr * p.ntx) * XD_SEG + l16;
+      const Seg sg = segment(4 * grp + v);
+      const int rr = sg.rr, pr = sg.row + g, q = sg.tt * XD_SEG + l16;
+      if (rr >= rq || pr >= p.th) continue;                     // no output of the tile
       const int iy = (py0 + pr) * STRIDE - PAD, ix = (qx0 + q) * STRIDE - PAD;
       const bf16_t* x = (const bf16_t*)(planes + cl * p.plane + rr * p.req_plane) + pr * STRIDE * p.CW + q * STRIDE + OFF;
       const bf16_t* w = (const bf16_t*)(ttab + 4 + cl * K * XD_TROW);
@@ -258,90 +264,113 @@ __global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs arg
     }
     return acc;
   };
-  constexpr int PAIRS = XD_CH / 2 / (XD_NT / 64);               // channel pairs per wave
-  unsigned packed[PAIRS][XD_GROUPS][4];
-  auto depthwise = [&](auto act_c) {
-    constexpr int ACT = decltype(act_c)::value;
+  static_assert(XD_CH == 2 * (XD_NT / 64), "a wave has one pair of channels");
+  unsigned packed[XD_GROUPS][4];                                // outputs of the pair: group g, segment 4 grp + v, column l16
+  auto depthwise = [&](auto act_c, auto ng_c) {
+    constexpr int ACT = decltype(act_c)::value, NG = decltype(ng_c)::value;
+    float first[NG][4];
 #pragma unroll
-    for (int pi = 0; pi < PAIRS; ++pi) {
-      float first[XD_GROUPS][4];
+    for (int h = 0; h < 2; ++h) {
+      const int cl = wave * 2 + h, c = c0 + cl;
+      const float sc = c < C ? p.sc_d[c] : 0.f, sh = c < C ? p.sh_d[c] : 0.f;
+      u32x4 band[K][KB];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int cl = (wave * PAIRS + pi) * 2 + h, c = c0 + cl;
-        const float sc = c < C ? p.sc_d[c] : 0.f, sh = c < C ? p.sh_d[c] : 0.f;
-        u32x4 band[K][KB];
+      for (int r = 0; r < K; ++r)
 #pragma unroll
-        for (int r = 0; r < K; ++r)
+        for (int kb = 0; kb < KB; ++kb) band[r][kb] = *(const u32x4w*)(ttab + 4 + (cl * K + r) * XD_TROW + t_off[kb]);
+      const char* src = planes + cl * p.plane + seg_off;
+      f32x4 acc[NG];
 #pragma unroll
-          for (int kb = 0; kb < KB; ++kb) band[r][kb] = *(const u32x4w*)(ttab + 4 + (cl * K + r) * XD_TROW + t_off[kb]);
+      for (int g = 0; g < NG; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int g = 0; g < XD_GROUPS; ++g) {
-          if (g >= ng) continue;
-          const char* src = planes + cl * p.plane + seg_off[g];
-          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      for (int d = 0; d < (NG - 1) * STRIDE + K; ++d) {         // plane rows from the segment's own on, kernel row d - g stride of group g
 #pragma unroll
-          for (int r = 0; r < K; ++r) {
+        for (int kb = 0; kb < KB; ++kb) {
+          const uint4 a = *(const uint4*)(src + col_off[kb]);
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) {
-              const uint4 a = *(const uint4*)(src + col_off[kb]);
-              acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, band[r][kb]), acc, 0, 0, 0);
-            }
-            src += p.CW * 2;
-          }
-          if (__builtin_expect(__any(!xd_finite((acc[0] + acc[1]) + (acc[2] + acc[3]))), 0)) acc = own_taps(acc, cl, g);
+          for (int g = 0; g < NG; ++g)
+            if (d >= g * STRIDE && d - g * STRIDE < K)
+              acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, band[d - g * STRIDE][kb]), acc[g], 0, 0, 0);
+        }
+        src += p.CW * 2;
+      }
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const float y = apply_act(fmaf(acc[v], sc, sh), ACT);
-            if (h == 0) first[g][v] = y;
-            else packed[pi][g][v] = pack_bf16x2(first[g][v], y);
-          }
+      for (int g = 0; g < NG; ++g) {
+        if (__builtin_expect(__any(!xd_finite((acc[g][0] + acc[g][1]) + (acc[g][2] + acc[g][3]))), 0)) acc[g] = own_taps(acc[g], cl, g);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float y = apply_act(fmaf(acc[g][v], sc, sh), ACT);
+          if (h == 0) first[g][v] = y;
+          else packed[g][v] = pack_bf16x2(first[g][v], y);
         }
       }
     }
+#pragma unroll
+    for (int g = NG; g < XD_GROUPS; ++g)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) packed[g][v] = 0;
   };
-  if (p.act == SNA_ACT_RELU) depthwise(std::integral_constant<int, SNA_ACT_RELU>{});
-  else depthwise(std::integral_constant<int, SNA_ACT_HSWISH>{});
+  auto depthwise_act = [&](auto act_c) {
+    if (ng == 4) depthwise(act_c, std::integral_constant<int, 4>{});
+    else if (ng == 3) depthwise(act_c, std::integral_constant<int, 3>{});
+    else if (ng == 2) depthwise(act_c, std::integral_constant<int, 2>{});
+    else depthwise(act_c, std::integral_constant<int, 1>{});
+  };
+  if (p.act == SNA_ACT_RELU) depthwise_act(std::integral_constant<int, SNA_ACT_RELU>{});
+  else depthwise_act(std::integral_constant<int, SNA_ACT_HSWISH>{});
+
+  // ---- pool: this wave's two channels, per request; a lane over its outputs in order, the lanes by a fixed tree ---------
+  if (p.pool_part) {
+    bool ok[4];
+    int row[4], req[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const Seg sg = segment(4 * grp + v);
+      row[v] = sg.row; req[v] = sg.rr;
+      ok[v] = sg.rr < rq && sg.tt * XD_SEG + l16 < tw_v;
+    }
+    const int c = c0 + wave * 2;
+    for (int rr = 0; rr < rq; ++rr) {
+      float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+      for (int g = 0; g < XD_GROUPS; ++g)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const unsigned w = ok[v] && req[v] == rr && row[v] + g < th_v && g < ng ? packed[g][v] : 0u;
+          s0 += __uint_as_float(w << 16);
+          s1 += __uint_as_float(w & 0xffff0000u);
+        }
+#pragma unroll
+      for (int d = 1; d <= 32; d <<= 1) { s0 += __shfl_xor(s0, d, 64); s1 += __shfl_xor(s1, d, 64); }
+      if (lane == 0 && c < C)
+        *(float2*)(p.pool_part + ((long)((n0 + rr) * p.tiles_y + ty) * p.tiles_x + tx) * C + c) = make_float2(s0, s1);
+    }
+  }
   __syncthreads();                                              // every wave is done with the planes
 
-  // ---- output: [segment][16 columns][channel pairs] through LDS --------------------------------
+  // ---- output: [group][segment][16 columns][channel pairs] through LDS -------------------------
   unsigned* const outs = (unsigned*)smem;
 #pragma unroll
   for (int g = 0; g < XD_GROUPS; ++g) {
     if (g >= ng) continue;
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-      for (int pi = 0; pi < PAIRS; ++pi)
-        outs[(g * 16 + 4 * grp + v) * XD_OUT_SEG + l16 * XD_OUT_PX + wave * PAIRS + pi] = packed[pi][g][v];
+    for (int v = 0; v < 4; ++v) outs[(g * 16 + 4 * grp + v) * XD_OUT_SEG + l16 * XD_OUT_PX + wave] = packed[g][v];
   }
   __syncthreads();
-  const int cp = tid & 7, slot = tid >> 3, q = slot & 15, c = c0 + 2 * cp;
-  for (int rr = 0; rr < rq; ++rr) {
-    float s0 = 0.f, s1 = 0.f;
-    for (int i = slot >> 4; i < seg_req; i += XD_NT / 128) {
-      const int pr = p.ntx > 1 ? (int)__umulhi((unsigned)i, magic_ntx) : i, qq = (i - pr * p.ntx) * XD_SEG + q;
-      const unsigned v = outs[(rr * seg_req + i) * XD_OUT_SEG + q * XD_OUT_PX + cp];
-      if (pr < th_v && qq < tw_v && c < C) {
-        __builtin_amdgcn_raw_buffer_store_b32(v, rsrc_y, (unsigned)(((((n0 + rr) * p.Ho + py0 + pr) * p.Wo + qx0 + qq) * C + c) * 2), 0, 0);
-        s0 += __uint_as_float(v << 16);
-        s1 += __uint_as_float(v & 0xffff0000u);
+  // a thread stores 8 channels of one pixel per group: segment tid / 32, column tid / 2 % 16
+  static_assert(XD_NT == 16 * XD_SEG * 2 && XD_CH == 16, "one thread per 8 channels of a group's pixels");
+  const int oh = tid & 1, oq = (tid >> 1) & 15, ol = tid >> 5;
+  const Seg so = segment(ol);
+  const int qq = so.tt * XD_SEG + oq, c = c0 + oh * 8;
+  if (so.rr < rq && qq < tw_v && c < C) {
+    const unsigned* src = outs + ol * XD_OUT_SEG + oq * XD_OUT_PX + oh * 4;
+    const unsigned off = (unsigned)(((((n0 + so.rr) * p.Ho + py0 + so.row) * p.Wo + qx0 + qq) * C + c) * 2);
+#pragma unroll
+    for (int g = 0; g < XD_GROUPS; ++g)
+      if (g < ng && so.row + g < th_v) {
+        const uint2 lo = *(const uint2*)(src + g * 16 * XD_OUT_SEG), hi = *(const uint2*)(src + g * 16 * XD_OUT_SEG + 2);
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{lo.x, lo.y, hi.x, hi.y}, rsrc_y, off + (unsigned)(g * p.Wo * C * 2), 0, 0);
       }
-    }
-    if (!p.pool_part) continue;
-    // pool: each thread over its segments in order, the 8 columns of a wave by a fixed tree, the waves in order
-#pragma unroll
-    for (int d = 8; d <= 32; d <<= 1) { s0 += __shfl_xor(s0, d, 64); s1 += __shfl_xor(s1, d, 64); }
-    float2* const red = (float2*)ttab;
-    __syncthreads();
-    if (lane < 8) red[wave * 8 + lane] = make_float2(s0, s1);
-    __syncthreads();
-    if (tid < 8 && c < C) {
-      float2 a = red[tid];
-#pragma unroll
-      for (int w = 1; w < XD_NT / 64; ++w) { const float2 b = red[w * 8 + tid]; a.x += b.x; a.y += b.y; }
-      float* out = p.pool_part + ((long)((n0 + rr) * p.tiles_y + ty) * p.tiles_x + tx) * C + c;
-      out[0] = a.x; out[1] = a.y;
-    }
   }
 #endif
 }
@@ -361,7 +390,7 @@ static XdGeom xd_geometry(int Ho, int Wo, int k, int stride) {
   units |= 1;                                                   // odd: 16 rows then start on 16 different bank groups
   g.CW = units * 8;
   auto plane = [&](int th) { return ((((th - 1) * stride + k) * units) | 1) * 16; };
-  int th = XD_GROUPS * 16 / g.ntx;
+  int th = XD_GROUPS * (16 / g.ntx);
   if (stride == 2 && th > 16) th = 16;
   if (th > Ho) th = Ho;
   while (th > 1 && (size_t)plane(th) * XD_CH > XD_PLANES_MAX) --th;
@@ -374,14 +403,17 @@ static XdGeom xd_geometry(int Ho, int Wo, int k, int stride) {
   g.rq = 1;
   if (g.tiles_x == 1 && g.tiles_y == 1)
     while (g.rq < 4 && (g.rq + 1) * g.th * g.ntx <= 32 && (size_t)(g.rq + 1) * g.req_plane <= XD_PLANES_MAX) ++g.rq;
+  // as few groups as hold the segments; four always do (th <= 4 floor(16 / ntx); with several requests, at most 32 segments)
+  for (g.ng = 1; g.ng < XD_GROUPS && g.rq * ((g.th + g.ng - 1) / g.ng) * g.ntx > 16; ++g.ng) {}
+  g.na = (g.th + g.ng - 1) / g.ng;
   return g;
 }
-static size_t xd_planes(const XdGeom& g) {                      // also holds the staged output
-  const size_t x = (size_t)g.rq * g.req_plane, o = (size_t)((g.rq * g.th * g.ntx + 15) / 16 * 16) * XD_OUT_SEG * 4;
-  return (x > o ? x : o);
+static size_t xd_planes(const XdGeom& g, int stride) {          // with the rows past the tile that B reads; also holds the staged output
+  const size_t x = (size_t)g.rq * g.req_plane + (size_t)(g.na * g.ng - g.th) * stride * g.CW * 2, o = (size_t)g.ng * 16 * XD_OUT_SEG * 4;
+  return ((x > o ? x : o) + 15) / 16 * 16;
 }
-static size_t xd_lds(const XdGeom& g, int k, int Cin) {
-  return xd_planes(g) + (size_t)(4 + XD_CH * k * XD_TROW) * 4 + (size_t)((Cin + 31) / 32) * 1024 +
+static size_t xd_lds(const XdGeom& g, int k, int stride, int Cin) {
+  return xd_planes(g, stride) + (size_t)(4 + XD_CH * k * XD_TROW) * 4 + (size_t)((Cin + 31) / 32) * 1024 +
          (size_t)(g.rq * g.IH * (g.CW / 4) + 3) / 4 * 4 * 16;
 }
 constexpr size_t XD_LDS_MAX = 160 * 1024;
@@ -391,7 +423,7 @@ int expand_dw_pool_parts(int Ho, int Wo, int k, int stride) {
   return g.tiles_x * g.tiles_y;
 }
 // Each tile column has at least one 16-wide segment, and there are at most ceil(Ho / 16) tile rows: before the rows are
-// spread evenly a tile has min(16, Ho) at least (64 segments over at most 4 a row, and the planes of 17 rows fit for
+// spread evenly a tile has min(16, Ho) at least (four groups of 16 segments over at most 4 a row, and the planes of 17 rows fit for
 // every k and stride), and spreading them adds no tile.
 int expand_dw_pool_parts_max(int side) { return ((side + 15) / 16) * ((side + 15) / 16); }
 
@@ -399,7 +431,7 @@ bool expand_dw_ok(const ExpDwProblem& p) {
   if ((p.k != 3 && p.k != 5 && p.k != 7) || (p.stride != 1 && p.stride != 2) || p.Cin % 8 || p.C % 8) return false;
   if (p.act != SNA_ACT_RELU && p.act != SNA_ACT_HSWISH) return false;
   const XdGeom g = xd_geometry(p.Ho, p.Wo, p.k, p.stride);
-  return xd_lds(g, p.k, p.Cin) <= XD_LDS_MAX && g.tiles_x * g.tiles_y <= expand_dw_pool_parts_max(p.Ho > p.Wo ? p.Ho : p.Wo);
+  return xd_lds(g, p.k, p.stride, p.Cin) <= XD_LDS_MAX && g.tiles_x * g.tiles_y <= expand_dw_pool_parts_max(p.Ho > p.Wo ? p.Ho : p.Wo);
 }
 
 hipError_t launch_expand_dw(const ExpDwArgs& a, hipStream_t s) {
@@ -418,13 +450,13 @@ hipError_t launch_expand_dw(const ExpDwArgs& a, hipStream_t s) {
         if ((double)p.N * p.H * p.W * p.Cin * 2 >= 2147483648.0 || (double)p.N * p.Ho * p.Wo * p.C * 2 >= 2147483648.0)
           return hipErrorInvalidValue;                          // 32-bit buffer offsets; slice_conv has refused such a call
         const XdGeom g = xd_geometry(p.Ho, p.Wo, k, st);
-        p.th = g.th; p.ntx = g.ntx; p.rq = g.rq; p.tiles_x = g.tiles_x; p.tiles_y = g.tiles_y;
-        p.CW = g.CW; p.plane = g.plane; p.req_plane = g.req_plane; p.x_lds = (int)xd_planes(g);
+        p.th = g.th; p.ntx = g.ntx; p.rq = g.rq; p.ng = g.ng; p.na = g.na; p.tiles_x = g.tiles_x; p.tiles_y = g.tiles_y;
+        p.CW = g.CW; p.plane = g.plane; p.req_plane = g.req_plane; p.x_lds = (int)xd_planes(g, st);
         p.chunks = (p.C + XD_CH - 1) / XD_CH;
         p.tile_start = start;
         p.tiles = (p.N + g.rq - 1) / g.rq * g.tiles_x * g.tiles_y * p.chunks;
         start += tile_rows(p.tiles);
-        const size_t l = xd_lds(g, k, p.Cin);
+        const size_t l = xd_lds(g, k, st, p.Cin);
         if (l > lds) lds = l;
       }
       if (!b.n) continue;
