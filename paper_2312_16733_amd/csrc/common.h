@@ -101,6 +101,21 @@ struct DwProblem {
 };
 struct DwGroupArgs { int n; DwProblem p[SNA_MAX_GROUPS]; };
 
+// x / d for 0 <= x < 2^31, d made ready on the host: a multiplier of 31 + ceil(log2 d) fractional bits, rounded up, is off by
+// at most d / 2^(31 + ceil(log2 d)) <= 2^-31
+struct FastDiv {
+  unsigned m; int shift;            // shift < 0: d == 1
+  static FastDiv by(int d) {
+    if (d <= 1) return {0u, -1};
+    int l = 1;
+    while ((1ll << l) < d) ++l;
+    return {(unsigned)(((1ull << (31 + l)) / (unsigned)d) + 1), l - 1};
+  }
+#if defined(__HIPCC__)
+  __device__ __forceinline__ int div(int x) const { return shift < 0 ? x : (int)(__umulhi((unsigned)x, m) >> shift); }
+#endif
+};
+
 // Pointwise expand and depthwise convolution of an inverted-residual block in one launch
 struct ExpDwProblem {
   const void* x;        // [N][H][W][Cin] block input
@@ -114,6 +129,7 @@ struct ExpDwProblem {
   unsigned x_bytes, we_bytes;
   // filled by the launcher: output rows, 16-wide row segments and requests per block; tiles, channel groups; LDS layout
   int th, ntx, rq, ng, na, tiles_x, tiles_y, chunks, CW, plane, req_plane, x_lds;
+  FastDiv by_chunks, by_tiles_x, by_tiles_y;
   int tile_start, tiles;
 };
 struct ExpDwArgs { int n; int total_tiles; ExpDwProblem p[SNA_MAX_GROUPS]; };

@@ -56,6 +56,10 @@ struct XdGeom {
   int plane, req_plane;             // bytes per channel plane (an odd number of 16-byte units) and per request
 };
 
+// i / d for 0 <= i < 2^20, with inv = rcp(d): (i + 1/2) / d lies 1/(2 d) or more from an integer, the product within
+// (i + 1/2) / d * 2^-22 of it
+__device__ __forceinline__ int xd_div(int i, float inv) { return (int)(((float)i + 0.5f) * inv); }
+__device__ __forceinline__ float xd_rcp(int d) { return __builtin_amdgcn_rcpf((float)d); }
 __device__ __forceinline__ bool xd_finite(float v) { return fabsf(v) < __builtin_inff(); }
 
 template <int K, int STRIDE>
@@ -67,12 +71,11 @@ __global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs arg
     const int g = find_problem(args, blockIdx.x >> 3);
     if (g > 0) p = args.p[g];
   }
-  int local = tile_of_block(p);                     // the channel groups of a tile, which read the same input, on one XCD
+  const int local = tile_of_block(p);                           // the channel groups of a tile, which read the same input, on one XCD
   if (local < 0) return;
-  const int chunk = local % p.chunks; local /= p.chunks;
-  const int tx = local % p.tiles_x; local /= p.tiles_x;
-  const int ty = local % p.tiles_y;
-  const int n0 = local / p.tiles_y * p.rq;                      // first request of the block
+  const int t1 = p.by_chunks.div(local), t2 = p.by_tiles_x.div(t1), t3 = p.by_tiles_y.div(t2);
+  const int chunk = local - t1 * p.chunks, tx = t1 - t2 * p.tiles_x, ty = t2 - t3 * p.tiles_y;
+  const int n0 = t3 * p.rq;                                     // first request of the block
   const int rq = p.N - n0 < p.rq ? p.N - n0 : p.rq;
   constexpr int PAD = K / 2, OFF = 4 - PAD;                     // output column q reads plane columns q * STRIDE + OFF + s
   constexpr int KB = ((XD_SEG - 1) * STRIDE + OFF + K + 31) / 32;     // MFMAs per kernel row
@@ -120,10 +123,10 @@ __global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs arg
   const int ce = c0 + l16;                                      // this lane's expanded channel
   const float se = ce < C ? p.sc_e[ce] : 0.f, he = ce < C ? p.sh_e[ce] : 0.f;
 
-  const unsigned magic_nq = nq > 1 ? 0xFFFFFFFFu / (unsigned)nq + 1u : 0u, magic_rh = rh > 1 ? 0xFFFFFFFFu / (unsigned)rh + 1u : 0u;
+  const float inv_nq = xd_rcp(nq), inv_rh = xd_rcp(rh);
   for (int i = tid; i < ngroups * 4; i += XD_NT) {
-    const int t = nq > 1 ? (int)__umulhi((unsigned)i, magic_nq) : i, cq = i - t * nq;
-    const int rr = rh > 1 ? (int)__umulhi((unsigned)t, magic_rh) : t, ry = t - rr * rh;
+    const int t = xd_div(i, inv_nq), cq = i - t * nq;
+    const int rr = xd_div(t, inv_rh), ry = t - rr * rh;
     const int x = xa + 4 * cq, left = x1 - x;
     uint4 e;
     e.x = (unsigned)(rr * p.req_plane + ((y0 - iy0 + ry) * p.CW + x - ix0) * 2);
@@ -137,77 +140,99 @@ __global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs arg
   for (int i = tid; i < p.x_lds / 16; i += XD_NT) *(uint4*)(planes + i * 16) = make_uint4(0, 0, 0, 0);
   __syncthreads();
 
+  // what the loads above brought goes to LDS
+  auto finish_setup = [&] {
 #pragma unroll
-  for (int u = 0; u < WF_U; ++u)
-    if (tid + u * XD_NT < KS * 64) *(u32x4*)(wfrag + (tid + u * XD_NT) * 16) = wf[u];
-  for (int i = tid + WF_U * XD_NT; i < KS * 64; i += XD_NT)
-    *(u32x4*)(wfrag + i * 16) = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc_we, we_off(i), 0, 0));
-  if (tid < K * XD_CH) {
-    unsigned* const row = ttab + 4 + ((tid & 15) * K + (tid >> 4)) * XD_TROW;
-    *(uint4*)row = make_uint4(wrow[0] | (wrow[1] << 16), wrow[2] | (wrow[3] << 16), wrow[4] | (wrow[5] << 16), wrow[6]);
-    *(uint4*)(row + 4) = make_uint4(0, 0, 0, 0);
-    *(uint4*)(row + 8) = make_uint4(wrow[0] << 16, wrow[1] | (wrow[2] << 16), wrow[3] | (wrow[4] << 16), wrow[5] | (wrow[6] << 16));
-    *(uint4*)(row + 12) = make_uint4(0, 0, 0, 0);
-  }
-  if (tid == 0) *(uint4*)ttab = make_uint4(0, 0, 0, 0);
-  __syncthreads();
+    for (int u = 0; u < WF_U; ++u)
+      if (tid + u * XD_NT < KS * 64) *(u32x4*)(wfrag + (tid + u * XD_NT) * 16) = wf[u];
+    for (int i = tid + WF_U * XD_NT; i < KS * 64; i += XD_NT)
+      *(u32x4*)(wfrag + i * 16) = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc_we, we_off(i), 0, 0));
+    if (tid < K * XD_CH) {
+      unsigned* const row = ttab + 4 + ((tid & 15) * K + (tid >> 4)) * XD_TROW;
+      *(uint4*)row = make_uint4(wrow[0] | (wrow[1] << 16), wrow[2] | (wrow[3] << 16), wrow[4] | (wrow[5] << 16), wrow[6]);
+      *(uint4*)(row + 4) = make_uint4(0, 0, 0, 0);
+      *(uint4*)(row + 8) = make_uint4(wrow[0] << 16, wrow[1] | (wrow[2] << 16), wrow[3] | (wrow[4] << 16), wrow[5] | (wrow[6] << 16));
+      *(uint4*)(row + 12) = make_uint4(0, 0, 0, 0);
+    }
+    if (tid == 0) *(uint4*)ttab = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+  };
 
   // ---- A: expand ------------------------------------------------------------------------------
-  // A wave takes G groups of 16 pixels at a time, with the loads of the next G in flight: 4 where one step of 32 input
-  // channels is the whole reduction, 2 for two steps, else one group, 5 steps at a time.
-  auto expand = [&](auto act_c, auto g_c) {
-    constexpr int ACT = decltype(act_c)::value, G = decltype(g_c)::value, KU = G == 4 ? 1 : (G == 2 ? 2 : 5);
-    auto load_px = [&](int pg, int ks0, u32x4 (&v)[G][KU]) {
+  constexpr int NW = XD_NT / 64;
+  // Pixel loads: lane (l16, grp) takes channels 8 grp .. of 32 of pixel l16 of a group; past Cin it reads zeros
+  const unsigned px_lane = (unsigned)((l16 & 3) * Cin * 2 + grp * 16);
+  const unsigned px_tail = (KS - 1) * 32 + grp * 8 < Cin ? 0u : OOB;        // of the last 32 channels
+  char* const px_dst = planes + l16 * p.plane;
+  // rows 4 grp .. 4 grp + 3 of a group's 16 pixels, one quad, of channel l16
+  auto store_quad = [&](auto act_c, const f32x4& acc, const uint4& e) {
+    constexpr int ACT = decltype(act_c)::value;
+    float v[4];
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const unsigned off = pg + g < ngroups ? qtab[(pg + g) * 4 + (l16 >> 2)].w : OOB;
-        const unsigned base = off + (unsigned)((l16 & 3) * Cin * 2 + grp * 16);
+    for (int i = 0; i < 4; ++i) v[i] = apply_act(fmaf(acc[i], se, he), ACT);
+    if (e.x != 0xffffffffu) *(uint2*)(px_dst + e.x) = make_uint2(pack_bf16x2(v[0], v[1]) & e.y, pack_bf16x2(v[2], v[3]) & e.z);
+  };
+  // Up to 5 steps of 32 input channels: a wave has the loads of its next PF groups of 16 pixels in flight (one group ahead,
+  // waited for before the epilogue, a group took 2000 cycles, a load's round trip; 14^2, 112 -> 672, 7 x 7, four groups a
+  // wave: 9900 cycles for this phase), the first ones under the rest of the set-up.  Loads past the last group are
+  // out of range and cost no memory traffic; no branch stands between a load and its wait.
+  auto expand = [&](auto act_c, auto ku_c) {
+    constexpr int KU = decltype(ku_c)::value, PF = KU == 1 ? 8 : (KU == 2 ? 6 : (KU == 3 ? 4 : 3));
+    u32x4 px[PF][KU];
+    auto offset_of = [&](int pg) { return qtab[(pg < ngroups ? pg : 0) * 4 + (l16 >> 2)].w; };
+    auto request = [&](int pg, unsigned off, u32x4 (&v)[KU]) {
+      const unsigned base = (off + px_lane) | (pg < ngroups ? 0u : OOB);
 #pragma unroll
-        for (int j = 0; j < KU; ++j)
-          if (KU == 1 || ks0 + j < KS)
-            v[g][j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                rsrc_x, (ks0 + j) * 32 + grp * 8 < Cin && off != OOB ? base + (ks0 + j) * 64 : OOB, 0, 0));
-      }
+      for (int j = 0; j < KU; ++j)
+        v[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, (j + 1 < KU ? base : base | px_tail) + j * 64, 0, 0));
     };
-    u32x4 cur[G][KU], nxt[G][KU];
-    constexpr int STEP = G * (XD_NT / 64);
-    load_px(wave * G, 0, cur);
-    for (int pg = wave * G; pg < ngroups; pg += STEP) {
-      f32x4 acc[G];
 #pragma unroll
-      for (int g = 0; g < G; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int ks0 = 0; ks0 < KS; ks0 += KU) {
-        if (G == 1 && ks0 + KU < KS) load_px(pg, ks0 + KU, nxt);
-        else if (pg + STEP < ngroups) load_px(pg + STEP, 0, nxt);
+    for (int s = 0; s < PF; ++s) request(wave + s * NW, offset_of(wave + s * NW), px[s]);
+    finish_setup();
+    bf16x8 w[KU];
 #pragma unroll
-        for (int j = 0; j < KU; ++j)
-          if (KU == 1 || ks0 + j < KS) {
-            const uint4 w = *(const uint4*)(wfrag + ((ks0 + j) * 64 + lane) * 16);
+    for (int j = 0; j < KU; ++j) w[j] = *(const bf16x8*)(wfrag + (j * 64 + lane) * 16);
+    for (int pg = wave;;) {
 #pragma unroll
-            for (int g = 0; g < G; ++g)
-              acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, cur[g][j]), __builtin_bit_cast(bf16x8, w), acc[g], 0, 0, 0);
-          }
+      for (int s = 0; s < PF; ++s, pg += NW) {
+        if (pg >= ngroups) return;
+        uint4 e = qtab[pg * 4 + grp];
+        const unsigned off = offset_of(pg + PF * NW);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int g = 0; g < G; ++g)
-#pragma unroll
-          for (int j = 0; j < KU; ++j) cur[g][j] = nxt[g][j];
-      }
-#pragma unroll
-      for (int g = 0; g < G; ++g) {                             // rows 4 grp .. 4 grp + 3 of the 16 pixels: one quad
-        if (pg + g >= ngroups) break;
-        const uint4 e = qtab[(pg + g) * 4 + grp];
-        float v[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = apply_act(fmaf(acc[g][i], se, he), ACT);
-        if (e.x != 0xffffffffu)
-          *(uint2*)(planes + l16 * p.plane + e.x) = make_uint2(pack_bf16x2(v[0], v[1]) & e.y, pack_bf16x2(v[2], v[3]) & e.z);
+        for (int j = 0; j < KU; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, px[s][j]), w[j], acc, 0, 0, 0);
+        request(pg + PF * NW, off, px[s]);
+        asm volatile("" : "+v"(e.x), "+v"(e.y), "+v"(e.z));     // read up there, not behind the test of e.x
+        store_quad(act_c, acc, e);
       }
     }
   };
+  auto expand_wide = [&](auto act_c) {                          // more than 160 input channels
+    constexpr int KU = 5;
+    finish_setup();
+    for (int pg = wave; pg < ngroups; pg += NW) {
+      const unsigned base = qtab[pg * 4 + (l16 >> 2)].w + px_lane;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      for (int ks0 = 0; ks0 < KS; ks0 += KU) {
+        u32x4 v[KU];
+#pragma unroll
+        for (int j = 0; j < KU; ++j)
+          v[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, ks0 + j < KS - 1 ? base + (ks0 + j) * 64 : (ks0 + j == KS - 1 ? (base | px_tail) + (ks0 + j) * 64 : OOB), 0, 0));
+#pragma unroll
+        for (int j = 0; j < KU; ++j)
+          if (ks0 + j < KS)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v[j]), *(const bf16x8*)(wfrag + ((ks0 + j) * 64 + lane) * 16), acc, 0, 0, 0);
+      }
+      store_quad(act_c, acc, qtab[pg * 4 + grp]);
+    }
+  };
   auto expand_k = [&](auto act_c) {
-    if (KS == 1) expand(act_c, std::integral_constant<int, 4>{});
+    if (KS == 1) expand(act_c, std::integral_constant<int, 1>{});
     else if (KS == 2) expand(act_c, std::integral_constant<int, 2>{});
-    else expand(act_c, std::integral_constant<int, 1>{});
+    else if (KS == 3) expand(act_c, std::integral_constant<int, 3>{});
+    else if (KS == 4) expand(act_c, std::integral_constant<int, 4>{});
+    else if (KS == 5) expand(act_c, std::integral_constant<int, 5>{});
+    else expand_wide(act_c);
   };
   if (p.act == SNA_ACT_RELU) expand_k(std::integral_constant<int, SNA_ACT_RELU>{});
   else expand_k(std::integral_constant<int, SNA_ACT_HSWISH>{});
@@ -216,12 +241,11 @@ __global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs arg
   // ---- B: depthwise ---------------------------------------------------------------------------
   // Row l of every MFMA group is a segment (request rr, rows ng aa + g, column segment tt)
   const int ng = p.ng, seg_req = p.na * p.ntx;
-  const unsigned magic_ntx = p.ntx > 1 ? 0xFFFFFFFFu / (unsigned)p.ntx + 1u : 0u;
-  const unsigned magic_sr = seg_req > 1 ? 0xFFFFFFFFu / (unsigned)seg_req + 1u : 0u;
+  const float inv_ntx = xd_rcp(p.ntx), inv_sr = xd_rcp(seg_req);
   struct Seg { int rr, row, tt; };                              // row: of group 0
   auto segment = [&](int l) {
-    const int rr = seg_req > 1 ? (int)__umulhi((unsigned)l, magic_sr) : l, ii = l - rr * seg_req;
-    const int aa = p.ntx > 1 ? (int)__umulhi((unsigned)ii, magic_ntx) : ii;
+    const int rr = xd_div(l, inv_sr), ii = l - rr * seg_req;
+    const int aa = xd_div(ii, inv_ntx);
     return Seg{rr, aa * ng, ii - aa * p.ntx};
   };
   int seg_off;                                                  // plane offset of this lane's segment, MFMA row l16
@@ -453,6 +477,7 @@ hipError_t launch_expand_dw(const ExpDwArgs& a, hipStream_t s) {
         p.th = g.th; p.ntx = g.ntx; p.rq = g.rq; p.ng = g.ng; p.na = g.na; p.tiles_x = g.tiles_x; p.tiles_y = g.tiles_y;
         p.CW = g.CW; p.plane = g.plane; p.req_plane = g.req_plane; p.x_lds = (int)xd_planes(g, st);
         p.chunks = (p.C + XD_CH - 1) / XD_CH;
+        p.by_chunks = FastDiv::by(p.chunks); p.by_tiles_x = FastDiv::by(p.tiles_x); p.by_tiles_y = FastDiv::by(p.tiles_y);
         p.tile_start = start;
         p.tiles = (p.N + g.rq - 1) / g.rq * g.tiles_x * g.tiles_y * p.chunks;
         start += tile_rows(p.tiles);
