@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/subnetact.h"
 #include "tile_map.h"
 
@@ -70,6 +72,10 @@ struct ConvProblem {
   // kernel writes the raw sums to y and splitk_reduce_kernel finishes the layer in a second launch.
   float* part_buf;
   int* counters;                 // [tiles_base] zero-initialised ints of this problem
+  // Squeeze-excite gate of a pointwise stride-1 layer's input: x[n][pixel][c] is multiplied by gate[n * gate_stride + c] and
+  // rounded to bf16 on its way to the matrix pipe (nullptr: no gate)
+  const float* gate;
+  int gate_stride;
 };
 
 struct ConvGroupArgs {
@@ -140,6 +146,8 @@ struct SeProblem {
   const void* w1; const float* b1;  // [Q_max][C_max] stored; leading [Q][C] used
   const void* w2; const float* b2;  // [C_max][Q_max]
   float* pooled;        // [N][pool_segs][C] partial sums of the pool, written by the depthwise kernel's blocks
+  float* gate;          // [N][pool_segs * C], the first C of each row: the gate is left here and the layer that follows applies
+                        // it (may be `pooled`); nullptr: y = x * gate
   float* hidden;        // [N][Q] scratch
   int N, HW, C, Q;
   int w1_stride, w2_stride;
@@ -234,6 +242,7 @@ constexpr size_t kTileCounters = 16384;
 // ---- launchers (defined in the .hip files) ---------------------------------------------------
 hipError_t launch_igemm(const ConvGroupArgs& a, int variant, bool chunked, hipStream_t s);
 bool igemm_variant_ok(int variant, const ConvProblem& p);   // can this tile variant run this problem (some take 3x3 stride-1 layers only)
+bool igemm_gate_ok(const ConvProblem& p);                   // can any tile variant apply a gate to this problem's input
 hipError_t launch_splitk_reduce(const ConvGroupArgs& a, hipStream_t s);
 hipError_t launch_stem_pool(const StemPoolArgs& a, hipStream_t s);
 hipError_t launch_mbv3_head(const Mbv3HeadArgs& a, hipStream_t s);
@@ -292,6 +301,24 @@ __device__ __forceinline__ float apply_act(float v, int act) {
   if (act == SNA_ACT_RELU) return fmaxf(v, 0.f);
   if (act == SNA_ACT_HSWISH) return v * fminf(fmaxf(v + 3.f, 0.f), 6.f) * (1.f / 6.f);
   if (act == SNA_ACT_GELU) return v * normal_cdf(v);
+  return v;
+}
+// Sum over the 64 lanes, in a fixed order, left in lane 63: within rows of 16 lanes by shifts of 1, 2, 4, 8, then lane 15's
+// over rows 1 and 3, lane 31's over rows 2 and 3.  In the vector pipe, where shuffles go through LDS one after the other.
+__device__ __forceinline__ float lane_sum(float v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  auto add = [&](auto ctrl_c, auto rows_c) {
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl_c)::value, decltype(rows_c)::value, 0xf, false));
+  };
+  using std::integral_constant;
+  typedef integral_constant<int, 0xf> all_t;
+  add(integral_constant<int, 0x111>{}, all_t{});                // row_shr:1, zeros shifted in
+  add(integral_constant<int, 0x112>{}, all_t{});
+  add(integral_constant<int, 0x114>{}, all_t{});
+  add(integral_constant<int, 0x118>{}, all_t{});
+  add(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});      // row_bcast:15
+  add(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});      // row_bcast:31
+#endif
   return v;
 }
 // problem lookup for a grouped launch: linear scan over <= 16 entries (uniform per block)

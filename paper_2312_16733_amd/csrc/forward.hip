@@ -151,9 +151,16 @@ struct Fwd {
       }
       return t;
     }();
+    std::vector<TileShape> gate_shapes;            // a gated launch: only the variants that can run all its gated problems
+    for (size_t i = 0; i < n; ++i)
+      if (ps[i].gate) {
+        if (gate_shapes.empty()) gate_shapes = shapes;
+        for (size_t v = 0; v < gate_shapes.size(); ++v)
+          if (!igemm_variant_ok((int)v, ps[i])) gate_shapes[v].max_steps = 0;
+      }
     std::vector<TileWork> ws(n);
     for (size_t i = 0; i < n; ++i) ws[i] = {ps[i].M, ps[i].K, (ps[i].K8 + 7) / 8, ps[i].R * ps[i].S};
-    return pick_tile(ws.data(), n, split_mode, shapes.data());
+    return pick_tile(ws.data(), n, split_mode, gate_shapes.empty() ? shapes.data() : gate_shapes.data());
   }
 
   // Fill the launch-side fields of a problem for tile variant v (parts already decided).
@@ -373,15 +380,16 @@ struct Fwd {
     for (size_t i = 0; i < n; ++i) order[i] = i;
     auto steps = [&](size_t i) { const int kt = (ps[i].K8 + 7) / 8; return kt < ps[i].kt_part ? kt : ps[i].kt_part; };
     std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return steps(a) > steps(b); });
-    for (int chunked = 0; chunked < 2; ++chunked)
+    for (int flavour = 0; flavour < 3; ++flavour)          // plain, chunk-folding, gated
       for (int v = 0; v < igemm_num_variants(); ++v) {
+        const int chunked = flavour == 1;
         ConvGroupArgs a;
         a.n = 0;
         int start = 0;
         double flops = 0, bytes = 0;
         for (size_t i : order) {
           ConvProblem& p = ps[i];
-          if (var[i] != v || walks[v] != chunked) continue;
+          if (var[i] != v || (p.gate ? 2 : walks[v]) != flavour) continue;
           if (a.n == SNA_MAX_GROUPS) {       // more problems than one launch carries: flush
             a.total_tiles = start * kXcds;
             emit(PlanOp::IGEMM, v, chunked, KC_IGEMM, flops, bytes, a);
@@ -659,7 +667,7 @@ struct Fwd {
       if (!fill(g, p)) continue;
       flops += 4.0 * p.N * p.C * p.Q;
       macs += (int64_t)2 * p.N * p.C * p.Q;
-      bytes += 4.0 * p.N * p.HW * p.C + 4.0 * p.C * p.Q;
+      bytes += (p.gate ? 0.0 : 4.0 * p.N * p.HW * p.C) + 4.0 * p.C * p.Q;
       a.p[a.n++] = p;
     }
     if (a.n) emit(PlanOp::SE, 0, 0, KC_SE, flops, bytes, a);
@@ -1014,6 +1022,13 @@ sna_status Fwd::run_mbv3(const void*, float* logits) {
       const int st = j == 0 ? a.stage_stride[s] : 1;
       const int act = a.stage_act[s];
       auto on = [&](const Group& g) { return j < g.cfg->depth[s]; };      // LayerSelect
+      auto project = [&](Group& g, ConvProblem& p) {
+        p.x = g.buf[3]; p.N = g.n; p.H = out_size(g.H, 3, st); p.W = out_size(g.W, 3, st);
+        p.C = g.cfg->block_mid_ch[s][j];
+        slice_conv(p, tensor(pre + "project.w"), a.stage_ch[s], 1, 1);
+        sn(p, pre + "sn3", g);
+        p.act = SNA_ACT_NONE;
+      };
       expand_dw_slot(pre, s, j, st);
       conv_slot(false, [&](Group& g, ConvProblem& p) {
         if (!on(g) || g.fused_xd) return false;
@@ -1057,17 +1072,22 @@ sna_status Fwd::run_mbv3(const void*, float* logits) {
           if (net->calibrating) { p.pool_segs = 1; p.inv_hw = 1.f; }      // g.small holds the mean itself
           p.pooled = g.small;                                  // written by the depthwise launch above
           p.hidden = g.small + (size_t)p.pool_segs * g.n * m;
+          // The project layer scales its input itself where a tile variant can (a matter of its shape alone): then only
+          // the gate is computed here, into the request's first row of pool sums, which nothing reads any more.
+          ConvProblem c;
+          memset(&c, 0, sizeof(c));
+          project(g, c);
+          c.gate = p.pooled;
+          g.gate_stride = !net->calibrating && igemm_gate_ok(c) ? p.pool_segs * m : 0;
+          p.gate = g.gate_stride ? p.pooled : nullptr;
           return true;
         });
       }
       conv_slot(false, [&](Group& g, ConvProblem& p) {
         if (!on(g)) return false;
         const int co = a.stage_ch[s];
-        p.x = g.buf[3]; p.N = g.n; p.H = out_size(g.H, 3, st); p.W = out_size(g.W, 3, st);
-        p.C = g.cfg->block_mid_ch[s][j];
-        slice_conv(p, tensor(pre + "project.w"), co, 1, 1);
-        sn(p, pre + "sn3", g);
-        p.act = SNA_ACT_NONE;
+        project(g, p);
+        if (a.stage_se[s] && g.gate_stride) { p.gate = g.small; p.gate_stride = g.gate_stride; }
         if (st == 1 && g.C == co) p.res = g.cur;
         const int dst = g.cur_buf == 0 ? 1 : 0;
         p.y = g.buf[dst];

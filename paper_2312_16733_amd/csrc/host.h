@@ -46,6 +46,7 @@ struct Group {
   std::vector<int> reqs;             // their positions in the call, ascending
   bool contiguous = true;
   bool raw_input = false;            // cur points at the caller's unpadded request images
+  int gate_stride = 0;               // the block being emitted: floats between the requests' gates its project layer applies (0: scaled before it)
   bool fused_xd = false;             // the block being emitted runs its expand and depthwise layers as one launch
   char* buf[NBUF] = {nullptr};
   char* inbuf = nullptr;

@@ -233,16 +233,10 @@ int depthwise_pool_blocks(int Ho, int Wo, int C) {
 //   h = relu(W1[:Q,:C] z + b1[:Q]);  gate = hardsigmoid(W2[:C,:Q] h + b2[:C]);  y = x * gate
 // Two launches: h per request, then gate and scaling together.
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // h[n][o] = relu(W1[o, :C] . z[n] + b1[o]).  A block owns one request and 32 outputs.  It first
 // builds z in LDS (partial sums added in block order, then scaled by 1 / HW); each of its 4 waves
 // then computes 8 outputs together: lanes read 8 consecutive bf16 weights (16 bytes) of each row and
-// the matching z, and the wave reduces each output in a fixed butterfly order.
+// the matching z, and the wave reduces each output in a fixed order.
 __global__ __launch_bounds__(256) void se_hidden_kernel(const SeGroupArgs args) {
   extern __shared__ __attribute__((aligned(16))) float z[];
   const int g = find_problem(args, blockIdx.x);
@@ -295,25 +289,27 @@ __global__ __launch_bounds__(256) void se_hidden_kernel(const SeGroupArgs args) 
   float mine = 0.f;                          // lane t keeps output t's sum
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
-    const float sum = wave_sum(a[t]);
-    if (lane == t) mine = sum;
+    const float sum = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lane_sum(a[t])), 63));
+    mine = lane == t ? sum : mine;
   }
   if (lane < 8 && o0 + lane < p.Q) p.hidden[(long)n * p.Q + o0 + lane] = fmaxf(mine + bias, 0.f);
 }
 
 // gate[n][c] = hardsigmoid(W2[c, :Q] . h[n] + b2[c]);  y[n, hw, c] = bf16(x[n, hw, c] * gate[n][c]).
 // A block owns one request, 64 channels and SE_PIX pixels: its threads first compute the 64 gate
-// values (4 threads per channel, each a quarter of Q in order, the quarters added in order), then
+// values (4 threads per channel, each every fourth octet of Q in order, so that they read a row together, their sums added in
+// a fixed order; a quarter of the row each, 64 cache lines per load, took 8.5 us instead of 5.2 for 64 x 960 gates of 240), then
 // stream the pixels, 8 lanes per pixel row of 128 bytes.  The gate is recomputed by every pixel
 // segment of a request: 64 x Q multiply-adds against one more launch and a round trip through memory.
 constexpr int SE_PIX = 256;
 constexpr int SE_MAX_Q = 512;       // squeeze channels per gate (host-checked)
-__global__ __launch_bounds__(256) void se_gate_scale_kernel(const SeGroupArgs args) {
+template <bool SCALE>       // false: the gate goes to p.gate and the layer that follows applies it
+__global__ __launch_bounds__(256) void se_gate_kernel(const SeGroupArgs args) {
   __shared__ float gate_s[64];
   __shared__ __attribute__((aligned(16))) float h_s[SE_MAX_Q];
   const int g = find_problem(args, blockIdx.x);
   const SeProblem& p = args.p[g];
-  const int cgroups = (p.C + 63) / 64, psegs = (p.HW + SE_PIX - 1) / SE_PIX;
+  const int cgroups = (p.C + 63) / 64, psegs = SCALE ? (p.HW + SE_PIX - 1) / SE_PIX : 1;
   int local = blockIdx.x - p.tile_start;
   const int pseg = local % psegs; local /= psegs;
   const int cg = local % cgroups;
@@ -328,19 +324,18 @@ __global__ __launch_bounds__(256) void se_gate_scale_kernel(const SeGroupArgs ar
   uint4 px[SE_PIX / 32];
 #pragma unroll
   for (int j = 0; j < SE_PIX / 32; ++j)
-    px[j] = (live && h0 + 32 * j < h_end) ? *(const uint4*)(x + (long)(h0 + 32 * j) * p.C) : make_uint4(0, 0, 0, 0);
+    px[j] = (SCALE && live && h0 + 32 * j < h_end) ? *(const uint4*)(x + (long)(h0 + 32 * j) * p.C) : make_uint4(0, 0, 0, 0);
   // so do the gate's weights: a fixed trip count, loads first (a loop over [begin, end) paid the L2 latency once per 8
   // weights), and ahead of the hidden vector, which the barrier waits for
   const int gc = cg * 64 + (threadIdx.x >> 2), quarter = threadIdx.x & 3;
-  const int q8n = p.Q >> 3, per = (q8n + 3) >> 2;            // per <= SE_MAX_Q / 32
-  const int end = (quarter + 1) * per < q8n ? (quarter + 1) * per : q8n;
+  const int q8n = p.Q >> 3;
   uint4 wq[SE_MAX_Q / 32];
   {
     const bf16_t* w = (const bf16_t*)p.w2 + (long)gc * p.w2_stride;
 #pragma unroll
     for (int j = 0; j < SE_MAX_Q / 32; ++j) {
-      const int i8 = quarter * per + j;
-      wq[j] = (gc < p.C && j < per && i8 < end) ? *(const uint4*)(w + i8 * 8) : make_uint4(0, 0, 0, 0);
+      const int i8 = j * 4 + quarter;
+      wq[j] = (gc < p.C && i8 < q8n) ? *(const uint4*)(w + i8 * 8) : make_uint4(0, 0, 0, 0);
     }
   }
   const float b2 = gc < p.C ? p.b2[gc] : 0.f;
@@ -351,8 +346,8 @@ __global__ __launch_bounds__(256) void se_gate_scale_kernel(const SeGroupArgs ar
     if (gc < p.C) {
 #pragma unroll
       for (int j = 0; j < SE_MAX_Q / 32; ++j) {
-        const int i8 = quarter * per + j;
-        if (j < per && i8 < end) {
+        const int i8 = j * 4 + quarter;
+        if (i8 < q8n) {
           float wv[8];
           unpack8(wq[j], wv);
           const float4 x0 = *(const float4*)(h_s + i8 * 8), x1 = *(const float4*)(h_s + i8 * 8 + 4);
@@ -361,10 +356,15 @@ __global__ __launch_bounds__(256) void se_gate_scale_kernel(const SeGroupArgs ar
         }
       }
     }
-    // quarters 0..3 of a channel sit in adjacent lanes: ((q0 + q1) + (q2 + q3))
+    // the channel's four sums sit in adjacent lanes: ((0 + 1) + (2 + 3))
     a += __shfl_xor(a, 1, 64);
     a += __shfl_xor(a, 2, 64);
-    if (quarter == 0 && gc < p.C) gate_s[threadIdx.x >> 2] = fminf(fmaxf(a + b2 + 3.f, 0.f), 6.f) * (1.f / 6.f);
+    const float gate = fminf(fmaxf(a + b2 + 3.f, 0.f), 6.f) * (1.f / 6.f);
+    if (!SCALE) {
+      if (quarter == 0 && gc < p.C) p.gate[(long)n * p.pool_segs * p.C + gc] = gate;
+      return;
+    }
+    if (quarter == 0 && gc < p.C) gate_s[threadIdx.x >> 2] = gate;
   }
   __syncthreads();
   if (!live) return;
@@ -384,28 +384,144 @@ __global__ __launch_bounds__(256) void se_gate_scale_kernel(const SeGroupArgs ar
   }
 }
 
+// Pool, hidden layer and gate of one request in one launch, for gates that the next layer applies: a block of 16 waves per
+// request, with the arithmetic of the two kernels above (same bits).  Taken for layers of up to SE_ONE_MACS weights, which
+// one CU reads in about the time that the second launch costs.
+constexpr int SE_ONE_NT = 1024, SE_ONE_MACS = 32 * 1024, SE_ONE_Q = 256;
+__global__ __launch_bounds__(SE_ONE_NT) void se_one_kernel(const SeGroupArgs args) {
+  extern __shared__ __attribute__((aligned(16))) float z[];
+  __shared__ __attribute__((aligned(16))) float h_s[SE_ONE_Q];
+  const int g = find_problem(args, blockIdx.x);
+  const SeProblem& p = args.p[g];
+  const int n = blockIdx.x - p.tile_start;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bf16_t* w1 = (const bf16_t*)p.w1;
+  auto rows = [&](int o0, int i8, uint4 (&wq)[8]) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      wq[t] = i8 < (p.C >> 3) && o0 + t < p.Q ? *(const uint4*)(w1 + (long)(o0 + t) * p.w1_stride + i8 * 8) : make_uint4(0, 0, 0, 0);
+  };
+  uint4 cur[8], nxt[8];
+  rows(wave * 8, lane, cur);
+  // weights of the first 256 gates, four threads a channel
+  const int quarter = tid & 3, q8n = p.Q >> 3;
+  uint4 wq[SE_ONE_Q / 32];
+  float b2 = 0.f;
+  auto gate_weights = [&](int c) {
+    const bf16_t* w = (const bf16_t*)p.w2 + (long)c * p.w2_stride;
+#pragma unroll
+    for (int j = 0; j < SE_ONE_Q / 32; ++j) {
+      const int i8 = j * 4 + quarter;
+      wq[j] = (c < p.C && i8 < q8n) ? *(const uint4*)(w + i8 * 8) : make_uint4(0, 0, 0, 0);
+    }
+    b2 = c < p.C ? p.b2[c] : 0.f;
+  };
+  gate_weights(tid >> 2);
+  const float* part = p.pooled + (long)n * p.pool_segs * p.C;
+  for (int c4 = tid; c4 < (p.C >> 2); c4 += SE_ONE_NT) {
+    float4 a = *(const float4*)(part + c4 * 4);
+#pragma unroll 8
+    for (int sgm = 1; sgm < p.pool_segs; ++sgm) {
+      const float4 b = *(const float4*)(part + (long)sgm * p.C + c4 * 4);
+      a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+    }
+    a.x *= p.inv_hw; a.y *= p.inv_hw; a.z *= p.inv_hw; a.w *= p.inv_hw;
+    *(float4*)(z + c4 * 4) = a;
+  }
+  __syncthreads();                           // from here on nobody reads the pool sums, whose first row takes the gate
+  for (int o0 = wave * 8; o0 < p.Q; o0 += SE_ONE_NT / 8) {
+    if (o0 != wave * 8) rows(o0, lane, cur);
+    const float bias = lane < 8 && o0 + lane < p.Q ? p.b1[o0 + lane] : 0.f;
+    float a[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) a[t] = 0.f;
+    for (int i8 = lane; i8 < (p.C >> 3); i8 += 64) {
+      const float4 x0 = *(const float4*)(z + i8 * 8), x1 = *(const float4*)(z + i8 * 8 + 4);
+      rows(o0, i8 + 64, nxt);
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        float wv[8];
+        unpack8(cur[t], wv);
+        a[t] = fmaf(wv[0], x0.x, a[t]); a[t] = fmaf(wv[1], x0.y, a[t]); a[t] = fmaf(wv[2], x0.z, a[t]); a[t] = fmaf(wv[3], x0.w, a[t]);
+        a[t] = fmaf(wv[4], x1.x, a[t]); a[t] = fmaf(wv[5], x1.y, a[t]); a[t] = fmaf(wv[6], x1.z, a[t]); a[t] = fmaf(wv[7], x1.w, a[t]);
+      }
+#pragma unroll
+      for (int t = 0; t < 8; ++t) cur[t] = nxt[t];
+    }
+    float mine = 0.f;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const float sum = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lane_sum(a[t])), 63));
+      mine = lane == t ? sum : mine;
+    }
+    if (lane < 8 && o0 + lane < p.Q) h_s[o0 + lane] = fmaxf(mine + bias, 0.f);
+  }
+  __syncthreads();
+  for (int c = tid >> 2; c < p.C; c += SE_ONE_NT / 4) {
+    if (c != tid >> 2) gate_weights(c);
+    float a = 0.f;
+#pragma unroll
+    for (int j = 0; j < SE_ONE_Q / 32; ++j) {
+      const int i8 = j * 4 + quarter;
+      if (i8 < q8n) {
+        float wv[8];
+        unpack8(wq[j], wv);
+        const float4 x0 = *(const float4*)(h_s + i8 * 8), x1 = *(const float4*)(h_s + i8 * 8 + 4);
+        a = fmaf(wv[0], x0.x, a); a = fmaf(wv[1], x0.y, a); a = fmaf(wv[2], x0.z, a); a = fmaf(wv[3], x0.w, a);
+        a = fmaf(wv[4], x1.x, a); a = fmaf(wv[5], x1.y, a); a = fmaf(wv[6], x1.z, a); a = fmaf(wv[7], x1.w, a);
+      }
+    }
+    a += __shfl_xor(a, 1, 64);
+    a += __shfl_xor(a, 2, 64);
+    if (quarter == 0) p.gate[(long)n * p.pool_segs * p.C + c] = fminf(fmaxf(a + b2 + 3.f, 0.f), 6.f) * (1.f / 6.f);
+  }
+}
+
 hipError_t launch_se(const SeGroupArgs& a, hipStream_t s) {
-  if (a.n == 0) return hipSuccess;
-  SeGroupArgs b = a;
-  int start = 0, c_max = 0;
-  for (int i = 0; i < b.n; ++i) {
-    if (b.p[i].C % 8 || b.p[i].Q % 8 || b.p[i].Q > SE_MAX_Q || b.p[i].w1_stride % 8 || b.p[i].w2_stride % 8 || b.p[i].pool_segs < 1)
+  for (int i = 0; i < a.n; ++i) {
+    const SeProblem& p = a.p[i];
+    if (p.C % 8 || p.Q % 8 || p.Q > SE_MAX_Q || p.w1_stride % 8 || p.w2_stride % 8 || p.pool_segs < 1 || p.C * 4 > 64 * 1024)
       return hipErrorInvalidValue;
-    b.p[i].tiles = b.p[i].N * ((b.p[i].Q + 31) / 32);
-    b.p[i].tile_start = start; start += b.p[i].tiles;
-    if (b.p[i].C > c_max) c_max = b.p[i].C;
   }
-  if (c_max * 4 > 64 * 1024) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(se_hidden_kernel, dim3(start), dim3(256), c_max * 4, s, b);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  start = 0;
-  for (int i = 0; i < b.n; ++i) {
-    b.p[i].tiles = b.p[i].N * ((b.p[i].C + 63) / 64) * ((b.p[i].HW + SE_PIX - 1) / SE_PIX);
-    b.p[i].tile_start = start; start += b.p[i].tiles;
+  enum { ONE, TWO, SCALED };                 // gate in one launch; in two; in two with the scaling pass
+  auto way = [](const SeProblem& p) { return !p.gate ? SCALED : (p.Q <= SE_ONE_Q && p.Q * p.C <= SE_ONE_MACS ? ONE : TWO); };
+  // the problems that `take` accepts, `tiles` blocks each
+  SeGroupArgs b;
+  int blocks = 0, c_max = 0;
+  auto gather = [&](auto take, auto tiles) {
+    b.n = 0; blocks = 0; c_max = 0;
+    for (int i = 0; i < a.n; ++i) {
+      if (!take(way(a.p[i]))) continue;
+      SeProblem& p = b.p[b.n++];
+      p = a.p[i];
+      p.tiles = tiles(p);
+      p.tile_start = blocks;
+      blocks += p.tiles;
+      if (p.C > c_max) c_max = p.C;
+    }
+    return b.n > 0;
+  };
+  if (gather([](int w) { return w == ONE; }, [](const SeProblem& p) { return p.N; })) {
+    hipLaunchKernelGGL(se_one_kernel, dim3(blocks), dim3(SE_ONE_NT), c_max * 4, s, b);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(se_gate_scale_kernel, dim3(start), dim3(256), 0, s, b);
-  return hipGetLastError();
+  if (gather([](int w) { return w != ONE; }, [](const SeProblem& p) { return p.N * ((p.Q + 31) / 32); })) {
+    hipLaunchKernelGGL(se_hidden_kernel, dim3(blocks), dim3(256), c_max * 4, s, b);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (gather([](int w) { return w == TWO; }, [](const SeProblem& p) { return p.N * ((p.C + 63) / 64); })) {
+    hipLaunchKernelGGL(se_gate_kernel<false>, dim3(blocks), dim3(256), 0, s, b);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (gather([](int w) { return w == SCALED; }, [](const SeProblem& p) { return p.N * ((p.C + 63) / 64) * ((p.HW + SE_PIX - 1) / SE_PIX); })) {
+    hipLaunchKernelGGL(se_gate_kernel<true>, dim3(blocks), dim3(256), 0, s, b);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace sna

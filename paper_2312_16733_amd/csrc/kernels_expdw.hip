@@ -345,29 +345,32 @@ __global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs arg
 
   // ---- pool: this wave's two channels, per request; a lane over its outputs in order, the lanes by a fixed tree ---------
   if (p.pool_part) {
-    bool ok[4];
-    int row[4], req[4];
+    float s0[4], s1[4];
+    int req[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
+    for (int v = 0; v < 4; ++v) {                               // the groups' rows of a segment belong to one request
       const Seg sg = segment(4 * grp + v);
-      row[v] = sg.row; req[v] = sg.rr;
-      ok[v] = sg.rr < rq && sg.tt * XD_SEG + l16 < tw_v;
+      const int rows = sg.rr < rq && sg.tt * XD_SEG + l16 < tw_v ? th_v - sg.row : 0;     // valid rows g = 0 ..
+      req[v] = sg.rr;
+      s0[v] = s1[v] = 0.f;
+#pragma unroll
+      for (int g = 0; g < XD_GROUPS; ++g) {
+        const unsigned w = g < rows && g < ng ? packed[g][v] : 0u;
+        s0[v] += __uint_as_float(w << 16);
+        s1[v] += __uint_as_float(w & 0xffff0000u);
+      }
     }
     const int c = c0 + wave * 2;
     for (int rr = 0; rr < rq; ++rr) {
-      float s0 = 0.f, s1 = 0.f;
+      float a0 = 0.f, a1 = 0.f;
 #pragma unroll
-      for (int g = 0; g < XD_GROUPS; ++g)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const unsigned w = ok[v] && req[v] == rr && row[v] + g < th_v && g < ng ? packed[g][v] : 0u;
-          s0 += __uint_as_float(w << 16);
-          s1 += __uint_as_float(w & 0xffff0000u);
-        }
-#pragma unroll
-      for (int d = 1; d <= 32; d <<= 1) { s0 += __shfl_xor(s0, d, 64); s1 += __shfl_xor(s1, d, 64); }
-      if (lane == 0 && c < C)
-        *(float2*)(p.pool_part + ((long)((n0 + rr) * p.tiles_y + ty) * p.tiles_x + tx) * C + c) = make_float2(s0, s1);
+      for (int v = 0; v < 4; ++v) {
+        a0 += req[v] == rr ? s0[v] : 0.f;
+        a1 += req[v] == rr ? s1[v] : 0.f;
+      }
+      a0 = lane_sum(a0); a1 = lane_sum(a1);
+      if (lane == 63 && c < C)
+        *(float2*)(p.pool_part + ((long)((n0 + rr) * p.tiles_y + ty) * p.tiles_x + tx) * C + c) = make_float2(a0, a1);
     }
   }
   __syncthreads();                                              // every wave is done with the planes

@@ -1,6 +1,7 @@
 // Tile variants of the implicit-GEMM kernel and their launcher, the 3x3 slab kernel, and the reduction kernel of split
 // reductions.
 #include "igemm_kernel.h"
+#include "tile_choice.h"
 
 #include <atomic>
 
@@ -382,20 +383,28 @@ hipError_t launch_splitk_reduce(const ConvGroupArgs& a, hipStream_t s) {
 
 #define SNA_VARIANT(BM, BN, WM, WN, NS) \
   { BM, BN, 64 * WM * WN, IgemmCfg<BM, BN, WM, WN, NS>::SMEM, NS, IgemmCfg<BM, BN, WM, WN, NS>::STAGE_B, \
-    IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, 0>, igemm_kernel<BM, BN, WM, WN, NS, true, 0>, false, false, false }
+    IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, 0>, igemm_kernel<BM, BN, WM, WN, NS, true, 0>, nullptr, false, false, false }
+#define SNA_GATED_VARIANT(BM, BN, WM, WN, NS) \
+  { BM, BN, 64 * WM * WN, IgemmCfg<BM, BN, WM, WN, NS>::SMEM, NS, IgemmCfg<BM, BN, WM, WN, NS>::STAGE_B, \
+    IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, 0>, igemm_kernel<BM, BN, WM, WN, NS, true, 0>, \
+    igemm_kernel<BM, BN, WM, WN, NS, false, 0, true>, false, false, false }
 #define SNA_WS_VARIANT(BM, BN, WM, WN, NS) \
   { BM, BN, 128 * WM * WN, IgemmCfg<BM, BN, WM, WN, NS>::SMEM, NS, IgemmCfg<BM, BN, WM, WN, NS>::STAGE_B, \
-    IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, WM * WN>, igemm_kernel<BM, BN, WM, WN, NS, true, WM * WN>, false, false, false }
+    IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, WM * WN>, igemm_kernel<BM, BN, WM, WN, NS, true, WM * WN>, nullptr, false, false, false, true }
+#define SNA_WS_GATED_VARIANT(BM, BN, WM, WN, NS) \
+  { BM, BN, 128 * WM * WN, IgemmCfg<BM, BN, WM, WN, NS>::SMEM, NS, IgemmCfg<BM, BN, WM, WN, NS>::STAGE_B, \
+    IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, WM * WN>, igemm_kernel<BM, BN, WM, WN, NS, true, WM * WN>, \
+    igemm_kernel<BM, BN, WM, WN, NS, false, WM * WN, true>, false, false, false, true }
 #define SNA_SLAB_VARIANT(BM, BN, WM, WN, NS) \
   { BM, BN, 64 * WM * WN, 0, NS, BN * ROW_B, IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, \
-    conv3_slab_kernel<BM, BN, WM, WN, NS, false>, conv3_slab_kernel<BM, BN, WM, WN, NS, true>, true, false, false }
+    conv3_slab_kernel<BM, BN, WM, WN, NS, false>, conv3_slab_kernel<BM, BN, WM, WN, NS, true>, nullptr, true, false, false }
 // The formula of pick_tile chooses from 14 variants; the others are reached through tuning.  Ids 28.. are the deep rings.
 static const Variant kPlain[] = {
-    SNA_VARIANT(128, 128, 2, 2, 2), SNA_VARIANT(128, 64, 2, 2, 2), SNA_VARIANT(128, 96, 4, 1, 2),
-    SNA_VARIANT(128, 32, 4, 1, 4),  SNA_VARIANT(64, 64, 2, 2, 4),  SNA_VARIANT(64, 128, 1, 4, 3),
+    SNA_VARIANT(128, 128, 2, 2, 2), SNA_GATED_VARIANT(128, 64, 2, 2, 2), SNA_VARIANT(128, 96, 4, 1, 2),
+    SNA_VARIANT(128, 32, 4, 1, 4),  SNA_GATED_VARIANT(64, 64, 2, 2, 4),  SNA_VARIANT(64, 128, 1, 4, 3),
     SNA_VARIANT(32, 128, 1, 4, 4),
-    SNA_WS_VARIANT(64, 64, 2, 2, 4), SNA_WS_VARIANT(64, 128, 1, 4, 3), SNA_WS_VARIANT(128, 64, 2, 2, 3),
-    SNA_WS_VARIANT(128, 96, 4, 1, 3), SNA_WS_VARIANT(128, 128, 2, 2, 3), SNA_VARIANT(128, 32, 4, 1, 2),
+    SNA_WS_VARIANT(64, 64, 2, 2, 4), SNA_WS_GATED_VARIANT(64, 128, 1, 4, 3), SNA_WS_VARIANT(128, 64, 2, 2, 3),
+    SNA_WS_VARIANT(128, 96, 4, 1, 3), SNA_WS_VARIANT(128, 128, 2, 2, 3), SNA_GATED_VARIANT(128, 32, 4, 1, 2),
     SNA_WS_VARIANT(32, 128, 1, 4, 4), SNA_VARIANT(128, 192, 2, 2, 2), SNA_WS_VARIANT(128, 192, 2, 2, 3),
     // 16..: 3x3 stride-1 layers with the activation slab in LDS
     SNA_SLAB_VARIANT(128, 128, 2, 2, 2), SNA_SLAB_VARIANT(128, 64, 2, 2, 2), SNA_SLAB_VARIANT(128, 96, 4, 1, 2),
@@ -427,9 +436,27 @@ static int steps_of(const ConvProblem& p) {
   return kt < p.kt_part ? kt : p.kt_part;
 }
 
+// Bytes of the gates of the requests that one tile of the problem can touch
+static int gate_bytes(const Variant& v, const ConvProblem& p) {
+  const int hw = p.Ho * p.Wo, most = (v.bm - 1 + hw - 1) / hw + 1;
+  return (most < p.N ? most : p.N) * p.C * 4;
+}
+
+bool igemm_gate_ok(const ConvProblem& p) {
+  for (int v = 0; v < kNumVariants; ++v)
+    if (igemm_variant_ok(v, p)) return true;
+  return false;
+}
+
 bool igemm_variant_ok(int variant, const ConvProblem& p) {
   if (variant < 0 || variant >= kNumVariants) return false;
   const Variant& v = variant_of(variant);
+  if (p.gate) {
+    const int kt = (p.K8 + 7) >> 3, stages = kt < v.ns ? kt : v.ns, gates = gate_bytes(v, p);
+    if (!v.fn_gated || p.R * p.S != 1 || p.stride != 1 || p.pad != 0 || p.parts != 1 || kt > chunk_steps(kt) ||
+        (!v.fetchers && gates > kGateLoads * 16 * v.threads) ||
+        stages * v.stage_bytes + gates > kLdsMax) return false;
+  }
   if (v.deep) return steps_of(p) <= igemm_max_steps(variant);
   if (!v.slab) return true;
   return p.R == 3 && p.S == 3 && p.stride == 1 && p.pad == 1 && p.parts == 1 && !p.out_fp32 && p.W >= 2 &&
@@ -440,13 +467,16 @@ bool igemm_variant_ok(int variant, const ConvProblem& p) {
 hipError_t launch_igemm(const ConvGroupArgs& a, int variant, bool chunked, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
   if (variant < 0 || variant >= kNumVariants) return hipErrorInvalidValue;
-  static std::atomic<bool> attr_done[kNumVariants][2];     // handles on several threads may get here together
+  static std::atomic<bool> attr_done[kNumVariants][3];     // handles on several threads may get here together
   const Variant& v = variant_of(variant);
-  void (*fn)(const ConvGroupArgs) = chunked ? v.fn_chunked : v.fn;
-  if (!attr_done[variant][chunked].load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, v.slab || v.deep ? kLdsMax : v.smem);
+  const bool gated = a.p[0].gate != nullptr;               // of all problems or of none
+  void (*fn)(const ConvGroupArgs) = gated ? v.fn_gated : (chunked ? v.fn_chunked : v.fn);
+  const int flavour = gated ? 2 : (chunked ? 1 : 0);
+  if (!fn || (gated && chunked)) return hipErrorInvalidValue;
+  if (!attr_done[variant][flavour].load(std::memory_order_acquire)) {
+    hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, v.slab || v.deep || gated ? kLdsMax : v.smem);
     if (e != hipSuccess) return e;
-    attr_done[variant][chunked].store(true, std::memory_order_release);
+    attr_done[variant][flavour].store(true, std::memory_order_release);
   }
   // a launch whose problems all have fewer K steps than the ring has stages only touches the
   // leading stages: asking for less LDS lets more blocks share a CU
@@ -459,6 +489,14 @@ hipError_t launch_igemm(const ConvGroupArgs& a, int variant, bool chunked, hipSt
   const int stages = kt_max < v.ns ? kt_max : v.ns;
   int smem = stages * v.stage_bytes;
   if (v.deep) smem += (kt_taps + 1) / 2 * 2 * ROW_B + (chunked && v.totals_lds ? v.bm * v.bn * 4 : 0);      // tap table, running totals
+  if (gated) {
+    smem = 0;
+    for (int i = 0; i < a.n; ++i) {
+      if (!a.p[i].gate || !igemm_variant_ok(variant, a.p[i])) return hipErrorInvalidValue;
+      const int kt = steps_of(a.p[i]), need = (kt < v.ns ? kt : v.ns) * v.stage_bytes + gate_bytes(v, a.p[i]);
+      if (need > smem) smem = need;
+    }
+  }
   if (smem < v.epi_bytes) smem = v.epi_bytes;
   if (v.deep && kt_max > kDeepMaxSteps) return hipErrorInvalidValue;
   if (v.slab) {
