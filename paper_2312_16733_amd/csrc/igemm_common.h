@@ -45,6 +45,12 @@ __device__ __forceinline__ u32x4 lds_read_b128(unsigned addr, int imm) {
   return v;
 }
 
+__device__ __forceinline__ void lds_write_b128(unsigned addr, u32x4 v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("ds_write_b128 %0, %1" :: "v"(addr), "v"(v) : "memory");
+#endif
+}
+
 // N such reads and the wait for them in one block, so that nothing can come between: no copy of a register whose data is
 // still on its way, and no address in a register that a read returns to.
 template <int N>
@@ -60,6 +66,11 @@ __device__ __forceinline__ void lds_read_b128_now(u32x4 (&v)[N], const unsigned 
                  "ds_read_b128 %4, %9\n\ts_waitcnt lgkmcnt(0)"
                  : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4])
                  : "v"(addr[0]), "v"(addr[1]), "v"(addr[2]), "v"(addr[3]), "v"(addr[4]) : "memory");
+  } else if constexpr (N == 6) {
+    asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %7\n\tds_read_b128 %2, %8\n\tds_read_b128 %3, %9\n\t"
+                 "ds_read_b128 %4, %10\n\tds_read_b128 %5, %11\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5])
+                 : "v"(addr[0]), "v"(addr[1]), "v"(addr[2]), "v"(addr[3]), "v"(addr[4]), "v"(addr[5]) : "memory");
   } else {
     static_assert(N == 8, "as many as the rings ask for");
     asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
