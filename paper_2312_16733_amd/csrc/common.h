@@ -28,6 +28,21 @@ enum KClass {
   KC_COUNT = 12
 };
 
+// x / d for 0 <= x < 2^31, d made ready on the host: a multiplier of 31 + ceil(log2 d) fractional bits, rounded up, is off by
+// at most d / 2^(31 + ceil(log2 d)) <= 2^-31
+struct FastDiv {
+  unsigned m; int shift;            // shift < 0: d == 1
+  static FastDiv by(int d) {
+    if (d <= 1) return {0u, -1};
+    int l = 1;
+    while ((1ll << l) < d) ++l;
+    return {(unsigned)(((1ull << (31 + l)) / (unsigned)d) + 1), l - 1};
+  }
+#if defined(__HIPCC__)
+  __device__ __forceinline__ int div(int x) const { return shift < 0 ? x : (int)(__umulhi((unsigned)x, m) >> shift); }
+#endif
+};
+
 // ---- one problem of a grouped launch -------------------------------------------------------
 // A grouped launch carries up to SNA_MAX_GROUPS problems by value in the kernel
 // arguments; block b belongs to the problem whose [tile_start, tile_start + tiles)
@@ -50,6 +65,7 @@ struct ConvProblem {
   unsigned magic_wo, magic_ho;   // floor(2^32 / d) + 1 for d = Wo, Ho (0 when d == 1): x / d = mulhi(x, magic) while x * d < 2^32
   int inv_s;            // ceil(2^16 / S): tap row r = (rs * inv_s) >> 16
   int tiles_n;          // tiles along K (igemm)
+  FastDiv by_tiles_n, by_tiles_base, by_c8;      // (igemm)
   int tile_start, tiles;
   int act;              // sna_act
   int out_fp32;         // 1: y is float (logits), else storage dtype
@@ -106,21 +122,6 @@ struct DwProblem {
   int tile_start, tiles;
 };
 struct DwGroupArgs { int n; DwProblem p[SNA_MAX_GROUPS]; };
-
-// x / d for 0 <= x < 2^31, d made ready on the host: a multiplier of 31 + ceil(log2 d) fractional bits, rounded up, is off by
-// at most d / 2^(31 + ceil(log2 d)) <= 2^-31
-struct FastDiv {
-  unsigned m; int shift;            // shift < 0: d == 1
-  static FastDiv by(int d) {
-    if (d <= 1) return {0u, -1};
-    int l = 1;
-    while ((1ll << l) < d) ++l;
-    return {(unsigned)(((1ull << (31 + l)) / (unsigned)d) + 1), l - 1};
-  }
-#if defined(__HIPCC__)
-  __device__ __forceinline__ int div(int x) const { return shift < 0 ? x : (int)(__umulhi((unsigned)x, m) >> shift); }
-#endif
-};
 
 // Pointwise expand and depthwise convolution of an inverted-residual block in one launch
 struct ExpDwProblem {

@@ -127,7 +127,7 @@ struct Fwd {
     p.K = K; p.R = ksize; p.S = ksize; p.stride = stride; p.pad = ksize / 2;
     p.Ho = out_size(p.H, ksize, stride); p.Wo = out_size(p.W, ksize, stride);
     p.M = p.N * p.Ho * p.Wo;
-    p.C8 = p.C / 8; p.K8 = p.R * p.S * p.C8;
+    p.C8 = p.C / 8; p.K8 = p.R * p.S * p.C8; p.by_c8 = FastDiv::by(p.C8);
     p.magic_wo = p.Wo > 1 ? (unsigned)((1ull << 32) / (unsigned)p.Wo + 1) : 0;
     p.magic_ho = p.Ho > 1 ? (unsigned)((1ull << 32) / (unsigned)p.Ho + 1) : 0;
     if ((double)p.M * (p.Wo > p.Ho ? p.Wo : p.Ho) >= 4294967296.0) err = hipErrorInvalidValue;   // reciprocal range
@@ -170,6 +170,7 @@ struct Fwd {
     q.tiles_n = (q.K + bn - 1) / bn;
     q.tiles_base = ((q.M + bm - 1) / bm) * q.tiles_n;
     q.tiles = q.tiles_base * q.parts;
+    q.by_tiles_n = FastDiv::by(q.tiles_n); q.by_tiles_base = FastDiv::by(q.tiles_base);
     // reduction inside the matrix kernel: the chunk sums are kept tile by tile (bm x bn floats each)
     if (q.counters) q.part_stride = (unsigned long)q.tiles_base * bm * bn * 4;
   }

@@ -55,6 +55,13 @@ __device__ __forceinline__ void store_f8_agent(float* ptr, const float* v) {    
     __hip_atomic_store(q + i, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
+__device__ __forceinline__ void store_f4_agent(float* ptr, const float* v) {      // 4 floats, 16-byte aligned
+  unsigned long long* q = (unsigned long long*)ptr;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    __hip_atomic_store(q + i, (unsigned long long)__float_as_uint(v[2 * i]) | ((unsigned long long)__float_as_uint(v[2 * i + 1]) << 32),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ __forceinline__ void load_f8_agent(const float* ptr, float4& lo, float4& hi) {
   const unsigned long long* q = (const unsigned long long*)ptr;
   unsigned long long w[4];
@@ -199,10 +206,10 @@ void igemm_kernel(const ConvGroupArgs args) {
   if (local < 0) return;
   int part = 0;                            // which K range of the problem this block reduces over
   if (p.parts > 1) {
-    part = local / p.tiles_base;
+    part = p.by_tiles_base.div(local);
     local -= part * p.tiles_base;
   }
-  const int tn = local % p.tiles_n, tm = local / p.tiles_n;
+  const int tm = p.by_tiles_n.div(local), tn = local - tm * p.tiles_n;
   const int m0 = tm * BM, n0 = tn * BN;
 
   constexpr int NW = WARPS_M * WARPS_N;
@@ -227,7 +234,7 @@ void igemm_kernel(const ConvGroupArgs args) {
     // in the activations, in the weights, the tap's number, and bit 31 set past the end of the reduction.
     for (int e = threadIdx.x; e < tab_steps * 8; e += 64 * (WARPS_M * WARPS_N + FW)) {
       const unsigned u = (unsigned)(kt0 * 8 + e);
-      const unsigned t = u / (unsigned)p.C8, o = u - t * (unsigned)p.C8;
+      const unsigned t = (unsigned)p.by_c8.div((int)u), o = u - t * (unsigned)p.C8;
       const int r = ((int)t * p.inv_s) >> 16, s = (int)t - r * S;
       u32x4 v = {(unsigned)(((r * Wd + s) * C + (int)o * 8) * 2), (unsigned)((r * p.wr + s * p.ws + (int)o * 8) * 2), t & 63u,
                  (int)t < RS ? 0u : 0x80000000u};
@@ -319,7 +326,7 @@ void igemm_kernel(const ConvGroupArgs args) {
   // reduction position of this thread's unit: tap rs and channel octet c8 (the deep rings look it up instead)
   int rs = 0, c8 = 0;
   if constexpr (!DEEP) {
-    rs = (kt0 * 8 + kc) / p.C8;
+    rs = p.by_c8.div(kt0 * 8 + kc);
     c8 = kt0 * 8 + kc - rs * p.C8;
   }
 
@@ -581,16 +588,14 @@ void igemm_kernel(const ConvGroupArgs args) {
     sh[j] = (do_math && !in_kernel_reduce && p.shift && k < p.K) ? p.shift[k] : 0.f;
   }
 
-  // The deep rings' tiles have the registers to request the residual rows here, too (one round trip less at the end)
-  constexpr bool RES_EARLY = DEEP && !LARGE;
-  uint4 res_early[RES_EARLY ? 32 * (WTN / 8) / 64 : 1];
-  if (RES_EARLY && do_math && p.res && !in_kernel_reduce) {
+  // The small deep rings have the registers to request the residual rows here, too (one round trip less at the end)
+  constexpr bool DIRECT = DEEP && !LARGE;
+  const int px_m = m0 + wm * WTM + (lane & 31), px_k = n0 + wn * WTN + (lane >> 5) * 4;      // DIRECT: this lane's pixel, channels px_k + 8 q ..
+  uint2 res_early[DIRECT ? 4 : 1];
+  if (DIRECT && do_math && p.res && !in_kernel_reduce) {
 #pragma unroll
-    for (int t = 0; t < 32 * (WTN / 8) / 64; ++t) {
-      const int id = t * 64 + lane, row = id / (WTN / 8), oct = id - row * (WTN / 8);
-      const int m = m0 + wm * WTM + row, k = n0 + wn * WTN + oct * 8;
-      res_early[t] = (m < p.M && k < p.K) ? *(const uint4*)((const bf16_t*)p.res + (long)m * p.res_stride + k) : make_uint4(0, 0, 0, 0);
-    }
+    for (int q = 0; q < 4; ++q)
+      res_early[q] = (px_m < p.M && px_k + 8 * q < p.K) ? *(const uint2*)((const bf16_t*)p.res + (long)px_m * p.res_stride + px_k + 8 * q) : make_uint2(0, 0);
   }
 
   // CHUNKED: the reduction is summed in chunks of p.kt_chunk steps, each accumulated from zero and
@@ -745,9 +750,9 @@ void igemm_kernel(const ConvGroupArgs args) {
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
       };
-      auto mfma = [&](int b, int ks) {
-        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[b][ks]),
-                                                            __builtin_bit_cast(bf16x8, fb[b][ks]), acc[0][0], 0, 0, 0);
+      auto mfma = [&](int b, int ks) {           // channels as rows, pixels as columns: see the epilogue
+        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[b][ks]),
+                                                            __builtin_bit_cast(bf16x8, fa[b][ks]), acc[0][0], 0, 0, 0);
       };
       auto step = [&](auto i_c, auto more_c) {   // step i of a group; more: another one follows
         constexpr int b = decltype(i_c)::value & 1;
@@ -841,7 +846,53 @@ void igemm_kernel(const ConvGroupArgs args) {
   constexpr int PAIRS = 32 * OCT / 64;         // (row, octet) pairs per lane
   // ACT, RES (0 none, 1 added before the activation, 2 after) and F32 are uniform over the launch's
   // problem: one dispatch below instead of per-element tests.
-  auto epilogue = [&](auto act_c, auto res_c, auto f32_c) {
+  // Small deep rings: the product was taken transposed, so that accumulator elements 4 q .. 4 q + 3 of a lane are channels
+  // 8 q + 4 (l / 32) .. + 3 of pixel l % 32, and go out as four 8-byte pieces with no turn through LDS, which is on the
+  // critical path of a launch of few tiles (0.48 us of a lone request's 3.5 us a launch).  Only SubnetNorm's vectors do.
+  auto epilogue_direct = [&](auto act_c, auto res_c, auto f32_c) __attribute__((always_inline)) {
+    constexpr int ACT = decltype(act_c)::value, RES = decltype(res_c)::value;
+    constexpr bool F32 = decltype(f32_c)::value;
+    float* const norm = (float*)smem + wave * 64;               // this wave's 32 scales, then 32 shifts
+    norm[lane] = lane < 32 ? sc[0] : sh[0];
+    __builtin_amdgcn_wave_barrier();
+    float4 sc4[4], sh4[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      sc4[q] = *(const float4*)(norm + 8 * q + (lane >> 5) * 4);
+      sh4[q] = *(const float4*)(norm + 32 + 8 * q + (lane >> 5) * 4);
+    }
+    if (px_m >= p.M) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = px_k + 8 * q;
+      const float scq[4] = {sc4[q].x, sc4[q].y, sc4[q].z, sc4[q].w}, shq[4] = {sh4[q].x, sh4[q].y, sh4[q].z, sh4[q].w};
+      const float rv[4] = {__uint_as_float(res_early[DIRECT ? q : 0].x << 16), __uint_as_float(res_early[DIRECT ? q : 0].x & 0xffff0000u),
+                           __uint_as_float(res_early[DIRECT ? q : 0].y << 16), __uint_as_float(res_early[DIRECT ? q : 0].y & 0xffff0000u)};
+      float val[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int v = 4 * q + e;
+        val[e] = fmaf(CHUNKED ? tot[0][0][v] + acc[0][0][v] : acc[0][0][v], scq[e], shq[e]);
+        if (RES == 1) val[e] += rv[e];
+        val[e] = apply_act(val[e], ACT);
+        if (RES == 2) val[e] += rv[e];
+      }
+      if (k >= p.K) continue;
+      if (F32) {
+        if (in_kernel_reduce)
+          store_f4_agent((float*)((char*)p.part_buf + (size_t)part * p.part_stride) + (size_t)local * (BM * BN) + (px_m - m0) * BN + (k - n0), val);
+        else
+          *(float4*)((float*)((char*)p.y + (size_t)part * p.part_stride) + (long)px_m * p.y_stride + k) = make_float4(val[0], val[1], val[2], val[3]);
+      } else {
+        *(uint2*)((bf16_t*)p.y + (long)px_m * p.y_stride + k) = make_uint2(pack_bf16x2(val[0], val[1]), pack_bf16x2(val[2], val[3]));
+      }
+    }
+  };
+  auto epilogue = [&](auto act_c, auto res_c, auto f32_c) __attribute__((always_inline)) {
+    if constexpr (DIRECT) {
+      epilogue_direct(act_c, res_c, f32_c);
+      return;
+    }
     constexpr int ACT = decltype(act_c)::value, RES = decltype(res_c)::value;
     constexpr bool F32 = decltype(f32_c)::value;
     // Residual rows.  With several 32-row strips per wave they are all requested up front, so that
@@ -850,11 +901,6 @@ void igemm_kernel(const ConvGroupArgs args) {
     constexpr bool RES_UP_FRONT = TM > 1;
     uint4 r4[TM][PAIRS];
     auto load_res = [&](int i) {
-      if constexpr (RES_EARLY) {
-#pragma unroll
-        for (int t = 0; t < PAIRS; ++t) r4[i][t] = res_early[t];
-        return;
-      }
 #pragma unroll
       for (int t = 0; t < PAIRS; ++t) {
         const int id = t * 64 + lane;

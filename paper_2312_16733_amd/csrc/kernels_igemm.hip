@@ -49,7 +49,7 @@ void conv3_slab_kernel(const ConvGroupArgs args) {
   }
   const int local = tile_of_block(p);
   if (local < 0) return;
-  const int tn = local % p.tiles_n, tm = local / p.tiles_n;
+  const int tm = p.by_tiles_n.div(local), tn = local - tm * p.tiles_n;
   const int m0 = tm * BM, n0 = tn * BN;
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tid = threadIdx.x;
@@ -93,7 +93,7 @@ void conv3_slab_kernel(const ConvGroupArgs args) {
     if (row < BN && k < p.K) b_ok |= 1u << j;
     b_base[j] = k * p.wk * 2;
   }
-  int rs = kc / C8;
+  int rs = p.by_c8.div(kc);
   int c8 = kc - rs * C8;
   const int KT = (p.K8 + 7) >> 3;
   lds_char* const dma_b = (lds_char*)smem + n_it * NT * 16 + (wave * 8) * ROW_B;
@@ -147,7 +147,7 @@ void conv3_slab_kernel(const ConvGroupArgs args) {
   }
   const unsigned zero_addr = lds0 + (unsigned)units * 16;
   // reduction position of this lane's unit in the slice about to be read: tap (ar, as), octet ac8
-  int ars = frag_hi / C8, ac8 = frag_hi - ars * C8;
+  int ars = p.by_c8.div(frag_hi), ac8 = frag_hi - ars * C8;
   int a_r = 0, a_s = ars;                                   // ars <= 1 here
   unsigned a_addr[TM];
   auto a_next = [&]() {                                     // addresses of the current slice, then advance by two units
