@@ -10,7 +10,9 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsubnetact.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # leading scalar kernel arguments arrive in registers
+         "-mllvm", "-amdgpu-kernarg-preload-count=14"]
 
 
 def sources():

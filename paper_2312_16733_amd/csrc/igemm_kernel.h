@@ -173,11 +173,13 @@ __device__ __forceinline__ int gate_request(const ConvProblem& p, int m) {      
 // MFMAs.  (Scaled between LDS and the matrix pipe, 20 instructions a fragment and by every wave that reads it, the 64x128
 // tile took 13.6 us instead of 12.1 on 12544 x 112 outputs over 672 channels.)  The gates of the tile's requests lie in LDS behind
 // the ring's stages.
-template <int BM, int BN, int WARPS_M, int WARPS_N, int NS, bool CHUNKED, int FW, bool GATED = false>
-__global__ __launch_bounds__(64 * (WARPS_M * WARPS_N + FW),
-                             FW ? (BM * BN >= 128 * 128 || deep_large(BM, BN, WARPS_M * WARPS_N, NS, FW) ? 2 : 4)
-                                : (CHUNKED ? (BM * BN == 128 * 64 ? 3 : (BM * BN > 128 * 128 ? 1 : 2)) : igemm_min_waves(BM, BN, NS)))
-void igemm_kernel(const ConvGroupArgs args) {
+constexpr int igemm_waves(int bm, int bn, int n_math, int ns, bool chunked, int fw) {
+  return fw ? (bm * bn >= 128 * 128 || deep_large(bm, bn, n_math, ns, fw) ? 2 : 4)
+            : (chunked ? (bm * bn == 128 * 64 ? 3 : (bm * bn > 128 * 128 ? 1 : 2)) : igemm_min_waves(bm, bn, ns));
+}
+// Tile `local` of problem p, which comes by value: uniform fields live in SGPRs across the asm blocks.
+template <int BM, int BN, int WARPS_M, int WARPS_N, int NS, bool CHUNKED, int FW, bool GATED>
+__device__ __forceinline__ void igemm_tile(const ConvProblem p, int local) {
 #if defined(__HIP_DEVICE_COMPILE__)        // the host pass needs the symbol only, not the body
   using Cfg = IgemmCfg<BM, BN, WARPS_M, WARPS_N, NS, FW>;
   constexpr bool WS = FW > 0;
@@ -195,15 +197,6 @@ void igemm_kernel(const ConvGroupArgs args) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const unsigned lds0 = (unsigned)(size_t)(lds_char*)smem;              // LDS byte address of the tiles
 
-  // by value: uniform fields live in SGPRs across the asm blocks.  The first problem's descriptor sits at
-  // a fixed kernarg offset, so its load does not wait for the problem search (most launches carry one).
-  ConvProblem p = args.p[0];
-  if (args.n > 1) {
-    const int g = find_problem(args, blockIdx.x >> 3);
-    if (g > 0) p = args.p[g];
-  }
-  int local = tile_of_block(p);
-  if (local < 0) return;
   int part = 0;                            // which K range of the problem this block reduces over
   if (p.parts > 1) {
     part = p.by_tiles_base.div(local);
@@ -1027,6 +1020,48 @@ void igemm_kernel(const ConvGroupArgs args) {
 #endif
 }
 
+template <int BM, int BN, int WARPS_M, int WARPS_N, int NS, bool CHUNKED, int FW, bool GATED = false>
+__global__ __launch_bounds__(64 * (WARPS_M * WARPS_N + FW), igemm_waves(BM, BN, WARPS_M * WARPS_N, NS, CHUNKED, FW))
+void igemm_kernel(const ConvGroupArgs args) {
+  // The first problem's descriptor sits at a fixed offset of the arguments, so its load does not wait for the problem search.
+  ConvProblem p = args.p[0];
+  if (args.n > 1) {
+    const int g = find_problem(args, blockIdx.x >> 3);
+    if (g > 0) p = args.p[g];
+  }
+  const int local = tile_of_block(p);
+  if (local < 0) return;
+  igemm_tile<BM, BN, WARPS_M, WARPS_N, NS, CHUNKED, FW, GATED>(p, local);
+}
+
+// A lone pointwise stride-1 problem on a small deep ring.  What the first loads need comes in scalar arguments, which the
+// dispatch puts into registers (they lead the list: 12 of the 14 words there is room for); a struct's first use waits
+// 0.36 us for a load of it, in a launch of 3 us.  The rest of the descriptor is read under the first loads.
+struct PwArgs {                        // host side of the scalars
+  const void *x, *w; unsigned x_bytes, w_bytes; int M, tiles; unsigned ck, tn, tn_m; int wk;
+  static bool fits(const ConvProblem& p) {
+    return p.R == 1 && p.S == 1 && p.stride == 1 && p.pad == 0 && p.parts == 1 && p.tile_start == 0 && p.C8 < 65536 && p.K / 8 < 65536 && p.tiles_n < (1 << 24);
+  }
+  static PwArgs of(const ConvProblem& p) {
+    return {p.x, p.w, p.x_bytes, p.w_bytes, p.M, p.tiles, (unsigned)p.C8 | (unsigned)(p.K / 8) << 16,
+            (unsigned)p.tiles_n | (unsigned)(p.by_tiles_n.shift + 1) << 24, p.by_tiles_n.m, p.wk};
+  }
+};
+template <int BM, int BN, int WARPS_M, int WARPS_N, int NS, bool CHUNKED, int FW, bool GATED>
+__global__ __launch_bounds__(64 * (WARPS_M * WARPS_N + FW), igemm_waves(BM, BN, WARPS_M * WARPS_N, NS, CHUNKED, FW))
+void igemm_pw_kernel(const void* x, const void* w, unsigned x_bytes, unsigned w_bytes, int M, int tiles, unsigned ck, unsigned tn,
+                     unsigned tn_m, int wk, const ConvProblem q) {
+  ConvProblem p = q;
+  p.x = x; p.w = w; p.x_bytes = x_bytes; p.w_bytes = w_bytes; p.M = M; p.wk = wk;
+  p.C8 = (int)(ck & 0xffffu); p.K8 = p.C8; p.C = p.C8 * 8; p.K = (int)(ck >> 16) * 8;
+  p.tiles = tiles; p.tile_start = 0; p.tiles_n = (int)(tn & 0xffffffu); p.by_tiles_n.m = tn_m; p.by_tiles_n.shift = (int)(tn >> 24) - 1;
+  p.R = 1; p.S = 1; p.stride = 1; p.pad = 0; p.parts = 1; p.counters = nullptr; p.kt_part = 1 << 30;
+  const int local = tile_of_block(p);
+  if (local < 0) return;
+  igemm_tile<BM, BN, WARPS_M, WARPS_N, NS, CHUNKED, FW, GATED>(p, local);
+}
+typedef void (*PwKernel)(const void*, const void*, unsigned, unsigned, int, int, unsigned, unsigned, unsigned, int, const ConvProblem);
+
 // One tile variant: the kernel with and without in-register chunk sums, and what its launch needs
 struct Variant {
   int bm, bn, threads, smem, ns, stage_bytes, epi_bytes;
@@ -1037,6 +1072,7 @@ struct Variant {
                          // bound for pointwise layers as well, which have no table but whose times were not measured beyond)
   bool totals_lds;       // its chunk-folding kernel keeps the running totals in LDS
   bool fetchers = false; // waves of its own fetch
+  PwKernel pw = nullptr, pw_chunked = nullptr, pw_gated = nullptr;      // for a lone pointwise problem
 };
 constexpr int kDeepMaxSteps = 128;
 constexpr int kDeepVariantCount = 3;

@@ -467,14 +467,16 @@ bool igemm_variant_ok(int variant, const ConvProblem& p) {
 hipError_t launch_igemm(const ConvGroupArgs& a, int variant, bool chunked, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
   if (variant < 0 || variant >= kNumVariants) return hipErrorInvalidValue;
-  static std::atomic<bool> attr_done[kNumVariants][3];     // handles on several threads may get here together
+  static std::atomic<bool> attr_done[kNumVariants][6];     // handles on several threads may get here together
   const Variant& v = variant_of(variant);
   const bool gated = a.p[0].gate != nullptr;               // of all problems or of none
   void (*fn)(const ConvGroupArgs) = gated ? v.fn_gated : (chunked ? v.fn_chunked : v.fn);
-  const int flavour = gated ? 2 : (chunked ? 1 : 0);
+  PwKernel pw = gated ? v.pw_gated : (chunked ? v.pw_chunked : v.pw);
+  if (a.n != 1 || !PwArgs::fits(a.p[0])) pw = nullptr;
+  const int flavour = (gated ? 2 : (chunked ? 1 : 0)) + (pw ? 3 : 0);
   if (!fn || (gated && chunked)) return hipErrorInvalidValue;
   if (!attr_done[variant][flavour].load(std::memory_order_acquire)) {
-    hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, v.slab || v.deep || gated ? kLdsMax : v.smem);
+    hipError_t e = hipFuncSetAttribute(pw ? (const void*)pw : (const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, v.slab || v.deep || gated ? kLdsMax : v.smem);
     if (e != hipSuccess) return e;
     attr_done[variant][flavour].store(true, std::memory_order_release);
   }
@@ -507,7 +509,12 @@ hipError_t launch_igemm(const ConvGroupArgs& a, int variant, bool chunked, hipSt
       if (need > smem) smem = need;
     }
   }
-  hipLaunchKernelGGL(fn, dim3(a.total_tiles), dim3(v.threads), smem, s, a);
+  if (pw) {
+    const PwArgs w = PwArgs::of(a.p[0]);
+    hipLaunchKernelGGL(pw, dim3(a.total_tiles), dim3(v.threads), smem, s, w.x, w.w, w.x_bytes, w.w_bytes, w.M, w.tiles, w.ck, w.tn, w.tn_m, w.wk, a.p[0]);
+  } else {
+    hipLaunchKernelGGL(fn, dim3(a.total_tiles), dim3(v.threads), smem, s, a);
+  }
   return hipGetLastError();
 }
 
