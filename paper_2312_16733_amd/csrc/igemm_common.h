@@ -23,7 +23,7 @@ template <int BM, int BN, int WARPS_M, int WARPS_N, int NS, int FW = 0>
 struct IgemmCfg {
   static constexpr int NWAVES = WARPS_M * WARPS_N, NTHREADS = 64 * (FW ? FW : NWAVES);   // computing waves, fetching threads
   static constexpr int WTM = BM / WARPS_M, WTN = BN / WARPS_N;
-  static constexpr int TM = WTM / 32, TN = WTN / 32;
+  static constexpr int TM = WTM < 32 ? 1 : WTM / 32, TN = WTN / 32;      // 32x32 tiles of a wave (half of one: see the small deep rings)
   static constexpr int PASS_ROWS = NTHREADS / 8;                 // tile rows fetched per pass of the block
   static constexpr int A_IT = (BM + PASS_ROWS - 1) / PASS_ROWS, B_IT = (BN + PASS_ROWS - 1) / PASS_ROWS;
   static constexpr int STAGE_B = (BM + BN) * ROW_B;

@@ -37,8 +37,8 @@ constexpr int igemm_min_waves(int bm, int bn, int ns) {
 }
 
 // Deep rings: tap table, waves that only fetch, fragments read ahead across K steps.  `small`: one 32x32 tile per computing
-// wave and eight stages, for launches of few tiles; `large`: several tiles per wave and four stages, one block per CU.
-constexpr bool deep_small(int bm, int bn, int n_math, int ns, int fw) { return fw > 0 && ns >= 5 && bm * bn == n_math * 32 * 32; }
+// wave or half of one, and eight stages, for launches of few tiles; `large`: several tiles per wave and four stages, one block per CU.
+constexpr bool deep_small(int bm, int bn, int n_math, int ns, int fw) { return fw > 0 && ns >= 5 && bm * bn <= n_math * 32 * 32; }
 constexpr bool deep_large(int bm, int bn, int n_math, int ns, int fw) { return fw > 0 && ns >= 4 && bm * bn > n_math * 32 * 32; }
 
 // Accesses that are coherent across the chip without cache-wide flushes: relaxed atomics at agent
@@ -187,7 +187,8 @@ __device__ __forceinline__ void igemm_tile(const ConvProblem p, int local) {
   constexpr int G = LARGE ? 1 : 2;         // deep rings: K steps between barriers
   static_assert(!DEEP || (NS % G == 0 && NS >= 3 * G && NS / G <= 7), "whole groups of stages");
   constexpr int WTM = Cfg::WTM, WTN = Cfg::WTN, TM = Cfg::TM, TN = Cfg::TN;
-  static_assert(TM >= 1 && TN >= 1 && WTM % 32 == 0 && WTN % 32 == 0, "wave tile");
+  constexpr bool HALF = DEEP && WTM == 16;       // a wave computes 16 pixels x 32 channels
+  static_assert(TM >= 1 && TN >= 1 && (WTM % 32 == 0 || HALF) && WTN % 32 == 0, "wave tile");
   static_assert(BM % 8 == 0 && BN % 8 == 0 && Cfg::PASS_ROWS % 16 == 0, "a thread's rows in all passes share one swizzle, (row >> 1) & 7");
   constexpr int A_IT = Cfg::A_IT, B_IT = Cfg::B_IT, L = A_IT + B_IT;   // DMA loads per thread per stage
   static_assert(NS >= 1 && (NS - 2) * L < 64, "vmcnt range");
@@ -283,7 +284,7 @@ __device__ __forceinline__ void igemm_tile(const ConvProblem p, int local) {
 
   // Gates of the tile's requests, [request][C] in LDS: brought by the computing waves where others fetch, else requested
   // ahead of the ring's first loads and written behind them
-  const unsigned gate_lds = GATED ? (unsigned)((KT < NS ? KT : NS) * Cfg::STAGE_B) : 0u;
+  const unsigned gate_lds = GATED ? (unsigned)((KT >= NS ? NS : (HALF ? (KT + G - 1) / G * G : KT)) * Cfg::STAGE_B) : 0u;
   const int gate_n0 = GATED ? gate_request(p, m0) : 0, gate_c4 = C >> 2;
   const int gate_cnt = GATED ? (gate_request(p, m0 + BM - 1 < p.M ? m0 + BM - 1 : p.M - 1) - gate_n0 + 1) * gate_c4 : 0;
   float4 gate_v[GATED ? kGateLoads : 1];
@@ -583,12 +584,15 @@ __device__ __forceinline__ void igemm_tile(const ConvProblem p, int local) {
 
   // The small deep rings have the registers to request the residual rows here, too (one round trip less at the end)
   constexpr bool DIRECT = DEEP && !LARGE;
-  const int px_m = m0 + wm * WTM + (lane & 31), px_k = n0 + wn * WTN + (lane >> 5) * 4;      // DIRECT: this lane's pixel, channels px_k + 8 q ..
-  uint2 res_early[DIRECT ? 4 : 1];
+  // DIRECT: this lane's pixel and its PIECES runs of four channels, px_k + PIECE q ..
+  constexpr int PIECES = HALF ? 2 : 4, PIECE = HALF ? 16 : 8;
+  const int lane_k = (HALF ? lane >> 4 : lane >> 5) * 4;
+  const int px_m = m0 + wm * WTM + (lane & (HALF ? 15 : 31)), px_k = n0 + wn * WTN + lane_k;
+  uint2 res_early[DIRECT ? PIECES : 1];
   if (DIRECT && do_math && p.res && !in_kernel_reduce) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      res_early[q] = (px_m < p.M && px_k + 8 * q < p.K) ? *(const uint2*)((const bf16_t*)p.res + (long)px_m * p.res_stride + px_k + 8 * q) : make_uint2(0, 0);
+    for (int q = 0; q < PIECES; ++q)
+      res_early[q] = (px_m < p.M && px_k + PIECE * q < p.K) ? *(const uint2*)((const bf16_t*)p.res + (long)px_m * p.res_stride + px_k + PIECE * q) : make_uint2(0, 0);
   }
 
   // CHUNKED: the reduction is summed in chunks of p.kt_chunk steps, each accumulated from zero and
@@ -612,10 +616,7 @@ __device__ __forceinline__ void igemm_tile(const ConvProblem p, int local) {
     // barrier and an LDS latency per step, the address arithmetic of a tap change in the fetching wave.  Here the taps are
     // looked up, the loads run NS - 2 G steps ahead, a step's fragments are read under the MFMAs of the step before, and
     // the fetching and the computing waves meet once in G steps, in the second: then the next group has landed, and the
-    // group before is in registers, its stages free.  0.10 us a step for a 32x32 tile on its own (49 x 720 outputs, 16 to
-    // 64 steps); with nothing but its four dependent MFMAs left in a step it took 0.11, so that chain is all there is (its
-    // order is the bits' order).  One request of the largest ResNet-shaped subnet 991 -> 491 us, of the smallest 412 -> 263,
-    // 3 sequences 703 -> 502.
+    // group before is in registers, its stages free.
     if (do_load) {
       // wait until at most the n newest groups are in flight (n >= NG - 1 is the start of the ring)
       constexpr int NG = NS / G;
@@ -641,8 +642,8 @@ __device__ __forceinline__ void igemm_tile(const ConvProblem p, int local) {
       for (int kt = 0; kt + G < KT; kt += G) {
         landed((requested - kt - 2 * G) / G);
         scale_group(kt + G);
-        __builtin_amdgcn_s_barrier();            // the group after step kt's is in LDS, the one before it is free (LARGE: step kt's too)
-        if ((LARGE || kt != 0) && requested < KT) {
+        __builtin_amdgcn_s_barrier();            // the group after step kt's is in LDS, the one before it is free (LARGE and HALF: step kt's too)
+        if ((LARGE || HALF || kt != 0) && requested < KT) {
           request_steps(requested, std::integral_constant<int, G>{});
           requested += G;
         }
@@ -717,6 +718,92 @@ __device__ __forceinline__ void igemm_tile(const ConvProblem p, int local) {
       read_half(stage, h1_t{});
       mfma_half(h0_t{});
       mfma_half(h1_t{});
+    } else if constexpr (HALF) {
+      // A 32x32 tile by two waves on v_mfma_f32_16x16x32_bf16, whose sum over 32 elements has the bits of two 32x32x16 in a
+      // row (fp32 sums in steps of 8 elements, in order).  A step's LDS reads (8 KB) and MFMAs (131 clocks) were one wave's;
+      // now each of two has 6 KB and 68 clocks, and requests a whole group ahead of the MFMAs of the group before.  What is
+      // left to bound a step is its fetch (8 KB at 57 B/ns of a CU where rows are not line-aligned, 0.14 us; 97 where they
+      // are).  One image: 196 x 360 outputs of a 3x3 over 360 channels, 51 steps 11.35 -> 10.41 us, in two parts 9.53 -> 8.54;
+      // 49 x 720 of a linear layer over 2048, 32 steps 7.55 -> 6.73, 196 x 360 over 1024, 16 steps 4.87 -> 4.47.  A request
+      // of the largest ResNet-shaped subnet 452 -> 412 us, of the smallest 235 -> 220; MBV3-shaped 258 -> 254, 3 sequences
+      // 477 -> 472.
+      typedef __attribute__((address_space(3))) const u32x4 lds_frag;
+      typedef __attribute__((address_space(3))) float lds_total;
+      typedef __attribute__((ext_vector_type(4))) float f32x4;
+      const int fr = lane & 15, fh = lane >> 4;
+      unsigned at[2];                            // by half of a step: this lane's unit of its row
+#pragma unroll
+      for (int h = 0; h < 2; ++h) at[h] = lds0 + tab_b + fr * ROW_B + (unsigned)(((h * 4 + fh) ^ ((fr >> 1) & 7)) * 16);
+      const unsigned a_rows = wm * 16 * ROW_B, b_rows = (BM + wn * WTN) * ROW_B;
+      lds_total* const tot_l = (lds_total*)(lds0 + tab_b + NS * Cfg::STAGE_B + wave * 2048 + lane * 4);
+      bool first_fold = true;
+      f32x4 sum[2];                              // channels 0 .. 15 and 16 .. 31 of the wave's tile
+#pragma unroll
+      for (int v = 0; v < 8; ++v) sum[v >> 2][v & 3] = 0.f;
+      u32x4 fa[2][G][2], fb[2][G][2][2];
+      auto read_group = [&](auto b_c) {
+        constexpr int b = decltype(b_c)::value;
+#pragma unroll
+        for (int i = 0; i < G; ++i)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const unsigned u = at[h] + (stage + i) * Cfg::STAGE_B;
+            fa[b][i][h] = *(lds_frag*)(u + a_rows);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) fb[b][i][h][j] = *(lds_frag*)(u + b_rows + j * 16 * ROW_B);
+          }
+        stage = stage + G == NS ? 0 : stage + G;
+      };
+      auto step = [&](auto b_c, auto i_c, bool more) {      // channels as rows, pixels as columns: see the epilogue
+        constexpr int b = decltype(b_c)::value, i = decltype(i_c)::value;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            sum[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fb[b][i][h][j]),
+                                                             __builtin_bit_cast(bf16x8, fa[b][i][h]), sum[j], 0, 0, 0);
+        if (CHUNKED && more && --to_fold == 0) {            // chunk boundary: bank the chunk's sum
+          to_fold = p.kt_chunk;
+#pragma unroll
+          for (int v = 0; v < 8; ++v) {
+            tot_l[v * 64] = first_fold ? sum[v >> 2][v & 3] : tot_l[v * 64] + sum[v >> 2][v & 3];
+            sum[v >> 2][v & 3] = 0.f;
+          }
+          first_fold = false;
+        }
+      };
+      auto meet = [&] {                          // barrier; no LDS read moves across it
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      };
+      typedef std::integral_constant<int, 0> i0_t;
+      typedef std::integral_constant<int, 1> i1_t;
+      // the group from step kt on, in buffer b: the next one is requested ahead of its MFMAs
+      auto group = [&](auto b_c, int kt) {
+        __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0): the group is in registers, its stages are free
+        if (kt + G < KT) {
+          meet();
+          read_group(std::integral_constant<int, decltype(b_c)::value ^ 1>{});
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        step(b_c, i0_t{}, kt + 1 < KT);
+        if (kt + 1 < KT) step(b_c, i1_t{}, kt + 2 < KT);
+      };
+      static_assert(G == 2, "unrolled above");
+      meet();
+      read_group(i0_t{});
+#pragma unroll 1
+      for (int kt = 0; kt < KT; kt += 2 * G) {
+        group(i0_t{}, kt);
+        if (kt + G < KT) group(i1_t{}, kt + G);
+      }
+#pragma unroll
+      for (int v = 0; v < 8; ++v) acc[0][0][v] = sum[v >> 2][v & 3];
+      if (CHUNKED && !first_fold) {
+#pragma unroll
+        for (int v = 0; v < 8; ++v) tot[0][0][v] = tot_l[v * 64];
+      }
     } else {
       u32x4 fa[2][BK / 16], fb[2][BK / 16];
 #pragma unroll
@@ -840,7 +927,7 @@ __device__ __forceinline__ void igemm_tile(const ConvProblem p, int local) {
   // ACT, RES (0 none, 1 added before the activation, 2 after) and F32 are uniform over the launch's
   // problem: one dispatch below instead of per-element tests.
   // Small deep rings: the product was taken transposed, so that accumulator elements 4 q .. 4 q + 3 of a lane are channels
-  // 8 q + 4 (l / 32) .. + 3 of pixel l % 32, and go out as four 8-byte pieces with no turn through LDS, which is on the
+  // 8 q + 4 (l / 32) .. + 3 of pixel l % 32 (HALF: 16 q + 4 (l / 16) .. + 3 of pixel l % 16), and go out as 8-byte pieces with no turn through LDS, which is on the
   // critical path of a launch of few tiles (0.48 us of a lone request's 3.5 us a launch).  Only SubnetNorm's vectors do.
   auto epilogue_direct = [&](auto act_c, auto res_c, auto f32_c) __attribute__((always_inline)) {
     constexpr int ACT = decltype(act_c)::value, RES = decltype(res_c)::value;
@@ -848,16 +935,16 @@ __device__ __forceinline__ void igemm_tile(const ConvProblem p, int local) {
     float* const norm = (float*)smem + wave * 64;               // this wave's 32 scales, then 32 shifts
     norm[lane] = lane < 32 ? sc[0] : sh[0];
     __builtin_amdgcn_wave_barrier();
-    float4 sc4[4], sh4[4];
+    float4 sc4[PIECES], sh4[PIECES];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      sc4[q] = *(const float4*)(norm + 8 * q + (lane >> 5) * 4);
-      sh4[q] = *(const float4*)(norm + 32 + 8 * q + (lane >> 5) * 4);
+    for (int q = 0; q < PIECES; ++q) {
+      sc4[q] = *(const float4*)(norm + PIECE * q + lane_k);
+      sh4[q] = *(const float4*)(norm + 32 + PIECE * q + lane_k);
     }
     if (px_m >= p.M) return;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int k = px_k + 8 * q;
+    for (int q = 0; q < PIECES; ++q) {
+      const int k = px_k + PIECE * q;
       const float scq[4] = {sc4[q].x, sc4[q].y, sc4[q].z, sc4[q].w}, shq[4] = {sh4[q].x, sh4[q].y, sh4[q].z, sh4[q].w};
       const float rv[4] = {__uint_as_float(res_early[DIRECT ? q : 0].x << 16), __uint_as_float(res_early[DIRECT ? q : 0].x & 0xffff0000u),
                            __uint_as_float(res_early[DIRECT ? q : 0].y << 16), __uint_as_float(res_early[DIRECT ? q : 0].y & 0xffff0000u)};
@@ -1073,6 +1160,7 @@ struct Variant {
   bool totals_lds;       // its chunk-folding kernel keeps the running totals in LDS
   bool fetchers = false; // waves of its own fetch
   PwKernel pw = nullptr, pw_chunked = nullptr, pw_gated = nullptr;      // for a lone pointwise problem
+  int group = 1;         // stages its computing waves read at a time
 };
 constexpr int kDeepMaxSteps = 128;
 constexpr int kDeepVariantCount = 3;

@@ -436,6 +436,12 @@ static int steps_of(const ConvProblem& p) {
   return kt < p.kt_part ? kt : p.kt_part;
 }
 
+// Ring stages that a launch of at most kt steps per block touches: a launch whose problems all have fewer steps than the ring
+// has stages asks for less LDS, and more blocks share a CU
+static int ring_stages(const Variant& v, int kt) {
+  return kt >= v.ns ? v.ns : (kt + v.group - 1) / v.group * v.group;
+}
+
 // Bytes of the gates of the requests that one tile of the problem can touch
 static int gate_bytes(const Variant& v, const ConvProblem& p) {
   const int hw = p.Ho * p.Wo, most = (v.bm - 1 + hw - 1) / hw + 1;
@@ -452,7 +458,7 @@ bool igemm_variant_ok(int variant, const ConvProblem& p) {
   if (variant < 0 || variant >= kNumVariants) return false;
   const Variant& v = variant_of(variant);
   if (p.gate) {
-    const int kt = (p.K8 + 7) >> 3, stages = kt < v.ns ? kt : v.ns, gates = gate_bytes(v, p);
+    const int kt = (p.K8 + 7) >> 3, stages = ring_stages(v, kt), gates = gate_bytes(v, p);
     if (!v.fn_gated || p.R * p.S != 1 || p.stride != 1 || p.pad != 0 || p.parts != 1 || kt > chunk_steps(kt) ||
         (!v.fetchers && gates > kGateLoads * 16 * v.threads) ||
         stages * v.stage_bytes + gates > kLdsMax) return false;
@@ -480,22 +486,19 @@ hipError_t launch_igemm(const ConvGroupArgs& a, int variant, bool chunked, hipSt
     if (e != hipSuccess) return e;
     attr_done[variant][flavour].store(true, std::memory_order_release);
   }
-  // a launch whose problems all have fewer K steps than the ring has stages only touches the
-  // leading stages: asking for less LDS lets more blocks share a CU
   int kt_max = 1, kt_taps = 0;         // of all problems; of those that look their taps up
   for (int i = 0; i < a.n; ++i) {
     const int kt = steps_of(a.p[i]);
     if (kt > kt_max) kt_max = kt;
     if (a.p[i].R * a.p[i].S > 1 && kt > kt_taps) kt_taps = kt;
   }
-  const int stages = kt_max < v.ns ? kt_max : v.ns;
-  int smem = stages * v.stage_bytes;
+  int smem = ring_stages(v, kt_max) * v.stage_bytes;
   if (v.deep) smem += (kt_taps + 1) / 2 * 2 * ROW_B + (chunked && v.totals_lds ? v.bm * v.bn * 4 : 0);      // tap table, running totals
   if (gated) {
     smem = 0;
     for (int i = 0; i < a.n; ++i) {
       if (!a.p[i].gate || !igemm_variant_ok(variant, a.p[i])) return hipErrorInvalidValue;
-      const int kt = steps_of(a.p[i]), need = (kt < v.ns ? kt : v.ns) * v.stage_bytes + gate_bytes(v, a.p[i]);
+      const int need = ring_stages(v, steps_of(a.p[i])) * v.stage_bytes + gate_bytes(v, a.p[i]);
       if (need > smem) smem = need;
     }
   }
