@@ -43,6 +43,10 @@ struct FastDiv {
 #endif
 };
 
+// Arguments of a launch of one problem: one descriptor instead of room for SNA_MAX_GROUPS
+template <class Problem>
+struct Lone { static constexpr int n = 1; Problem p[1]; };
+
 // ---- one problem of a grouped launch -------------------------------------------------------
 // A grouped launch carries up to SNA_MAX_GROUPS problems by value in the kernel
 // arguments; block b belongs to the problem whose [tile_start, tile_start + tiles)
@@ -330,6 +334,32 @@ __device__ __forceinline__ int find_problem(const Args& a, int b) {
   for (int i = 1; i < a.n; ++i)
     if (b >= a.p[i].tile_start) g = i;
   return g;
+}
+// A descriptor in scalar registers, all of it requested here and awaited once.  Read field by field it is awaited wherever a
+// field of another cache line is first needed, 0.25 us each time, in launches of 3 to 8 us.
+template <class Problem>
+__device__ __forceinline__ Problem pinned(const Problem& src) {
+  constexpr int N = sizeof(Problem) / 4;
+  static_assert(sizeof(Problem) % 4 == 0 && N <= 64, "fits the scalar registers");
+  unsigned w[N];
+  __builtin_memcpy(w, &src, sizeof(Problem));
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+s"(w[i]));
+#endif
+  Problem p;
+  __builtin_memcpy(&p, w, sizeof(Problem));
+  return p;
+}
+// A pinned pointer has lost that it points to global memory; without that its accesses are flat ones, which count as LDS
+// accesses too and take their whole address from vector registers.
+template <typename T>
+__device__ __forceinline__ T* in_global(T* p) {
+  __attribute__((address_space(1))) T* q = (__attribute__((address_space(1))) T*)p;
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("" : "+s"(q));                                       // two casts in a row would be folded
+#endif
+  return (T*)q;
 }
 template <class Problem>
 __device__ __forceinline__ int tile_of_block(const Problem& p) {

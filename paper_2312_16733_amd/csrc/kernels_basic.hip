@@ -167,13 +167,10 @@ hipError_t launch_maxpool(const PoolGroupArgs& a, int dtype, hipStream_t s) {
 // fixed order.
 // ---------------------------------------------------------------------------------------------
 template <typename T, int VEC>
-__global__ __launch_bounds__(256) void gap_kernel(const PoolGroupArgs args) {
+__device__ __forceinline__ void gap_block(const PoolProblem p, int local) {
   __shared__ float red[8][32][VEC];
-  const int g = find_problem(args, blockIdx.x);
-  const PoolProblem& p = args.p[g];
   const int cvn = p.C / VEC;
   const int cblocks = (cvn + 31) / 32;
-  const int local = blockIdx.x - p.tile_start;
   const int n = local / cblocks;
   const int cv = (local % cblocks) * 32 + (threadIdx.x & 31);
   const int hl = threadIdx.x >> 5;
@@ -206,8 +203,25 @@ __global__ __launch_bounds__(256) void gap_kernel(const PoolGroupArgs args) {
   }
 }
 
+template <typename T, int VEC>
+__global__ __launch_bounds__(256) void gap_kernel(const PoolGroupArgs args) {
+  const int g = find_problem(args, blockIdx.x);
+  gap_block<T, VEC>(args.p[g], blockIdx.x - args.p[g].tile_start);
+}
+// One problem: its descriptor comes in scalar arguments, which the dispatch puts into registers
+template <typename T, int VEC>
+__global__ __launch_bounds__(256) void gap_lone_kernel(const void* x, void* y, int H, int W, int C, int out_fp32) {
+  gap_block<T, VEC>(PoolProblem{x, y, 0, H, W, C, 0, 0, out_fp32, 0, 0}, blockIdx.x);
+}
+
 hipError_t launch_gap(const PoolGroupArgs& a, int dtype, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
+  const PoolProblem& p = a.p[0];
+  if (a.n == 1 && p.tile_start == 0) {
+    if (dtype == SNA_DTYPE_FP32) hipLaunchKernelGGL((gap_lone_kernel<float, 8>), dim3(p.tiles), dim3(256), 0, s, p.x, p.y, p.H, p.W, p.C, p.out_fp32);
+    else hipLaunchKernelGGL((gap_lone_kernel<bf16_t, 8>), dim3(p.tiles), dim3(256), 0, s, p.x, p.y, p.H, p.W, p.C, p.out_fp32);
+    return hipGetLastError();
+  }
   const int blocks = a.p[a.n - 1].tile_start + a.p[a.n - 1].tiles;
   if (dtype == SNA_DTYPE_FP32) hipLaunchKernelGGL((gap_kernel<float, 8>), dim3(blocks), dim3(256), 0, s, a);
   else hipLaunchKernelGGL((gap_kernel<bf16_t, 8>), dim3(blocks), dim3(256), 0, s, a);

@@ -233,14 +233,21 @@ int depthwise_pool_blocks(int Ho, int Wo, int C) {
 //   h = relu(W1[:Q,:C] z + b1[:Q]);  gate = hardsigmoid(W2[:C,:Q] h + b2[:C]);  y = x * gate
 // Two launches: h per request, then gate and scaling together.
 // ---------------------------------------------------------------------------------------------
+__device__ __forceinline__ SeProblem se_problem(const SeProblem& src) {
+  SeProblem p = pinned(src);
+  p.x = in_global(p.x); p.y = in_global(p.y); p.w1 = in_global(p.w1); p.b1 = in_global(p.b1); p.w2 = in_global(p.w2);
+  p.b2 = in_global(p.b2); p.pooled = in_global(p.pooled); p.gate = in_global(p.gate); p.hidden = in_global(p.hidden);
+  return p;
+}
 // h[n][o] = relu(W1[o, :C] . z[n] + b1[o]).  A block owns one request and 32 outputs.  It first
 // builds z in LDS (partial sums added in block order, then scaled by 1 / HW); each of its 4 waves
 // then computes 8 outputs together: lanes read 8 consecutive bf16 weights (16 bytes) of each row and
 // the matching z, and the wave reduces each output in a fixed order.
-__global__ __launch_bounds__(256) void se_hidden_kernel(const SeGroupArgs args) {
+template <class Args>
+__global__ __launch_bounds__(256) void se_hidden_kernel(const Args args) {
   extern __shared__ __attribute__((aligned(16))) float z[];
   const int g = find_problem(args, blockIdx.x);
-  const SeProblem& p = args.p[g];
+  const SeProblem p = se_problem(args.p[g]);
   const int oblocks = (p.Q + 31) / 32;
   const int local = blockIdx.x - p.tile_start;
   const int n = local / oblocks, ob = local % oblocks;
@@ -303,12 +310,12 @@ __global__ __launch_bounds__(256) void se_hidden_kernel(const SeGroupArgs args) 
 // segment of a request: 64 x Q multiply-adds against one more launch and a round trip through memory.
 constexpr int SE_PIX = 256;
 constexpr int SE_MAX_Q = 512;       // squeeze channels per gate (host-checked)
-template <bool SCALE>       // false: the gate goes to p.gate and the layer that follows applies it
-__global__ __launch_bounds__(256) void se_gate_kernel(const SeGroupArgs args) {
+template <bool SCALE, class Args>       // SCALE false: the gate goes to p.gate and the layer that follows applies it
+__global__ __launch_bounds__(256) void se_gate_kernel(const Args args) {
   __shared__ float gate_s[64];
   __shared__ __attribute__((aligned(16))) float h_s[SE_MAX_Q];
   const int g = find_problem(args, blockIdx.x);
-  const SeProblem& p = args.p[g];
+  const SeProblem p = se_problem(args.p[g]);
   const int cgroups = (p.C + 63) / 64, psegs = SCALE ? (p.HW + SE_PIX - 1) / SE_PIX : 1;
   int local = blockIdx.x - p.tile_start;
   const int pseg = local % psegs; local /= psegs;
@@ -388,37 +395,37 @@ __global__ __launch_bounds__(256) void se_gate_kernel(const SeGroupArgs args) {
 // request, with the arithmetic of the two kernels above (same bits).  Taken for layers of up to SE_ONE_MACS weights, which
 // one CU reads in about the time that the second launch costs.
 constexpr int SE_ONE_NT = 1024, SE_ONE_MACS = 32 * 1024, SE_ONE_Q = 256;
-__global__ __launch_bounds__(SE_ONE_NT) void se_one_kernel(const SeGroupArgs args) {
+template <class Args>
+__global__ __launch_bounds__(SE_ONE_NT) void se_one_kernel(const Args args) {
   extern __shared__ __attribute__((aligned(16))) float z[];
   __shared__ __attribute__((aligned(16))) float h_s[SE_ONE_Q];
   const int g = find_problem(args, blockIdx.x);
-  const SeProblem& p = args.p[g];
+  const SeProblem p = se_problem(args.p[g]);
   const int n = blockIdx.x - p.tile_start;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const bf16_t* w1 = (const bf16_t*)p.w1;
   auto rows = [&](int o0, int i8, uint4 (&wq)[8]) {
 #pragma unroll
     for (int t = 0; t < 8; ++t)
-      wq[t] = i8 < (p.C >> 3) && o0 + t < p.Q ? *(const uint4*)(w1 + (long)(o0 + t) * p.w1_stride + i8 * 8) : make_uint4(0, 0, 0, 0);
+      wq[t] = i8 < (p.C >> 3) && o0 + t < p.Q ? *(const uint4*)(w1 + (unsigned)((o0 + t) * p.w1_stride + i8 * 8)) : make_uint4(0, 0, 0, 0);
   };
-  uint4 cur[8], nxt[8];
+  uint4 cur[8];
   rows(wave * 8, lane, cur);
   // weights of the first 256 gates, four threads a channel
   const int quarter = tid & 3, q8n = p.Q >> 3;
   uint4 wq[SE_ONE_Q / 32];
   float b2 = 0.f;
   auto gate_weights = [&](int c) {
-    const bf16_t* w = (const bf16_t*)p.w2 + (long)c * p.w2_stride;
 #pragma unroll
     for (int j = 0; j < SE_ONE_Q / 32; ++j) {
       const int i8 = j * 4 + quarter;
-      wq[j] = (c < p.C && i8 < q8n) ? *(const uint4*)(w + i8 * 8) : make_uint4(0, 0, 0, 0);
+      wq[j] = (c < p.C && i8 < q8n) ? *(const uint4*)((const bf16_t*)p.w2 + (unsigned)(c * p.w2_stride + i8 * 8)) : make_uint4(0, 0, 0, 0);
     }
     b2 = c < p.C ? p.b2[c] : 0.f;
   };
   gate_weights(tid >> 2);
   const float* part = p.pooled + (long)n * p.pool_segs * p.C;
-  for (int c4 = tid; c4 < (p.C >> 2); c4 += SE_ONE_NT) {
+  for (unsigned c4 = tid; c4 < (unsigned)(p.C >> 2); c4 += SE_ONE_NT) {
     float4 a = *(const float4*)(part + c4 * 4);
 #pragma unroll 8
     for (int sgm = 1; sgm < p.pool_segs; ++sgm) {
@@ -437,7 +444,6 @@ __global__ __launch_bounds__(SE_ONE_NT) void se_one_kernel(const SeGroupArgs arg
     for (int t = 0; t < 8; ++t) a[t] = 0.f;
     for (int i8 = lane; i8 < (p.C >> 3); i8 += 64) {
       const float4 x0 = *(const float4*)(z + i8 * 8), x1 = *(const float4*)(z + i8 * 8 + 4);
-      rows(o0, i8 + 64, nxt);
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
         float wv[8];
@@ -445,8 +451,8 @@ __global__ __launch_bounds__(SE_ONE_NT) void se_one_kernel(const SeGroupArgs arg
         a[t] = fmaf(wv[0], x0.x, a[t]); a[t] = fmaf(wv[1], x0.y, a[t]); a[t] = fmaf(wv[2], x0.z, a[t]); a[t] = fmaf(wv[3], x0.w, a[t]);
         a[t] = fmaf(wv[4], x1.x, a[t]); a[t] = fmaf(wv[5], x1.y, a[t]); a[t] = fmaf(wv[6], x1.z, a[t]); a[t] = fmaf(wv[7], x1.w, a[t]);
       }
-#pragma unroll
-      for (int t = 0; t < 8; ++t) cur[t] = nxt[t];
+      // not ahead of the products as in se_hidden_kernel: no register is left for it, and hardly a gate this small has 512 channels
+      if (i8 + 64 < (p.C >> 3)) rows(o0, i8 + 64, cur);
     }
     float mine = 0.f;
 #pragma unroll
@@ -502,22 +508,25 @@ hipError_t launch_se(const SeGroupArgs& a, hipStream_t s) {
     return b.n > 0;
   };
   if (gather([](int w) { return w == ONE; }, [](const SeProblem& p) { return p.N; })) {
-    hipLaunchKernelGGL(se_one_kernel, dim3(blocks), dim3(SE_ONE_NT), c_max * 4, s, b);
+    if (b.n == 1) hipLaunchKernelGGL(se_one_kernel<Lone<SeProblem>>, dim3(blocks), dim3(SE_ONE_NT), c_max * 4, s, Lone<SeProblem>{{b.p[0]}});
+    else hipLaunchKernelGGL(se_one_kernel<SeGroupArgs>, dim3(blocks), dim3(SE_ONE_NT), c_max * 4, s, b);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   if (gather([](int w) { return w != ONE; }, [](const SeProblem& p) { return p.N * ((p.Q + 31) / 32); })) {
-    hipLaunchKernelGGL(se_hidden_kernel, dim3(blocks), dim3(256), c_max * 4, s, b);
+    if (b.n == 1) hipLaunchKernelGGL(se_hidden_kernel<Lone<SeProblem>>, dim3(blocks), dim3(256), c_max * 4, s, Lone<SeProblem>{{b.p[0]}});
+    else hipLaunchKernelGGL(se_hidden_kernel<SeGroupArgs>, dim3(blocks), dim3(256), c_max * 4, s, b);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   if (gather([](int w) { return w == TWO; }, [](const SeProblem& p) { return p.N * ((p.C + 63) / 64); })) {
-    hipLaunchKernelGGL(se_gate_kernel<false>, dim3(blocks), dim3(256), 0, s, b);
+    if (b.n == 1) hipLaunchKernelGGL((se_gate_kernel<false, Lone<SeProblem>>), dim3(blocks), dim3(256), 0, s, Lone<SeProblem>{{b.p[0]}});
+    else hipLaunchKernelGGL((se_gate_kernel<false, SeGroupArgs>), dim3(blocks), dim3(256), 0, s, b);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   if (gather([](int w) { return w == SCALED; }, [](const SeProblem& p) { return p.N * ((p.C + 63) / 64) * ((p.HW + SE_PIX - 1) / SE_PIX); })) {
-    hipLaunchKernelGGL(se_gate_kernel<true>, dim3(blocks), dim3(256), 0, s, b);
+    hipLaunchKernelGGL((se_gate_kernel<true, SeGroupArgs>), dim3(blocks), dim3(256), 0, s, b);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

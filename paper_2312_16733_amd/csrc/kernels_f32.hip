@@ -34,13 +34,28 @@ __host__ __device__ __forceinline__ int f32_k_waves(int steps) {
   return steps >= 32 ? 8 : (steps >= 16 ? 4 : (steps >= 8 ? 2 : 1));
 }
 
+// What the kernel takes of a descriptor
+struct F32Problem {
+  const void* x; const void* w; const float* scale; const float* shift; const void* res; void* y;
+  int H, W, C, Ho, Wo, K, R, S, stride, pad, wk, wr, ws, M;
+  unsigned magic_wo, magic_ho;
+  int inv_s, tiles_n, tile_start, act, y_stride, res_stride;
+  unsigned x_bytes, w_bytes;
+  int res_after_act, unused;
+};
+__device__ __forceinline__ F32Problem f32_problem(const ConvProblem& q) {
+  return {q.x, q.w, q.scale, q.shift, q.res, q.y, q.H, q.W, q.C, q.Ho, q.Wo, q.K, q.R, q.S, q.stride, q.pad, q.wk, q.wr, q.ws, q.M,
+          q.magic_wo, q.magic_ho, q.inv_s, q.tiles_n, q.tile_start, q.act, q.y_stride, q.res_stride, q.x_bytes, q.w_bytes, q.res_after_act, 0};
+}
+
 // VEC: the input channels come in fours, so that a lane's 4 elements lie inside one tap
-template <bool VEC>
-__global__ __launch_bounds__(64 * F32_WAVES) void conv_f32_kernel(const ConvGroupArgs args) {
+template <bool VEC, class Args>
+__global__ __launch_bounds__(64 * F32_WAVES) void conv_f32_kernel(const Args args) {
 #if defined(__HIP_DEVICE_COMPILE__)
   __shared__ float red[F32_WAVES][F32_TILE * F32_TILE];
   const int g = find_problem(args, blockIdx.x);
-  const ConvProblem& p = args.p[g];
+  F32Problem p = pinned(f32_problem(args.p[g]));
+  p.scale = in_global(p.scale); p.shift = in_global(p.shift); p.res = in_global(p.res); p.y = in_global(p.y);
   const int local = blockIdx.x - p.tile_start;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int RSC = p.R * p.S * p.C;
@@ -183,8 +198,15 @@ hipError_t launch_conv_f32(const ConvGroupArgs& a, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
   bool vec = true;
   for (int i = 0; i < a.n; ++i) vec = vec && a.p[i].C % 4 == 0;
-  if (vec) hipLaunchKernelGGL(conv_f32_kernel<true>, dim3(a.total_tiles), dim3(64 * F32_WAVES), 0, s, a);
-  else hipLaunchKernelGGL(conv_f32_kernel<false>, dim3(a.total_tiles), dim3(64 * F32_WAVES), 0, s, a);
+  const dim3 grid(a.total_tiles), block(64 * F32_WAVES);
+  typedef Lone<ConvProblem> One;
+  if (a.n == 1) {
+    if (vec) hipLaunchKernelGGL((conv_f32_kernel<true, One>), grid, block, 0, s, One{{a.p[0]}});
+    else hipLaunchKernelGGL((conv_f32_kernel<false, One>), grid, block, 0, s, One{{a.p[0]}});
+  } else {
+    if (vec) hipLaunchKernelGGL((conv_f32_kernel<true, ConvGroupArgs>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((conv_f32_kernel<false, ConvGroupArgs>), grid, block, 0, s, a);
+  }
   return hipGetLastError();
 }
 

@@ -24,11 +24,8 @@ constexpr int AT_LD = AT_S + 8;    // LDS row stride (bf16) for V^T and P
 // LDS gives each lane its two runs of 4 keys as two 8-byte reads.
 // Q and K fragments come straight from global memory (a lane's 8 consecutive head-dim values are
 // contiguous); V is transposed through LDS.
-__global__ __launch_bounds__(256) void attention_kernel(const AttnGroupArgs args) {
+__device__ __forceinline__ void attention_block(const AttnProblem p, int local) {
   __shared__ __attribute__((aligned(16))) bf16_t Vt[AT_D * AT_LD];
-  const int g = find_problem(args, blockIdx.x);
-  const AttnProblem& p = args.p[g];
-  const int local = blockIdx.x - p.tile_start;
   const int h = local % p.heads, b = local / p.heads;
   const int S = p.S, ld = p.ld;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -148,6 +145,15 @@ __global__ __launch_bounds__(256) void attention_kernel(const AttnGroupArgs args
   }
 }
 
+__global__ __launch_bounds__(256) void attention_kernel(const AttnGroupArgs args) {
+  const int g = find_problem(args, blockIdx.x);
+  attention_block(args.p[g], blockIdx.x - args.p[g].tile_start);
+}
+// One problem: its descriptor comes in scalar arguments, which the dispatch puts into registers
+__global__ __launch_bounds__(256) void attention_lone_kernel(const void* q, const void* k, const void* v, void* o, int S, int heads, int ld) {
+  attention_block(AttnProblem{q, k, v, o, 0, S, heads, ld, 0, 0}, blockIdx.x);
+}
+
 hipError_t launch_attention(const AttnGroupArgs& a, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
   AttnGroupArgs b = a;
@@ -158,7 +164,9 @@ hipError_t launch_attention(const AttnGroupArgs& a, hipStream_t s) {
     b.p[i].tiles = b.p[i].B * b.p[i].heads;
     start += b.p[i].tiles;
   }
-  hipLaunchKernelGGL(attention_kernel, dim3(start), dim3(256), 0, s, b);
+  const AttnProblem& p = b.p[0];
+  if (b.n == 1) hipLaunchKernelGGL(attention_lone_kernel, dim3(start), dim3(256), 0, s, p.q, p.k, p.v, p.o, p.S, p.heads, p.ld);
+  else hipLaunchKernelGGL(attention_kernel, dim3(start), dim3(256), 0, s, b);
   return hipGetLastError();
 }
 
@@ -168,11 +176,9 @@ hipError_t launch_attention(const AttnGroupArgs& a, hipStream_t s) {
 // ---------------------------------------------------------------------------------------------
 constexpr int LN_MAX_OCT = 4;      // octets per lane -> cols <= 2048
 
-__global__ __launch_bounds__(256) void layernorm_kernel(const LnGroupArgs args) {
-  const int g = find_problem(args, blockIdx.x);
-  const LnProblem& p = args.p[g];
+__device__ __forceinline__ void layernorm_block(const LnProblem p, int local) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const long row = (long)(blockIdx.x - p.tile_start) * 4 + wave;
+  const long row = (long)local * 4 + wave;
   if (row >= p.rows) return;
   const int octs = p.cols >> 3;
   const bf16_t* x = (const bf16_t*)p.x + row * p.cols;
@@ -239,6 +245,14 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const LnGroupArgs args) 
   }
 }
 
+__global__ __launch_bounds__(256) void layernorm_kernel(const LnGroupArgs args) {
+  const int g = find_problem(args, blockIdx.x);
+  layernorm_block(args.p[g], blockIdx.x - args.p[g].tile_start);
+}
+__global__ __launch_bounds__(256) void layernorm_lone_kernel(const void* x, const float* gamma, const float* beta, void* y, int rows, int cols) {
+  layernorm_block(LnProblem{x, gamma, beta, y, rows, cols, 0, 0}, blockIdx.x);
+}
+
 hipError_t launch_layernorm(const LnGroupArgs& a, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
   LnGroupArgs b = a;
@@ -249,7 +263,9 @@ hipError_t launch_layernorm(const LnGroupArgs& a, hipStream_t s) {
     b.p[i].tiles = (b.p[i].rows + 3) / 4;
     start += b.p[i].tiles;
   }
-  hipLaunchKernelGGL(layernorm_kernel, dim3(start), dim3(256), 0, s, b);
+  const LnProblem& p = b.p[0];
+  if (b.n == 1) hipLaunchKernelGGL(layernorm_lone_kernel, dim3(start), dim3(256), 0, s, p.x, p.gamma, p.beta, p.y, p.rows, p.cols);
+  else hipLaunchKernelGGL(layernorm_kernel, dim3(start), dim3(256), 0, s, b);
   return hipGetLastError();
 }
 
