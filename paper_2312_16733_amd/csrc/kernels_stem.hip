@@ -94,9 +94,11 @@ __global__ __launch_bounds__(256, 2) void stem_pool_kernel(const StemPoolArgs ar
 
   // The input patch of a tile goes through registers: three channel loads per pixel at the image's own
   // pixel stride (so a 3-channel request image is read in place, no padded copy), zeros outside the
-  // image; store_patch() then writes 8 bytes per pixel (3 channels and a zero) where the MFMAs expect them.
-  unsigned pk[PASSES][2];
-  auto load_patch = [&](int t) {
+  // image; store_patch() then writes 8 bytes per pixel (3 channels and a zero) where the MFMAs expect them.  join_patch() puts
+  // the channels together, which awaits them: done where they are loaded, and with branches between the loads, it cost a
+  // round trip to HBM for every tile; left to store_patch() it would await the pool's stores as well.
+  unsigned pk[PASSES][3];
+  auto load_patch = [&](int t, const bool any) {           // any: false asks for nothing
     const int gp = find_problem(args, t);
     const StemPoolProblem& q = args.p[gp];
     const int local = t - q.tile_start;
@@ -108,51 +110,63 @@ __global__ __launch_bounds__(256, 2) void stem_pool_kernel(const StemPoolArgs ar
     // bounds-checked 2-byte loads at 32-bit offsets: a pixel outside the image gets an out-of-range
     // offset, which reads as zero (the padding)
     const __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc((void*)q.x, 0, (int)q.x_bytes, 0x00020000);
-    const int row_b = q.W * q.pix_b;
-    const int base = (n * q.H + iy0) * row_b + ix0 * q.pix_b;       // may be negative; only used where ok
+    const int H = q.H, W = q.W, pix_b = q.pix_b, row_b = W * pix_b;
+    const int base = (n * q.H + iy0) * row_b + ix0 * pix_b;       // may be negative; only used where ok
 #pragma unroll
     for (int pass = 0; pass < PASSES; ++pass) {
       const int ly = lane_yx[pass] >> 16, lx = lane_yx[pass] & 0xffff;
       const int gy = iy0 + ly, gx = ix0 + lx;
-      const bool ok = lane_yx[pass] >= 0 && gy >= 0 && gy < q.H && gx >= 0 && gx < q.W;
-      const int off = ok ? base + ly * row_b + lx * q.pix_b : (int)0x80000000;
-      const unsigned c0 = __builtin_amdgcn_raw_buffer_load_b16(rsrc_x, off, 0, 0);
-      const unsigned c1 = __builtin_amdgcn_raw_buffer_load_b16(rsrc_x, off + 2, 0, 0);
-      const unsigned c2 = __builtin_amdgcn_raw_buffer_load_b16(rsrc_x, off + 4, 0, 0);
-      pk[pass][0] = c0 | (c1 << 16);
-      pk[pass][1] = c2;
+      const bool ok = any & (lane_yx[pass] >= 0) & ((unsigned)gy < (unsigned)H) & ((unsigned)gx < (unsigned)W);
+      int off = base + ly * row_b + lx * pix_b;
+      asm volatile("" : "+v"(off));                          // computed for all lanes, so that nothing branches between the loads
+      off = ok ? off : (int)0x80000000;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) pk[pass][c] = __builtin_amdgcn_raw_buffer_load_b16(rsrc_x, off + 2 * c, 0, 0);
+    }
+  };
+  auto join_patch = [&]() {
+#pragma unroll
+    for (int pass = 0; pass < PASSES; ++pass) {
+      pk[pass][0] |= pk[pass][1] << 16;
+      asm volatile("" : "+v"(pk[pass][0]), "+v"(pk[pass][2]));
     }
   };
   auto store_patch = [&]() {
 #pragma unroll
     for (int pass = 0; pass < PASSES; ++pass)
-      *(uint2*)(patch + (pass * 256 + tid) * 8) = make_uint2(pk[pass][0], pk[pass][1]);
+      *(uint2*)(patch + (pass * 256 + tid) * 8) = make_uint2(pk[pass][0], pk[pass][2]);
   };
 
   int cur_g = -1;
-  if ((int)blockIdx.x < args.total_tiles) { load_patch(blockIdx.x); store_patch(); }
+  if ((int)blockIdx.x < args.total_tiles) load_patch(blockIdx.x, true);
   for (int tile = blockIdx.x; tile < args.total_tiles; tile += gridDim.x) {
     const int g = find_problem(args, tile);
     const StemPoolProblem& p = args.p[g];
     const int K = p.K;
     if (g != cur_g) {
       // the barrier that ends every tile guarantees that no wave still reads w_lds or ss
+      // all loads first, from rows and taps clamped to those there are (a guarded load is awaited before the next guard: seven
+      // round trips, half of a lone request's launch)
       const bf16_t* w = (const bf16_t*)p.w;
-      for (int i = tid; i < KMAX * SLOTS; i += 256) {
-        const int k = i / SLOTS, slot = i - k * SLOTS;
+      constexpr int W_IT = KMAX * SLOTS / 256;
+      static_assert(W_IT * 256 == KMAX * SLOTS, "whole passes");
+      bf16_t tap[W_IT][6];
+#pragma unroll
+      for (int it = 0; it < W_IT; ++it) {
+        const int i = it * 256 + tid, k = i / SLOTS, slot = i - k * SLOTS;
         const int r = slot / PAIRS, c = 2 * (slot - r * PAIRS);          // taps (r, c) and (r, c + 1), 3 channels each
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (k < K) {
-          const bf16_t* t0 = w + (long)k * p.wk + (long)r * p.wr + (long)c * p.ws;
-          v.x = (unsigned)t0[0] | ((unsigned)t0[1] << 16);
-          v.y = (unsigned)t0[2];
-          if (c + 1 < KS) {
-            const bf16_t* t1 = t0 + p.ws;
-            v.z = (unsigned)t1[0] | ((unsigned)t1[1] << 16);
-            v.w = (unsigned)t1[2];
-          }
-        }
-        *(uint4*)(w_lds + k * W_ROW_B + slot * 16) = v;
+        const bf16_t* t0 = w + (long)(k < K ? k : 0) * p.wk + (long)r * p.wr + (long)c * p.ws;
+        const bf16_t* t1 = t0 + (c + 1 < KS ? p.ws : 0);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) { tap[it][e] = t0[e]; tap[it][3 + e] = t1[e]; }
+      }
+#pragma unroll
+      for (int it = 0; it < W_IT; ++it) {
+        const int i = it * 256 + tid, k = i / SLOTS, slot = i - k * SLOTS;
+        const unsigned m0 = k < K ? ~0u : 0u, m1 = 2 * (slot % PAIRS) + 1 < KS ? m0 : 0u;
+        *(uint4*)(w_lds + k * W_ROW_B + slot * 16) =
+            make_uint4(((unsigned)tap[it][0] | ((unsigned)tap[it][1] << 16)) & m0, (unsigned)tap[it][2] & m0,
+                       ((unsigned)tap[it][3] | ((unsigned)tap[it][4] << 16)) & m1, (unsigned)tap[it][5] & m1);
       }
       if (tid < KMAX) {
         ss[tid] = tid < K ? p.scale[tid] : 0.f;
@@ -160,15 +174,22 @@ __global__ __launch_bounds__(256, 2) void stem_pool_kernel(const StemPoolArgs ar
       }
       cur_g = g;
     }
+    if (tile == (int)blockIdx.x) join_patch();
+    store_patch();                                           // the barrier that ends every tile has freed the patch
     const int local = tile - p.tile_start;
     const int per_img = p.tiles_x * p.tiles_y;
     const int n = local / per_img;
     const int rem = local - n * per_img;
     const int ty = rem / p.tiles_x, tx = rem - ty * p.tiles_x;
+    const int Ho = p.Ho, Wo = p.Wo;
     const int py0 = ty * PH, px0 = tx * PW;
     const int sy0 = 2 * py0 - 1, sx0 = 2 * px0 - 1;          // first conv pixel of the tile (may be -1)
 
     __syncthreads();                                         // patch, weights, scale / shift visible to all
+    // The next tile's patch, which arrives under all that follows.  Asked for without a branch even where there is none: joined
+    // with the values before it, it would be copied, and awaited, here.
+    const bool more = tile + (int)gridDim.x < args.total_tiles;
+    load_patch(more ? tile + (int)gridDim.x : tile, more);
 
     // ---- MFMAs out of LDS ---------------------------------------------------------------------
     // No branches in this loop (a wave without a third row tile recomputes pixel 0 and drops it), so
@@ -206,8 +227,6 @@ __global__ __launch_bounds__(256, 2) void stem_pool_kernel(const StemPoolArgs ar
     }
 
     __syncthreads();                                         // every wave is done with the patch
-    const bool more = tile + (int)gridDim.x < args.total_tiles;
-    if (more) load_patch(tile + gridDim.x);                  // arrives under the epilogue and the pool
 
     // ---- SubnetNorm + ReLU, conv tile -> LDS as bf16 ------------------------------------------
     float4 sc[TNJ][4], sh[TNJ][4];
@@ -224,7 +243,7 @@ __global__ __launch_bounds__(256, 2) void stem_pool_kernel(const StemPoolArgs ar
       const int sp = 32 * (wave + 4 * i) + l32;
       const int sy = sp / SW, sx = sp - sy * SW;
       const int ay = sy0 + sy, ax = sx0 + sx;
-      const bool valid = sp < NSP && ay >= 0 && ay < p.Ho && ax >= 0 && ax < p.Wo;
+      const bool valid = (sp < NSP) & ((unsigned)ay < (unsigned)Ho) & ((unsigned)ax < (unsigned)Wo);
       if (sp >= ROW_TILES * 32) continue;                    // the third row tile of waves 2 and 3 does not exist
 #pragma unroll
       for (int j = 0; j < TNJ; ++j) {
@@ -244,6 +263,7 @@ __global__ __launch_bounds__(256, 2) void stem_pool_kernel(const StemPoolArgs ar
         }
       }
     }
+    join_patch();                                            // the next tile's
     __syncthreads();                                         // conv tile complete
 
     // ---- 3x3 stride-2 max pool out of LDS, 16-byte stores -------------------------------------
@@ -272,8 +292,6 @@ __global__ __launch_bounds__(256, 2) void stem_pool_kernel(const StemPoolArgs ar
       *(uint4*)((bf16_t*)p.y + (((long)n * p.Po + py) * p.Qo + px) * K + oct * 8) = o;
     }
     __syncthreads();                                         // every thread is done reading the conv tile, which lies over the patch
-    if (more) store_patch();
-    __syncthreads();                                         // the next tile's patch in place
   }
 #endif
 }
