@@ -13,7 +13,8 @@
 //
 // Measured on the largest tiny subnet (thread per pixel -> here, event-bracketed): 4 images, 64 x 128 x 1152 (pixels x
 // channels x reduction) 153 -> 10.1 us, 256 x 64 x 576 96 -> 8.2, 1024 x 32 x 288 63 -> 8.1, the whole forward
-// 514 -> 51 us, where an empty launch takes 6; 64 images, 1024 x 128 x 1152 166 -> 14.5, 16384 x 32 x 288 62 -> 17.5.
+// 514 -> 51 us, where an empty launch takes 6; 64 images, 1024 x 128 x 1152 166 -> 12.6, 16384 x 32 x 288 62 -> 14.3
+// (with one block a CU instead of two, 13.8 and 17.0).
 //
 // The reduction order depends on the layer's reduction length alone (wave w sums its run of steps in order, the waves'
 // sums are added in wave order), so a request's result does not depend on what it is batched with.
@@ -27,7 +28,9 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
 constexpr int F32_WAVES = 8;          // waves per block
 constexpr int F32_TILE = 16;
 constexpr int F32_STEP = 16;          // reduction elements per step: 4 lanes groups x 4 elements
-constexpr int F32_AHEAD = 5;          // steps whose loads are requested together, twice that many in flight (a wave's share of 18, 36 and 72 steps is 5, 5 and 9)
+// Steps whose loads are requested together, twice that many in flight: a wave's share of 18, 36 and 72 steps is 5, 5 and 9.
+// Without fours of channels a step is eight loads with an address each, and the layers are images' first ones, of two steps.
+constexpr int f32_ahead(bool vec) { return vec ? 5 : 2; }
 
 // Waves that share one output tile: with fewer than 4 steps each, adding up through LDS costs more than it saves.
 __host__ __device__ __forceinline__ int f32_k_waves(int steps) {
@@ -49,9 +52,11 @@ __device__ __forceinline__ F32Problem f32_problem(const ConvProblem& q) {
 }
 
 // VEC: the input channels come in fours, so that a lane's 4 elements lie inside one tap
+// Four waves a SIMD, which is two blocks a CU; at 130 registers it was one.
 template <bool VEC, class Args>
-__global__ __launch_bounds__(64 * F32_WAVES) void conv_f32_kernel(const Args args) {
+__global__ __launch_bounds__(64 * F32_WAVES, 4) void conv_f32_kernel(const Args args) {
 #if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int F32_AHEAD = f32_ahead(VEC);
   __shared__ float red[F32_WAVES][F32_TILE * F32_TILE];
   const int g = find_problem(args, blockIdx.x);
   F32Problem p = pinned(f32_problem(args.p[g]));
