@@ -5,27 +5,32 @@
 namespace sna {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 constexpr int AT_S = 128;          // max tokens per request
 constexpr int AT_D = 64;           // head dim
-constexpr int AT_LD = AT_S + 8;    // LDS row stride (bf16) for V^T and P
+constexpr int AT_LD = AT_S + 8;    // LDS row stride (bf16) of V^T
+constexpr int AT_KD = AT_D + 8;    // and of K
 
-// One block = one (request, head); wave w owns queries [32w, 32w + 32).
+constexpr int AT_NT = 64 * (AT_S / 16);      // threads: a wave per 16 queries
+
+// One block = one (request, head); wave w owns queries [16w, 16w + 16).
 //   scores = Q K^T / 8 (fp32) -> softmax over keys (fp32) -> P rounded to bf16 -> ctx = P V -> bf16.
 // The scores are computed transposed (K as the row operand, Q as the column operand), so that a lane
-// of the accumulator holds one query (column lane % 32) and 16 of the 32 keys of each key block:
-// the softmax reduction over keys runs inside a lane plus one exchange with lane ^ 32, and the
+// of the accumulator holds one query (column lane % 16) and 4 of the 16 keys of each key block:
+// the softmax reduction over keys runs inside a lane plus exchanges with lanes ^ 16 and ^ 32, and the
 // probabilities are already laid out as the column operand of the second product (column = query, 8
-// values per K slice) without a trip through LDS.  The slice's 8 values are keys
-// {base + 4 hi + 0..3, base + 8 + 4 hi + 0..3} (hi = lane / 32) instead of 8 consecutive keys; a
+// values per slice of 32 keys) without a trip through LDS.  The slice's 8 values are keys
+// {base + 4 hi + 0..3, base + 16 + 4 hi + 0..3} (hi = lane / 16) instead of 8 consecutive keys; a
 // sum over keys may take them in any order as long as the V operand uses the same one, and V^T in
 // LDS gives each lane its two runs of 4 keys as two 8-byte reads.
-// Q and K fragments come straight from global memory (a lane's 8 consecutive head-dim values are
-// contiguous); V is transposed through LDS.
+// K and V^T lie in LDS: read by each wave from global memory, K came in as many times over as there are waves, and the CU's
+// fetch of it was half of the launch (3 requests of 128 tokens x 12 heads 7.1 -> 5.8 us, 32 requests 12.0 -> 9.9, with 16
+// queries a wave instead of 32).
 __device__ __forceinline__ void attention_block(const AttnProblem p, int local) {
   __shared__ __attribute__((aligned(16))) bf16_t Vt[AT_D * AT_LD];
+  __shared__ __attribute__((aligned(16))) bf16_t Ks[AT_S * AT_KD];
   const int h = local % p.heads, b = local / p.heads;
   const int S = p.S, ld = p.ld;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -33,124 +38,114 @@ __device__ __forceinline__ void attention_block(const AttnProblem p, int local) 
   const bf16_t* Kp = (const bf16_t*)p.k + (long)b * S * ld + h * AT_D;
   const bf16_t* V = (const bf16_t*)p.v + (long)b * S * ld + h * AT_D;
 
-  // Bound by latency: a load round trip, two short chains of MFMAs and the softmax between them (36 to 384 blocks), so
-  // all of a thread's loads go out together, from rows clamped to the last one: a guarded load would be waited for
-  // before the next guard.  128 tokens x 3 requests x 12 heads: 9.6 -> 7.1 us a launch, 32 requests 13.4 -> 11.9, with
-  // the dword V^T writes and 8-byte output stores below.  Scores of keys >= S are masked below and query rows >= S are not stored, so only V needs zeros.
-  const int r32 = lane & 31, hi = lane >> 5;
-  const int qrow = wave * 32 + r32;
+  // All of a thread's loads go out together, from rows clamped to the last one: a guarded load would be waited for
+  // before the next guard.  Scores of keys >= S are masked below and query rows >= S are not stored, so only V needs zeros.
+  const int l16 = lane & 15, hi = lane >> 4;
+  const int qrow = wave * 16 + l16;
   const int qld = qrow < S ? qrow : S - 1;
-  uint4 qv[4], kv[4][4], vv[2][2];
+  u32x4 qv[2], kv[AT_S * AT_D / 8 / AT_NT], vv[2];
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) qv[ks] = *(const uint4*)(Q + (long)qld * ld + ks * 16 + hi * 8);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int key = j * 32 + r32 < S ? j * 32 + r32 : S - 1;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) kv[j][ks] = *(const uint4*)(Kp + (long)key * ld + ks * 16 + hi * 8);
+  for (int i = 0; i < AT_S * AT_D / 8 / AT_NT; ++i) {
+    const int key = i * (AT_NT / 8) + (tid >> 3);
+    kv[i] = *(const u32x4*)(Kp + (long)(key < S ? key : S - 1) * ld + (tid & 7) * 8);
   }
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) qv[ks] = *(const u32x4*)(Q + (long)qld * ld + ks * 32 + hi * 8);
   // V: a lane takes two neighbouring keys of a head-dim octet, so that it writes V^T as whole dwords and a wave's 64
   // lanes write 64 consecutive ones
+  static_assert(AT_NT == 64 * (AT_D / 8) && AT_S == 128, "a wave per octet, two keys a lane");
 #pragma unroll
-  for (int it = 0; it < 2; ++it)
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int key = 2 * lane + e < S ? 2 * lane + e : S - 1;
-      vv[it][e] = *(const uint4*)(V + (long)key * ld + (wave + 4 * it) * 8);
-    }
+  for (int e = 0; e < 2; ++e) {
+    const int key = 2 * lane + e < S ? 2 * lane + e : S - 1;
+    vv[e] = *(const u32x4*)(V + (long)key * ld + wave * 8);
+  }
   __builtin_amdgcn_sched_barrier(0);     // keep the loads ahead of everything that waits for one of them
 
-  // sc[j][v]: query qrow, key 32 j + 8 (v / 4) + 4 hi + v % 4
-  f32x16 sc[4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-#pragma unroll
-    for (int v = 0; v < 16; ++v) sc[j][v] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-      sc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kv[j][ks]),
-                                                      __builtin_bit_cast(bf16x8, qv[ks]), sc[j], 0, 0, 0);
-  }
+  for (int i = 0; i < AT_S * AT_D / 8 / AT_NT; ++i) *(u32x4*)(Ks + (i * (AT_NT / 8) + (tid >> 3)) * AT_KD + (tid & 7) * 8) = kv[i];
   // V^T into LDS: Vt[d][key], zero for keys >= S
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
+  {
     const unsigned lo_ok = 2 * lane < S ? 0xffffffffu : 0u, hi_ok = 2 * lane + 1 < S ? 0xffffffffu : 0u;
-    const unsigned a[4] = {vv[it][0].x & lo_ok, vv[it][0].y & lo_ok, vv[it][0].z & lo_ok, vv[it][0].w & lo_ok};
-    const unsigned c[4] = {vv[it][1].x & hi_ok, vv[it][1].y & hi_ok, vv[it][1].z & hi_ok, vv[it][1].w & hi_ok};
-    bf16_t* col = Vt + (wave + 4 * it) * 8 * AT_LD + 2 * lane;
+    const unsigned a[4] = {vv[0].x & lo_ok, vv[0].y & lo_ok, vv[0].z & lo_ok, vv[0].w & lo_ok};
+    const unsigned c[4] = {vv[1].x & hi_ok, vv[1].y & hi_ok, vv[1].z & hi_ok, vv[1].w & hi_ok};
+    bf16_t* col = Vt + wave * 8 * AT_LD + 2 * lane;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       *(unsigned*)(col + (2 * e) * AT_LD) = (a[e] & 0xffffu) | (c[e] << 16);
       *(unsigned*)(col + (2 * e + 1) * AT_LD) = (a[e] >> 16) | (c[e] & 0xffff0000u);
     }
   }
+  __syncthreads();
+  // sc[j][v]: query qrow, key 16 j + 4 hi + v
+  f32x4 sc[AT_S / 16];
+#pragma unroll
+  for (int j = 0; j < AT_S / 16; ++j) {
+    sc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+      sc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const bf16x8*)(Ks + (16 * j + l16) * AT_KD + ks * 32 + hi * 8),
+                                                      __builtin_bit_cast(bf16x8, qv[ks]), sc[j], 0, 0, 0);
+  }
   // softmax over the keys of this lane's query, in base 2: exp(x / 8 - max) = exp2((x - max') * log2(e) / 8)
   const float kScale = 0.125f * 1.44269504088896340736f;
   float m = -3.0e38f;
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+  for (int j = 0; j < AT_S / 16; ++j)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int key = 32 * j + 8 * (v >> 2) + 4 * hi + (v & 3);
+    for (int v = 0; v < 4; ++v) {
+      const int key = 16 * j + 4 * hi + v;
       sc[j][v] = key < S ? sc[j][v] * kScale : -3.0e38f;
       m = fmaxf(m, sc[j][v]);
     }
+  m = fmaxf(m, __shfl_xor(m, 16, 64));
   m = fmaxf(m, __shfl_xor(m, 32, 64));
   float sum = 0.f;
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+  for (int j = 0; j < AT_S / 16; ++j)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int key = 32 * j + 8 * (v >> 2) + 4 * hi + (v & 3);
+    for (int v = 0; v < 4; ++v) {
+      const int key = 16 * j + 4 * hi + v;
       sc[j][v] = key < S ? __builtin_amdgcn_exp2f(sc[j][v] - m) : 0.f;
       sum += sc[j][v];
     }
+  sum += __shfl_xor(sum, 16, 64);
   sum += __shfl_xor(sum, 32, 64);
   const float inv = 1.f / sum;
-  __syncthreads();                     // V^T complete (all waves)
-  f32x16 oc[2];
+  f32x4 oc[AT_D / 16];
 #pragma unroll
-  for (int jd = 0; jd < 2; ++jd)
+  for (int jd = 0; jd < AT_D / 16; ++jd) oc[jd] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int v = 0; v < 16; ++v) oc[jd][v] = 0.f;
+  for (int ks = 0; ks < AT_S / 32; ++ks) {
+    // probabilities rounded to bf16: key blocks 2 ks and 2 ks + 1
+    u32x4 pw;
+    pw.x = pack_bf16x2(sc[2 * ks][0] * inv, sc[2 * ks][1] * inv);
+    pw.y = pack_bf16x2(sc[2 * ks][2] * inv, sc[2 * ks][3] * inv);
+    pw.z = pack_bf16x2(sc[2 * ks + 1][0] * inv, sc[2 * ks + 1][1] * inv);
+    pw.w = pack_bf16x2(sc[2 * ks + 1][2] * inv, sc[2 * ks + 1][3] * inv);
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int ap = 0; ap < 2; ++ap) {
-      // probabilities rounded to bf16: elements 8 ap .. 8 ap + 7 of the key block
-      u32x4 pw;
-      pw.x = pack_bf16x2(sc[j][8 * ap + 0] * inv, sc[j][8 * ap + 1] * inv);
-      pw.y = pack_bf16x2(sc[j][8 * ap + 2] * inv, sc[j][8 * ap + 3] * inv);
-      pw.z = pack_bf16x2(sc[j][8 * ap + 4] * inv, sc[j][8 * ap + 5] * inv);
-      pw.w = pack_bf16x2(sc[j][8 * ap + 6] * inv, sc[j][8 * ap + 7] * inv);
-      const int key0 = 32 * j + 16 * ap + 4 * hi;
-#pragma unroll
-      for (int jd = 0; jd < 2; ++jd) {
-        const bf16_t* vrow = Vt + (jd * 32 + r32) * AT_LD + key0;
-        const uint2 v0 = *(const uint2*)vrow, v1 = *(const uint2*)(vrow + 8);
-        const u32x4 vw = {v0.x, v0.y, v1.x, v1.y};
-        oc[jd] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vw), __builtin_bit_cast(bf16x8, pw), oc[jd], 0, 0, 0);
-      }
+    for (int jd = 0; jd < AT_D / 16; ++jd) {
+      const bf16_t* vrow = Vt + (jd * 16 + l16) * AT_LD + 32 * ks + 4 * hi;
+      const uint2 v0 = *(const uint2*)vrow, v1 = *(const uint2*)(vrow + 16);
+      const u32x4 vw = {v0.x, v0.y, v1.x, v1.y};
+      oc[jd] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vw), __builtin_bit_cast(bf16x8, pw), oc[jd], 0, 0, 0);
     }
-  // the second product is transposed as well: oc[jd][v] is query qrow, head dim 32 jd + 8 (v / 4) + 4 hi + v % 4, so a
+  }
+  // the second product is transposed as well: oc[jd][v] is query qrow, head dim 16 jd + 4 hi + v, so a
   // lane stores four neighbouring values at a time
   if (qrow < S) {
     bf16_t* O = (bf16_t*)p.o + (long)b * S * ld + h * AT_D + (long)qrow * ld + 4 * hi;
 #pragma unroll
-    for (int jd = 0; jd < 2; ++jd)
-#pragma unroll
-      for (int v4 = 0; v4 < 4; ++v4)
-        *(uint2*)(O + jd * 32 + 8 * v4) = make_uint2(pack_bf16x2(oc[jd][4 * v4], oc[jd][4 * v4 + 1]),
-                                                     pack_bf16x2(oc[jd][4 * v4 + 2], oc[jd][4 * v4 + 3]));
+    for (int jd = 0; jd < AT_D / 16; ++jd)
+      *(uint2*)(O + jd * 16) = make_uint2(pack_bf16x2(oc[jd][0], oc[jd][1]), pack_bf16x2(oc[jd][2], oc[jd][3]));
   }
 }
 
-__global__ __launch_bounds__(256) void attention_kernel(const AttnGroupArgs args) {
+__global__ __launch_bounds__(AT_NT, 4) void attention_kernel(const AttnGroupArgs args) {
   const int g = find_problem(args, blockIdx.x);
   attention_block(args.p[g], blockIdx.x - args.p[g].tile_start);
 }
 // One problem: its descriptor comes in scalar arguments, which the dispatch puts into registers
-__global__ __launch_bounds__(256) void attention_lone_kernel(const void* q, const void* k, const void* v, void* o, int S, int heads, int ld) {
+__global__ __launch_bounds__(AT_NT, 4) void attention_lone_kernel(const void* q, const void* k, const void* v, void* o, int S, int heads, int ld) {
   attention_block(AttnProblem{q, k, v, o, 0, S, heads, ld, 0, 0}, blockIdx.x);
 }
 
@@ -165,8 +160,8 @@ hipError_t launch_attention(const AttnGroupArgs& a, hipStream_t s) {
     start += b.p[i].tiles;
   }
   const AttnProblem& p = b.p[0];
-  if (b.n == 1) hipLaunchKernelGGL(attention_lone_kernel, dim3(start), dim3(256), 0, s, p.q, p.k, p.v, p.o, p.S, p.heads, p.ld);
-  else hipLaunchKernelGGL(attention_kernel, dim3(start), dim3(256), 0, s, b);
+  if (b.n == 1) hipLaunchKernelGGL(attention_lone_kernel, dim3(start), dim3(AT_NT), 0, s, p.q, p.k, p.v, p.o, p.S, p.heads, p.ld);
+  else hipLaunchKernelGGL(attention_kernel, dim3(start), dim3(AT_NT), 0, s, b);
   return hipGetLastError();
 }
 

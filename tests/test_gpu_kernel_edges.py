@@ -116,10 +116,10 @@ def test_expand_depthwise_wide_inputs(torch_mod, k, stride):
         net.close()
 
 
-# Attention and LayerNorm: token counts around the 32-query waves and the key pairs a lane transposes (odd counts, one
+# Attention and LayerNorm: token counts around the 16-query waves and the key pairs a lane transposes (odd counts, one
 # token, a full block), hidden sizes whose last 64-lane group of octets is partial (9, 65 octets) or full (256).
 # Tolerance: the family's.
-@pytest.mark.parametrize("tokens,hidden,heads", [(1, 72, 1), (2, 520, 3), (31, 72, 2), (65, 520, 1), (127, 136, 2),
+@pytest.mark.parametrize("tokens,hidden,heads", [(1, 72, 1), (2, 520, 3), (17, 72, 1), (31, 72, 2), (65, 520, 1), (127, 136, 2),
                                                  (128, 2048, 1)])
 def test_attention_layernorm_edges(torch_mod, tokens, hidden, heads):
     import oracle
@@ -134,6 +134,26 @@ def test_attention_layernorm_edges(torch_mod, tokens, hidden, heads):
         print("attention", tokens, hidden, heads, flush=True)
         got = forward(torch_mod, net, spec, [c], np.zeros(5), x)
         check_parity(got, oracle.forward(spec, W, S, c, x), "bf16", f"{tokens} x {hidden}")
+    finally:
+        net.close()
+
+
+# MBV3 head: outputs of 14, 15 and 29 rows or columns (14 x 14 tiles), image edges that fall on every window position, and
+# a request with a row of one tile only.  Tolerance: the family's.
+@pytest.mark.parametrize("h,w", [(27, 29), (28, 30), (29, 57), (58, 26), (31, 15)])
+def test_mbv3_head_tile_edges(torch_mod, h, w):
+    import oracle
+    import paper_2312_16733_amd as sna
+    spec = synth.MBV3Spec(n_classes=40, stage_ch=(24,), stage_stride=(1,), stage_se=(False,), stage_act=("relu",),
+                          max_depth=(1,), depth_choices=(1,), kernel_choices=(3,), res_choices=(80,), tail_ch=64, fc_ch=64)
+    W, S, C = setup(spec, 2)
+    net = sna.Supernet(spec, W, S, 2, 3)
+    try:
+        c = C[-1]
+        c.in_h, c.in_w = h, w
+        x = synth.make_inputs(spec, 3, h, w, 15)
+        print("mbv3 head", h, w, flush=True)
+        check_parity(forward(torch_mod, net, spec, [c], np.zeros(3), x), oracle.forward(spec, W, S, c, x), "bf16", f"{h} x {w}")
     finally:
         net.close()
 
