@@ -13,9 +13,10 @@ constexpr int AT_D = 64;           // head dim
 constexpr int AT_LD = AT_S + 8;    // LDS row stride (bf16) of V^T
 constexpr int AT_KD = AT_D + 8;    // and of K
 
-constexpr int AT_NT = 64 * (AT_S / 16);      // threads: a wave per 16 queries
+constexpr int AT_Q = 64;           // queries per block
+constexpr int AT_NT = 64 * (AT_Q / 16);      // threads: a wave per 16 queries
 
-// One block = one (request, head); wave w owns queries [16w, 16w + 16).
+// One block = 64 queries of one (request, head); wave w owns 16 of them, from 16w on.
 //   scores = Q K^T / 8 (fp32) -> softmax over keys (fp32) -> P rounded to bf16 -> ctx = P V -> bf16.
 // The scores are computed transposed (K as the row operand, Q as the column operand), so that a lane
 // of the accumulator holds one query (column lane % 16) and 4 of the 16 keys of each key block:
@@ -27,10 +28,13 @@ constexpr int AT_NT = 64 * (AT_S / 16);      // threads: a wave per 16 queries
 // LDS gives each lane its two runs of 4 keys as two 8-byte reads.
 // K and V^T lie in LDS: read by each wave from global memory, K came in as many times over as there are waves, and the CU's
 // fetch of it was half of the launch (3 requests of 128 tokens x 12 heads 7.1 -> 5.8 us, 32 requests 12.0 -> 9.9, with 16
-// queries a wave instead of 32).
+// queries a wave instead of 32).  Two blocks a head rather than one of eight waves: 5.8 -> 4.9 and 9.9 -> 9.2, since two
+// thirds of the CUs had one block and the others two, and a few heads occupy twice the CUs.
 __device__ __forceinline__ void attention_block(const AttnProblem p, int local) {
   __shared__ __attribute__((aligned(16))) bf16_t Vt[AT_D * AT_LD];
   __shared__ __attribute__((aligned(16))) bf16_t Ks[AT_S * AT_KD];
+  const int pairs = p.B * p.heads, part = local / pairs;
+  local -= part * pairs;
   const int h = local % p.heads, b = local / p.heads;
   const int S = p.S, ld = p.ld;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -41,9 +45,9 @@ __device__ __forceinline__ void attention_block(const AttnProblem p, int local) 
   // All of a thread's loads go out together, from rows clamped to the last one: a guarded load would be waited for
   // before the next guard.  Scores of keys >= S are masked below and query rows >= S are not stored, so only V needs zeros.
   const int l16 = lane & 15, hi = lane >> 4;
-  const int qrow = wave * 16 + l16;
+  const int qrow = part * AT_Q + wave * 16 + l16;
   const int qld = qrow < S ? qrow : S - 1;
-  u32x4 qv[2], kv[AT_S * AT_D / 8 / AT_NT], vv[2];
+  u32x4 qv[2], kv[AT_S * AT_D / 8 / AT_NT], vv[2][2];
 #pragma unroll
   for (int i = 0; i < AT_S * AT_D / 8 / AT_NT; ++i) {
     const int key = i * (AT_NT / 8) + (tid >> 3);
@@ -53,26 +57,28 @@ __device__ __forceinline__ void attention_block(const AttnProblem p, int local) 
   for (int ks = 0; ks < 2; ++ks) qv[ks] = *(const u32x4*)(Q + (long)qld * ld + ks * 32 + hi * 8);
   // V: a lane takes two neighbouring keys of a head-dim octet, so that it writes V^T as whole dwords and a wave's 64
   // lanes write 64 consecutive ones
-  static_assert(AT_NT == 64 * (AT_D / 8) && AT_S == 128, "a wave per octet, two keys a lane");
+  static_assert(AT_NT == 64 * (AT_D / 16) && AT_S == 128, "two octets a wave, two keys a lane");
 #pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    const int key = 2 * lane + e < S ? 2 * lane + e : S - 1;
-    vv[e] = *(const u32x4*)(V + (long)key * ld + wave * 8);
-  }
+  for (int it = 0; it < 2; ++it)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int key = 2 * lane + e < S ? 2 * lane + e : S - 1;
+      vv[it][e] = *(const u32x4*)(V + (long)key * ld + (wave + 4 * it) * 8);
+    }
   __builtin_amdgcn_sched_barrier(0);     // keep the loads ahead of everything that waits for one of them
 
 #pragma unroll
   for (int i = 0; i < AT_S * AT_D / 8 / AT_NT; ++i) *(u32x4*)(Ks + (i * (AT_NT / 8) + (tid >> 3)) * AT_KD + (tid & 7) * 8) = kv[i];
   // V^T into LDS: Vt[d][key], zero for keys >= S
-  {
+#pragma unroll
+  for (int it = 0; it < 2; ++it) {
     const unsigned lo_ok = 2 * lane < S ? 0xffffffffu : 0u, hi_ok = 2 * lane + 1 < S ? 0xffffffffu : 0u;
-    const unsigned a[4] = {vv[0].x & lo_ok, vv[0].y & lo_ok, vv[0].z & lo_ok, vv[0].w & lo_ok};
-    const unsigned c[4] = {vv[1].x & hi_ok, vv[1].y & hi_ok, vv[1].z & hi_ok, vv[1].w & hi_ok};
-    bf16_t* col = Vt + wave * 8 * AT_LD + 2 * lane;
+    bf16_t* col = Vt + (wave + 4 * it) * 8 * AT_LD + 2 * lane;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      *(unsigned*)(col + (2 * e) * AT_LD) = (a[e] & 0xffffu) | (c[e] << 16);
-      *(unsigned*)(col + (2 * e + 1) * AT_LD) = (a[e] >> 16) | (c[e] & 0xffff0000u);
+      const unsigned a = vv[it][0][e] & lo_ok, c = vv[it][1][e] & hi_ok;
+      *(unsigned*)(col + (2 * e) * AT_LD) = (a & 0xffffu) | (c << 16);
+      *(unsigned*)(col + (2 * e + 1) * AT_LD) = (a >> 16) | (c & 0xffff0000u);
     }
   }
   __syncthreads();
@@ -145,8 +151,8 @@ __global__ __launch_bounds__(AT_NT, 4) void attention_kernel(const AttnGroupArgs
   attention_block(args.p[g], blockIdx.x - args.p[g].tile_start);
 }
 // One problem: its descriptor comes in scalar arguments, which the dispatch puts into registers
-__global__ __launch_bounds__(AT_NT, 4) void attention_lone_kernel(const void* q, const void* k, const void* v, void* o, int S, int heads, int ld) {
-  attention_block(AttnProblem{q, k, v, o, 0, S, heads, ld, 0, 0}, blockIdx.x);
+__global__ __launch_bounds__(AT_NT, 4) void attention_lone_kernel(const void* q, const void* k, const void* v, void* o, int B, int S, int heads, int ld) {
+  attention_block(AttnProblem{q, k, v, o, B, S, heads, ld, 0, 0}, blockIdx.x);
 }
 
 hipError_t launch_attention(const AttnGroupArgs& a, hipStream_t s) {
@@ -156,11 +162,11 @@ hipError_t launch_attention(const AttnGroupArgs& a, hipStream_t s) {
   for (int i = 0; i < b.n; ++i) {
     if (b.p[i].S > AT_S || b.p[i].S < 1 || b.p[i].ld % 8) return hipErrorInvalidValue;
     b.p[i].tile_start = start;
-    b.p[i].tiles = b.p[i].B * b.p[i].heads;
+    b.p[i].tiles = b.p[i].B * b.p[i].heads * ((b.p[i].S + AT_Q - 1) / AT_Q);
     start += b.p[i].tiles;
   }
   const AttnProblem& p = b.p[0];
-  if (b.n == 1) hipLaunchKernelGGL(attention_lone_kernel, dim3(start), dim3(AT_NT), 0, s, p.q, p.k, p.v, p.o, p.S, p.heads, p.ld);
+  if (b.n == 1) hipLaunchKernelGGL(attention_lone_kernel, dim3(start), dim3(AT_NT), 0, s, p.q, p.k, p.v, p.o, p.B, p.S, p.heads, p.ld);
   else hipLaunchKernelGGL(attention_kernel, dim3(start), dim3(AT_NT), 0, s, b);
   return hipGetLastError();
 }
