@@ -310,19 +310,23 @@ __global__ __launch_bounds__(256) void channel_stats_partial_kernel(const NormCa
   float n = 0.f, mean = 0.f, m2 = 0.f;
   if (ch < a.K) {
     const float* src = a.raw + ch;
-    // groups of 8 rows of this lane, r, r + 4, ..., r + 28; the loads of four groups go out together (a group at a time
+    // groups of 8 rows of this lane, r, r + 4, ..., r + 28; the loads of all eight groups go out together (a group at a time
     // was a round trip each, eight in a row: 7.2 us whatever the layer)
-    for (int r = r0 + rl; r < r1; r += 128) {
-      float v[4][8];
+    constexpr int GROUPS = SNA_CAL_ROWS / 32;
+    const int r = r0 + rl;
+    {
+      float v[GROUPS][8];
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
+      for (int g = 0; g < GROUPS; ++g)
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
           const int rr = r + 32 * g + 4 * j;
-          v[g][j] = rr < r1 ? src[(long)rr * a.K] : 0.f;
+          const float q = src[(long)(rr < r1 ? rr : r1 - 1) * a.K];
+          v[g][j] = rr < r1 ? q : 0.f;
         }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int g = 0; g < GROUPS; ++g) {
         if (r + 32 * g >= r1) break;
         int cnt = 0;
         float sum = 0.f;
