@@ -1112,11 +1112,14 @@ __global__ __launch_bounds__(64 * (WARPS_M * WARPS_N + FW), igemm_waves(BM, BN, 
 void igemm_kernel(const ConvGroupArgs args) {
   // The first problem's descriptor sits at a fixed offset of the arguments, so its load does not wait for the problem search.
   ConvProblem p = args.p[0];
+  int local;
   if (args.n > 1) {
-    const int g = find_problem(args, blockIdx.x >> 3);
-    if (g > 0) p = args.p[g];
+    const TilePlace at = place_of_block(args, blockIdx.x);
+    if (at.problem > 0) p = args.p[at.problem];
+    local = at.tile;
+  } else {
+    local = tile_of_block(p);
   }
-  const int local = tile_of_block(p);
   if (local < 0) return;
   igemm_tile<BM, BN, WARPS_M, WARPS_N, NS, CHUNKED, FW, GATED>(p, local);
 }

@@ -67,11 +67,14 @@ __global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs arg
 #if defined(__HIP_DEVICE_COMPILE__)
   extern __shared__ __attribute__((aligned(16))) char smem[];
   ExpDwProblem p = args.p[0];
+  int local;
   if (args.n > 1) {
-    const int g = find_problem(args, blockIdx.x >> 3);
-    if (g > 0) p = args.p[g];
-  }
-  const int local = tile_of_block(p);                           // the channel groups of a tile, which read the same input, on one XCD
+    const TilePlace at = place_of_block(args, blockIdx.x);
+    if (at.problem > 0) p = args.p[at.problem];
+    local = at.tile;
+  } else {
+    local = tile_of_block(p);
+  }                           // the channel groups of a tile, which read the same input, on one XCD
   if (local < 0) return;
   const int t1 = p.by_chunks.div(local), t2 = p.by_tiles_x.div(t1), t3 = p.by_tiles_y.div(t2);
   const int chunk = local - t1 * p.chunks, tx = t1 - t2 * p.tiles_x, ty = t2 - t3 * p.tiles_y;
@@ -488,7 +491,7 @@ hipError_t launch_expand_dw(const ExpDwArgs& a, hipStream_t s) {
         if (l > lds) lds = l;
       }
       if (!b.n) continue;
-      b.total_tiles = start * kXcds;
+      b.total_tiles = launch_blocks(b);
       const int blocks = b.total_tiles;
       hipError_t e = hipSuccess;
 #define SNA_XD(KK, SS)                                                                                                \

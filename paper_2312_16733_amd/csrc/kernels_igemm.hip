@@ -43,11 +43,14 @@ void conv3_slab_kernel(const ConvGroupArgs args) {
   const unsigned lds0 = (unsigned)(size_t)(lds_char*)smem;
 
   ConvProblem p = args.p[0];
+  int local;
   if (args.n > 1) {
-    const int g = find_problem(args, blockIdx.x >> 3);
-    if (g > 0) p = args.p[g];
+    const TilePlace at = place_of_block(args, blockIdx.x);
+    if (at.problem > 0) p = args.p[at.problem];
+    local = at.tile;
+  } else {
+    local = tile_of_block(p);
   }
-  const int local = tile_of_block(p);
   if (local < 0) return;
   const int tm = p.by_tiles_n.div(local), tn = local - tm * p.tiles_n;
   const int m0 = tm * BM, n0 = tn * BN;
@@ -516,7 +519,7 @@ hipError_t launch_igemm(const ConvGroupArgs& a, int variant, bool chunked, hipSt
     const PwArgs w = PwArgs::of(a.p[0]);
     hipLaunchKernelGGL(pw, dim3(a.total_tiles), dim3(v.threads), smem, s, w.x, w.w, w.x_bytes, w.w_bytes, w.M, w.tiles, w.ck, w.tn, w.tn_m, w.wk, a.p[0]);
   } else {
-    hipLaunchKernelGGL(fn, dim3(a.total_tiles), dim3(v.threads), smem, s, a);
+    hipLaunchKernelGGL(fn, dim3(launch_blocks(a)), dim3(v.threads), smem, s, a);
   }
   return hipGetLastError();
 }

@@ -12,18 +12,23 @@ DRIVER = r"""
 int main() {                                  // per launch: number of problems, their tile counts -> "problem tile xcd" per working block
   int n;
   while (std::scanf("%d", &n) == 1) {
-    int tiles[64], start[64], rows = 0;
+    struct { int n; struct { int tiles, tile_start; } p[64]; } a;
+    a.n = n;
+    int rows = 0;
     for (int i = 0; i < n; ++i) {
-      if (std::scanf("%d", &tiles[i]) != 1) return 1;
-      start[i] = rows;
-      rows += sna::tile_rows(tiles[i]);
+      if (std::scanf("%d", &a.p[i].tiles) != 1) return 1;
+      a.p[i].tile_start = rows;
+      rows += sna::tile_rows(a.p[i].tiles);
     }
-    for (int b = 0; b < rows * sna::kXcds; ++b) {
-      int g = 0;
-      for (int i = 1; i < n; ++i)
-        if ((b >> 3) >= start[i]) g = i;      // the kernels' find_problem
-      const int t = sna::tile_of_block(tiles[g], start[g], b);
-      if (t >= 0) std::printf("%d %d %d\n", g, t, b % sna::kXcds);
+    const int blocks = sna::launch_blocks(a);
+    if (blocks > rows * sna::kXcds) return 2;
+    bool ended[sna::kXcds] = {};
+    for (int b = 0; b < blocks; ++b) {
+      const sna::TilePlace at = sna::place_of_block(a, b);
+      if (n == 1 && at.tile != sna::tile_of_block(a.p[0].tiles, a.p[0].tile_start, b)) return 3;
+      if (at.tile < 0) ended[b % sna::kXcds] = true;
+      else if (ended[b % sna::kXcds]) return 4;         // a block without a tile ahead of one with
+      else std::printf("%d %d %d\n", at.problem, at.tile, b % sna::kXcds);
     }
     std::printf("end\n");
   }
@@ -32,7 +37,7 @@ int main() {                                  // per launch: number of problems,
 
 
 @pytest.mark.parametrize("launches", [[[t] for t in list(range(1, 42)) + [255, 256, 257, 9408, 200000]],
-                                      [[1] * 16, [7, 8, 9], [3, 1568, 1, 17, 64, 5, 2, 31], list(range(1, 33))]])
+                                      [[1] * 16, [7, 8, 9], [84, 84, 84], [3, 1568, 1, 17, 64, 5, 2, 31], list(range(1, 33))]])
 def test_every_tile_once_and_evenly_over_xcds(tmp_path, launches):
     (tmp_path / "driver.cpp").write_text(DRIVER)
     subprocess.run(["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2312_16733_amd", "csrc"),
