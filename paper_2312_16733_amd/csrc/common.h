@@ -139,7 +139,7 @@ struct ExpDwProblem {
   int act;              // of both layers
   unsigned x_bytes, we_bytes;
   // filled by the launcher: output rows, 16-wide row segments and requests per block; tiles, channel groups; LDS layout
-  int th, ntx, rq, ng, na, tiles_x, tiles_y, chunks, CW, plane, req_plane, x_lds;
+  int th, ntx, rq, ng, na, seg, tiles_x, tiles_y, chunks, CW, plane, req_plane, x_lds;
   FastDiv by_chunks, by_tiles_x, by_tiles_y;
   int tile_start, tiles;
 };
@@ -308,23 +308,27 @@ __device__ __forceinline__ float apply_act(float v, int act) {
   if (act == SNA_ACT_GELU) return v * normal_cdf(v);
   return v;
 }
-// Sum over the 64 lanes, in a fixed order, left in lane 63: within rows of 16 lanes by shifts of 1, 2, 4, 8, then lane 15's
-// over rows 1 and 3, lane 31's over rows 2 and 3.  In the vector pipe, where shuffles go through LDS one after the other.
-__device__ __forceinline__ float lane_sum(float v) {
+// v plus the value that CTRL's lane has, in the rows of 16 lanes that ROWS has bits for; lanes without one add zero
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float add_dpp(float v) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  auto add = [&](auto ctrl_c, auto rows_c) {
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl_c)::value, decltype(rows_c)::value, 0xf, false));
-  };
-  using std::integral_constant;
-  typedef integral_constant<int, 0xf> all_t;
-  add(integral_constant<int, 0x111>{}, all_t{});                // row_shr:1, zeros shifted in
-  add(integral_constant<int, 0x112>{}, all_t{});
-  add(integral_constant<int, 0x114>{}, all_t{});
-  add(integral_constant<int, 0x118>{}, all_t{});
-  add(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});      // row_bcast:15
-  add(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});      // row_bcast:31
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, false));
 #endif
   return v;
+}
+// Sum over each row of 16 lanes, in a fixed order, left in its lane 15: by shifts of 1, 2, 4, 8.  In the vector pipe, where
+// shuffles go through LDS one after the other.
+__device__ __forceinline__ float row_sum(float v) {
+  v = add_dpp<0x111, 0xf>(v);                               // row_shr:1, zeros shifted in
+  v = add_dpp<0x112, 0xf>(v);
+  v = add_dpp<0x114, 0xf>(v);
+  return add_dpp<0x118, 0xf>(v);
+}
+// Sum over the 64 lanes, in a fixed order, left in lane 63: within the rows, then lane 15's over rows 1 and 3, lane 31's over
+// rows 2 and 3.
+__device__ __forceinline__ float lane_sum(float v) {
+  v = add_dpp<0x142, 0xa>(row_sum(v));                      // row_bcast:15
+  return add_dpp<0x143, 0xc>(v);                            // row_bcast:31
 }
 // problem lookup for a grouped launch: linear scan over <= 16 entries (uniform per block)
 template <class Args>

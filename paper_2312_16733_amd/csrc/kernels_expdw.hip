@@ -50,7 +50,8 @@ typedef unsigned u32x4w __attribute__((ext_vector_type(4), aligned(4)));
 // LDS layout and tile of one problem, the same on host and device
 struct XdGeom {
   int th, ntx, rq;                  // output rows, 16-wide segments per row, requests per block
-  int ng, na;                       // MFMA groups, rows of a request in one (group g has rows g, g + ng, ..): rq na ntx <= 16 segments
+  int ng, na;                       // MFMA groups, rows of a request in one (group g has rows g, g + ng, ..)
+  int seg;                          // segments of a request in a group, na ntx and those that are left empty: rq seg <= 16
   int tiles_y, tiles_x;
   int IH, CW;                       // rows and columns (elements) of a channel plane; column 0 is input column x0 * stride - 4
   int plane, req_plane;             // bytes per channel plane (an odd number of 16-byte units) and per request
@@ -242,19 +243,19 @@ __global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs arg
   __syncthreads();
 
   // ---- B: depthwise ---------------------------------------------------------------------------
-  // Row l of every MFMA group is a segment (request rr, rows ng aa + g, column segment tt)
-  const int ng = p.ng, seg_req = p.na * p.ntx;
-  const float inv_ntx = xd_rcp(p.ntx), inv_sr = xd_rcp(seg_req);
+  // Row l of every MFMA group is a segment (request rr, rows ng aa + g, column segment tt); of an empty one the row is th or more
+  const int ng = p.ng;
+  const float inv_ntx = xd_rcp(p.ntx), inv_sr = xd_rcp(p.seg);
   struct Seg { int rr, row, tt; };                              // row: of group 0
   auto segment = [&](int l) {
-    const int rr = xd_div(l, inv_sr), ii = l - rr * seg_req;
+    const int rr = xd_div(l, inv_sr), ii = l - rr * p.seg;
     const int aa = xd_div(ii, inv_ntx);
     return Seg{rr, aa * ng, ii - aa * p.ntx};
   };
   int seg_off;                                                  // plane offset of this lane's segment, MFMA row l16
   {
-    const Seg s = segment(l16 < p.rq * seg_req ? l16 : 0);
-    seg_off = s.rr * p.req_plane + (s.row * STRIDE * p.CW + s.tt * XD_SEG * STRIDE) * 2;
+    const Seg s = segment(l16);
+    seg_off = s.rr < p.rq && s.row < p.th ? s.rr * p.req_plane + (s.row * STRIDE * p.CW + s.tt * XD_SEG * STRIDE) * 2 : 0;
   }
   // this lane's 8 elements of the band: columns 32 kb + 8 grp .. + 7 against output l16
   int col_off[KB], t_off[KB];
@@ -346,7 +347,8 @@ __global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs arg
   if (p.act == SNA_ACT_RELU) depthwise_act(std::integral_constant<int, SNA_ACT_RELU>{});
   else depthwise_act(std::integral_constant<int, SNA_ACT_HSWISH>{});
 
-  // ---- pool: this wave's two channels, per request; a lane over its outputs in order, the lanes by a fixed tree ---------
+  // ---- pool: this wave's two channels, per request; a lane over its outputs in order, the lanes by a fixed tree, in an order
+  // that does not depend on the request's place in the block ------------------------------------------
   if (p.pool_part) {
     float s0[4], s1[4];
     int req[4];
@@ -364,16 +366,41 @@ __global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs arg
       }
     }
     const int c = c0 + wave * 2;
-    for (int rr = 0; rr < rq; ++rr) {
-      float a0 = 0.f, a1 = 0.f;
+    auto out = [&](int rr) { return p.pool_part + ((long)((n0 + rr) * p.tiles_y + ty) * p.tiles_x + tx) * C + c; };
+    if (__builtin_expect(p.rq > 1 && p.seg > 2 && (p.seg & 3) != 0, 0)) {
+      // A lane's four segments are not all of one request, and in which way depends on the request's place in the block.  So
+      // each segment's columns first, and a lane for each request and channel adds that request's segments in order, from where
+      // the expand weights lay.
+      float* const tot = (float*)wfrag + wave * 32;             // 16 segments of the first channel, then of the second
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        a0 += req[v] == rr ? s0[v] : 0.f;
-        a1 += req[v] == rr ? s1[v] : 0.f;
+      for (int v = 0; v < 4; ++v) { s0[v] = row_sum(s0[v]); s1[v] = row_sum(s1[v]); }
+      if (l16 == 15) {
+        *(float4*)(tot + 4 * grp) = make_float4(s0[0], s0[1], s0[2], s0[3]);
+        *(float4*)(tot + 16 + 4 * grp) = make_float4(s1[0], s1[1], s1[2], s1[3]);
       }
-      a0 = lane_sum(a0); a1 = lane_sum(a1);
-      if (lane == 63 && c < C)
-        *(float2*)(p.pool_part + ((long)((n0 + rr) * p.tiles_y + ty) * p.tiles_x + tx) * C + c) = make_float2(a0, a1);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_wave_barrier();
+      const int rr = lane >> 1, ch = lane & 1;
+      if (rr < rq && c < C) {
+        float a = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {                           // two requests or more: 8 segments at most
+          const float t = tot[ch * 16 + rr * p.seg + (i < p.seg ? i : 0)];
+          a += i < p.seg ? t : 0.f;
+        }
+        out(rr)[ch] = a;
+      }
+    } else {
+      for (int rr = 0; rr < rq; ++rr) {
+        float a0 = 0.f, a1 = 0.f;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          a0 += req[v] == rr ? s0[v] : 0.f;
+          a1 += req[v] == rr ? s1[v] : 0.f;
+        }
+        a0 = lane_sum(a0); a1 = lane_sum(a1);
+        if (lane == 63 && c < C) *(float2*)out(rr) = make_float2(a0, a1);
+      }
     }
   }
   __syncthreads();                                              // every wave is done with the planes
@@ -436,6 +463,12 @@ static XdGeom xd_geometry(int Ho, int Wo, int k, int stride) {
   // as few groups as hold the segments; four always do (th <= 4 floor(16 / ntx); with several requests, at most 32 segments)
   for (g.ng = 1; g.ng < XD_GROUPS && g.rq * ((g.th + g.ng - 1) / g.ng) * g.ntx > 16; ++g.ng) {}
   g.na = (g.th + g.ng - 1) / g.ng;
+  // Of several requests, each begins with a lane's first segment, or fits into half a lane, where there is room for it: then
+  // the pool's sums are as if it were alone in the block.  (There is not for three requests of 5 segments, 9 or 10 rows: with
+  // two requests 64 of them took 2.6 % of a forward longer, with one group more 1 to 2 % at any batch.)
+  g.seg = g.na * g.ntx;
+  const int whole = (g.seg + 3) / 4 * 4;
+  if (g.rq > 1 && g.seg > 2 && g.rq * whole <= 16) g.seg = whole;
   return g;
 }
 static size_t xd_planes(const XdGeom& g, int stride) {          // with the rows past the tile that B reads; also holds the staged output
@@ -480,7 +513,7 @@ hipError_t launch_expand_dw(const ExpDwArgs& a, hipStream_t s) {
         if ((double)p.N * p.H * p.W * p.Cin * 2 >= 2147483648.0 || (double)p.N * p.Ho * p.Wo * p.C * 2 >= 2147483648.0)
           return hipErrorInvalidValue;                          // 32-bit buffer offsets; slice_conv has refused such a call
         const XdGeom g = xd_geometry(p.Ho, p.Wo, k, st);
-        p.th = g.th; p.ntx = g.ntx; p.rq = g.rq; p.ng = g.ng; p.na = g.na; p.tiles_x = g.tiles_x; p.tiles_y = g.tiles_y;
+        p.th = g.th; p.ntx = g.ntx; p.rq = g.rq; p.ng = g.ng; p.na = g.na; p.seg = g.seg; p.tiles_x = g.tiles_x; p.tiles_y = g.tiles_y;
         p.CW = g.CW; p.plane = g.plane; p.req_plane = g.req_plane; p.x_lds = (int)xd_planes(g, st);
         p.chunks = (p.C + XD_CH - 1) / XD_CH;
         p.by_chunks = FastDiv::by(p.chunks); p.by_tiles_x = FastDiv::by(p.tiles_x); p.by_tiles_y = FastDiv::by(p.tiles_y);

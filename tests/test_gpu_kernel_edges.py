@@ -88,6 +88,32 @@ def test_expand_depthwise_tile_edges(torch_mod, h, w, batch):
         net.close()
 
 
+# Several requests per block of the fused layer, whose squeeze-excite pool sums a request's segments over lanes: outputs of
+# 5, 6, 9 and 14 rows, of two and three column segments, and at stride 2, where a request's 3, 5, 6 or 7 segments begin in the
+# middle of a lane's four.  One pixel of each request is 2^16 larger, so that the sums round.  Every request has the bits that
+# it has alone.
+@pytest.mark.parametrize("h,w,k,stride", [(10, 10, 7, 1), (12, 12, 5, 1), (18, 18, 3, 1), (28, 28, 5, 1), (12, 40, 3, 1), (10, 80, 3, 1),
+                                          (27, 28, 3, 2), (20, 20, 5, 2)])
+def test_pool_sums_at_every_place_of_a_block(torch_mod, h, w, k, stride):
+    import paper_2312_16733_amd as sna
+    spec = synth.MBV3Spec(n_classes=200, stage_ch=(160,), stage_stride=(stride,), stage_se=(True,), stage_act=("hswish",),
+                          max_depth=(4,), depth_choices=(4,), expand_choices=(6,), kernel_choices=(k,), res_choices=(80,))
+    W, S, C = setup(spec, 2)
+    c, batch = C[-1], 17
+    c.in_h, c.in_w = h, w
+    x = synth.make_inputs(spec, batch, h, w, 18)
+    for i in range(batch):
+        x[i, i % h, (3 * i) % w] *= 2.0 ** 16
+    net = sna.Supernet(spec, W, S, 2, batch)
+    try:
+        print("pool sums", h, w, k, stride, flush=True)
+        got = forward(torch_mod, net, spec, [c], np.zeros(batch), x)
+        alone = [forward(torch_mod, net, spec, [c], np.zeros(1), x[i:i + 1])[0] for i in range(batch)]
+        assert [i for i in range(batch) if not np.array_equal(got[i], alone[i])] == []
+    finally:
+        net.close()
+
+
 # Wide block inputs.  168 and 264 channels: a reduction of more than one pass of five steps, and more weight fragments than
 # one per thread.  4800 channels: the expand weights no longer fit in LDS beside the tile, and the block runs as separate
 # expand and depthwise launches, with the gate's pool in the depthwise one.  Tolerance: the family's.
