@@ -1813,7 +1813,7 @@ sna_status sna_subnet_tune(sna_supernet* net, const sna_subnet_cfg* cfgs, int32_
     kv.second = Fwd::choose_tile(std::vector<ConvProblem>(k[6], q).data(), k[6], k[5] > 1 ? 2 : 1).variant;
   }
   const int nv = igemm_num_variants(), rounds = 7;
-  std::map<TuneKey, std::vector<std::vector<double>>> samples;   // key -> [variant][round]
+  std::map<TuneKey, std::vector<TuneSample>> samples;            // key -> [variant]
   for (int round = 0; round <= rounds && st == SNA_OK; ++round)             // round 0 warms up, not recorded
     for (int v = 0; v < nv && st == SNA_OK; ++v) {
       net->forced_variant = v;
@@ -1821,20 +1821,22 @@ sna_status sna_subnet_tune(sna_supernet* net, const sna_subnet_cfg* cfgs, int32_
       net->ev_used = 0;
       st = sna_subnet_forward(net, cfgs, n_cfgs, req_cfg, n_requests, inputs_dev, logits_dev, hidden_dev, hip_stream);
       if (st != SNA_OK) break;
-      std::map<TuneKey, double> sum;
+      std::map<TuneKey, std::pair<double, int>> sum;      // time and number of the key's launches that ran with v
       for (const ProfRec& r : net->prof_recs) {
         if (!r.igemm || r.variant != v) continue;       // a variant that cannot run this shape was not applied
         float ms = 0;
         hipError_t e = hipEventSynchronize(r.b);
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, r.a, r.b);
         if (e != hipSuccess) { st = fail(SNA_E_HIP, "event: %s", hipGetErrorString(e)); break; }
-        sum[r.key] += ms;
+        sum[r.key].first += ms;
+        sum[r.key].second += 1;
       }
       if (round == 0) continue;
       for (const auto& kv : sum) {
         auto& per_variant = samples[kv.first];
         per_variant.resize(nv);
-        per_variant[v].push_back(kv.second);
+        per_variant[v].ms.push_back(kv.second.first);
+        per_variant[v].launches = kv.second.second;
       }
     }
   net->prof_recs.clear();
@@ -1845,22 +1847,10 @@ sna_status sna_subnet_tune(sna_supernet* net, const sna_subnet_cfg* cfgs, int32_
   net->forced_variant = forced_was;
   if (st != SNA_OK) return st;
   std::map<TuneKey, int> picked = plain;
-  for (auto& kv : samples) {
+  for (const auto& kv : samples) {
     const auto without = plain.find(kv.first);
     if (known.count(kv.first) || without == plain.end()) continue;
-    int best = -1;
-    double best_t = 0;
-    for (int v = 0; v < nv; ++v) {
-      std::vector<double>& t = kv.second[v];
-      if (t.empty()) continue;
-      std::sort(t.begin(), t.end());
-      const double med = t[t.size() / 2];
-      if (best < 0 || med < best_t) { best = v; best_t = med; }
-    }
-    if (best < 0) continue;
-    // (the least of some thirty noisy medians is often a slower variant's)
-    const std::vector<double>& tp = kv.second[without->second];
-    if (tp.empty() || best_t <= 0.98 * tp[tp.size() / 2]) picked[kv.first] = best;
+    picked[kv.first] = measured_variant(kv.second, without->second);
   }
   // Step 3: launches timed one by one, forced neighbours and events between them, do not add up to the forward: a lone
   // request of the largest ResNet-shaped subnet took 0.51-0.54 ms with such picks and 0.49 without.  So the forward is

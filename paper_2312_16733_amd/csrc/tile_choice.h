@@ -1,8 +1,10 @@
 // Which tile variant of the matrix kernel a launch takes, and whether its long reductions are spread over blocks.
 // Plain host code.
 #pragma once
+#include <algorithm>
 #include <cmath>
 #include <cstddef>
+#include <vector>
 
 namespace sna {
 
@@ -99,6 +101,27 @@ inline TileChoice pick_tile(const TileWork* ws, size_t n, int split_mode, const 
         best = {kTileCosts[c].variant, split != 0};
       }
     }
+  return best;
+}
+
+// The variant that a tuned shape gets, from forwards run with every launch forced to one variant after the other.
+// samples[v].ms: the time of the shape's launches that ran with v, one sum per forward; samples[v].launches: how many
+// those were.  A shape's launches need not all take a variant (an input scaled on its way takes few), and a variant that
+// ran on fewer of them than another is not compared: its sum is of less work.  The variant `without` an entry stays unless
+// another is 2 % faster (the least of some thirty noisy medians is often a slower variant's).
+struct TuneSample { std::vector<double> ms; int launches = 0; };
+inline int measured_variant(const std::vector<TuneSample>& samples, int without) {
+  int all = 0, best = -1;
+  for (const TuneSample& s : samples) all = std::max(all, s.launches);
+  auto median = [](std::vector<double> t) { std::sort(t.begin(), t.end()); return t[t.size() / 2]; };
+  auto whole = [&](size_t v) { return v < samples.size() && !samples[v].ms.empty() && samples[v].launches == all; };
+  double best_ms = 0;
+  for (size_t v = 0; v < samples.size(); ++v) {
+    if (!whole(v)) continue;
+    const double ms = median(samples[v].ms);
+    if (best < 0 || ms < best_ms) { best = (int)v; best_ms = ms; }
+  }
+  if (best < 0 || (whole((size_t)without) && best_ms > 0.98 * median(samples[without].ms))) return without;
   return best;
 }
 

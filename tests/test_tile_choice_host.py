@@ -125,3 +125,42 @@ def test_choice_for_a_mixed_launch_takes_little_host_time(driver):
     submission (2.4 us).  Walking fourteen variants twice over sixteen descriptors took 4 to 8."""
     _, got = driver([(0, [(3136 + i, 720 - 8 * i, -(-9 * (90 - i) // 8), 9) for i in range(16)])])
     assert got[0][2] < 2.4, got
+
+
+TUNE_DRIVER = r"""
+#include "tile_choice.h"
+#include <cstdio>
+int main() {                                  // variants, the variant without an entry; per variant: launches, number of sums, the sums
+  int nv, without;
+  while (scanf("%d %d", &nv, &without) == 2) {
+    std::vector<sna::TuneSample> s(nv);
+    for (auto& v : s) {
+      int n;
+      if (scanf("%d %d", &v.launches, &n) != 2) return 1;
+      v.ms.resize(n);
+      for (double& t : v.ms)
+        if (scanf("%lf", &t) != 1) return 1;
+    }
+    printf("%d\n", sna::measured_variant(s, without));
+  }
+}
+"""
+
+
+def test_tuner_compares_variants_over_the_same_launches(tmp_path):
+    """A shape that two launches of a forward share, one of which only some variants can run: a variant's sum over one
+    launch is no better for being smaller."""
+    (tmp_path / "d.cpp").write_text(TUNE_DRIVER)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2312_16733_amd", "csrc"), str(tmp_path / "d.cpp"),
+                    "-o", str(tmp_path / "d")], check=True)
+    calls = [  # (variant without an entry, [(launches, sums)]) -> variant
+        ((0, [(2, [10, 11, 12]), (1, [5, 5, 5]), (2, [9, 9, 9])]), 2),            # variant 1 ran on one launch only
+        ((0, [(2, [10, 11, 12]), (1, [5, 5, 5]), (2, [11, 10.9, 10.9])]), 0),     # and 0.9 % are noise
+        ((1, [(2, [10, 10, 10]), (1, [5, 5, 5]), (2, [9, 9, 9])]), 2),            # the one without an entry ran on one only
+        ((1, [(1, [10, 10, 10]), (1, [9, 9, 50]), (0, [])]), 1),                  # medians; nothing measured for variant 2
+        ((2, [(1, [10, 10, 10]), (1, [9, 9, 9]), (0, [])]), 1),
+        ((2, [(0, []), (0, []), (0, [])]), 2),
+    ]
+    text = "\n".join(f"{len(v)} {w} " + " ".join(f"{n} {len(t)} " + " ".join(map(str, t)) for n, t in v) for (w, v), _ in calls)
+    out = subprocess.run([str(tmp_path / "d")], input=text, capture_output=True, text=True, check=True).stdout.split()
+    assert [int(o) for o in out] == [want for _, want in calls]
