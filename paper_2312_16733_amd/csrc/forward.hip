@@ -1073,8 +1073,10 @@ sna_status Fwd::run_mbv3(const void*, float* logits) {
           if (net->calibrating) { p.pool_segs = 1; p.inv_hw = 1.f; }      // g.small holds the mean itself
           p.pooled = g.small;                                  // written by the depthwise launch above
           p.hidden = g.small + (size_t)p.pool_segs * g.n * m;
-          // The project layer scales its input itself where a tile variant can (a matter of its shape alone): then only
-          // the gate is computed here, into the request's first row of pool sums, which nothing reads any more.
+          // The project layer scales its input itself where a tile variant can: then only the gate is computed here, into the
+          // request's first row of pool sums, which nothing reads any more.  That is a matter of the layer's shape and, for
+          // maps of a few pixels, of the number of requests (those of a tile need room for their gates); both ways round the
+          // same products to bf16, so a request has the same bits.
           ConvProblem c;
           memset(&c, 0, sizeof(c));
           project(g, c);

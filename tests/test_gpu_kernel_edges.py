@@ -142,6 +142,83 @@ def test_expand_depthwise_wide_inputs(torch_mod, k, stride):
         net.close()
 
 
+# Squeeze-excite gates that no matrix tile can apply, so that a pass of its own scales the tensor: 1632 expanded channels,
+# whose project layer sums in two chunks, and 1 x 1 maps of more requests than have room for their gates beside a tile's ring
+# (960 channels: 24 have, 40 have not).  The launch list says how many gates were scaled by the pass.  Tolerance: the
+# family's; requests are bitwise independent of the batch, which takes them one way or the other, and of their call's subnets.
+def scaled_gates(torch, net, spec, cfgs, route, x):
+    """-> (gates applied by the project layer, gates applied by a pass of its own) of a forward, by their bytes."""
+    net.profile_enable(True)
+    try:
+        forward(torch, net, spec, cfgs, route, x)
+        lines = [l for l in net.profile_read_launches().split("\n") if " squeeze_excite " in l]
+        net.profile_read()
+    finally:
+        net.profile_enable(False)
+    n = [0, 0]
+    for l in lines:
+        gates = [[int(t.split("=")[1]) for t in g.split("]")[0].split()] for g in l.split(" [")[1:]]       # N, HW, C, Q
+        left = float(l.split("bytes=")[1].split()[0]) - sum(4.0 * c * q for _, _, c, q in gates)
+        # the subnets of a call differ in their channels, so that the bytes tell which of them were scaled
+        ways = [m for m in range(1 << len(gates)) if left == sum(4.0 * g[0] * g[1] * g[2] for i, g in enumerate(gates) if m >> i & 1)]
+        assert len(ways) == 1, l
+        n[1] += bin(ways[0]).count("1")
+        n[0] += len(gates) - bin(ways[0]).count("1")
+    return tuple(n)
+
+
+def test_gates_scaled_by_a_pass_of_their_own(torch_mod):
+    import oracle
+    import paper_2312_16733_amd as sna
+    spec = synth.MBV3Spec(n_classes=40, stage_ch=(272,), stage_stride=(2,), stage_se=(True,), stage_act=("hswish",), max_depth=(3,),
+                          depth_choices=(3,), expand_choices=(3, 6), kernel_choices=(3,), res_choices=(80,), tail_ch=64, fc_ch=64)
+    W, S, C = setup(spec, 2)
+    batch, h, w = 5, 28, 36
+    x = synth.make_inputs(spec, batch, h, w, 21)
+    net = sna.Supernet(spec, W, S, 2, batch)
+    try:
+        alone = []
+        for c, mid, want in ((C[0], 816, (3, 0)), (C[-1], 1632, (1, 2))):
+            c.in_h, c.in_w = h, w
+            assert c.block_mid_ch[0][1] == mid
+            print("scaled gates", mid, flush=True)
+            got = forward(torch_mod, net, spec, [c], np.zeros(batch), x)
+            check_parity(got, oracle.forward(spec, W, S, c, x), "bf16", f"mid {mid}")
+            assert scaled_gates(torch_mod, net, spec, [c], np.zeros(batch), x) == want
+            np.testing.assert_array_equal(got[3:4], forward(torch_mod, net, spec, [c], np.zeros(1), x[3:4]))
+            alone.append(got)
+        route = np.array([0, 1, 1, 0, 1])
+        mixed = forward(torch_mod, net, spec, [C[0], C[-1]], route, x)
+        np.testing.assert_array_equal(mixed, np.stack([alone[r][i] for i, r in enumerate(route)]))
+        assert scaled_gates(torch_mod, net, spec, [C[0], C[-1]], route, x) == (4, 2)
+    finally:
+        net.close()
+
+
+def test_gates_of_many_one_pixel_maps(torch_mod):
+    import oracle
+    import paper_2312_16733_amd as sna
+    spec = synth.MBV3Spec(n_classes=40, stage_ch=(24, 160), stage_stride=(2, 2), stage_se=(False, True), stage_act=("relu", "hswish"),
+                          max_depth=(3, 3), depth_choices=(3,), expand_choices=(6,), kernel_choices=(3,), res_choices=(80,), tail_ch=64,
+                          fc_ch=64)
+    W, S, C = setup(spec, 2)
+    c = C[-1]
+    c.in_h = c.in_w = 8
+    x = synth.make_inputs(spec, 40, 8, 8, 22)
+    ref = oracle.forward(spec, W, S, c, x)
+    net = sna.Supernet(spec, W, S, 2, 40)
+    try:
+        alone = [forward(torch_mod, net, spec, [c], np.zeros(1), x[i:i + 1])[0] for i in range(40)]
+        check_parity(np.stack(alone), ref, "bf16", "alone")
+        for batch, scaled in ((1, 0), (24, 0), (40, 2)):
+            print("one-pixel maps", batch, flush=True)
+            got = forward(torch_mod, net, spec, [c], np.zeros(batch), x[:batch])
+            np.testing.assert_array_equal(got, np.stack(alone[:batch]))
+            assert scaled_gates(torch_mod, net, spec, [c], np.zeros(batch), x[:batch])[1] == scaled
+    finally:
+        net.close()
+
+
 # Attention and LayerNorm: token counts around the 16-query waves and the key pairs a lane transposes (odd counts, one
 # token, a full block), hidden sizes whose last 64-lane group of octets is partial (9, 65 octets) or full (256).
 # Tolerance: the family's.
