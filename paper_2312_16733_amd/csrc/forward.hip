@@ -1857,8 +1857,8 @@ sna_status sna_subnet_tune(sna_supernet* net, const sna_subnet_cfg* cfgs, int32_
   // Step 3: launches timed one by one, forced neighbours and events between them, do not add up to the forward: a lone
   // request of the largest ResNet-shaped subnet took 0.51-0.54 ms with such picks and 0.49 without.  So the forward is
   // timed whole, with the picks and without, in turn, and they stay only where it gets 1 % shorter by them.  With tables
-  // made so, 30 calls of two families (batch 1 to 64) take 0.96 to 1.002 of their time without a table, where they took
-  // 0.96 to 1.09 (a margin of 4 % in step 2 leaves 0.97 to 1.02).
+  // made so, 36 calls of three families (batch 1 to 64) take 0.957 to 1.003 of their time without a table (mean of two
+  // handles with and without, and the other way round: two handles with the same choices differ by up to 1.5 %).
   net->tuned = plain;
   if (picked != plain) {
     hipEvent_t e0 = nullptr, e1 = nullptr;
