@@ -157,7 +157,7 @@ __device__ __forceinline__ void reduce_octet(const ConvProblem& p, const float* 
   }
 }
 
-constexpr int kGateLoads = 4;               // 16-byte loads a thread makes of its tile's gates, at most (see igemm_variant_ok)
+constexpr int kGateLoads = 4;               // 16-byte loads of its tile's gates that a thread has in flight
 __device__ __forceinline__ int gate_request(const ConvProblem& p, int m) {      // the request that output row m belongs to
   const int t = p.Wo == 1 ? m : (int)__umulhi((unsigned)m, p.magic_wo);
   return p.Ho == 1 ? t : (int)__umulhi((unsigned)t, p.magic_ho);
@@ -169,10 +169,13 @@ __device__ __forceinline__ int gate_request(const ConvProblem& p, int m) {      
 // which matters when a CU has a single block to overlap with itself.
 // GATED: the input of a pointwise stride-1 layer is multiplied by its request's squeeze-excite gate, which saves the pass
 // that wrote the scaled tensor.  Every thread that fetches scales what it fetched itself, in LDS, once its loads have
-// landed and ahead of the barrier that hands the step over: each element once, and in the wave-specialised rings beside the
-// MFMAs.  (Scaled between LDS and the matrix pipe, 20 instructions a fragment and by every wave that reads it, the 64x128
-// tile took 13.6 us instead of 12.1 on 12544 x 112 outputs over 672 channels.)  The gates of the tile's requests lie in LDS behind
-// the ring's stages.
+// landed and ahead of the barrier that hands the step over: each element once, and beside the MFMAs of the computing waves.
+// (Scaled between LDS and the matrix pipe, 20 instructions a fragment and by every wave that reads it, the 64x128
+// tile took 13.6 us instead of 12.1 on 12544 x 112 outputs over 672 channels.)  Built for tiles with fetching waves alone:
+// where the same waves compute, scaling lies in the chain of their steps, and on none of 114 launch shapes were 64x64,
+// 128x64 and 128x32 plain rings ahead by more than 3 % (12800 x 40 over 240: 9.1, 11.0 and 10.3 us, 64x64 deep ring 7.5;
+// 3200 x 112 over 480: 10.4, 14.0 and 13.0, 32x32 deep ring 8.0).  The gates of the tile's requests lie in LDS behind the
+// ring's stages.
 constexpr int igemm_waves(int bm, int bn, int n_math, int ns, bool chunked, int fw) {
   return fw ? (bm * bn >= 128 * 128 || deep_large(bm, bn, n_math, ns, fw) ? 2 : 4)
             : (chunked ? (bm * bn == 128 * 64 ? 3 : (bm * bn > 128 * 128 ? 1 : 2)) : igemm_min_waves(bm, bn, ns));
@@ -282,28 +285,25 @@ __device__ __forceinline__ void igemm_tile(const ConvProblem p, int local) {
     b_base[j] = k * p.wk * 2;
   }
 
-  // Gates of the tile's requests, [request][C] in LDS: brought by the computing waves where others fetch, else requested
-  // ahead of the ring's first loads and written behind them
+  // Gates of the tile's requests, [request][C] in LDS, brought by the computing waves
   const unsigned gate_lds = GATED ? (unsigned)((KT >= NS ? NS : (HALF ? (KT + G - 1) / G * G : KT)) * Cfg::STAGE_B) : 0u;
   const int gate_n0 = GATED ? gate_request(p, m0) : 0, gate_c4 = C >> 2;
   const int gate_cnt = GATED ? (gate_request(p, m0 + BM - 1 < p.M ? m0 + BM - 1 : p.M - 1) - gate_n0 + 1) * gate_c4 : 0;
-  float4 gate_v[GATED ? kGateLoads : 1];
-  auto gates_request = [&](int e0, int step) {
+  auto bring_gates = [&] {
     if constexpr (GATED) {
       const float inv = __builtin_amdgcn_rcpf((float)gate_c4);          // e / gate_c4 for e < 2^20: within 2^-22 of it, 1 / (2 gate_c4) from an integer
+      for (int e0 = tid; e0 < gate_cnt; e0 += 64 * NW * kGateLoads) {
+        float4 v[kGateLoads];
 #pragma unroll
-      for (int i = 0; i < kGateLoads; ++i) {
-        const int e = e0 + i * step, n = (int)(((float)e + 0.5f) * inv);
-        gate_v[i] = e < gate_cnt ? *(const float4*)(p.gate + (long)(gate_n0 + n) * p.gate_stride + (e - n * gate_c4) * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-    }
-  };
-  auto gates_write = [&](int e0, int step) {
-    if constexpr (GATED) {
+        for (int i = 0; i < kGateLoads; ++i) {
+          const int e = e0 + i * 64 * NW, n = (int)(((float)e + 0.5f) * inv);
+          v[i] = e < gate_cnt ? *(const float4*)(p.gate + (long)(gate_n0 + n) * p.gate_stride + (e - n * gate_c4) * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
 #pragma unroll
-      for (int i = 0; i < kGateLoads; ++i) {
-        const int e = e0 + i * step;
-        if (e < gate_cnt) *(float4*)(smem + gate_lds + e * 16) = gate_v[i];
+        for (int i = 0; i < kGateLoads; ++i) {
+          const int e = e0 + i * 64 * NW;
+          if (e < gate_cnt) *(float4*)(smem + gate_lds + e * 16) = v[i];
+        }
       }
     }
   };
@@ -314,7 +314,6 @@ __device__ __forceinline__ void igemm_tile(const ConvProblem p, int local) {
       const int m = m0 + lrow + Cfg::PASS_ROWS * i;
       gate_row[i] = lds0 + gate_lds + (unsigned)((m < p.M ? gate_request(p, m) - gate_n0 : 0) * C + kc * 8) * 4;
     }
-    if (!WS) gates_request(threadIdx.x, 64 * WARPS_M * WARPS_N);
   }
 
   // reduction position of this thread's unit: tap rs and channel octet c8 (the deep rings look it up instead)
@@ -554,15 +553,8 @@ __device__ __forceinline__ void igemm_tile(const ConvProblem p, int local) {
       if (st < KT) issue(st);
   }
   if constexpr (GATED) {
-    static_assert(!LARGE, "not built");
-    if (!WS) {
-      gates_write(threadIdx.x, 64 * WARPS_M * WARPS_N);
-    } else if (do_math) {
-      for (int e = tid; e < gate_cnt; e += 64 * NW * kGateLoads) {
-        gates_request(e, 64 * NW);
-        gates_write(e, 64 * NW);
-      }
-    }
+    static_assert(WS && !LARGE, "not built");
+    if (do_math) bring_gates();
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -886,7 +878,6 @@ __device__ __forceinline__ void igemm_tile(const ConvProblem p, int local) {
       if (do_load) {
         issue(0);
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-        scale_steps(0, kt);
       }
       __builtin_amdgcn_s_barrier();                        // every wave's part of step kt is in LDS
     } else {
@@ -1161,7 +1152,6 @@ struct Variant {
   bool deep;             // a deep ring: at most kDeepMaxSteps K steps per block, which is the LDS its tap table has (and a
                          // bound for pointwise layers as well, which have no table but whose times were not measured beyond)
   bool totals_lds;       // its chunk-folding kernel keeps the running totals in LDS
-  bool fetchers = false; // waves of its own fetch
   PwKernel pw = nullptr, pw_chunked = nullptr, pw_gated = nullptr;      // for a lone pointwise problem
   int group = 1;         // stages its computing waves read at a time
 };

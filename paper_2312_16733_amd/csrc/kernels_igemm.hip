@@ -387,27 +387,23 @@ hipError_t launch_splitk_reduce(const ConvGroupArgs& a, hipStream_t s) {
 #define SNA_VARIANT(BM, BN, WM, WN, NS) \
   { BM, BN, 64 * WM * WN, IgemmCfg<BM, BN, WM, WN, NS>::SMEM, NS, IgemmCfg<BM, BN, WM, WN, NS>::STAGE_B, \
     IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, 0>, igemm_kernel<BM, BN, WM, WN, NS, true, 0>, nullptr, false, false, false }
-#define SNA_GATED_VARIANT(BM, BN, WM, WN, NS) \
-  { BM, BN, 64 * WM * WN, IgemmCfg<BM, BN, WM, WN, NS>::SMEM, NS, IgemmCfg<BM, BN, WM, WN, NS>::STAGE_B, \
-    IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, 0>, igemm_kernel<BM, BN, WM, WN, NS, true, 0>, \
-    igemm_kernel<BM, BN, WM, WN, NS, false, 0, true>, false, false, false }
 #define SNA_WS_VARIANT(BM, BN, WM, WN, NS) \
   { BM, BN, 128 * WM * WN, IgemmCfg<BM, BN, WM, WN, NS>::SMEM, NS, IgemmCfg<BM, BN, WM, WN, NS>::STAGE_B, \
-    IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, WM * WN>, igemm_kernel<BM, BN, WM, WN, NS, true, WM * WN>, nullptr, false, false, false, true }
+    IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, WM * WN>, igemm_kernel<BM, BN, WM, WN, NS, true, WM * WN>, nullptr, false, false, false }
 #define SNA_WS_GATED_VARIANT(BM, BN, WM, WN, NS) \
   { BM, BN, 128 * WM * WN, IgemmCfg<BM, BN, WM, WN, NS>::SMEM, NS, IgemmCfg<BM, BN, WM, WN, NS>::STAGE_B, \
     IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, igemm_kernel<BM, BN, WM, WN, NS, false, WM * WN>, igemm_kernel<BM, BN, WM, WN, NS, true, WM * WN>, \
-    igemm_kernel<BM, BN, WM, WN, NS, false, WM * WN, true>, false, false, false, true }
+    igemm_kernel<BM, BN, WM, WN, NS, false, WM * WN, true>, false, false, false }
 #define SNA_SLAB_VARIANT(BM, BN, WM, WN, NS) \
   { BM, BN, 64 * WM * WN, 0, NS, BN * ROW_B, IgemmCfg<BM, BN, WM, WN, NS>::EPI_BYTES, \
     conv3_slab_kernel<BM, BN, WM, WN, NS, false>, conv3_slab_kernel<BM, BN, WM, WN, NS, true>, nullptr, true, false, false }
 // The formula of pick_tile chooses from 14 variants; the others are reached through tuning.  Ids 28.. are the deep rings.
 static const Variant kPlain[] = {
-    SNA_VARIANT(128, 128, 2, 2, 2), SNA_GATED_VARIANT(128, 64, 2, 2, 2), SNA_VARIANT(128, 96, 4, 1, 2),
-    SNA_VARIANT(128, 32, 4, 1, 4),  SNA_GATED_VARIANT(64, 64, 2, 2, 4),  SNA_VARIANT(64, 128, 1, 4, 3),
+    SNA_VARIANT(128, 128, 2, 2, 2), SNA_VARIANT(128, 64, 2, 2, 2), SNA_VARIANT(128, 96, 4, 1, 2),
+    SNA_VARIANT(128, 32, 4, 1, 4),  SNA_VARIANT(64, 64, 2, 2, 4),  SNA_VARIANT(64, 128, 1, 4, 3),
     SNA_VARIANT(32, 128, 1, 4, 4),
     SNA_WS_VARIANT(64, 64, 2, 2, 4), SNA_WS_GATED_VARIANT(64, 128, 1, 4, 3), SNA_WS_VARIANT(128, 64, 2, 2, 3),
-    SNA_WS_VARIANT(128, 96, 4, 1, 3), SNA_WS_VARIANT(128, 128, 2, 2, 3), SNA_GATED_VARIANT(128, 32, 4, 1, 2),
+    SNA_WS_VARIANT(128, 96, 4, 1, 3), SNA_WS_VARIANT(128, 128, 2, 2, 3), SNA_VARIANT(128, 32, 4, 1, 2),
     SNA_WS_VARIANT(32, 128, 1, 4, 4), SNA_VARIANT(128, 192, 2, 2, 2), SNA_WS_VARIANT(128, 192, 2, 2, 3),
     // 16..: 3x3 stride-1 layers with the activation slab in LDS
     SNA_SLAB_VARIANT(128, 128, 2, 2, 2), SNA_SLAB_VARIANT(128, 64, 2, 2, 2), SNA_SLAB_VARIANT(128, 96, 4, 1, 2),
@@ -463,7 +459,6 @@ bool igemm_variant_ok(int variant, const ConvProblem& p) {
   if (p.gate) {
     const int kt = (p.K8 + 7) >> 3, stages = ring_stages(v, kt), gates = gate_bytes(v, p);
     if (!v.fn_gated || p.R * p.S != 1 || p.stride != 1 || p.pad != 0 || p.parts != 1 || kt > chunk_steps(kt) ||
-        (!v.fetchers && gates > kGateLoads * 16 * v.threads) ||
         stages * v.stage_bytes + gates > kLdsMax) return false;
   }
   if (v.deep) return steps_of(p) <= igemm_max_steps(variant);

@@ -219,6 +219,39 @@ def test_gates_of_many_one_pixel_maps(torch_mod):
         net.close()
 
 
+# A tile that scales its input has waves of its own that fetch (8, 28 and 29): the price of a step that the choice goes by
+# holds for scaling only where others compute meanwhile.  Forcing any other variant, or none, leaves one of the three.
+@pytest.mark.parametrize("batch,res", [(1, 64), (48, 80)])
+def test_gated_layers_run_where_waves_fetch(torch_mod, batch, res):
+    import paper_2312_16733_amd as sna
+    spec = synth.MBV3Spec(n_classes=40, stage_ch=(40,), stage_stride=(2,), stage_se=(True,), stage_act=("relu",), max_depth=(3,),
+                          depth_choices=(3,), expand_choices=(3,), kernel_choices=(3,), res_choices=(80,), tail_ch=64, fc_ch=64)
+    W, S, C = setup(spec, 2)
+    c = C[-1]
+    c.in_h = c.in_w = res
+    x = synth.make_inputs(spec, batch, res, res, 23)
+    net = sna.Supernet(spec, W, S, 2, batch)
+    try:
+        ref = None
+        for v in [-1] + list(range(sna.lib().sna_tile_variant_count())):
+            net.set_tile_variant(v)
+            got = forward(torch_mod, net, spec, [c], np.zeros(batch), x)
+            ref = got if ref is None else ref
+            np.testing.assert_array_equal(got, ref)
+            net.profile_enable(True)
+            try:
+                forward(torch_mod, net, spec, [c], np.zeros(batch), x)
+                lines = [l for l in net.profile_read_launches().split("\n") if " igemm_conv_linear " in l and " K=40 C=" in l]
+                net.profile_read()
+            finally:
+                net.profile_enable(False)
+            lines = [l for l in lines if " M=1 " not in l and f"M={batch} " not in l]             # not the classifier
+            assert len(lines) == 3, lines
+            assert {int(l.split("tile=")[1].split(" ")[0]) for l in lines} <= {8, 28, 29}, (v, lines)
+    finally:
+        net.close()
+
+
 # Attention and LayerNorm: token counts around the 16-query waves and the key pairs a lane transposes (odd counts, one
 # token, a full block), hidden sizes whose last 64-lane group of octets is partial (9, 65 octets) or full (256).
 # Tolerance: the family's.
