@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "../../include/subnetact.h"
+#include "fast_div.h"
 #include "tile_map.h"
 
 namespace sna {
@@ -26,21 +27,6 @@ enum KClass {
   KC_STEMPOOL = 10,  // fused 7x7/2 stem conv + SubnetNorm + ReLU + 3x3/2 max pool
   KC_CALIB = 11,     // SubnetNorm calibration: channel statistics and the normalise pass
   KC_COUNT = 12
-};
-
-// x / d for 0 <= x < 2^31, d made ready on the host: a multiplier of 31 + ceil(log2 d) fractional bits, rounded up, is off by
-// at most d / 2^(31 + ceil(log2 d)) <= 2^-31
-struct FastDiv {
-  unsigned m; int shift;            // shift < 0: d == 1
-  static FastDiv by(int d) {
-    if (d <= 1) return {0u, -1};
-    int l = 1;
-    while ((1ll << l) < d) ++l;
-    return {(unsigned)(((1ull << (31 + l)) / (unsigned)d) + 1), l - 1};
-  }
-#if defined(__HIPCC__)
-  __device__ __forceinline__ int div(int x) const { return shift < 0 ? x : (int)(__umulhi((unsigned)x, m) >> shift); }
-#endif
 };
 
 // Arguments of a launch of one problem: one descriptor instead of room for SNA_MAX_GROUPS
