@@ -86,7 +86,7 @@ struct ConvProblem {
 
 struct ConvGroupArgs {
   int n;
-  int total_tiles;      // blocks of the launch (matrix kernel: 8 per row of blocks)
+  int total_tiles;      // blocks of the launch (matrix kernel: 8 per row of blocks of every problem, at least as many as launch_blocks gives)
   ConvProblem p[SNA_MAX_GROUPS];
 };
 

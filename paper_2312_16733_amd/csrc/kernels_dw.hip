@@ -231,7 +231,8 @@ int depthwise_pool_blocks(int Ho, int Wo, int C) {
 // Squeeze-excite gate:
 //   z = mean over pixels of the depthwise output (from the depthwise blocks' partial sums)
 //   h = relu(W1[:Q,:C] z + b1[:Q]);  gate = hardsigmoid(W2[:C,:Q] h + b2[:C]);  y = x * gate
-// Two launches: h per request, then gate and scaling together.
+// The layer that follows applies the gate where its matrix tile can; pool, h and gate then take one launch for gates of up
+// to SE_ONE_MACS weights and two for larger ones (h, then the gate).  Where it cannot, the second launch scales x as well.
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ SeProblem se_problem(const SeProblem& src) {
   SeProblem p = pinned(src);

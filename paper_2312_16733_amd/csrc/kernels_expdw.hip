@@ -23,12 +23,12 @@
 // the block is done with the planes, are turned channel-fastest through LDS and stored, 16 bytes per lane.
 //
 // Measured, batch 64, expand + depthwise as two launches -> here (event-bracketed): 56^2, 24 -> 144, 7 x 7: 23.7 + 91.5 ->
-// 55.6 us; 28^2, 40 -> 240: 12.6 + 47.9 -> 30.3; 14^2, 112 -> 672: 12.3 + 42.7 -> 35.2; 7^2, 160 -> 960: 8.5 + 21.1 -> 28.1;
-// 112^2, stride 2, 16 -> 96: 44.8 + 90.4 -> 105.9; 14^2, stride 2, 112 -> 672, the one layer of the largest and the smallest
-// subnet that loses: 12.3 + 22.5 -> 39.8; one request, 12^2, 112 -> 336: 7.1 + 17.9 -> 9.3.  With 4 waves per block
-// instead of 8 the first took 71.6 us (waves wait for each other's phases), with half the LDS per block, 3 blocks per CU
-// and more halo, 82; the same design with v_dot2_f32_bf16 in B (56 VGPRs of weight pairs) 87.8 us and 15.7 us for a lone
-// 6^2 x 960 layer against 8.7.
+// 42.7 us; 28^2, 40 -> 240: 12.6 + 47.9 -> 24.2; 14^2, 112 -> 672: 12.3 + 42.7 -> 31.6; 7^2, 160 -> 960: 8.5 + 21.1 -> 23.0;
+// 112^2, stride 2, 16 -> 96: 44.8 + 90.4 -> 93.1; 14^2, stride 2, 112 -> 672, the one layer of the largest and the smallest
+// subnet that loses: 12.3 + 22.5 -> 36.3; one request, 12^2, 80 -> 320: 8.2.  In the first version of this kernel, where the
+// first of these layers took 55.6 us: 4 waves per block instead of 8 71.6 us (waves wait for each other's phases), half the
+// LDS per block, 3 blocks per CU and more halo 82; the same design with v_dot2_f32_bf16 in B (56 VGPRs of weight pairs)
+// 87.8 us and 15.7 us for a lone 6^2 x 960 layer against 8.7.
 //
 // The tile depends on the layer's shape alone, and every sum is taken in a fixed order, so a request's result does not
 // depend on what it is batched with.
