@@ -28,9 +28,9 @@ inline int chunk_steps(int kt_all) {
 // close, to 612 launch shapes of the three bf16 families (batches 1 to 64, every variant with and without split
 // reductions, in place inside a forward), before the 32x32 deep ring was given two waves, lone pointwise launches their
 // preloaded arguments and blocks their XCDs of tile_map.h.  With the kernels as they are, 830 launch shapes of the same
-// families (medians of 7), the variant it picks is on average 2.0 % slower than the fastest of all, 1.6 % by time: 0.3 %
-// where it picks 28 to 30, 1 to 5 % for the others but 64x64 (9 %, mostly gated launches of 8000 rows and more, which
-// are priced as if they did not scale).  128-row tiles with 64-row ones for launches below 256 tiles were 35 % slower.
+// families (medians of 7), the variant it picks is on average 1.3 % slower than the fastest of all, and by time: 0.3 %
+// where it picks 28 to 30, 1 to 5 % for the others.  128-row tiles with 64-row ones for launches below 256 tiles were 35 %
+// slower.
 struct TileCost { int variant; float launch, block, step, step_taps, walk; };
 constexpr TileCost kTileCosts[] = {
     {28, 2.76f, 0.36f, 0.111f, 0.134f, 0.f},            // 32x32, deep ring
