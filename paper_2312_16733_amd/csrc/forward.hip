@@ -158,6 +158,19 @@ struct Fwd {
         for (size_t v = 0; v < gate_shapes.size(); ++v)
           if (!igemm_variant_ok((int)v, ps[i])) gate_shapes[v].max_steps = 0;
       }
+    // Gated 32x32 tiles up to two blocks a CU, where another can run: a block's scaling runs under its own chain of steps, and
+    // from three on it adds up (8624 x 40 over 240, three blocks: 8.3 us against 7.1 of 64x64 tiles; 12544 x 112 over 672, six:
+    // 22.0, 17.7 and 13.2 of 64x128; at two, 3200 x 112 over 480, 8.0, 9.0 and 10.9), which the formula does not price.
+    if (!gate_shapes.empty()) {
+      auto small = [](const TileShape& t) { return t.bm == 32 && t.bn == 32; };
+      bool other = false;
+      long blocks = 0;
+      for (const TileShape& t : gate_shapes) other = other || (t.max_steps > 0 && !small(t));
+      for (size_t i = 0; i < n; ++i) blocks += (long)((ps[i].M + 31) / 32) * ((ps[i].K + 31) / 32);
+      if (other && blocks > 2 * 256)
+        for (TileShape& t : gate_shapes)
+          if (small(t)) t.max_steps = 0;
+    }
     std::vector<TileWork> ws(n);
     for (size_t i = 0; i < n; ++i) ws[i] = {ps[i].M, ps[i].K, (ps[i].K8 + 7) / 8, ps[i].R * ps[i].S};
     return pick_tile(ws.data(), n, split_mode, gate_shapes.empty() ? shapes.data() : gate_shapes.data());

@@ -247,7 +247,10 @@ def test_gated_layers_run_where_waves_fetch(torch_mod, batch, res):
                 net.profile_enable(False)
             lines = [l for l in lines if " M=1 " not in l and f"M={batch} " not in l]             # not the classifier
             assert len(lines) == 3, lines
-            assert {int(l.split("tile=")[1].split(" ")[0]) for l in lines} <= {8, 28, 29}, (v, lines)
+            ran = {int(l.split("tile=")[1].split(" ")[0]) for l in lines}
+            assert ran <= {8, 28, 29}, (v, lines)
+            if v == -1 and batch == 48:                            # 1200 blocks of 32x32: beyond two a CU another tile is faster
+                assert 28 not in ran, lines
     finally:
         net.close()
 
