@@ -125,7 +125,7 @@ struct ExpDwProblem {
   int act;              // of both layers
   unsigned x_bytes, we_bytes;
   // filled by the launcher: output rows, 16-wide row segments and requests per block; tiles, channel groups; LDS layout
-  int th, ntx, rq, ng, na, seg, tiles_x, tiles_y, chunks, CW, plane, req_plane, x_lds;
+  int th, ntx, rq, ng, seg, tiles_x, tiles_y, chunks, CW, plane, req_plane, x_lds;
   FastDiv by_chunks, by_tiles_x, by_tiles_y;
   int tile_start, tiles;
 };

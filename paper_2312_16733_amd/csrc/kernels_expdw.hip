@@ -270,7 +270,8 @@ __global__ __launch_bounds__(XD_NT, 4) void expand_dw_kernel(const ExpDwArgs arg
   int seg_off;                                                  // plane offset of this lane's segment, MFMA row l16
   {
     const Seg s = segment(l16);
-    seg_off = s.rr < p.rq && s.row < p.th ? s.rr * p.req_plane + (s.row * STRIDE * p.CW + s.tt * XD_SEG * STRIDE) * 2 : 0;
+    const int off = s.rr * p.req_plane + (s.row * STRIDE * p.CW + s.tt * XD_SEG * STRIDE) * 2;
+    seg_off = (s.rr < p.rq) & (s.row < p.th) ? off : 0;
   }
   // this lane's 8 elements of the band: columns 32 kb + 8 grp .. + 7 against output l16
   int col_off[KB], t_off[KB];
@@ -528,7 +529,7 @@ hipError_t launch_expand_dw(const ExpDwArgs& a, hipStream_t s) {
         if ((double)p.N * p.H * p.W * p.Cin * 2 >= 2147483648.0 || (double)p.N * p.Ho * p.Wo * p.C * 2 >= 2147483648.0)
           return hipErrorInvalidValue;                          // 32-bit buffer offsets; slice_conv has refused such a call
         const XdGeom g = xd_geometry(p.Ho, p.Wo, k, st);
-        p.th = g.th; p.ntx = g.ntx; p.rq = g.rq; p.ng = g.ng; p.na = g.na; p.seg = g.seg; p.tiles_x = g.tiles_x; p.tiles_y = g.tiles_y;
+        p.th = g.th; p.ntx = g.ntx; p.rq = g.rq; p.ng = g.ng; p.seg = g.seg; p.tiles_x = g.tiles_x; p.tiles_y = g.tiles_y;
         p.CW = g.CW; p.plane = g.plane; p.req_plane = g.req_plane; p.x_lds = (int)xd_planes(g, st);
         p.chunks = (p.C + XD_CH - 1) / XD_CH;
         p.by_chunks = FastDiv::by(p.chunks); p.by_tiles_x = FastDiv::by(p.tiles_x); p.by_tiles_y = FastDiv::by(p.tiles_y);
